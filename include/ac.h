@@ -142,7 +142,7 @@ ac_status ac_gemm_i8_acc32(const int8_t* A, int64_t lda, const int8_t* B, int64_
  * is ac_gemm_i8 without a workspace.  An operand is staged in LDS in its memory order and the transposition
  * happens in the LDS read.  Operands that qualify for the direct-to-LDS kernels (16-byte aligned base pointers
  * and row pitches; M (when trans_a), N and K multiples of 16) run on those, at the rate of the untransposed
- * product and never with a cut K range; anything else, any alignment included, on a register-staged kernel.
+ * product and never with a cut K range; anything else, any alignment included, on a register-staged kernel (one vector load per 16-byte chunk).
  */
 ac_status ac_gemm_i8_t(const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb,
                        const int32_t* bias, int64_t bias_ld, int8_t* C, int64_t ldc,
@@ -304,8 +304,8 @@ ac_status ac_tinympc_forward_f32(const float* Adyn, const float* Bdyn, const flo
  *           K = KH KW Cin) named by the caller; "qualify" there means 16-byte aligned in / w, Cin and Cout
  *           multiples of 16, out 4-byte aligned; workspace size from ac_gemm_i8_planned_workspace_bytes(M, N, K, ...).
  * ac_gemm_*_auto_plan report what the unplanned call would choose for a shape (pure host arithmetic).
- * Operands that do not qualify for the direct-to-LDS kernels run on a generic kernel with square tiles, which
- * takes code 192 as 128.
+ * Operands that do not qualify for the direct-to-LDS kernels run on a kernel for any alignment with tiles of 64 x 64
+ * and 128 x 128, which takes codes 192 and 256 as 128.
  */
 ac_status ac_gemm_i8_planned(const int8_t* A, int64_t lda, const int8_t* B, int64_t ldb,
                              const int32_t* bias, int64_t bias_ld, int8_t* C, int64_t ldc,

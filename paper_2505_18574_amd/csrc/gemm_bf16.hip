@@ -1,7 +1,7 @@
 // bf16 GEMM, fp32 accumulate and output: tile selection, split-K and launch.
 #include <algorithm>
 
-#include "gemm_dtl.hpp"
+#include "gemm_ragged.hpp"
 
 namespace ac {
 
@@ -70,46 +70,34 @@ bool gemm_bf16_fast_path(const GemmParams& p) {
 
 hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const GemmPlan* forced) {
   GemmParams p = p0;
-  const bool aligned = (((uintptr_t)p.A & 15) == 0) && (((uintptr_t)p.B & 15) == 0) && (p.lda % 8 == 0) && (p.ldb % 8 == 0) &&
-                       (((uintptr_t)p.C & 15) == 0) && (p.ldc % 4 == 0);
   // direct-to-LDS fast path: additionally K and N in whole 16-byte chunks
   const bool fast = gemm_bf16_fast_path(p);
   GemmPlan plan = forced ? *forced : plan_gemm_bf16(p.M, p.N, p.K);
-  if (plan.splits > 1 && !fast) {
-    if (forced) return hipErrorInvalidValue;
-    make_plan_bf16(p.K, choose_tile(p.M, p.N), 1, &plan);  // the generic kernels do not slice K and have square tiles
+  if (!fast) {  // the ragged kernel does not slice K: the call is the same with and without a workspace
+    if (forced && plan.splits > 1) return hipErrorInvalidValue;
+    p.splits = 1;
+    p.kt_per_split = 0;
+    return launch_ragged<TypeBF16, EpilogueF32, true, false>(forced ? plan.tile : ragged_tile(p.M, p.N), p, stream);
   }
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
-  if (fast) {
-    if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order
-      hipError_t e = launch_dtl_tile<TypeBF16, EpiloguePartialF32, 0>(plan.tile, p, stream);
-      if (e != hipSuccess) return e;
-      // one-wave workgroups for small outputs, as for the int8 combine (64 x 64 x 65536 in 128 slices: 15.3 -> 13.5 us)
-      const int64_t quads = (int64_t)p.M * (p.N / 4);
-      if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, p);
-      else hipLaunchKernelGGL(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, p);
-      return hipGetLastError();
-    }
-    if (plan.splits > 1) {  // no workspace: slices add into C with fp32 atomics
-      const int64_t n = (int64_t)p.M * p.N;
-      hipLaunchKernelGGL(scale_c_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (float*)p.C, p.ldc, p.M, p.N, p.beta);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      return launch_dtl_tile<TypeBF16, EpilogueAtomicF32, 0>(plan.tile, p, stream);
-    }
-    return launch_dtl_tile<TypeBF16, EpilogueF32, 0>(plan.tile, p, stream);
+  if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order
+    const hipError_t e = launch_dtl_tile<TypeBF16, EpiloguePartialF32, 0>(plan.tile, p, stream);
+    if (e != hipSuccess) return e;
+    // one-wave workgroups for small outputs, as for the int8 combine (64 x 64 x 65536 in 128 slices: 15.3 -> 13.5 us)
+    const int64_t quads = (int64_t)p.M * (p.N / 4);
+    if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, p);
+    else hipLaunchKernelGGL(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, p);
+    return hipGetLastError();
   }
-#define AC_BF16_LAUNCH(TILE)                                                                        \
-  (aligned ? launch_tile<TypeBF16, EpilogueF32, TILE, TILE, 2, 2, 0, true>(p, stream)               \
-           : launch_tile<TypeBF16, EpilogueF32, TILE, TILE, 2, 2, 0, false>(p, stream))
-  switch (plan.tile) {  // the generic kernel has square tiles only: 192 falls to 128
-    case 256: return AC_BF16_LAUNCH(256);
-    case 192:
-    case 128: return AC_BF16_LAUNCH(128);
-    default: return AC_BF16_LAUNCH(64);
+  if (plan.splits > 1) {  // no workspace: slices add into C with fp32 atomics
+    const int64_t n = (int64_t)p.M * p.N;
+    hipLaunchKernelGGL(scale_c_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (float*)p.C, p.ldc, p.M, p.N, p.beta);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_dtl_tile<TypeBF16, EpilogueAtomicF32, 0>(plan.tile, p, stream);
   }
-#undef AC_BF16_LAUNCH
+  return launch_dtl_tile<TypeBF16, EpilogueF32, 0>(plan.tile, p, stream);
 }
 
 }  // namespace ac

@@ -3,8 +3,8 @@
 // XOR-swizzled instead of padded, and the K loop is software-pipelined over a
 // ring of LDS stages with one workgroup barrier per K tile.
 //
-// Preconditions (checked by the host launcher; anything else takes the generic
-// kernel in gemm_mfma.hpp): all base pointers 16-byte aligned, row pitches of A
+// Preconditions (checked by the host launcher; anything else takes the ragged
+// kernel in gemm_ragged.hpp): all base pointers 16-byte aligned, row pitches of A
 // and B multiples of 16 bytes, K and N multiples of 16 bytes' worth of elements,
 // C suitably aligned for vector stores.  M, N, K need not be multiples of the
 // tile: out-of-range 16-byte chunks are fetched from a 16-byte block of zeros.

@@ -1,5 +1,6 @@
 // int8 GEMM / implicit-GEMM convolution with the accelerator output stage: tile selection, split-K and launch.
 #include "conv_halo.hpp"
+#include "gemm_ragged.hpp"
 #include "gemm_small.hpp"
 #include "gemm_wstat.hpp"
 
@@ -272,87 +273,110 @@ void plan_few_tiles(int32_t M, int32_t N, int64_t kbytes, bool may_slice, const 
   if (*splits > 1 && best > model.split_margin * best_uncut) *tile = tile_uncut, *splits = 1;
 }
 
-// Output stage of a split-K launch: sum the K slices, then bias / shift / saturate / ReLU, 4 outputs per thread.
-template <int THREADS>
+// Output stage of a split-K launch: sum the K slices, then bias / shift / saturate / ReLU.  VEC outputs of a row per
+// thread: 4 where N is a multiple of 4 and C takes packed stores, otherwise 1.
+template <int THREADS, int VEC>
 __global__ void __launch_bounds__(THREADS) splitk_reduce_i8_kernel(const GemmParams p) {
-  const int64_t quads_per_row = p.N / 4;  // split-K is only used on the fast path: N is a multiple of 16
+  typedef std::conditional_t<VEC == 4, v4i, int> vec;
+  const int64_t per_row = p.N / VEC;
   const int64_t q = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (q >= (int64_t)p.M * quads_per_row) return;
-  const int m = (int)(q / quads_per_row);
-  const int n = (int)(q - (int64_t)m * quads_per_row) * 4;
-  v4i s = {0, 0, 0, 0};
+  if (q >= (int64_t)p.M * per_row) return;
+  const int m = (int)(q / per_row);
+  const int n = (int)(q - (int64_t)m * per_row) * VEC;
+  vec s = {};
   const int32_t* part = p.partial + (int64_t)m * p.N + n;
   const int64_t slice = (int64_t)p.M * p.N;
   int k = 0;
   for (; k + 8 <= p.splits; k += 8) {  // eight loads in flight: the slices of one output are a latency chain otherwise
-    v4i v[8];
+    vec v[8];
 #pragma unroll
-    for (int u = 0; u < 8; u++) v[u] = *(const v4i*)(part + (k + u) * slice);
+    for (int u = 0; u < 8; u++) v[u] = *(const vec*)(part + (k + u) * slice);
 #pragma unroll
     for (int u = 0; u < 8; u++) s += v[u];
   }
-  for (; k < p.splits; k++) s += *(const v4i*)(part + k * slice);
-  int a4[4] = {s[0], s[1], s[2], s[3]};
-  EpilogueI8::store4<true>(p, m, n, a4);
+  for (; k < p.splits; k++) s += *(const vec*)(part + k * slice);
+  if constexpr (VEC == 4) {
+    int a4[4] = {s[0], s[1], s[2], s[3]};
+    EpilogueI8::store4<true>(p, m, n, a4);
+  } else {
+    EpilogueI8Any::one(p, m, n, s);
+  }
 }
 
 // One-wave workgroups for small outputs: the kernel is a chain of latencies, and four times the workgroups spread
 // it over four times the compute units (49 x 2048 x 4608 in 8 slices: 8.7 -> 7.3 us for the whole call, 32 x 2048 x
 // 2048 7.8 -> 6.6; level or within 0.3 us on nine other shapes; from 50176 outputs of four on, 256 threads again).
+template <int VEC>
 static hipError_t launch_splitk_reduce_i8(const GemmParams& p, hipStream_t stream) {
-  const int64_t quads = (int64_t)p.M * (p.N / 4);
-  if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_i8_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, p);
-  else hipLaunchKernelGGL(splitk_reduce_i8_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, p);
+  const int64_t items = (int64_t)p.M * (p.N / VEC);
+  if (items <= 32768) hipLaunchKernelGGL((splitk_reduce_i8_kernel<64, VEC>), dim3((unsigned)((items + 63) / 64)), dim3(64), 0, stream, p);
+  else hipLaunchKernelGGL((splitk_reduce_i8_kernel<256, VEC>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
+// Operands that the direct-to-LDS kernels do not take.  The K slices are as many as the shape's own plan has (which is
+// what the workspace was sized for), but no more than fill the chip twice with this kernel's tiles.
 template <int AMODE>
-hipError_t dispatch_i8(GemmParams p, hipStream_t stream, bool aligned, bool fast, const GemmPlan* forced) {
+static hipError_t launch_ragged_i8(GemmParams p, hipStream_t stream, const GemmPlan* forced) {
+  const int tile = forced ? forced->tile : ragged_tile(p.M, p.N);
+  p.splits = 1;
+  p.kt_per_split = 0;
+  if (!forced && p.partial != nullptr && !ragged_tiny<TypeI8, true, false, AMODE == 1>(p)) {
+    const int64_t kbytes = AMODE == 1 ? (int64_t)p.KH * conv_run_padded(p) : p.K, nkt = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
+    const int edge = tile >= 128 ? 128 : 64;
+    const int64_t tiles = (int64_t)((p.M + edge - 1) / edge) * ((p.N + edge - 1) / edge);
+    const int64_t most = std::min<int64_t>({(int64_t)plan_gemm_i8(p.M, p.N, p.K, true, 0).splits, nkt, 4 * PLAN_CUS / tiles});
+    if (most > 1) {
+      p.kt_per_split = (int)((nkt + most - 1) / most);
+      p.splits = (int)((nkt + p.kt_per_split - 1) / p.kt_per_split);
+    }
+  }
+  if (p.splits > 1) {
+    if (const hipError_t e = launch_ragged<TypeI8, EpiloguePartialI32, true, false, AMODE == 1>(tile, p, stream)) return e;
+    return launch_splitk_reduce_i8<1>(p, stream);
+  }
+  return launch_ragged<TypeI8, EpilogueI8Any, true, false, AMODE == 1>(tile, p, stream);
+}
+
+template <int AMODE>
+hipError_t dispatch_i8(GemmParams p, hipStream_t stream, bool fast, const GemmPlan* forced) {
+  if (!fast) {
+    const bool square = !forced || forced->tile == 64 || forced->tile == 128 || forced->tile == 192 || forced->tile == 256;
+    if (!square || (forced && forced->splits > 1)) return hipErrorInvalidValue;
+    return launch_ragged_i8<AMODE>(p, stream, forced);
+  }
   // the one-wave-per-tile kernel is planned only for operands it takes
-  GemmPlan plan = forced ? *forced : plan_gemm_i8(p.M, p.N, p.K, fast && p.partial != nullptr, fast && small_i8_eligible(p) ? 1 + AMODE : 0);
+  GemmPlan plan = forced ? *forced : plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 1 + AMODE : 0);
   int ws_bm;
-  if (!forced && wstat_tile_rows(plan.tile, &ws_bm) && !(fast && wstat_eligible(p, plan.tile))) {
+  if (!forced && wstat_tile_rows(plan.tile, &ws_bm) && !wstat_eligible(p, plan.tile)) {
     plan.tile = choose_tile_i8(p.M, p.N, p.K, false);  // operands the weight-stationary kernel does not take: the tiled kernels
     plan.ktb = ktb_of_tile(plan.tile);
   }
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
-  if (plan.splits > 1 && (!fast || p.partial == nullptr)) return hipErrorInvalidValue;
+  if (plan.splits > 1 && p.partial == nullptr) return hipErrorInvalidValue;
   if (wstat_tile_rows(plan.tile, &ws_bm)) {
-    if (!fast || !wstat_eligible(p, plan.tile)) return hipErrorInvalidValue;
+    if (!wstat_eligible(p, plan.tile)) return hipErrorInvalidValue;
     return launch_wstat_tile<AMODE>(plan.tile, p, stream);
   }
   if (plan.tile == 32) {
-    if (!fast || !small_i8_eligible(p)) return hipErrorInvalidValue;
+    if (!small_i8_eligible(p)) return hipErrorInvalidValue;
     const hipError_t e = launch_small_i8<AMODE>(p, stream);
     if (e != hipSuccess || plan.splits <= 1) return e;
-    return launch_splitk_reduce_i8(p, stream);
+    return launch_splitk_reduce_i8<4>(p, stream);
   }
   if (halo_tile_rows(plan.tile, &ws_bm)) {
     ConvHaloParams h;
     size_t lds = 0;
-    if (AMODE != 1 || !fast || !conv_halo_plan(p, ws_bm, &h, &lds)) return hipErrorInvalidValue;
+    if (AMODE != 1 || !conv_halo_plan(p, ws_bm, &h, &lds)) return hipErrorInvalidValue;
     return ws_bm == 256 ? launch_conv_halo<256>(p, h, lds, stream) : launch_conv_halo<128>(p, h, lds, stream);
   }
-  if (fast) {  // direct-to-LDS kernels
-    if (plan.splits > 1) {
-      hipError_t e = launch_dtl_tile<TypeI8, EpiloguePartialI32, AMODE>(plan.tile, p, stream);
-      if (e != hipSuccess) return e;
-      return launch_splitk_reduce_i8(p, stream);
-    }
-    return launch_dtl_tile<TypeI8, EpilogueI8, AMODE>(plan.tile, p, stream);
+  if (plan.splits > 1) {
+    const hipError_t e = launch_dtl_tile<TypeI8, EpiloguePartialI32, AMODE>(plan.tile, p, stream);
+    if (e != hipSuccess) return e;
+    return launch_splitk_reduce_i8<4>(p, stream);
   }
-#define AC_I8_CASE(TILE, WM, WN)                                                                         \
-  case TILE:                                                                                             \
-    return aligned ? launch_tile<TypeI8, EpilogueI8, TILE, TILE, WM, WN, AMODE, true>(p, stream)         \
-                   : launch_tile<TypeI8, EpilogueI8, TILE, TILE, WM, WN, AMODE, false>(p, stream);
-  switch (plan.tile == 192 ? 128 : plan.tile) {  // the generic kernel has square tiles only
-    AC_I8_CASE(256, 2, 2)
-    AC_I8_CASE(128, 2, 2)
-    AC_I8_CASE(64, 2, 2)
-  }
-#undef AC_I8_CASE
-  return hipErrorInvalidValue;
+  return launch_dtl_tile<TypeI8, EpilogueI8, AMODE>(plan.tile, p, stream);
 }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -368,17 +392,13 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   GemmParams p = p0;
   p.splits = 1;
   p.kt_per_split = 0;
-  const bool aligned = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0);
-  const bool fast = aligned && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
+  const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
-  return aligned ? launch_tile<TypeI8, EpilogueRawI32, 64, 64, 2, 2, 0, true>(p, stream)
-                 : launch_tile<TypeI8, EpilogueRawI32, 64, 64, 2, 2, 0, false>(p, stream);
+  return launch_ragged<TypeI8, EpilogueRawI32, true, false>(ragged_tile(p.M, p.N), p, stream);
 }
 
 hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced) {
-  const bool aligned = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) &&
-                       (((uintptr_t)p.C & 3) == 0) && (p.ldc % 4 == 0);
-  return dispatch_i8<0>(p, stream, aligned, gemm_i8_fast_path(p), forced);
+  return dispatch_i8<0>(p, stream, gemm_i8_fast_path(p), forced);
 }
 
 // Direct-to-LDS path of the convolution: channel counts in multiples of 16 so that a 16-byte K chunk stays inside
@@ -400,8 +420,6 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     g.lda = p.Cin;
     return launch_gemm_i8(g, stream, nullptr);
   }
-  const bool aligned = aligned16(p.A) && aligned16(p.B) && (p.Cin % 16 == 0) && (p.ldb % 16 == 0) &&
-                       (((uintptr_t)p.C & 3) == 0) && (p.ldc % 4 == 0);
   const bool fast = conv_i8_fast_path(p);
   if (!forced && fast) {
     // The patch kernel (weights and the image patch of a unit both in LDS) as soon as the 64 x 64 tiles would
@@ -426,7 +444,7 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
       // 18.5 us on the best tiled kernel, 128 images 29.6 against 33.6)
       if (h.units * nblk >= 512) return launch_conv_halo<128>(q, h, lds, stream);
     } else {
-      return dispatch_i8<1>(p, stream, aligned, fast, forced);
+      return dispatch_i8<1>(p, stream, fast, forced);
     }
     // a convolution the patch kernel could take but that is too small for it: the tiled kernels (or one wave per
     // tile, by the GEMM's rule: 56 x 56 x 64 -> 64, one image, 4.4 us against 5.4; K = 1152 gains 0.5 us with the
@@ -435,9 +453,9 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0);
     int ws_bm;
     if (wstat_tile_rows(plan.tile, &ws_bm)) make_plan_i8(p.K, choose_tile(p.M, p.N), 1, &plan);  // unsplit: no workspace needed
-    return dispatch_i8<1>(p, stream, aligned, fast, &plan);
+    return dispatch_i8<1>(p, stream, fast, &plan);
   }
-  return dispatch_i8<1>(p, stream, aligned, fast, forced);
+  return dispatch_i8<1>(p, stream, fast, forced);
 }
 
 }  // namespace ac

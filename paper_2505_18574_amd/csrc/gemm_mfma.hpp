@@ -1,16 +1,5 @@
-// Tiled MFMA GEMM for gfx950 (CDNA4), shared by the int8 GEMM, the int8
-// implicit-GEMM convolution and the bf16 GEMM.
-//
-// One workgroup owns a BM x BN tile of C.  Per K step of 128 bytes of A-row:
-//   global (16 B per lane, coalesced) -> registers -> LDS (double buffered)
-//   LDS -> MFMA operands: A rows by ds_read_b128 (K is contiguous in A);
-//   B columns by the gfx950 transposing LDS reads (ds_read_b64_tr_b8/_b16),
-//   because B is K x N row-major and the matrix unit wants K contiguous per lane.
-//   32x32 MFMA tiles (i32_32x32x32_i8 / f32_32x32x16_bf16), accumulators in registers.
-// The two MFMA source operands are swapped (B^T tile as the row operand, A tile
-// as the column operand) so that each lane ends up holding 4 consecutive n of one
-// row m: the epilogue can then requantise in registers and store 4 packed int8
-// (or a float4) without an LDS transpose.
+// Operand types and output stages shared by the tiled MFMA kernels for gfx950 (CDNA4): int8 GEMM, int8 implicit-GEMM
+// convolution and bf16 GEMM.
 #pragma once
 #include "common.hpp"
 #include <type_traits>
@@ -67,28 +56,6 @@ struct TypeBF16 {
   }
 };
 
-// 16 bytes from p, of which only the first `valid` (may be <= 0 or >= 16) exist.
-static __device__ __forceinline__ v4i load16_bytes(const unsigned char* p, int valid) {
-  unsigned int w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int e = 0; e < 16; e++)
-    if (e < valid) w[e >> 2] |= (unsigned int)p[e] << (8 * (e & 3));
-  return (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-}
-
-// Without the 16-byte guarantee a whole chunk at a 4-byte aligned address is still four dword loads rather than
-// sixteen byte loads (a row pitch that is a multiple of 4 but not of 16, say N = 1000, keeps every chunk there).
-template <bool ALIGNED>
-static __device__ __forceinline__ v4i load16(const unsigned char* p, int valid) {
-  if (valid <= 0) return (v4i){0, 0, 0, 0};
-  if (ALIGNED && valid >= 16) return *(const v4i*)p;
-  if (!ALIGNED && valid >= 16 && (((uintptr_t)p) & 3) == 0) {
-    const int* q = (const int*)p;
-    return (v4i){q[0], q[1], q[2], q[3]};
-  }
-  return load16_bytes(p, valid);
-}
-
 // XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs (each
 // with its own L2), so workgroup b runs on XCD b % 8.  Give every XCD one
 // contiguous run of logical tile ids, and lay those ids out in bands of GROUP_M
@@ -108,9 +75,7 @@ static __device__ __forceinline__ void tile_coords(int b, int nblocks, int tiles
 }
 
 // Epilogue policies -----------------------------------------------------------
-// store4(): for one lane, 4 accumulators of row m at columns n .. n+3 (the generic kernel, which always swaps
-// the MFMA operands).  tile(): one 32x32 accumulator tile of the direct-to-LDS kernel, whose operand order the
-// policy chooses with SWAP:
+// tile(): one 32x32 accumulator tile, whose operand order the policy chooses with SWAP:
 //   SWAP (B^T tile as the row operand): register r of lane l is row l % 32, column 8 (r/4) + 4 (l/32) + r % 4:
 //     a lane owns runs of 4 consecutive columns of one row.  Right for 1-byte outputs, which pack 4 (and, after
 //     a lane exchange, 16) of them per store.
@@ -346,6 +311,41 @@ struct EpilogueI8 {
   }
 };
 
+// The same output stage for a C of any alignment and pitch (unswapped tiles: 32 lanes store 32 consecutive bytes).
+struct EpilogueI8Any {
+  static constexpr bool SWAP = false;
+  struct Pre {};
+  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, int v) {
+    if (p.bias) v += p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
+    ((int8_t*)p.C)[(int64_t)m * p.ldc + n] = (int8_t)EpilogueI8::requant(v, p.shift, p.act);
+  }
+  template <class ACC>
+  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+    const int n = ncol0 + (lane & 31), mb = mrow0 + 4 * (lane >> 5);
+    if (n >= p.N) return;
+    int8_t* C = (int8_t*)p.C + (int64_t)mb * p.ldc + n;
+    const int row_bias = p.bias && p.bias_ld == 0 ? p.bias[n] : 0;
+    const bool matrix_bias = p.bias && p.bias_ld != 0;
+    auto rows = [&](auto quant) {
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int dm = 8 * (r >> 2) + (r & 3);
+        if (mb + dm < p.M) {
+          int v = acc[r] + row_bias;
+          if (matrix_bias) v += p.bias[(int64_t)(mb + dm) * p.bias_ld + n];
+          C[(int64_t)dm * p.ldc] = (int8_t)quant(v);
+        }
+      }
+    };
+    if (p.shift >= 1 && p.shift <= 17) {
+      const EpilogueI8::FastQuant f = EpilogueI8::fast_quant(p.shift, p.act);
+      rows([&](int v) { return EpilogueI8::requant_fast<true>(v, f); });
+    } else {
+      rows([&](int v) { return EpilogueI8::requant(v, p.shift, p.act); });
+    }
+  }
+};
+
 // Split-K partial sums: raw int32 accumulators of K slice `split` go to partial[split][M][N]; the output stage
 // runs in splitk_reduce_i8_kernel once every slice has been written.
 struct EpiloguePartialI32 {
@@ -380,35 +380,16 @@ struct EpilogueRawI32 {
     }
     *(v4i*)((int32_t*)p.C + (int64_t)m * p.ldc + n) = o;
   }
-  template <bool VEC>
-  static __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const int* a, int = 0) {
-    if (m >= p.M || n >= p.N) return;
-    int32_t* dst = (int32_t*)p.C + (int64_t)m * p.ldc + n;
-    int v[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      int b = 0;
-      if (p.bias && n + e < p.N) b = p.bias_ld == 0 ? p.bias[n + e] : p.bias[(int64_t)m * p.bias_ld + n + e];
-      v[e] = a[e] + b;
-    }
-    if (VEC && n + 3 < p.N) {
-      *(v4i*)dst = (v4i){v[0], v[1], v[2], v[3]};
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (n + e < p.N) dst[e] = v[e];
-    }
-  }
   struct Pre {};
   static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
+  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, int v) {
+    if (p.bias) v += p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
+    ((int32_t*)p.C)[(int64_t)m * p.ldc + n] = v;
+  }
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
-      if (m < p.M && n < p.N) {
-        int b = 0;
-        if (p.bias) b = p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
-        ((int32_t*)p.C)[(int64_t)m * p.ldc + n] = acc[r] + b;
-      }
+      if (m < p.M && n < p.N) one(p, m, n, acc[r]);
     });
   }
 };
@@ -426,39 +407,18 @@ struct EpilogueF32 {
     if (p.beta != 0.f) o += p.beta * *(const v4f*)dst;
     *(v4f*)dst = o;
   }
-  template <bool VEC>
-  static __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const float* a, int = 0) {
-    if (m >= p.M || n >= p.N) return;
-    float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
-    const bool full = n + 3 < p.N;
-    if (VEC && full) {
-      v4f o = {p.alpha * a[0], p.alpha * a[1], p.alpha * a[2], p.alpha * a[3]};
-      if (p.beta != 0.f) {
-        v4f c = *(const v4f*)dst;
-        o += p.beta * c;
-      }
-      *(v4f*)dst = o;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (n + e < p.N) {
-          float o = p.alpha * a[e];
-          if (p.beta != 0.f) o += p.beta * dst[e];
-          dst[e] = o;
-        }
-    }
-  }
   struct Pre {};
   static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
+  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, float v) {
+    float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
+    float o = p.alpha * v;
+    if (p.beta != 0.f) o += p.beta * *dst;
+    *dst = o;
+  }
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
-      if (m < p.M && n < p.N) {
-        float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
-        float o = p.alpha * acc[r];
-        if (p.beta != 0.f) o += p.beta * *dst;
-        *dst = o;
-      }
+      if (m < p.M && n < p.N) one(p, m, n, acc[r]);
     });
   }
 };
@@ -499,211 +459,5 @@ struct EpiloguePartialF32 {
     });
   }
 };
-
-// A-operand addressing ----------------------------------------------------------
-// AMODE 0: A is an M x K matrix.  AMODE 1: A(m, k) is gathered from an NHWC image
-// (m -> (image, oh, ow), k -> (kh, kw, ci)), zero outside the image.
-template <int AMODE>
-struct ARow;
-
-template <>
-struct ARow<0> {
-  const unsigned char* ptr;  // start of the row, null when the row is outside M
-  __device__ __forceinline__ void init(const GemmParams& p, int m, int EB) {
-    ptr = m < p.M ? (const unsigned char*)p.A + (int64_t)m * p.lda * EB : nullptr;
-  }
-};
-
-template <>
-struct ARow<1> {
-  int base;  // element offset of (image, ih0, iw0, 0); may be negative-side of the image, only used when in range
-  short ih0, iw0;
-  bool ok;
-  __device__ __forceinline__ void init(const GemmParams& p, int m, int) {
-    ok = m < p.M;
-    int mm = ok ? m : 0;
-    int ow = mm % p.OW;
-    int t = mm / p.OW;
-    int oh = t % p.OH;
-    int img = t / p.OH;
-    ih0 = (short)(oh * p.stride - p.pad);
-    iw0 = (short)(ow * p.stride - p.pad);
-    base = ((img * p.H + ih0) * p.W + iw0) * p.Cin;
-  }
-};
-
-template <class T, int BM, int BN, int WAVES_M, int WAVES_N>
-struct TileGeometry {
-  static constexpr int EB = T::EB;
-  static constexpr int KTB = 128;            // bytes of K per A row per step
-  static constexpr int BK = KTB / EB;        // elements of K per step
-  static constexpr int THREADS = 64 * WAVES_M * WAVES_N;
-  static constexpr int A_STRIDE = KTB + 16;  // padded LDS row: conflict-free b128 reads
-  static constexpr int B_STRIDE = BN * EB + 16;
-  static constexpr int A_BYTES = BM * A_STRIDE;
-  static constexpr int B_BYTES = BK * B_STRIDE;
-  static constexpr int STAGE = A_BYTES + B_BYTES;
-  static constexpr int LDS_BYTES = 2 * STAGE;
-  static constexpr int A_ROWS_PER_PASS = THREADS / 8;
-  static constexpr int A_IT = BM / A_ROWS_PER_PASS;
-  static constexpr int B_CPR = BN * EB / 16;  // 16-byte chunks per B row
-  static constexpr int B_ROWS_PER_PASS = THREADS / B_CPR;
-  static constexpr int B_IT = BK / B_ROWS_PER_PASS;
-  static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  static constexpr int TM = WTM / 32, TN = WTN / 32;
-  static_assert(BM % A_ROWS_PER_PASS == 0 && A_IT >= 1, "A tile / thread mismatch");
-  static_assert(THREADS % B_CPR == 0 && BK % B_ROWS_PER_PASS == 0 && B_IT >= 1, "B tile / thread mismatch");
-  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA");
-};
-
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, bool ALIGNED>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_mfma_kernel(const GemmParams p, const int tiles_m, const int tiles_n) {
-  using G = TileGeometry<T, BM, BN, WAVES_M, WAVES_N>;
-  constexpr int EB = G::EB;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  int tm, tn;
-  tile_coords(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  typename T::accv acc[G::TM][G::TN];
-#pragma unroll
-  for (int i = 0; i < G::TM; i++)
-#pragma unroll
-    for (int j = 0; j < G::TN; j++) acc[i][j] = T::zero();
-
-  // ---- per-thread staging assignment
-  const int a_cc = t & 7, a_r0 = t >> 3;
-  const int b_cc = t % G::B_CPR, b_r0 = t / G::B_CPR;
-  ARow<AMODE> arow[G::A_IT];
-#pragma unroll
-  for (int i = 0; i < G::A_IT; i++) arow[i].init(p, m0 + a_r0 + i * G::A_ROWS_PER_PASS, EB);
-  const int kbytes = p.K * EB;               // valid bytes per A row
-  const int nbytes = p.N * EB;               // valid bytes per B row
-  const int b_col = n0 * EB + b_cc * 16;     // byte column of this thread's B chunks
-  const unsigned char* Bp = (const unsigned char*)p.B;
-
-  v4i ra[G::A_IT], rb[G::B_IT];
-
-  auto gload = [&](int kt) {
-    const int ka = kt * G::KTB + a_cc * 16;  // byte offset along K of this thread's A chunks
-    if constexpr (AMODE == 0) {
-#pragma unroll
-      for (int i = 0; i < G::A_IT; i++) {
-        const unsigned char* rp = arow[i].ptr;
-        ra[i] = rp ? load16<ALIGNED>(rp + ka, kbytes - ka) : (v4i){0, 0, 0, 0};
-      }
-    } else {
-      const unsigned char* in = (const unsigned char*)p.A;
-      if constexpr (ALIGNED) {  // Cin % 16 == 0: a chunk never straddles a kernel tap
-        int tap = ka / p.Cin, ci = ka - tap * p.Cin;
-        int kh = tap / p.KW, kw = tap - kh * p.KW;
-        int koff = (kh * p.W + kw) * p.Cin + ci;
-#pragma unroll
-        for (int i = 0; i < G::A_IT; i++) {
-          const ARow<1>& r = arow[i];
-          int ih = r.ih0 + kh, iw = r.iw0 + kw;
-          bool ok = r.ok && ka < kbytes && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-          ra[i] = ok ? *(const v4i*)(in + r.base + koff) : (v4i){0, 0, 0, 0};
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < G::A_IT; i++) {
-          const ARow<1>& r = arow[i];
-          unsigned int w[4] = {0u, 0u, 0u, 0u};
-          for (int e = 0; e < 16; e++) {
-            int k = ka + e;
-            if (r.ok && k < kbytes) {
-              int tap = k / p.Cin, ci = k - tap * p.Cin;
-              int kh = tap / p.KW, kw = tap - kh * p.KW;
-              int ih = r.ih0 + kh, iw = r.iw0 + kw;
-              if ((unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
-                w[e >> 2] |= (unsigned int)in[r.base + (kh * p.W + kw) * p.Cin + ci] << (8 * (e & 3));
-            }
-          }
-          ra[i] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < G::B_IT; i++) {
-      int k = kt * G::BK + b_r0 + i * G::B_ROWS_PER_PASS;
-      rb[i] = k < p.K ? load16<ALIGNED>(Bp + ((int64_t)k * p.ldb) * EB + b_col, nbytes - b_col) : (v4i){0, 0, 0, 0};
-    }
-  };
-
-  auto lstore = [&](int buf) {
-    unsigned char* As = smem + buf * G::STAGE;
-    unsigned char* Bs = As + G::A_BYTES;
-#pragma unroll
-    for (int i = 0; i < G::A_IT; i++) *(v4i*)(As + (a_r0 + i * G::A_ROWS_PER_PASS) * G::A_STRIDE + a_cc * 16) = ra[i];
-#pragma unroll
-    for (int i = 0; i < G::B_IT; i++) *(v4i*)(Bs + (b_r0 + i * G::B_ROWS_PER_PASS) * G::B_STRIDE + b_cc * 16) = rb[i];
-  };
-
-  auto compute = [&](int buf) {
-    const unsigned char* As = smem + buf * G::STAGE;
-    const unsigned char* Bs = As + G::A_BYTES;
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {  // 4 MFMA K-steps of 32 bytes per tile
-      v4i af[G::TM], bf[G::TN];
-      const int kb = ks * 32 + (lane >> 5) * 16;  // this lane's 16 bytes of K
-#pragma unroll
-      for (int i = 0; i < G::TM; i++) af[i] = *(const v4i*)(As + (wm * G::WTM + i * 32 + (lane & 31)) * G::A_STRIDE + kb);
-#pragma unroll
-      for (int j = 0; j < G::TN; j++)
-        bf[j] = T::read_col(Bs, G::B_STRIDE, kb / EB, (wn * G::WTN + j * 32 + 16 * ((lane >> 4) & 1)) * EB, lane);
-#pragma unroll
-      for (int i = 0; i < G::TM; i++)
-#pragma unroll
-        for (int j = 0; j < G::TN; j++) acc[i][j] = T::mfma(bf[j], af[i], acc[i][j]);
-    }
-  };
-
-  const int nkt = (kbytes + G::KTB - 1) / G::KTB;
-  if (nkt > 0) {
-    gload(0);
-    lstore(0);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < nkt; kt++) {
-    const bool more = kt + 1 < nkt;
-    if (more) gload(kt + 1);
-    compute(kt & 1);
-    if (more) lstore((kt + 1) & 1);
-    __syncthreads();
-  }
-
-  // ---- epilogue: lane holds, per 32x32 tile and per q, row m and columns n..n+3
-  const bool vec = ALIGNED;  // host guarantees C alignment / ldc divisibility when ALIGNED
-#pragma unroll
-  for (int i = 0; i < G::TM; i++) {
-    const int m = m0 + wm * G::WTM + i * 32 + (lane & 31);
-#pragma unroll
-    for (int j = 0; j < G::TN; j++) {
-#pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const int n = n0 + wn * G::WTN + j * 32 + 8 * q + 4 * (lane >> 5);
-        decltype(acc[i][j][0] + 0) a4[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        if (vec) EPI::template store4<true>(p, m, n, a4);
-        else EPI::template store4<false>(p, m, n, a4);
-      }
-    }
-  }
-}
-
-// Host-side launcher for one instantiation.
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, bool ALIGNED>
-static hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
-  using G = TileGeometry<T, BM, BN, WAVES_M, WAVES_N>;
-  auto kern = gemm_mfma_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, ALIGNED>;
-  static std::atomic<bool> configured{G::LDS_BYTES <= 64 * 1024};
-  if (const hipError_t e = allow_dynamic_lds_once(configured, kern, G::LDS_BYTES)) return e;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(G::THREADS), G::LDS_BYTES, stream, p, tiles_m, tiles_n);
-  return hipGetLastError();
-}
 
 }  // namespace ac

@@ -1,0 +1,490 @@
+// Tiled MFMA GEMM / implicit-GEMM convolution for operands of any size, pitch and alignment: whatever the
+// direct-to-LDS kernels (gemm_dtl.hpp) do not take.  int8 and bf16, either operand transposed in memory, and
+// convolutions with any channel count.
+//
+// Every 16-byte chunk of an operand tile comes in with ONE vector load, wherever it starts (a vector load takes any
+// byte address; a chunk fetched byte by byte is sixteen loads and as many waits on the address unit, which is what
+// bounded the kernel this one replaces).  A chunk that would reach past the end of its row or of the buffer is loaded
+// from the nearest address at which 16 bytes exist and is shifted and masked in registers on its way into LDS, so no
+// load is conditional and the pipeline never depends on where a tile lies:
+//   K-contiguous operand (A, B^T): rows beyond the extent are clamped to the last row (their products are never
+//     stored); bytes beyond K are zeroed, which only the last K tile has.
+//   K-strided operand (B, A^T): k-rows beyond K are zeroed; the chunk across the row's end is shifted, the bytes that
+//     follow the last column belong to outputs that are never stored.
+//   Convolution input: K is ordered (kh, kw, ci), so the KW * Cin bytes of one kernel row are contiguous in the NHWC
+//     image.  The kernel pads that run to whole chunks (the weight rows of the padding are zeroed, so whatever the
+//     image bytes there are does not matter) and a chunk then lies in one image row: one load, plus a mask where the
+//     window hangs over the left or right edge.
+//
+// global (16 bytes per lane, R tiles ahead in registers) -> LDS (two stages, padded rows) -> MFMA, one barrier per
+// K tile.  The MFMA operands are not swapped: a half-wave then owns 32 consecutive columns of one output row, so even
+// byte stores leave as whole 32-byte pieces whatever the alignment of C.
+//
+// Bound: latency for the sizes that fill the chip once, LDS writes beyond (some 72 bytes per clock and compute unit).
+// Against the byte-guarded kernel, kernel time: bf16 1023 x 1537 x 1021 98.4 -> 18.6 us, int8 1000^3 21.5 -> 9.9,
+// 44 x 316 x 1992 (with a workspace: cut along K, which that kernel never was) 42.1 -> 6.8, both operands transposed
+// 888 x 1368 x 720 20.1 -> 11.1, 7 x 7 stride 2 on eight 224 x 224 x 3 images 69 -> 35, 5 x 5 on one 13 x 13 x 59
+// image 124 -> 20.
+#pragma once
+#include "gemm_dtl.hpp"
+
+namespace ac {
+
+struct __attribute__((packed)) Unaligned16 {
+  v4i v;
+};
+static __device__ __forceinline__ v4i load16_any(const unsigned char* p) { return ((const Unaligned16*)p)->v; }
+
+// What has to happen to a loaded chunk on its way into LDS: shift its bytes down by `s` (up when negative) and keep
+// bytes [lo, hi).  One word: s + 16 | lo << 8 | hi << 16.
+constexpr int CHUNK_AS_IS = 16 | (16 << 16);
+static __device__ __forceinline__ int chunk_fix(int s, int lo, int hi) { return (s + 16) | (lo << 8) | (hi << 16); }
+struct Chunk {
+  uint64_t a, b;
+};
+static __device__ __forceinline__ Chunk chunk_down(Chunk c, int bytes) {  // 0 .. 16; zeros come in at the top
+  const bool big = bytes >= 8;
+  const int n = 8 * (bytes & 7);
+  const uint64_t lo = big ? c.b : c.a, hi = big ? 0 : c.b;
+  const bool all = bytes >= 16;
+  return {all ? 0 : (lo >> n) | ((hi << 1) << (63 - n)), all ? 0 : hi >> n};
+}
+static __device__ __forceinline__ Chunk chunk_up(Chunk c, int bytes) {
+  const bool big = bytes >= 8;
+  const int n = 8 * (bytes & 7);
+  const uint64_t hi = big ? c.a : c.b, lo = big ? 0 : c.a;
+  const bool all = bytes >= 16;
+  return {all ? 0 : lo << n, all ? 0 : (hi << n) | ((lo >> 1) >> (63 - n))};
+}
+// BOTH_ENDS: the fix may shift upwards and cut at the low end (a convolution window over the left edge); otherwise it
+// shifts down only and lo == 0.
+template <bool BOTH_ENDS>
+static __device__ __forceinline__ v4i chunk_apply(v4i v, int fix) {
+  if (fix != CHUNK_AS_IS) {
+    const int s = (fix & 0xff) - 16, lo = (fix >> 8) & 0xff, hi = fix >> 16;
+    Chunk c = {(uint64_t)(unsigned)v[0] | ((uint64_t)(unsigned)v[1] << 32), (uint64_t)(unsigned)v[2] | ((uint64_t)(unsigned)v[3] << 32)};
+    c = chunk_down(c, BOTH_ENDS && s < 0 ? 0 : s);
+    if constexpr (BOTH_ENDS) c = chunk_up(c, s < 0 ? -s : 0);
+    const Chunk m = chunk_down({~(uint64_t)0, ~(uint64_t)0}, 16 - hi);
+    c.a &= m.a, c.b &= m.b;
+    if constexpr (BOTH_ENDS) {
+      const Chunk l = chunk_up({~(uint64_t)0, ~(uint64_t)0}, lo);
+      c.a &= l.a, c.b &= l.b;
+    }
+    v = (v4i){(int)(unsigned)c.a, (int)(unsigned)(c.a >> 32), (int)(unsigned)c.b, (int)(unsigned)(c.b >> 32)};
+  }
+  return v;
+}
+
+constexpr int RAGGED_KTB = 128;  // bytes of K per tile
+
+// One operand tile.  EXT: tile extent along m (or n).  KC: K-contiguous in memory, tile [EXT][KTB]; otherwise
+// K-strided, tile [KTB / EB k-rows][EXT * EB bytes].  Rows carry 16 bytes of padding, as in the direct reads of
+// TypeI8::read_col / TypeBF16::read_col: both fragment reads are then free of bank conflicts.
+template <class T, int EXT, int THREADS, bool KC>
+struct RaggedTile {
+  static constexpr int EB = T::EB;
+  static constexpr int ROW = KC ? RAGGED_KTB : EXT * EB;
+  static constexpr int ROWS = KC ? EXT : RAGGED_KTB / EB;
+  static constexpr int STRIDE = ROW + 16;
+  static constexpr int BYTES = ROWS * STRIDE;
+  static constexpr int CPR = ROW / 16;              // chunks per row
+  static constexpr int RPP = THREADS / CPR;         // rows per pass of the workgroup
+  static constexpr int IT = ROWS / RPP;             // chunks per thread
+  static_assert(THREADS % CPR == 0 && ROWS % RPP == 0 && IT >= 1, "tile / thread mismatch");
+  static __device__ __forceinline__ void store(unsigned char* tile, int t, const v4i (&reg)[IT]) {
+    const int cc = t % CPR, r0 = t / CPR;
+#pragma unroll
+    for (int i = 0; i < IT; i++) *(v4i*)(tile + (r0 + i * RPP) * STRIDE + cc * 16) = reg[i];
+  }
+  // MFMA operand: rows (columns) off .. off + 31 of the tile, this lane's K bytes kb .. kb + 15
+  static __device__ __forceinline__ v4i fragment(const unsigned char* tile, int off, int kb, int lane) {
+    if constexpr (KC) return *(const v4i*)(tile + (off + (lane & 31)) * STRIDE + kb);
+    else return T::read_col(tile, STRIDE, kb / EB, (off + 16 * ((lane >> 4) & 1)) * EB, lane);
+  }
+};
+
+// Source of a matrix operand (see the head of the file).
+template <class T, int EXT, int THREADS, bool KC>
+struct RaggedMatrix {
+  using Tile = RaggedTile<T, EXT, THREADS, KC>;
+  static constexpr int EB = T::EB, IT = Tile::IT;
+  const unsigned char *base, *last;  // first byte of the matrix, last address with 16 bytes behind it (the launcher makes sure there is one)
+  const unsigned char* ptr[IT];      // this thread's chunks of the next tile to load
+  int64_t step;                      // bytes from one K tile to the next
+  int kb, kbytes;                    // KC: byte of K of this thread's chunk in the next tile; bytes of K
+  int k, K;                          // !KC: k-row of its first chunk in the next tile; K
+  int edge;                          // !KC: the fix of this thread's column (the same for every k-row)
+
+  __device__ __forceinline__ void init(const void* p, int64_t ld_elems, int origin, int extent, int K_, int kt0, int t) {
+    base = (const unsigned char*)p;
+    const int64_t ld = ld_elems * EB;
+    const int cc = t % Tile::CPR, r0 = t / Tile::CPR;
+    K = K_, kbytes = K_ * EB;
+    kb = k = 0, edge = CHUNK_AS_IS;
+    if constexpr (KC) {
+      last = base + (int64_t)(extent - 1) * ld + kbytes - 16;
+      step = RAGGED_KTB;
+      kb = kt0 * RAGGED_KTB + cc * 16;
+#pragma unroll
+      for (int i = 0; i < IT; i++) {
+        const int row = origin + r0 + i * Tile::RPP;
+        ptr[i] = base + (int64_t)(row < extent ? row : extent - 1) * ld + kb;
+      }
+    } else {
+      last = base + (int64_t)(K_ - 1) * ld + (int64_t)extent * EB - 16;
+      step = (int64_t)(RAGGED_KTB / EB) * ld;
+      k = kt0 * (RAGGED_KTB / EB) + r0;
+      int64_t col = (int64_t)origin * EB + cc * 16;
+      const int64_t over = col + 16 - (int64_t)extent * EB;
+      if (over >= 16) col = 0;  // outside the matrix: any column does
+      else if (over > 0 && col >= over) edge = chunk_fix((int)over, 0, 16), col -= over;
+      // over > col: a row of fewer than 16 bytes, whose 16 bytes reach into the next row (or, at the end, see guarded())
+#pragma unroll
+      for (int i = 0; i < IT; i++) ptr[i] = base + (int64_t)(k + i * Tile::RPP) * ld + col;
+    }
+  }
+  // 16 bytes at an address that need not have 16 bytes behind it
+  __device__ __forceinline__ v4i guarded(const unsigned char* p, int lo, int hi, int& fix) const {
+    const unsigned char* q = p > last ? last : p;
+    const int64_t s = p - q;  // 16 and more only for a chunk of which nothing is kept
+    fix = s >= 16 ? chunk_fix(0, 0, 0) : chunk_fix((int)s, lo, hi);
+    return load16_any(q);
+  }
+  // the next tile in order, which must lie inside K with every row of it at least 16 bytes long
+  __device__ __forceinline__ void load_whole(v4i (&reg)[IT]) {
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      reg[i] = load16_any(ptr[i]);
+      ptr[i] += step;
+    }
+    if constexpr (KC) kb += RAGGED_KTB;
+    else k += RAGGED_KTB / EB;
+  }
+  // any tile
+  __device__ __forceinline__ void load(v4i (&reg)[IT], int (&fix)[IT]) {
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      if constexpr (KC) {
+        const int valid = kbytes - kb;
+        reg[i] = guarded(valid > 0 ? ptr[i] : base, 0, valid < 0 ? 0 : (valid < 16 ? valid : 16), fix[i]);
+      } else {
+        const bool in = k + i * Tile::RPP < K;
+        reg[i] = guarded(in ? ptr[i] : base, 0, in ? 16 : 0, fix[i]);
+        // the shift of the row's last chunk; it was loaded 16 bytes before the row's end, which is never beyond `last`
+        if (in && edge != CHUNK_AS_IS) fix[i] = edge;
+      }
+      ptr[i] += step;
+    }
+    if constexpr (KC) kb += RAGGED_KTB;
+    else k += RAGGED_KTB / EB;
+  }
+};
+
+// K of a convolution as the kernel walks it: KH runs of KW * Cin bytes, each padded to whole chunks.
+static __host__ __device__ __forceinline__ int conv_run(const GemmParams& p) { return p.KW * p.Cin; }
+static __host__ __device__ __forceinline__ int conv_run_padded(const GemmParams& p) { return p.Cin > 0 ? (p.KW * p.Cin + 15) & ~15 : 16; }
+
+// Position (kh, r) of a K index inside that walk, advanced by one K tile at a time without a division.
+struct ConvWalk {
+  int kh, r, dkh, dr, runp;
+  __device__ __forceinline__ void init(int kp, int runp_) {
+    runp = runp_;
+    kh = kp / runp, r = kp - kh * runp;
+    dkh = RAGGED_KTB / runp, dr = RAGGED_KTB - dkh * runp;
+  }
+  __device__ __forceinline__ void next() {
+    kh += dkh, r += dr;
+    if (r >= runp) r -= runp, kh++;
+  }
+};
+
+// Source of the A operand of a convolution: the NHWC input.
+template <int EXT, int THREADS>
+struct RaggedImage {
+  using Tile = RaggedTile<TypeI8, EXT, THREADS, true>;
+  static constexpr int IT = Tile::IT;
+  const unsigned char* in;
+  int base[IT];     // byte of (image, ih0, iw0, 0), possibly outside the image on its own
+  int ih0[IT];      // far outside the image for a row beyond M
+  int left[IT];     // bytes of a kernel row that hang over the left edge (<= 0: none)
+  int right[IT];    // bytes from the window's first column to the right edge
+  int pitch, H, total, KH;
+  ConvWalk w;
+
+  // a distance that is only ever compared with positions inside a kernel row (below 2^29 + 16)
+  static __device__ __forceinline__ int bounded(int64_t d) {
+    const int64_t lim = 1 << 30;
+    return (int)(d > lim ? lim : (d < -lim ? -lim : d));
+  }
+  __device__ __forceinline__ void init(const GemmParams& p, int m0, int kt0, int t) {
+    in = (const unsigned char*)p.A;
+    pitch = p.W * p.Cin, H = p.H, total = p.a_bytes, KH = p.KH;
+    const int cc = t % Tile::CPR, r0 = t / Tile::CPR;
+    w.init(kt0 * RAGGED_KTB + cc * 16, conv_run_padded(p));
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      const int m = m0 + r0 + i * Tile::RPP;
+      const unsigned mm = m < p.M ? (unsigned)m : 0u;
+      const unsigned q = mm / (unsigned)p.OW, img = q / (unsigned)p.OH;
+      const int ow = (int)(mm - q * p.OW), oh = (int)(q - img * p.OH);
+      const int iw0 = ow * p.stride - p.pad, ih = oh * p.stride - p.pad;
+      ih0[i] = m < p.M ? ih : -(1 << 24);
+      left[i] = bounded(-(int64_t)iw0 * p.Cin);
+      right[i] = bounded((int64_t)(p.W - iw0) * p.Cin);
+      base[i] = (((int)img * p.H + ih) * p.W + iw0) * p.Cin;
+    }
+  }
+  __device__ __forceinline__ void load(v4i (&reg)[IT], int (&fix)[IT]) {
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      const int ih = ih0[i] + w.kh;
+      const int g = base[i] + w.kh * pitch + w.r;
+      int lo = left[i] - w.r, hi = right[i] - w.r;  // the bytes of the chunk inside the image row
+      const bool in_row = (unsigned)ih < (unsigned)H && w.kh < KH && lo < 16 && hi > 0;
+      lo = lo < 0 ? 0 : lo;
+      hi = hi > 16 ? 16 : hi;
+      int q = g < 0 ? 0 : g;
+      q = q > total - 16 ? total - 16 : q;  // the launcher makes sure that there are 16 bytes
+      reg[i] = load16_any(in + (unsigned)(in_row ? q : 0));
+      fix[i] = in_row ? chunk_fix(g - q, lo, hi) : chunk_fix(0, 0, 0);
+    }
+    w.next();
+  }
+};
+
+// Source of the weights of a convolution: a K x N matrix whose rows are picked along the padded walk.
+template <int EXT, int THREADS>
+struct RaggedWeights {
+  using Tile = RaggedTile<TypeI8, EXT, THREADS, false>;
+  static constexpr int IT = Tile::IT;
+  RaggedMatrix<TypeI8, EXT, THREADS, false> m;  // column handling, guarded loads
+  ConvWalk w[IT];
+  int64_t ld;
+  int run, KH, col;
+
+  __device__ __forceinline__ void init(const GemmParams& p, int n0, int kt0, int t) {
+    m.init(p.B, p.ldb, n0, p.N, p.K, 0, t);
+    ld = p.ldb, run = conv_run(p), KH = p.KH;
+    col = (int)(m.ptr[0] - m.base - (int64_t)(t / Tile::CPR) * ld);  // this thread's column after clamping and shifting
+#pragma unroll
+    for (int i = 0; i < IT; i++) w[i].init(kt0 * RAGGED_KTB + t / Tile::CPR + i * Tile::RPP, conv_run_padded(p));
+  }
+  __device__ __forceinline__ void load(v4i (&reg)[IT], int (&fix)[IT]) {
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      const bool in = w[i].kh < KH && w[i].r < run;
+      reg[i] = m.guarded(in ? m.base + (int64_t)(w[i].kh * run + w[i].r) * ld + col : m.base, 0, in ? 16 : 0, fix[i]);
+      if (in && m.edge != CHUNK_AS_IS) fix[i] = m.edge;
+      w[i].next();
+    }
+  }
+};
+
+// AKC / BKC: A (B) is K-contiguous in memory: plain A and B^T are, plain B and A^T are not.  CONV: A is the NHWC input
+// and B the weights of a convolution.  R: K tiles in flight in registers.
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV, int R>
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(const GemmParams p, const int tiles_m, const int tiles_n) {
+  constexpr int THREADS = 64 * WAVES_M * WAVES_N;
+  constexpr int EB = T::EB;
+  using SA = std::conditional_t<CONV, RaggedImage<BM, THREADS>, RaggedMatrix<T, BM, THREADS, AKC>>;
+  using SB = std::conditional_t<CONV, RaggedWeights<BN, THREADS>, RaggedMatrix<T, BN, THREADS, BKC>>;
+  using TA = typename SA::Tile;
+  using TB = typename SB::Tile;
+  constexpr int TM = BM / WAVES_M / 32, TN = BN / WAVES_N / 32, STAGE = TA::BYTES + TB::BYTES;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int ntiles = tiles_m * tiles_n;
+  const int kbytes = CONV ? p.KH * conv_run_padded(p) : p.K * EB;
+  const int nkt_total = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
+  // tiles before this one lie inside K and (K-strided operands) have rows of 16 bytes and more: unconditional loads
+  const bool long_rows = (AKC || (int64_t)p.M * EB >= 16) && (BKC || (int64_t)p.N * EB >= 16);
+  const int nkt_whole = CONV || !long_rows ? 0 : kbytes / RAGGED_KTB;
+
+  for (int64_t item = blockIdx.x; item < (int64_t)ntiles * p.splits; item += gridDim.x) {
+    const int split = (int)(item / ntiles);
+    int tm, tn;
+    tile_coords((int)(item - (int64_t)split * ntiles), ntiles, tiles_m, tiles_n, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int kt0 = p.splits > 1 ? split * p.kt_per_split : 0;
+    const int nkt = p.splits > 1 && nkt_total - kt0 > p.kt_per_split ? p.kt_per_split : nkt_total - kt0;
+
+    SA a;
+    SB b;
+    if constexpr (CONV) {
+      a.init(p, m0, kt0, t);
+      b.init(p, n0, kt0, t);
+    } else {
+      a.init(p.A, p.lda, m0, p.M, p.K, kt0, t);
+      b.init(p.B, p.ldb, n0, p.N, p.K, kt0, t);
+    }
+    typename T::accv acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) acc[i][j] = T::zero();
+
+    v4i ra[R][SA::IT], rb[R][SB::IT];
+    int fa[R][SA::IT], fb[R][SB::IT];
+    auto stage_rt = [&](int buf, int s) {  // register set s (a constant after unrolling) -> LDS
+#pragma unroll
+      for (int i = 0; i < SA::IT; i++) ra[s][i] = chunk_apply<CONV>(ra[s][i], fa[s][i]);
+#pragma unroll
+      for (int i = 0; i < SB::IT; i++) rb[s][i] = chunk_apply<false>(rb[s][i], fb[s][i]);
+      TA::store(smem + buf * STAGE, t, ra[s]);
+      TB::store(smem + buf * STAGE + TA::BYTES, t, rb[s]);
+    };
+    auto stage_whole = [&](int buf, auto sc) {  // a whole tile: only the last chunk of a K-strided row needs its shift
+      constexpr int S = decltype(sc)::value;
+      if constexpr (!CONV && !AKC) {
+#pragma unroll
+        for (int i = 0; i < SA::IT; i++) ra[S][i] = chunk_apply<false>(ra[S][i], a.edge);
+      }
+      if constexpr (!CONV && !BKC) {
+#pragma unroll
+        for (int i = 0; i < SB::IT; i++) rb[S][i] = chunk_apply<false>(rb[S][i], b.edge);
+      }
+      TA::store(smem + buf * STAGE, t, ra[S]);
+      TB::store(smem + buf * STAGE + TA::BYTES, t, rb[S]);
+    };
+    auto multiply = [&](int buf) {
+      const unsigned char* As = smem + buf * STAGE;
+      const unsigned char* Bs = As + TA::BYTES;
+#pragma unroll
+      for (int ks = 0; ks < RAGGED_KTB / 32; ks++) {
+        const int kb = ks * 32 + (lane >> 5) * 16;
+        v4i af[TM], bf[TN];
+#pragma unroll
+        for (int i = 0; i < TM; i++) af[i] = TA::fragment(As, (wm * TM + i) * 32, kb, lane);
+#pragma unroll
+        for (int j = 0; j < TN; j++) bf[j] = TB::fragment(Bs, (wn * TN + j) * 32, kb, lane);
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++) acc[i][j] = T::mfma(af[i], bf[j], acc[i][j]);
+      }
+    };
+    int kt = 0, buf = 0;
+    const int whole = nkt_whole - kt0 < nkt ? nkt_whole - kt0 : nkt;  // whole tiles of this slice, from its first
+    auto fetch_whole = [&](auto sc) {
+      constexpr int S = decltype(sc)::value;
+      if constexpr (!CONV) {  // (a convolution has no whole tiles in this sense)
+        a.load_whole(ra[S]);
+        b.load_whole(rb[S]);
+#pragma unroll
+        for (int i = 0; i < SA::IT; i++) fa[S][i] = a.edge;
+#pragma unroll
+        for (int i = 0; i < SB::IT; i++) fb[S][i] = b.edge;
+      }
+    };
+    if (whole >= R) {
+      for_each_stage(fetch_whole, std::make_integer_sequence<int, R>{});
+    } else {
+#pragma unroll
+      for (int s = 0; s < R; s++) {
+        a.load(ra[s], fa[s]);
+        b.load(rb[s], fb[s]);
+      }
+    }
+    // Steady trips: tile kt + R is whole too, so its loads are plain and the fixes are constants of the thread.
+    if constexpr (!CONV) {
+      for (; kt + 2 * R - 1 < whole; kt += R) {
+        for_each_stage([&](auto sc) {
+          stage_whole(buf, sc);
+          fetch_whole(sc);
+          block_sync();
+          multiply(buf);
+          buf ^= 1;
+        }, std::make_integer_sequence<int, R>{});
+      }
+    }
+    // The rest.  Tiles beyond the last are requested like any other (nothing of them is kept): a request that depended
+    // on the tile would make every wait below drain all of them.
+    for (;;) {
+#pragma unroll
+      for (int s = 0; s < R; s++) {
+        if (kt >= nkt) goto multiplied;
+        stage_rt(buf, s);
+        a.load(ra[s], fa[s]);
+        b.load(rb[s], fb[s]);
+        block_sync();
+        multiply(buf);
+        buf ^= 1;
+        kt++;
+      }
+    }
+  multiplied:
+    {
+    typename EPI::Pre pre = {};
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) EPI::tile(p, m0 + (wm * TM + i) * 32, n0 + (wn * TN + j) * 32, acc[i][j], lane, split, pre);
+    }
+    block_sync();  // every wave has read its last fragments before the next item's tiles arrive
+  }
+}
+
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV>
+static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
+  constexpr int THREADS = 64 * WAVES_M * WAVES_N, R = CONV ? 2 : 3;
+  constexpr int LDS = 2 * (RaggedTile<T, BM, THREADS, AKC>::BYTES + RaggedTile<T, BN, THREADS, BKC>::BYTES);
+  auto kern = gemm_ragged_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AKC, BKC, CONV, R>;
+  static std::atomic<bool> configured{LDS <= 64 * 1024};
+  if (const hipError_t e = allow_dynamic_lds_once(configured, kern, LDS)) return e;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  const int64_t items = (int64_t)tiles_m * tiles_n * p.splits;
+  const unsigned grid = (unsigned)(items < (1 << 20) ? items : (1 << 20));  // beyond that the workgroups walk over the items
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, p, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+// An operand of fewer than 16 bytes in all has no chunk to load: one output per thread.  (A matrix of that size has
+// K < 16, a convolution input that many values in all, so an output is a handful of products.)
+template <class T, class EPI, bool AKC, bool BKC, bool CONV>
+__global__ void __launch_bounds__(256) gemm_tiny_kernel(const GemmParams p) {
+  typedef std::conditional_t<T::EB == 1, int, float> val;
+  typedef std::conditional_t<T::EB == 1, int8_t, __bf16> elem;
+  const elem *A = (const elem*)p.A, *B = (const elem*)p.B;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < (int64_t)p.M * p.N; i += (int64_t)gridDim.x * 256) {
+    const int m = (int)(i / p.N), n = (int)(i - (int64_t)m * p.N);
+    val s = 0;
+    if constexpr (CONV) {
+      const int q = m / p.OW, ow = m - q * p.OW, img = q / p.OH, oh = q - img * p.OH;
+      const int ih0 = oh * p.stride - p.pad, iw0 = ow * p.stride - p.pad;
+      for (int ih = ih0 < 0 ? 0 : ih0; ih < p.H && ih - ih0 < p.KH; ih++)
+        for (int iw = iw0 < 0 ? 0 : iw0; iw < p.W && iw - iw0 < p.KW; iw++)
+          for (int ci = 0; ci < p.Cin; ci++)
+            s += (val)A[((int64_t)(img * p.H + ih) * p.W + iw) * p.Cin + ci] * (val)B[(int64_t)(((ih - ih0) * p.KW + iw - iw0) * p.Cin + ci) * p.ldb + n];
+    } else {
+      for (int k = 0; k < p.K; k++) s += (val)A[AKC ? (int64_t)m * p.lda + k : (int64_t)k * p.lda + m] * (val)B[BKC ? (int64_t)n * p.ldb + k : (int64_t)k * p.ldb + n];
+    }
+    EPI::one(p, m, n, s);
+  }
+}
+template <class T, bool AKC, bool BKC, bool CONV>
+static bool ragged_tiny(const GemmParams& p) {
+  auto bytes = [&](bool kc, int64_t ld, int64_t extent) { return ((kc ? extent - 1 : p.K - 1) * ld + (kc ? p.K : extent)) * T::EB; };
+  return p.K > 0 && ((CONV ? (int64_t)p.a_bytes : bytes(AKC, p.lda, p.M)) < 16 || bytes(BKC, p.ldb, p.N) < 16);
+}
+
+// Tile of the ragged kernel: 128 x 128 (eight waves) once such tiles fill half the chip, 64 x 64 otherwise.
+static inline int ragged_tile(int32_t M, int32_t N) {
+  return M >= 96 && N >= 96 && (int64_t)((M + 127) / 128) * ((N + 127) / 128) >= 128 ? 128 : 64;
+}
+template <class T, class EPI, bool AKC, bool BKC, bool CONV = false>
+static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t stream) {
+  if constexpr (!std::is_same_v<EPI, EpiloguePartialI32>) {  // (K slices: K is deep)
+    if (ragged_tiny<T, AKC, BKC, CONV>(p)) {
+      const int64_t blocks = ((int64_t)p.M * p.N + 255) / 256;
+      hipLaunchKernelGGL((gemm_tiny_kernel<T, EPI, AKC, BKC, CONV>), dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, stream, p);
+      return hipGetLastError();
+    }
+  }
+  return tile >= 128 ? launch_ragged_tile<T, EPI, 128, 128, 2, 4, AKC, BKC, CONV>(p, stream)
+                     : launch_ragged_tile<T, EPI, 64, 64, 2, 2, AKC, BKC, CONV>(p, stream);
+}
+
+}  // namespace ac

@@ -1,0 +1,99 @@
+"""GPU parity of the kernel for operands of any size, pitch and alignment, at the sizes where its loads change form:
+chunk, tile and pipeline edges of every dimension, rows and whole operands shorter than a 16-byte chunk, views at odd
+addresses, windows that hang over every edge of an image.  int8 bit for bit; bf16 within 4 (K + 2) 2^-24 of the sum of
+magnitudes per element (exact products, K fp32 additions)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev, host
+from paper_2505_18574_amd import inputs, ops
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): one under / over a chunk, a tile of 64 and of 128, whole K tiles (128 bytes), 3 and 5 tiles in flight
+SIZES = [(1, 1, 1), (3, 2, 1), (1, 5, 3), (2, 7, 15), (5, 16, 17), (63, 15, 127), (65, 17, 128), (64, 65, 129), (33, 63, 383),
+         (31, 129, 385), (7, 127, 641), (129, 33, 769), (200, 50, 1000), (1, 300, 77), (300, 1, 1111), (1441, 1003, 97)]
+
+
+def odd_view(a):
+    """The array in device memory one element off an aligned address, rows an odd pitch apart."""
+    buf = torch.zeros((a.shape[0], a.shape[1] + 3), dtype=dev(a).dtype, device="cuda")
+    view = buf[:, 1:1 + a.shape[1]]
+    view.copy_(dev(a))
+    return view
+
+
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_int8_every_layout(M, N, K):
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=M + 3 * N + 7 * K)
+    want = oracle.gemm_i8(A, B, bias, 9, 0)
+    At, Bt = np.zeros((K, M), np.int8) + A.T, np.zeros((N, K), np.int8) + B.T
+    for put in (dev, odd_view):
+        for ta, tb in ((False, False), (True, False), (False, True), (True, True)):
+            C = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+            ops.ac_gemm_i8_t(put(At if ta else A), put(Bt if tb else B), dev(bias), C, 9, 0, trans_a=ta, trans_b=tb)
+            np.testing.assert_array_equal(host(C), want, err_msg=f"{put.__name__} ta={ta} tb={tb}")
+        raw = torch.full((M, N), 33, dtype=torch.int32, device="cuda")
+        ops.ac_gemm_i8_acc32(put(A), put(B), dev(bias), raw)
+        np.testing.assert_array_equal(host(raw), A.astype(np.int64) @ B.astype(np.int64) + bias)
+
+
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_bf16(M, N, K):
+    A, B = inputs.gemm_bf16_inputs(M, N, K, seed=M + 3 * N + 7 * K)
+    want = oracle.gemm_bf16(A, B)
+    mag = np.abs(inputs.bf16_bits_to_f32(A).astype(np.float64)) @ np.abs(inputs.bf16_bits_to_f32(B).astype(np.float64))
+    for put in (dev, odd_view):
+        C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ops.ac_gemm_bf16(put(A), put(B), C)
+        assert (np.abs(host(C) - want) <= 4.0 * (K + 2) * 2.0 ** -24 * mag + 1e-30).all(), put.__name__
+
+
+def test_bf16_neighbours_of_a_row_stay_out():
+    """The bytes that follow a row (of K and of N) in memory are infinities: none may reach a product."""
+    M, N, K = 70, 75, 203
+    A, B = inputs.gemm_bf16_inputs(M, N, K, seed=5)
+    Ai = torch.full((M, K + 9), float("inf"), dtype=torch.bfloat16, device="cuda")
+    Bi = torch.full((K + 9, N + 9), float("inf"), dtype=torch.bfloat16, device="cuda")
+    Ai[:, 3:3 + K].copy_(dev(A))
+    Bi[4:4 + K, 3:3 + N].copy_(dev(B))
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    ops.ac_gemm_bf16(Ai[:, 3:3 + K], Bi[4:4 + K, 3:3 + N], C)
+    got, want = host(C), oracle.gemm_bf16(A, B)
+    assert np.isfinite(got).all() and np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("M,N,K", [(44, 316, 1992), (17, 33, 5001), (49, 1000, 2305)])
+def test_int8_cut_along_k(M, N, K):
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=K)
+    want = oracle.gemm_i8(A, B, bias, 12, 1)
+    ws = torch.full((ops.ac_gemm_i8_workspace_bytes(M, N, K),), 0x5A, dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 0
+    C = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+    ops.ac_gemm_i8(dev(A), dev(B), dev(bias), C, 12, 1, workspace=ws)
+    np.testing.assert_array_equal(host(C), want)
+
+
+@pytest.mark.parametrize("Nb,H,W,Cin,Cout,KH,KW,stride,pad", [
+    (2, 37, 41, 3, 64, 7, 7, 2, 3),     # few channels: windows over every edge
+    (1, 5, 3, 1, 1, 3, 3, 1, 1),        # an image of 15 bytes
+    (1, 4, 4, 1, 17, 3, 3, 1, 1),       # an image of exactly one chunk
+    (3, 2, 2, 1, 5, 2, 2, 1, 0),        # a weight array of 20 bytes, rows of 5
+    (1, 1, 1, 3, 8, 5, 5, 1, 2),        # everything but one tap is padding
+    (2, 9, 9, 4, 16, 4, 4, 1, 0),       # runs of exactly one chunk
+    (2, 9, 9, 17, 31, 3, 3, 2, 1),      # runs of three chunks and three bytes
+    (1, 20, 20, 16, 32, 7, 7, 1, 3),    # more than 32 taps
+    (2, 13, 11, 59, 57, 5, 5, 1, 2),    # a run longer than two K tiles
+    (1, 6, 6, 2, 100, 1, 1, 1, 0),      # 1 x 1, a plain product with K = 2
+    (4, 40, 40, 5, 130, 3, 3, 1, 1),    # tiles of 128
+])
+def test_convolutions(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
+    x, w, b = inputs.conv_i8_inputs(Nb, H, W, Cin, Cout, KH, KW, seed=H * W + Cin)
+    want = oracle.conv2d_i8(x, w, b, stride, pad, 8, 1)
+    nbytes = ops.ac_gemm_i8_workspace_bytes(want.shape[0] * want.shape[1] * want.shape[2], Cout, KH * KW * Cin)
+    for ws in (None, torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None):
+        out = torch.full(want.shape, 17, dtype=torch.int8, device="cuda")
+        ops.ac_conv2d_i8(dev(x), dev(w), dev(b), out, stride, pad, 8, 1, workspace=ws)
+        np.testing.assert_array_equal(host(out), want)
