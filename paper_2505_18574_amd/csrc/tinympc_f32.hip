@@ -4,60 +4,22 @@
 // Per problem the operation moves nx + horizon * nu floats in and horizon * nu out (plus the optional state
 // trajectory): with the paper's sizes (12, 4, 5) that is 208 bytes (496 with the trajectory) for 2400 flop, so HBM
 // bounds it.  Two families: the paper's sizes run on the matrix units, sixteen problems to a 16 x 16 product
-// (tinympc_forward_mfma_kernel); any other size, and unaligned arrays, on the vector ALU with one lane per problem,
-// its state vector in registers and the three shared matrices read from LDS with wave-uniform addresses.
+// (tinympc_forward_mfma_kernel); any other size, and unaligned arrays, on the vector ALU with four lanes per problem
+// (tinympc_forward_quad_kernel).
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace ac {
 
-template <int NX, int NU>
-__global__ void __launch_bounds__(256) tinympc_forward_kernel(const TinyMpcParams p) {
-  __shared__ float sA[NX * NX], sB[NX * NU], sK[NU * NX];
-  for (int i = threadIdx.x; i < NX * NX; i += 256) sA[i] = p.Adyn[i];
-  for (int i = threadIdx.x; i < NX * NU; i += 256) sB[i] = p.Bdyn[i];
-  for (int i = threadIdx.x; i < NU * NX; i += 256) sK[i] = p.Kinf[i];
-  __syncthreads();
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b >= p.batch) return;
-  float x[NX], u[NU], xn[NX];
-  const float* x0 = p.x0 + b * NX;
-#pragma unroll
-  for (int r = 0; r < NX; r++) x[r] = x0[r];
-  float* xo = p.x_out ? p.x_out + b * (p.horizon + 1) * NX : nullptr;
-  if (xo) {
-#pragma unroll
-    for (int r = 0; r < NX; r++) xo[r] = x[r];
-  }
-  const float* d = p.d + b * p.horizon * NU;
-  float* uo = p.u + b * p.horizon * NU;
-  for (int i = 0; i < p.horizon; i++) {
-#pragma unroll
-    for (int r = 0; r < NU; r++) {
-      float s = 0.f;
-#pragma unroll
-      for (int c = 0; c < NX; c++) s = __builtin_fmaf(sK[r * NX + c], x[c], s);
-      u[r] = -s - d[i * NU + r];
-      uo[i * NU + r] = u[r];
-    }
-    // the state after the last control is not needed for u; it is only produced when the trajectory is asked for
-    if (i + 1 < p.horizon || xo) {
-#pragma unroll
-      for (int r = 0; r < NX; r++) {
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < NX; c++) s = __builtin_fmaf(sA[r * NX + c], x[c], s);
-        float t = 0.f;
-#pragma unroll
-        for (int c = 0; c < NU; c++) t = __builtin_fmaf(sB[r * NU + c], u[c], t);
-        xn[r] = s + t;
-      }
-#pragma unroll
-      for (int r = 0; r < NX; r++) x[r] = xn[r];
-      if (xo) {
-#pragma unroll
-        for (int r = 0; r < NX; r++) xo[(i + 1) * NX + r] = x[r];
-      }
-    }
+// v of lane k of every quad
+static __device__ __forceinline__ float quad_broadcast(float v, int k) {
+  const int i = __builtin_bit_cast(int, v);
+  switch (k) {  // constant after unrolling: the DPP control is an immediate
+    case 0: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x00, 0xF, 0xF, true));
+    case 1: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x55, 0xF, 0xF, true));
+    case 2: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xAA, 0xF, 0xF, true));
+    default: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xFF, 0xF, 0xF, true));
   }
 }
 
@@ -70,7 +32,7 @@ __global__ void __launch_bounds__(256) tinympc_forward_kernel(const TinyMpcParam
 // four registers a lane RECEIVES from one product (rows 4 g + 0..3 of its problem) are exactly the four values it
 // FEEDS to the next, with no data movement in between; only the matrix operands are laid out to match (lane
 // (m, g) holds column 4 g + c of row m for instruction c: four registers per matrix for the whole kernel).
-// A wave owns 64 consecutive problems as four such column blocks; lanes g < 3 carry x, lanes g == 3 carry d and u.
+// A wave owns NB such column blocks of consecutive problems; lanes g < 3 carry x, lanes g == 3 carry d and u.
 // Some 500 instructions per 64 problems, 80 of them MFMAs, against 2100 on the vector ALU with one problem per
 // lane.  Sums are fp32 throughout, in the matrix unit's order and with the closed-loop matrix formed first: equal to
 // the recurrence in exact arithmetic, a few ulp from the ascending chains of the other kernels in fp32.
@@ -78,156 +40,144 @@ __global__ void __launch_bounds__(256) tinympc_forward_kernel(const TinyMpcParam
 // Memory: the inputs and outputs of a wave's 64 problems are four contiguous runs (x0 3 KB, d and u 5 KB each, the
 // trajectory 18 KB), but a lane's share of them is 16 bytes per step: stored as produced, a memory line is completed
 // by instructions a whole step apart and leaves the L2 half written in between (58 us for 262144 problems; 39 us
-// with the results held in registers and stored back to back at the end).  With HC > 0 (horizon HC) d is
-// therefore loaded, and u and the trajectory are stored, as whole runs of 16 bytes per lane through a wave-private
-// LDS window (u overwrites d in place, step by step; the trajectory goes block by block through a second window).
-// HC == 0: any horizon, per-lane loads and stores as the results are produced.
-constexpr int TMPC_XPITCH = 304;                         // LDS bytes per problem of a trajectory block (288 + padding)
-constexpr int TMPC_WAVE_LDS = 64 * 80 + 16 * TMPC_XPITCH;  // d / u window of 64 problems + trajectory window of 16
+// with the results held in registers and stored back to back at the end).  d is therefore loaded, and u and the
+// trajectory are stored, as whole runs of 16 bytes per lane through a wave-private LDS window (u overwrites d in place,
+// step by step; the trajectory goes block by block through a second window).  The results of a block stay in registers
+// until then, which fixes the horizon at compile time: the paper's 5.
+constexpr int TMPC_H = 5;
+constexpr int TMPC_XPITCH = 304;  // LDS bytes per problem of a trajectory block (288 + padding)
 
-template <bool WITH_X, int HC>
-__global__ void __launch_bounds__(256) tinympc_forward_mfma_kernel(const TinyMpcParams p) {
-  constexpr int NX = 12, NU = 4;
-  __shared__ __attribute__((aligned(16))) unsigned char tmpc_lds[HC > 0 ? 4 * TMPC_WAVE_LDS : 16];
+// NB: column blocks (of sixteen problems) per wave; WAVES per workgroup.  Four blocks hide a block's chain of 20 MFMAs behind
+// three others and are right once every compute unit has work; a small batch is one such chain after three memory
+// latencies, and one block to a wave, one wave to a workgroup, shortens the chain and spreads it over the chip (100
+// problems 7.0 -> 4.1 us, 4000 7.6 -> 4.4, up to four such waves per compute unit: 16384 problems, 5.0 us).
+template <bool WITH_X, int NB, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const TinyMpcParams p) {
+  constexpr int NX = 12, NU = 4, H = TMPC_H, PB = 16 * NB;      // PB: problems of a wave-block
+  constexpr int DN = (PB * H + 63) / 64;                        // 16-byte pieces of d per lane
+  constexpr int WAVE_LDS = DN * 1024 + 16 * TMPC_XPITCH;        // d / u window of PB problems + trajectory window of 16
+  __shared__ __attribute__((aligned(16))) unsigned char tmpc_lds[WAVES * WAVE_LDS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4;
-  // Wave-block k is problems 64 k .. 64 k + 63; a wave takes blocks first, first + stride, ... (HC > 0: persistent
+  // Wave-block k is problems PB k .. PB k + PB - 1; a wave takes blocks first, first + stride, ... (persistent
   // waves that request their next block's inputs before they compute and store the current one, so that loads,
   // products and stores of different blocks overlap; with one block per wave the whole chip loads, then
   // multiplies, then stores: 38 us for 262144 problems).
-  const int64_t nblk = (p.batch + 63) / 64, stride = (int64_t)gridDim.x * 4;
-  int64_t blk = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t nblk = (p.batch + PB - 1) / PB, stride = (int64_t)gridDim.x * WAVES;
+  int64_t blk = (int64_t)blockIdx.x * WAVES + wave;
   if (blk >= nblk) return;  // whole waves leave; no wave waits for another
-  const int H = HC > 0 ? HC : p.horizon;
-  unsigned char* dwin = tmpc_lds + wave * TMPC_WAVE_LDS;  // [64 problems][HC][4] floats: d, then u
-  unsigned char* xwin = dwin + 64 * 80;                   // [16 problems][TMPC_XPITCH]
+  unsigned char* dwin = tmpc_lds + wave * WAVE_LDS;  // [PB problems][H][4] floats: d, then u
+  unsigned char* xwin = dwin + DN * 1024;            // [16 problems][TMPC_XPITCH]
+
+  // inputs of a block: d as one contiguous run, 16 bytes per lane and instruction, and per column block the
+  // lane's 16 bytes of x0 (lanes past the end re-read the last problem and store nothing).  Every byte is read once
+  // and every result written once, so loads and stores carry the non-temporal hint (262144 problems: 27.0 -> 26.3 us
+  // with the trajectory, 18.7 -> 16.0 us without)
+  v4f din[DN], xin[NB];
+  auto request = [&](int64_t k) {
+    const int left = p.batch - k * PB < PB ? (int)(p.batch - k * PB) : PB;
+    const v4f* src = (const v4f*)(p.d + k * PB * H * NU);
+#pragma unroll
+    for (int j = 0; j < DN; j++) {
+      const int q = j * 64 + lane;
+      din[j] = q < left * H ? __builtin_nontemporal_load(src + q) : (v4f){0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+      const int64_t q = k * PB + 16 * b + n;
+      xin[b] = g < 3 ? __builtin_nontemporal_load((const v4f*)(p.x0 + (q < p.batch ? q : p.batch - 1) * NX + 4 * g)) : (v4f){0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  request(blk);
 
   // matrix operand of instruction c: row m = n, column k = 4 g + c of
   //   M = [ Adyn - Bdyn Kinf   -Bdyn ]     so that   M . [x[i]; d[i]] = [x[i + 1]; u[i]]
   //       [      -Kinf           -I  ]
   // (x[i + 1] = Adyn x[i] + Bdyn u[i] with u[i] = -Kinf x[i] - d[i] substituted; Adyn - Bdyn Kinf is formed here in
-  // fp32, four fused multiply-adds per entry in ascending order)
+  // fp32, four fused multiply-adds per entry in ascending order).  Every lane loads from clamped positions and picks
+  // afterwards: loads behind branches would wait for one another.
   float mat[4];
+  {
+    const int row = n < NX ? n : NX - 1, urow = n < NX ? 0 : n - NX;
+    float bd[NU], ad[4], kf[NU][4];
 #pragma unroll
-  for (int c = 0; c < 4; c++) {
-    const int k = 4 * g + c;
-    float v;
-    if (n < NX && k < NX) {
-      v = p.Adyn[n * NX + k];
+    for (int j = 0; j < NU; j++) bd[j] = p.Bdyn[row * NU + j];
 #pragma unroll
-      for (int j = 0; j < NU; j++) v = __builtin_fmaf(-p.Bdyn[n * NU + j], p.Kinf[j * NX + k], v);
-    } else if (n < NX) {
-      v = -p.Bdyn[n * NU + (k - NX)];
-    } else if (k < NX) {
-      v = -p.Kinf[(n - NX) * NX + k];
-    } else {
-      v = (k - NX == n - NX) ? -1.f : 0.f;
+    for (int c = 0; c < 4; c++) {
+      const int k = g < 3 ? 4 * g + c : c;
+      ad[c] = p.Adyn[row * NX + k];
+#pragma unroll
+      for (int j = 0; j < NU; j++) kf[j][c] = p.Kinf[j * NX + k];
     }
-    mat[c] = v;
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      float closed = ad[c];
+#pragma unroll
+      for (int j = 0; j < NU; j++) closed = __builtin_fmaf(-bd[j], kf[j][c], closed);
+      const float gain = urow == 0 ? kf[0][c] : urow == 1 ? kf[1][c] : urow == 2 ? kf[2][c] : kf[3][c];
+      mat[c] = n < NX ? (g < 3 ? closed : -bd[c]) : (g < 3 ? -gain : (c == urow ? -1.f : 0.f));
+    }
   }
 
-  // inputs of a block: d as one contiguous run, 16 bytes per lane and instruction (HC > 0), and per column block the
-  // lane's 16 bytes of x0 (lanes past the end re-read the last problem and store nothing).  Every byte is read once
-  // and every result written once, so loads and stores carry the non-temporal hint (262144 problems: 27.0 -> 26.3 us
-  // with the trajectory, 18.7 -> 16.0 us without)
-  v4f din[HC > 0 ? HC : 1], xin[4];
-  auto request = [&](int64_t k) {
-    const int left = p.batch - k * 64 < 64 ? (int)(p.batch - k * 64) : 64;
-    if constexpr (HC > 0) {
-      const v4f* src = (const v4f*)(p.d + k * 64 * HC * NU);
+  for (; blk < nblk; blk += stride) {
+    const int nvalid = p.batch - blk * PB < PB ? (int)(p.batch - blk * PB) : PB;
 #pragma unroll
-      for (int j = 0; j < HC; j++) {
-        const int q = j * 64 + lane;
-        din[j] = q < left * HC ? __builtin_nontemporal_load(src + q) : (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < DN; j++) *(v4f*)(dwin + 16 * (j * 64 + lane)) = din[j];
+    v4f z[NB];  // lanes g < 3: x0 rows 4 g .. 4 g + 3; lanes g == 3 take d[0] below
+#pragma unroll
+    for (int b = 0; b < NB; b++) z[b] = xin[b];
+    if (blk + stride < nblk) request(blk + stride);
+    v4f hist[H + 1][NB];  // lanes g < 3: the lane's rows of x[0 .. H]
+#pragma unroll
+    for (int b = 0; b < NB; b++) hist[0][b] = z[b];
+
+    // z = [x[i]; d[i]]: lanes g == 3 take d[i] from the window
+    auto d_of = [&](int b, int i) { return *(const v4f*)(dwin + (16 * b + n) * (H * 16) + i * 16); };
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+      if (g == 3) z[b] = d_of(b, 0);
+#pragma unroll
+    for (int i = 0; i < H; i++) {
+      v4f acc[NB];
+#pragma unroll
+      for (int b = 0; b < NB; b++) acc[b] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; c++)  // the column blocks are independent: their instructions alternate
+#pragma unroll
+        for (int b = 0; b < NB; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(mat[c], z[b][c], acc[b], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        if (g == 3) {  // rows 12..15: u[i], into the place of d[i]; then d[i + 1]
+          *(v4f*)(dwin + (16 * b + n) * (H * 16) + i * 16) = acc[b];
+          if (i + 1 < H) z[b] = d_of(b, i + 1);
+        } else {       // rows 0..11: x[i + 1]
+          z[b] = acc[b];
+          hist[i + 1][b] = acc[b];
+        }
       }
     }
-#pragma unroll
-    for (int b = 0; b < 4; b++) {
-      const int64_t q = k * 64 + 16 * b + n;
-      xin[b] = g < 3 ? __builtin_nontemporal_load((const v4f*)(p.x0 + (q < p.batch ? q : p.batch - 1) * NX + 4 * g)) : (v4f){0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  request(blk);
-  for (; blk < nblk; blk += HC > 0 ? stride : nblk) {
-  const int nvalid = p.batch - blk * 64 < 64 ? (int)(p.batch - blk * 64) : 64;
-  if constexpr (HC > 0) {
-#pragma unroll
-    for (int j = 0; j < HC; j++) *(v4f*)(dwin + 16 * (j * 64 + lane)) = din[j];
-  }
-  v4f z[4];  // lanes g < 3: x0 rows 4 g .. 4 g + 3; lanes g == 3 take d[0] below
-  int64_t prob[4];
-  bool live[4];
-#pragma unroll
-  for (int b = 0; b < 4; b++) {
-    const int64_t q = blk * 64 + 16 * b + n;
-    live[b] = q < p.batch;
-    prob[b] = live[b] ? q : p.batch - 1;
-    z[b] = xin[b];
-  }
-  if (HC > 0 && blk + stride < nblk) request(blk + stride);
-  v4f hist[HC > 0 ? HC + 1 : 1][4];  // HC > 0, lanes g < 3: the lane's rows of x[0 .. HC]
-  if constexpr (HC > 0) {
-#pragma unroll
-    for (int b = 0; b < 4; b++) hist[0][b] = z[b];
-  } else if constexpr (WITH_X) {
-#pragma unroll
-    for (int b = 0; b < 4; b++)
-      if (g < 3 && live[b]) *(v4f*)(p.x_out + prob[b] * (int64_t)(H + 1) * NX + 4 * g) = z[b];  // x[0] = x0
-  }
 
-  // z = [x[i]; d[i]]: lanes g == 3 take d[i] (from the window, or from memory)
-  auto d_of = [&](int b, int i) {
-    if constexpr (HC > 0) return *(const v4f*)(dwin + (16 * b + n) * (HC * 16) + i * 16);
-    else return *(const v4f*)(p.d + (prob[b] * H + i) * NU);
-  };
-#pragma unroll
-  for (int b = 0; b < 4; b++)
-    if (g == 3) z[b] = d_of(b, 0);
-#pragma unroll
-  for (int i = 0; i < H; i++) {
-    v4f acc[4];
-#pragma unroll
-    for (int b = 0; b < 4; b++) acc[b] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 4; c++)  // the four column blocks are independent: their instructions alternate
-#pragma unroll
-      for (int b = 0; b < 4; b++) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(mat[c], z[b][c], acc[b], 0, 0, 0);
-#pragma unroll
-    for (int b = 0; b < 4; b++) {
-      if (g == 3) {  // rows 12..15: u[i], into the place of d[i]; then d[i + 1]
-        if constexpr (HC > 0) *(v4f*)(dwin + (16 * b + n) * (HC * 16) + i * 16) = acc[b];
-        else if (live[b]) *(v4f*)(p.u + (prob[b] * H + i) * NU) = acc[b];
-        if (i + 1 < H) z[b] = d_of(b, i + 1);
-      } else {       // rows 0..11: x[i + 1]
-        z[b] = acc[b];
-        if constexpr (HC > 0) hist[i + 1 <= HC ? i + 1 : 0][b] = acc[b];
-        else if (WITH_X && live[b]) *(v4f*)(p.x_out + (prob[b] * (int64_t)(H + 1) + i + 1) * NX + 4 * g) = acc[b];
-      }
-    }
-  }
-
-  if constexpr (HC > 0) {
     // u: the window, in memory order, 16 bytes per lane (LDS serves a wave's operations in order: the reads below
     // see the writes above without a wait of their own beyond the compiler's)
     {
-      v4f* dst = (v4f*)(p.u + blk * 64 * HC * NU);
-      const int pieces = nvalid * HC;
+      v4f* dst = (v4f*)(p.u + blk * PB * H * NU);
+      const int pieces = nvalid * H;
 #pragma unroll
-      for (int k = 0; k < HC; k++) {
+      for (int k = 0; k < DN; k++) {
         const int q = k * 64 + lane;
         if (q < pieces) __builtin_nontemporal_store(*(const v4f*)(dwin + 16 * q), dst + q);
       }
     }
     if constexpr (WITH_X) {
-      constexpr int XROW = (HC + 1) * NX * 4;  // bytes of trajectory per problem
-      constexpr int PPB = XROW / 16;           // 16-byte pieces per problem
+      constexpr int XROW = (H + 1) * NX * 4;  // bytes of trajectory per problem
+      constexpr int PPB = XROW / 16;          // 16-byte pieces per problem
 #pragma unroll
-      for (int b = 0; b < 4; b++) {
+      for (int b = 0; b < NB; b++) {
         if (g < 3) {
 #pragma unroll
-          for (int i = 0; i <= HC; i++) *(v4f*)(xwin + n * TMPC_XPITCH + i * (NX * 4) + g * 16) = hist[i][b];
+          for (int i = 0; i <= H; i++) *(v4f*)(xwin + n * TMPC_XPITCH + i * (NX * 4) + g * 16) = hist[i][b];
         }
-        v4f* dst = (v4f*)(p.x_out + (blk * 64 + 16 * b) * (int64_t)(HC + 1) * NX);
+        v4f* dst = (v4f*)(p.x_out + (blk * PB + 16 * b) * (int64_t)(H + 1) * NX);
         const int left = nvalid - 16 * b;  // problems of this block that exist
         const int pieces = (left < 0 ? 0 : left > 16 ? 16 : left) * PPB;
 #pragma unroll
@@ -238,94 +188,202 @@ __global__ void __launch_bounds__(256) tinympc_forward_mfma_kernel(const TinyMpc
       }
     }
   }
-  }  // blocks of this wave
 }
 
-// Any 1 <= nx, nu <= 16: same algorithm with run-time sizes (state vectors padded to 16 registers).
-__global__ void __launch_bounds__(256) tinympc_forward_generic_kernel(const TinyMpcParams p) {
-  constexpr int MAXN = 16;
-  __shared__ float sA[MAXN * MAXN], sB[MAXN * MAXN], sK[MAXN * MAXN];
-  const int nx = p.nx, nu = p.nu;
-  for (int i = threadIdx.x; i < nx * nx; i += 256) sA[i] = p.Adyn[i];
-  for (int i = threadIdx.x; i < nx * nu; i += 256) sB[i] = p.Bdyn[i];
-  for (int i = threadIdx.x; i < nu * nx; i += 256) sK[i] = p.Kinf[i];
-  __syncthreads();
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b >= p.batch) return;
-  float x[MAXN], u[MAXN], xn[MAXN];
+// Any 1 <= nx, nu <= 16 and any alignment: the recurrence as written, on the vector ALU, four lanes (a quad) to a
+// problem and sixteen problems to a wave.  Lane q of a quad owns the state rows q + 4 i and the control rows q + 4 j and
+// keeps its rows of the three matrices in registers for the whole kernel (RX = ceil(nx / 4), RU = ceil(nu / 4): at most
+// 192 values); x[c] reaches the quad by a DPP quad broadcast, which all of the lane's row sums share.  Every sum is still
+// one fused multiply-add chain in ascending index order from zero; indices beyond nx / nu add 0 * 0.
+//
+// One lane per problem, which this replaces, keeps the matrices in LDS: one LDS read per multiply-add, and a chain of
+// nx (nx + 2 nu) of both per step that a small batch has nothing to hide behind.  With the trajectory, before -> now:
+// 100 problems of (10, 2, 4) 27.5 -> 4.5 us, of (13, 8, 8) 115 -> 7.0, of (12, 4, 8) 12.0 -> 5.6; 262144 of them 94 -> 28,
+// 563 -> 70 and 101 -> 44 us (5 TB/s: 16, 54 and 39).  Here a step is 4 RX broadcasts and 4 RX (RX + RU) + 4 RU RX multiply-adds, RX + RU of
+// them independent.
+//
+// d comes in and u and the trajectory leave as whole contiguous runs through a wave-private LDS window (u overwrites d
+// in place).  A horizon too long for the window goes through it `chunk` steps at a time, a run per problem.
+// WHOLE: chunk == horizon.
+template <int RX, int RU, bool WHOLE>
+__global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpcParams p, const int window, const int chunk) {
+  extern __shared__ __attribute__((aligned(16))) float tmpc_quad_lds[];
+  const int nx = p.nx, nu = p.nu, H = p.horizon;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int q = lane & 3, pr = lane >> 2;
+  const int64_t nblk = (p.batch + 15) / 16, stride = (int64_t)gridDim.x * waves;
+  const bool traj = p.x_out != nullptr;
+  const int dpitch = chunk * nu, xpitch = (WHOLE ? H + 1 : chunk) * nx;  // floats per problem; x[0] has no place in a chunk
+  float* dwin = tmpc_quad_lds + wave * window;  // [16 problems][chunk][nu]: d, then u (before that: the matrices)
+  float* xwin = dwin + ((16 * dpitch + 3) & ~3);
+  float *dmine = dwin + pr * dpitch, *xmine = xwin + pr * xpitch;
+
+  // The matrices pass through the wave's LDS window, padded with zeros to whole fours, so that a lane picks its rows up
+  // 16 bytes at a time (entry by entry from memory it is 192 loads and their addresses: 16 us of a 21 us launch).
+  float a[RX][4 * RX], k[RU][4 * RX], b[RX][4 * RU];
+  auto rows_of = [&](const float* m, int rows, int cols, auto& reg, auto rc, auto cc) {
+    constexpr int R = decltype(rc)::value, C = decltype(cc)::value, PC = C == 3 ? 4 : C;  // padded size / 4 (columns: a power of two)
+    float v[(16 * R * PC + 63) / 64];
 #pragma unroll
-  for (int r = 0; r < MAXN; r++) x[r] = r < nx ? p.x0[b * nx + r] : 0.f;
-  float* xo = p.x_out ? p.x_out + b * (p.horizon + 1) * nx : nullptr;
-  if (xo) {
-#pragma unroll
-    for (int r = 0; r < MAXN; r++)
-      if (r < nx) xo[r] = x[r];
-  }
-  const float* d = p.d + b * p.horizon * nu;
-  float* uo = p.u + b * p.horizon * nu;
-  for (int i = 0; i < p.horizon; i++) {
-#pragma unroll
-    for (int r = 0; r < MAXN; r++) {
-      u[r] = 0.f;
-      if (r < nu) {
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < MAXN; c++)
-          if (c < nx) s = __builtin_fmaf(sK[r * nx + c], x[c], s);
-        u[r] = -s - d[i * nu + r];
-        uo[i * nu + r] = u[r];
-      }
+    for (int e = 0; e < (16 * R * PC + 63) / 64; e++) {
+      const int i = e * 64 + lane, r = i / (4 * PC), c = i % (4 * PC);
+      const float x = m[(r < rows ? r : rows - 1) * cols + (c < cols ? c : cols - 1)];
+      v[e] = r < rows && c < cols ? x : 0.f;
     }
-    if (i + 1 < p.horizon || xo) {
 #pragma unroll
-      for (int r = 0; r < MAXN; r++) {
-        xn[r] = 0.f;
-        if (r < nx) {
-          float s = 0.f, t = 0.f;
+    for (int e = 0; e < (16 * R * PC + 63) / 64; e++) dwin[e * 64 + lane] = v[e];
 #pragma unroll
-          for (int c = 0; c < MAXN; c++)
-            if (c < nx) s = __builtin_fmaf(sA[r * nx + c], x[c], s);
+    for (int i = 0; i < R; i++)
 #pragma unroll
-          for (int c = 0; c < MAXN; c++)
-            if (c < nu) t = __builtin_fmaf(sB[r * nu + c], u[c], t);
-          xn[r] = s + t;
+      for (int c = 0; c < C; c++) {
+        const v4f w = *(const v4f*)(dwin + (q + 4 * i) * (4 * PC) + 4 * c);
+#pragma unroll
+        for (int e = 0; e < 4; e++) reg[i][4 * c + e] = w[e];
+      }
+  };
+  constexpr std::integral_constant<int, RX> rx{};
+  constexpr std::integral_constant<int, RU> ru{};
+  rows_of(p.Adyn, nx, nx, a, rx, rx);
+  rows_of(p.Kinf, nu, nx, k, ru, rx);
+  rows_of(p.Bdyn, nx, nu, b, rx, ru);
+
+  auto copy = [&](float* dst, const float* src, int count) {  // one contiguous run, 16 bytes per lane where both ends allow it
+    const bool wide = ((((uintptr_t)dst) | ((uintptr_t)src)) & 15) == 0;
+    const int fours = wide ? count & ~3 : 0;
+#pragma unroll 4
+    for (int i = lane * 4; i < fours; i += 256) *(v4f*)(dst + i) = *(const v4f*)(src + i);
+#pragma unroll 4
+    for (int i = fours + lane; i < count; i += 64) dst[i] = src[i];
+  };
+  // One run of `count` values per problem.  Value i of all of them is number i - r count of run r = i / count, by one
+  // multiply: 16 runs fit the window, so count <= 255 and i * (count * magic - 2^20) < 2^20.
+  auto copy_runs = [&](float* dst, int64_t dst_pitch, const float* src, int64_t src_pitch, int runs, int count) {
+    const unsigned magic = (1u << 20) / (unsigned)count + 1u;
+#pragma unroll 8
+    for (int i = lane; i < runs * count; i += 64) {
+      const int r = (int)(((unsigned)i * magic) >> 20), e = i - r * count;
+      dst[r * dst_pitch + e] = src[r * src_pitch + e];
+    }
+  };
+
+  for (int64_t blk = (int64_t)blockIdx.x * waves + wave; blk < nblk; blk += stride) {  // no wave waits for another
+    const int64_t b0 = blk * 16;
+    const int nvalid = p.batch - b0 < 16 ? (int)(p.batch - b0) : 16;
+    const bool live = pr < nvalid;
+    const int64_t prob = b0 + (live ? pr : 0);
+    float x[RX], u[RU];
+#pragma unroll
+    for (int i = 0; i < RX; i++) x[i] = q + 4 * i < nx ? p.x0[prob * nx + q + 4 * i] : 0.f;
+    if (traj) {
+#pragma unroll
+      for (int i = 0; i < RX; i++)
+        if (live && q + 4 * i < nx) {
+          if constexpr (WHOLE) xmine[q + 4 * i] = x[i];
+          else p.x_out[prob * (H + 1) * nx + q + 4 * i] = x[i];
+        }
+    }
+    for (int s0 = 0; s0 < H; s0 += chunk) {
+      const int steps = H - s0 < chunk ? H - s0 : chunk;
+      if constexpr (WHOLE) copy(dwin, p.d + b0 * H * nu, nvalid * H * nu);
+      else copy_runs(dwin, dpitch, p.d + (b0 * H + s0) * nu, H * nu, nvalid, steps * nu);
+      float* xrow = xmine + (WHOLE ? nx : 0);
+      for (int step = 0; step < steps; step++) {
+        float dv[RU], su[RU], sx[RX];
+#pragma unroll
+        for (int j = 0; j < RU; j++) dv[j] = q + 4 * j < nu ? dmine[step * nu + q + 4 * j] : 0.f, su[j] = 0.f;
+#pragma unroll
+        for (int i = 0; i < RX; i++) sx[i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4 * RX; c++) {
+          const float v = quad_broadcast(x[c >> 2], c & 3);
+#pragma unroll
+          for (int j = 0; j < RU; j++) su[j] = __builtin_fmaf(k[j][c], v, su[j]);
+#pragma unroll
+          for (int i = 0; i < RX; i++) sx[i] = __builtin_fmaf(a[i][c], v, sx[i]);
+        }
+#pragma unroll
+        for (int j = 0; j < RU; j++) {
+          u[j] = q + 4 * j < nu ? -su[j] - dv[j] : 0.f;
+          if (q + 4 * j < nu) dmine[step * nu + q + 4 * j] = u[j];
+        }
+        // the state after the last control is not needed for u; it is only produced when the trajectory is asked for
+        if (s0 + step + 1 < H || traj) {
+          float t[RX];
+#pragma unroll
+          for (int i = 0; i < RX; i++) t[i] = 0.f;
+#pragma unroll
+          for (int c = 0; c < 4 * RU; c++) {
+            const float v = quad_broadcast(u[c >> 2], c & 3);
+#pragma unroll
+            for (int i = 0; i < RX; i++) t[i] = __builtin_fmaf(b[i][c], v, t[i]);
+          }
+#pragma unroll
+          for (int i = 0; i < RX; i++) {
+            x[i] = sx[i] + t[i];
+            if (traj && q + 4 * i < nx) xrow[step * nx + q + 4 * i] = x[i];
+          }
         }
       }
-#pragma unroll
-      for (int r = 0; r < MAXN; r++) x[r] = xn[r];
-      if (xo) {
-#pragma unroll
-        for (int r = 0; r < MAXN; r++)
-          if (r < nx) xo[(i + 1) * nx + r] = x[r];
+      if constexpr (WHOLE) {
+        copy(p.u + b0 * H * nu, dwin, nvalid * H * nu);
+        if (traj) copy(p.x_out + b0 * (H + 1) * nx, xwin, nvalid * (H + 1) * nx);
+      } else {
+        copy_runs(p.u + (b0 * H + s0) * nu, H * nu, dwin, dpitch, nvalid, steps * nu);
+        if (traj) copy_runs(p.x_out + (b0 * (H + 1) + s0 + 1) * nx, (H + 1) * nx, xwin, xpitch, nvalid, steps * nx);
       }
     }
   }
 }
 
-// Persistent workgroups per compute unit of the (12, 4, 5) kernel: one (27.3 us for 262144 problems; two, three,
-// four: 31.1, 33.0, 34.9 us).
-#ifndef TINYMPC_WGS_PER_CU
-#define TINYMPC_WGS_PER_CU 1
-#endif
-hipError_t launch_tinympc_forward(const TinyMpcParams& p, hipStream_t stream) {
-  const int64_t blocks = (p.batch + 255) / 256;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const bool aligned16 = ((((uintptr_t)p.x0) | ((uintptr_t)p.d) | ((uintptr_t)p.u) | ((uintptr_t)p.x_out)) & 15) == 0;
-  if (p.nx == 12 && p.nu == 4 && aligned16) {
-    const int64_t waves = (p.batch + 63) / 64;
-    const dim3 grid((unsigned)((waves + 3) / 4));
-    if (p.horizon == 5) {
-      const int64_t slots = (int64_t)compute_units() * TINYMPC_WGS_PER_CU;  // persistent waves
-      const dim3 pgrid((unsigned)(grid.x < slots ? grid.x : slots));
-      if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, 5>), pgrid, dim3(256), 0, stream, p);
-      else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, 5>), pgrid, dim3(256), 0, stream, p);
-    } else {
-      if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, 0>), grid, dim3(256), 0, stream, p);
-      else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, 0>), grid, dim3(256), 0, stream, p);
-    }
-  } else if (p.nx == 12 && p.nu == 4) hipLaunchKernelGGL((tinympc_forward_kernel<12, 4>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL(tinympc_forward_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+template <int RX, int RU>
+static hipError_t launch_quad(const TinyMpcParams& p, hipStream_t stream) {
+  // Floats of a wave's window: the whole horizon of 16 problems up to 16 KB (ten waves to a compute unit), chunks of it
+  // beyond; never less than the 256 a matrix needs on its way in.
+  constexpr int64_t MOST = 4096;
+  const int per_step = 16 * (p.nu + (p.x_out ? p.nx : 0));
+  const int64_t all = (int64_t)p.horizon * per_step + (p.x_out ? 16 * p.nx : 0) + 3;
+  const int chunk = all <= MOST ? p.horizon : (int)((MOST - 3) / per_step);
+  int64_t window = all <= MOST ? all : MOST;
+  window = window < 256 ? 256 : (window + 3) & ~3ll;
+  const int64_t blocks16 = (p.batch + 15) / 16;
+  // one-wave workgroups until every compute unit has four: a small batch then spreads over the chip
+  const int waves = blocks16 >= 4 * (int64_t)compute_units() ? 4 : 1;
+  const int64_t most = (int64_t)compute_units() * 16 / waves;  // persistent beyond that: the matrices are loaded once per wave
+  const int64_t wgs = (blocks16 + waves - 1) / waves;
+  const dim3 grid((unsigned)(wgs < most ? wgs : most)), block(64 * waves);
+  const size_t lds = (size_t)(waves * window * sizeof(float));
+  if (chunk == p.horizon) hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, true>), grid, block, lds, stream, p, (int)window, chunk);
+  else hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, false>), grid, block, lds, stream, p, (int)window, chunk);
   return hipGetLastError();
+}
+
+template <int NB, int WAVES>
+static hipError_t launch_mfma(const TinyMpcParams& p, hipStream_t stream) {
+  const int64_t blks = (p.batch + 16 * NB - 1) / (16 * NB), wgs = (blks + WAVES - 1) / WAVES;
+  // one persistent workgroup of four waves per compute unit (27.3 us for 262144 problems; two, three, four: 31.1,
+  // 33.0, 34.9 us)
+  const int64_t slots = (int64_t)compute_units() * (4 / WAVES);
+  const dim3 grid((unsigned)(wgs < slots ? wgs : slots)), block(64 * WAVES);
+  if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, NB, WAVES>), grid, block, 0, stream, p);
+  else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, NB, WAVES>), grid, block, 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_tinympc_forward(const TinyMpcParams& p, hipStream_t stream) {
+  if ((p.batch + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
+  const bool aligned16 = ((((uintptr_t)p.x0) | ((uintptr_t)p.d) | ((uintptr_t)p.u) | ((uintptr_t)p.x_out)) & 15) == 0;
+  if (p.nx == 12 && p.nu == 4 && p.horizon == TMPC_H && aligned16)
+    return p.batch <= 16 * 4 * (int64_t)compute_units() ? launch_mfma<1, 1>(p, stream) : launch_mfma<4, 4>(p, stream);
+  switch (4 * ((p.nx - 1) / 4) + (p.nu - 1) / 4) {
+#define AC_QUAD(RX, RU) \
+  case 4 * (RX - 1) + RU - 1: return launch_quad<RX, RU>(p, stream);
+    AC_QUAD(1, 1) AC_QUAD(1, 2) AC_QUAD(1, 3) AC_QUAD(1, 4)
+    AC_QUAD(2, 1) AC_QUAD(2, 2) AC_QUAD(2, 3) AC_QUAD(2, 4)
+    AC_QUAD(3, 1) AC_QUAD(3, 2) AC_QUAD(3, 3) AC_QUAD(3, 4)
+    AC_QUAD(4, 1) AC_QUAD(4, 2) AC_QUAD(4, 3) AC_QUAD(4, 4)
+#undef AC_QUAD
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace ac

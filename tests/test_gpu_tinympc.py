@@ -3,8 +3,8 @@
 fp32 sums of at most nx + nu terms per element and `horizon` dependent steps (fused multiply-add chains, or for the
 paper's sizes 16 x 16 products on the matrix units with u substituted into the state update): rounding stays near
 1e-6 relative to the magnitudes involved, so the bar is the fp32 one of the library (relative Frobenius error
-<= 1e-5 over the batch).  Both kernel families are covered: (12, 4) with aligned arrays takes the matrix units (horizon
-5 with whole-run loads and stores, other horizons per lane), everything else the vector ALU."""
+<= 1e-5 over the batch).  Both kernel families are covered: (12, 4) at horizon 5 with aligned arrays takes the matrix
+units, everything else the vector ALU."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +39,25 @@ def test_shapes(nx, nu, horizon, batch):
     assert rel_fro(u, uw) <= TOL and rel_fro(xs, xw) <= TOL
     u2, none = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
     assert none is None
+    np.testing.assert_array_equal(u2, u)
+
+
+@pytest.mark.parametrize("nx,nu,horizon,batch", [
+    (12, 4, 5, 16384), (12, 4, 5, 16385),            # the two launch shapes of the matrix-unit kernel
+    (4, 4, 3, 15), (5, 4, 3, 16), (4, 5, 3, 17),     # whole fours of rows and one beyond, blocks of sixteen problems
+    (8, 8, 2, 33), (9, 1, 1, 40), (13, 16, 4, 100), (16, 9, 3, 70),
+    (12, 4, 40, 35), (16, 16, 9, 19), (3, 2, 200, 50), (1, 1, 300, 37),  # horizons that go through the window in chunks
+    (7, 3, 6, 16500), (16, 8, 4, 16421),             # four waves per workgroup
+])
+def test_sizes_at_the_edges_of_the_kernels(nx, nu, horizon, batch):
+    Adyn, Bdyn, Kinf, x0, d = inputs.tinympc_inputs(batch, seed=nx * 100 + horizon, nx=nx, nu=nu, horizon=horizon)
+    # a contracting closed loop, so that the bar means the same at every horizon
+    Adyn, Bdyn, Kinf = ((m / (1.5 * nx ** 0.5)).astype(np.float32) for m in (Adyn, Bdyn, Kinf))
+    uw, xw = oracle.tinympc_forward(Adyn, Bdyn, Kinf, x0, d, return_x=True)
+    u, xs = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=True)
+    assert np.isfinite(u).all() and np.isfinite(xs).all()
+    assert rel_fro(u, uw) <= TOL and rel_fro(xs, xw) <= TOL
+    u2, _ = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
     np.testing.assert_array_equal(u2, u)
 
 
