@@ -274,7 +274,7 @@ static ac_status conv2d_i8_entry(const int8_t* in, const int8_t* w, const int32_
   if (planned) {
     // a K split, the weight-stationary, patch and one-wave-per-tile kernels need the direct-to-LDS path: 16-byte aligned
     // operands, channel counts in multiples of 16, at most 32 kernel taps
-    const bool fast = ac::conv_i8_fast_path(p);
+    const bool fast = ac::conv_i8_fast_path(p) && KH * KW <= 32;
     const bool ws = tile == 320 || tile == 160, patch = tile == 321 || tile == 161;
     if ((plan.splits > 1 || ws || patch || tile == 32) && !fast) return AC_ERR_PLAN;
     if (ws && !ac::wstat_eligible(p, tile)) return AC_ERR_PLAN;

@@ -247,10 +247,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   // to valid ones (their products land in accumulators that are never stored); only a partial last K tile
   // needs zeros and takes the slower per-lane pointer path.
   // Convolution (AMODE 1): the row's output pixel gives the byte offset of its window origin in the image
-  // (g_base, possibly "negative": only ever used together with an in-range tap) and one bit per kernel tap that
-  // says whether the tap falls inside the image (g_mask, bit kh * KW + kw; the host keeps KH * KW <= 32).  A
-  // load then costs an add, a bit test and an OR: a lane whose tap is padding, whose row is beyond M or whose K
-  // position is beyond K gets the offset 0xffffffff and the bounds check of the buffer load writes its zeros.
+  // (g_base, possibly "negative": only ever used together with an in-range tap) and one bit per kernel row and per
+  // kernel column that says whether it falls inside the image (g_rows bit kh, g_cols bit kw; the host keeps KH and KW
+  // at most 32).  A load then costs an add, two shifts and two bit operations: a lane whose tap is padding, whose row
+  // is beyond M or whose K position is beyond K gets the offset 0xffffffff and the bounds check of the buffer load
+  // writes its zeros.  (One bit per tap is one shift less and stops at 32 taps: 7 x 7 kernels then went through the
+  // any-alignment gather.  16 -> 112 channels on 22 images of 22 x 22: 16.9 us there, 8.4 here; 224 -> 32 on six of
+  // 9 x 9 14.7 and 10.0; 3 x 3 and 5 x 5 kernels 1-5 % faster, the bits being set up without a loop over kernel rows.)
   // The lane's chunk sits at K byte g_kb (the K position of its chunk in the next K tile to be requested), i.e.
   // tap g_kb / Cin, channel g_kb % Cin; both come from two multiply-high divisions per K tile instead of a carried
   // (kh, kw, ci) counter with its loops.
@@ -258,7 +261,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   unsigned a_voff[G::A_INSTR], b_voff[G::B_INSTR];
   int b_krow[G::B_INSTR], a_krow[G::A_INSTR];
   int g_base[G::A_INSTR];
-  unsigned g_mask[G::A_INSTR];
+  unsigned g_rows[G::A_INSTR], g_cols[G::A_INSTR];
   unsigned g_kb[NVAR];
   const unsigned char* a_base = nullptr;
   const unsigned char* b_base = nullptr;
@@ -274,7 +277,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     for (int i = 0; i < G::A_INSTR; i++) {
       const int row = (wave * G::A_INSTR + i) * G::A_ROWS_PER_INSTR + lane / G::A_SPR;
       const int v = (wave * G::A_INSTR + i) & (NVAR - 1);
-      g_base[i] = 0, g_mask[i] = 0u, a_voff[i] = 0, a_krow[i] = 0;
+      g_base[i] = 0, g_rows[i] = g_cols[i] = 0u, a_voff[i] = 0, a_krow[i] = 0;
       if constexpr (TA) {
         const int krow = (wave * G::A_INSTR + i) * AT_RPI + lane / AT_SPR;
         const int ls = BSwizzle<EB, AT_ROW>::slot(lane % AT_SPR, krow);
@@ -295,11 +298,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
           if (hi <= lo) return 0u;
           return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
         };
-        const unsigned rows = span(ih0, p.KH, p.H), cols = span(iw0, p.KW, p.W);
-        unsigned mask = 0u;
-        for (int kh = 0; kh < p.KH; kh++)
-          if ((rows >> kh) & 1u) mask |= cols << (kh * p.KW);
-        g_mask[i] = m < p.M ? mask : 0u;
+        g_rows[i] = m < p.M ? span(ih0, p.KH, p.H) : 0u;
+        g_cols[i] = span(iw0, p.KW, p.W);
       }
     }
 #pragma unroll
@@ -332,20 +332,20 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     const int kbase = kt * G::KTB;
     const bool full = kbase + G::KTB <= kbytes;  // wave-uniform
     if constexpr (AMODE == 1) {
-      unsigned g_off[NVAR], g_tap[NVAR], g_dead[NVAR];
+      unsigned g_off[NVAR], g_kh[NVAR], g_kw[NVAR], g_dead[NVAR];
 #pragma unroll
       for (int v = 0; v < NVAR; v++) {
         const unsigned tap = p.dCin.div(g_kb[v]), ci = g_kb[v] - tap * p.Cin;
         const unsigned kh = p.dKW.div(tap), kw = tap - kh * p.KW;
         g_off[v] = (kh * p.W + kw) * p.Cin + ci;
-        g_tap[v] = tap;
+        g_kh[v] = kh & 31u, g_kw[v] = kw & 31u;
         g_dead[v] = g_kb[v] < (unsigned)kbytes ? 0u : ~0u;
         g_kb[v] += G::KTB;
       }
 #pragma unroll
       for (int i = 0; i < G::A_INSTR; i++) {
         const int v = (wave * G::A_INSTR + i) & (NVAR - 1);
-        const unsigned inside = (g_mask[i] >> (g_tap[v] & 31u)) & 1u;
+        const unsigned inside = (g_rows[i] >> g_kh[v]) & (g_cols[i] >> g_kw[v]) & 1u;
         buffer_to_lds16(a_rsrc, ((unsigned)g_base[i] + g_off[v]) | (inside - 1u) | g_dead[v], As + (wave * G::A_INSTR + i) * 1024);
       }
     } else if (full) {

@@ -402,13 +402,13 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
 }
 
 // Direct-to-LDS path of the convolution: channel counts in multiples of 16 so that a 16-byte K chunk stays inside
-// one kernel tap, at most 32 taps (one validity bit each), and index ranges that the one-multiply divisions of the
-// gather cover (K * Cin, M * OW and (M / OW) * OH below 2^32).
+// one kernel tap, at most 32 kernel rows and columns (one validity bit each), and index ranges that the one-multiply
+// divisions of the gather cover (K * Cin, M * OW and (M / OW) * OH below 2^32).
 bool conv_i8_fast_path(const GemmParams& p) {
   const bool aligned = aligned16(p.A) && aligned16(p.B) && (p.Cin % 16 == 0) && (p.ldb % 16 == 0) &&
                        (((uintptr_t)p.C & 3) == 0) && (p.ldc % 4 == 0);
   const int64_t lim = 1ll << 32;
-  return aligned && p.KH >= 1 && p.KH * p.KW <= 32 && (int64_t)p.K * p.Cin < lim && (int64_t)p.M * p.OW < lim &&
+  return aligned && p.KH >= 1 && p.KH <= 32 && p.KW <= 32 && (int64_t)p.K * p.Cin < lim && (int64_t)p.M * p.OW < lim &&
          ((int64_t)p.M / (p.OW > 0 ? p.OW : 1) + 1) * p.OH < lim && p.a_bytes > 0 && lane_offsets_fit(0, p.ldb);
 }
 
@@ -436,14 +436,15 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     const int64_t nblk = (p.N + 63) / 64, tiles64 = (int64_t)((p.M + 63) / 64) * nblk;
     // a single kernel tap reuses nothing of a patch: such a convolution (1 x 1 with a stride) is a gather GEMM and
     // is planned as one (64 -> 256 on 64 images of 56 x 56, stride 2: 13.1 us weight-stationary, 21.3 us patch kernel)
-    const bool taps = p.KH * p.KW > 1;
+    // and the patch of a kernel of more than 32 taps is mostly halo
+    const bool taps = p.KH * p.KW > 1 && p.KH * p.KW <= 32;
     if (taps && conv_halo_plan(p, 256, &h, &lds)) {
       if (h.units * nblk >= 256 || tiles64 > 512) return launch_conv_halo<256>(q, h, lds, stream);
     } else if (taps && conv_halo_plan(p, 128, &h, &lds)) {
       // the patch of 256 pixels does not fit, that of 128 does (28 x 28 x 128 -> 128: 64 images 18.7 us against
       // 18.5 us on the best tiled kernel, 128 images 29.6 against 33.6)
       if (h.units * nblk >= 512) return launch_conv_halo<128>(q, h, lds, stream);
-    } else {
+    } else if (p.KH * p.KW <= 32) {
       return dispatch_i8<1>(p, stream, fast, forced);
     }
     // a convolution the patch kernel could take but that is too small for it: the tiled kernels (or one wave per

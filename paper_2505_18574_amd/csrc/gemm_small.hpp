@@ -23,7 +23,7 @@ constexpr int SMALL_KTB = 64;  // K bytes per stage at least; 128 where K is a m
 
 // KTB: bytes of K per stage, S: stages of a wave's ring, SMALL_WAVES: independent waves (tiles) per workgroup,
 // AMODE 0: A is the M x K matrix; 1: A is gathered from the NHWC input of a convolution (the per-lane window
-// origin and one validity bit per kernel tap of gemm_dtl_kernel; a chunk outside the image gets the offset
+// origin and validity bits of kernel rows and columns of gemm_dtl_kernel; a chunk outside the image gets the offset
 // 0xffffffff and the bounds check of the buffer load writes its zeros).  SPLIT: a wave owns (tile, K slice): slice s
 // covers K tiles s * kt_per_split ... and leaves its int32 sums in p.partial[s][M][N] for splitk_reduce_i8_kernel
 // (with few tiles and a deep K, slices are what puts enough loads in flight; ntiles then counts tiles, not items).
@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
   constexpr int NVAR = KTB == 128 ? 2 : 1;  // distinct swizzle terms of a lane over the A instructions
   unsigned a_voff[NA], b_voff[NB];
   int g_base[NA];
-  unsigned g_mask[NA], g_kb[NVAR];
+  unsigned g_rows[NA], g_cols[NA], g_kb[NVAR];
   v4i a_rsrc = {0, 0, 0, 0};
   if constexpr (AMODE == 1) {
     const uint64_t ab = (uint64_t)(uintptr_t)p.A;
@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
   for (int i = 0; i < NA; i++) {
     const int row = i * G::A_ROWS_PER_INSTR + lane / G::A_SPR;
     const int a_chunk = (lane % G::A_SPR) ^ G::a_xor(row);
-    g_base[i] = 0, g_mask[i] = 0u, a_voff[i] = 0u;
+    g_base[i] = 0, g_rows[i] = g_cols[i] = 0u, a_voff[i] = 0u;
     if constexpr (AMODE == 0) {
       const int rclamp = m0 + row < p.M ? row : p.M - 1 - m0;
       a_voff[i] = (unsigned)rclamp * (unsigned)p.lda + a_chunk * 16;
@@ -84,11 +84,8 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
         if (hi <= lo) return 0u;
         return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
       };
-      const unsigned rows = span(ih0, p.KH, p.H), cols = span(iw0, p.KW, p.W);
-      unsigned mask = 0u;
-      for (int kh = 0; kh < p.KH; kh++)
-        if ((rows >> kh) & 1u) mask |= cols << (kh * p.KW);
-      g_mask[i] = m < p.M ? mask : 0u;
+      g_rows[i] = m < p.M ? span(ih0, p.KH, p.H) : 0u;
+      g_cols[i] = span(iw0, p.KW, p.W);
     }
     const int brow = i * G::B_ROWS_PER_INSTR + lane / G::B_SPR;
     const int slot = lane % G::B_SPR;
@@ -109,18 +106,18 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
     const unsigned st = lds0 + wr * G::STAGE;
     if constexpr (AMODE == 1) {
       // the lane's chunk sits at K byte g_kb: tap g_kb / Cin, channel g_kb % Cin (K is in whole stages: never beyond K)
-      unsigned g_off[NVAR], g_tap[NVAR];
+      unsigned g_off[NVAR], g_kh[NVAR], g_kw[NVAR];
 #pragma unroll
       for (int v = 0; v < NVAR; v++) {
         const unsigned tap = p.dCin.div(g_kb[v]), ci = g_kb[v] - tap * p.Cin;
         const unsigned kh = p.dKW.div(tap), kw = tap - kh * p.KW;
         g_off[v] = (kh * p.W + kw) * p.Cin + ci;
-        g_tap[v] = tap;
+        g_kh[v] = kh & 31u, g_kw[v] = kw & 31u;
         g_kb[v] += KTB;
       }
 #pragma unroll
       for (int i = 0; i < NA; i++) {
-        const unsigned inside = (g_mask[i] >> (g_tap[i & (NVAR - 1)] & 31u)) & 1u;
+        const unsigned inside = (g_rows[i] >> g_kh[i & (NVAR - 1)]) & (g_cols[i] >> g_kw[i & (NVAR - 1)]) & 1u;
         buffer_to_lds16(a_rsrc, ((unsigned)g_base[i] + g_off[i & (NVAR - 1)]) | (inside - 1u), st + i * 1024);
       }
     } else {
