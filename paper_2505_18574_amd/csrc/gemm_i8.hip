@@ -1,5 +1,6 @@
 // int8 GEMM / implicit-GEMM convolution with the accelerator output stage: tile selection, split-K and launch.
 #include "conv_halo.hpp"
+#include "conv_image.hpp"
 #include "gemm_ragged.hpp"
 #include "gemm_small.hpp"
 #include "gemm_wstat.hpp"
@@ -413,6 +414,8 @@ bool conv_i8_fast_path(const GemmParams& p) {
 }
 
 hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced) {
+  const bool fast = conv_i8_fast_path(p);
+  if (hipError_t e; !forced && !fast && launch_conv_image(p, stream, &e)) return e;  // channels that are not whole chunks
   if (!forced && p.KH == 1 && p.KW == 1 && p.stride == 1 && p.pad == 0) {
     // a 1 x 1 convolution over every pixel is the GEMM (pixels x Cin) . (Cin x Cout): the plain operand loaders and
     // the GEMM planner (1 x 1, 256 -> 64 on 256 images of 56 x 56: 42 us against 71 us through the gather)
@@ -420,7 +423,6 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     g.lda = p.Cin;
     return launch_gemm_i8(g, stream, nullptr);
   }
-  const bool fast = conv_i8_fast_path(p);
   if (!forced && fast) {
     // The patch kernel (weights and the image patch of a unit both in LDS) as soon as the 64 x 64 tiles would
     // need a second round on the chip (more than two per compute unit), or the convolution has a unit of 256
@@ -438,6 +440,10 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     // is planned as one (64 -> 256 on 64 images of 56 x 56, stride 2: 13.1 us weight-stationary, 21.3 us patch kernel)
     // and the patch of a kernel of more than 32 taps is mostly halo
     const bool taps = p.KH * p.KW > 1 && p.KH * p.KW <= 32;
+    // sixteen channels are half a K-step of the patch kernel, which does not take them: the same rule sends 3 x 3 kernels
+    // over them to the kernel that pads its runs (16 -> 64 on 32 images of 56 x 56 11.2 us tiled and 8.9 there, 16 -> 32
+    // on 64 of 28 x 28 7.4 and 5.3; 5 x 5 with stride 2, 16 -> 368 on 13 of 54 x 54 12.2 and 12.8)
+    if (hipError_t e; p.Cin == 16 && p.KH * p.KW > 1 && p.KH * p.KW <= 9 && tiles64 > 512 && launch_conv_image(p, stream, &e)) return e;
     if (taps && conv_halo_plan(p, 256, &h, &lds)) {
       if (h.units * nblk >= 256 || tiles64 > 512) return launch_conv_halo<256>(q, h, lds, stream);
     } else if (taps && conv_halo_plan(p, 128, &h, &lds)) {

@@ -23,8 +23,8 @@
 // Bound: latency for the sizes that fill the chip once, LDS writes beyond (some 72 bytes per clock and compute unit).
 // Against the byte-guarded kernel, kernel time: bf16 1023 x 1537 x 1021 98.4 -> 18.6 us, int8 1000^3 21.5 -> 9.9,
 // 44 x 316 x 1992 (with a workspace: cut along K, which that kernel never was) 42.1 -> 6.8, both operands transposed
-// 888 x 1368 x 720 20.1 -> 11.1, 7 x 7 stride 2 on eight 224 x 224 x 3 images 69 -> 35, 5 x 5 on one 13 x 13 x 59
-// image 124 -> 20.
+// 888 x 1368 x 720 20.1 -> 11.1, 7 x 7, 51 -> 28 channels on three images of 19 x 19 (cut along K) 13.7.  Convolutions of
+// few channels or taps go to conv_image.hpp.
 #pragma once
 #include "gemm_dtl.hpp"
 
