@@ -135,52 +135,71 @@ def ac_gemm_bf16_auto_plan(M: int, N: int, K: int):
     return tile.value, splits.value
 
 
+# The functions below run once per launch, and on this path a launch takes the GPU no longer than the checks take the
+# host: addresses go to ctypes as plain integers, a tensor's properties are read once, and the current stream's handle is
+# asked for without building a Stream object (2.8 of the 9.7 us that a call
+# took; now 6.0, of which the launch is 2.8).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
-def _check2d(t, dtype, name):
-    if t.dtype != dtype or t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1) or not t.is_cuda:
-        raise ValueError(f"{name}: expected a 2-D row-major device tensor of {dtype}")
+def _bad2d(t, dtype, name):
+    return ValueError(f"{name}: expected a 2-D row-major device tensor of {dtype}")
+
+
+def _matrix(t, dtype, name):
+    """(rows, columns, row pitch) of a 2-D row-major device tensor of `dtype`."""
+    if t.dtype is not dtype or t.ndim != 2 or not t.is_cuda:
+        raise _bad2d(t, dtype, name)
+    rows, cols = t.shape
+    pitch, step = t.stride()
+    if cols > 1 and step != 1:
+        raise _bad2d(t, dtype, name)
+    return rows, cols, pitch
 
 
 def _ws(workspace):
     if workspace is None:
         return None, 0
-    return _ptr(workspace), workspace.numel() * workspace.element_size()
+    return workspace.data_ptr(), workspace.nbytes
+
+
+def _bias_i8(bias, M, N):
+    """(address, row pitch) of the bias of an M x N output: None, a row of N or an M x N matrix."""
+    if bias is None:
+        return None, 0
+    if bias.dtype is not torch.int32 or not bias.is_cuda:
+        raise ValueError("bias: expected int32 device tensor")
+    shape = bias.shape
+    if len(shape) == 2:
+        if tuple(shape) != (M, N) or bias.stride(1) != 1:
+            raise ValueError("bias matrix must be M x N row-major")
+        return bias.data_ptr(), bias.stride(0)
+    if tuple(shape) != (N,) or (N > 1 and bias.stride(0) != 1):
+        raise ValueError("bias vector must have N contiguous entries")
+    return bias.data_ptr(), 0
 
 
 def _gemm_i8_args(A, B, bias, C):
-    _check2d(A, torch.int8, "A")
-    _check2d(B, torch.int8, "B")
-    _check2d(C, torch.int8, "C")
-    M, K = A.shape
-    N = B.shape[1]
-    if B.shape[0] != K or tuple(C.shape) != (M, N):
+    M, K, lda = _matrix(A, torch.int8, "A")
+    K2, N, ldb = _matrix(B, torch.int8, "B")
+    M2, N2, ldc = _matrix(C, torch.int8, "C")
+    if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch")
-    bias_ld = 0
-    if bias is not None:
-        if bias.dtype != torch.int32 or not bias.is_cuda:
-            raise ValueError("bias: expected int32 device tensor")
-        if bias.dim() == 2:
-            if tuple(bias.shape) != (M, N) or bias.stride(1) != 1:
-                raise ValueError("bias matrix must be M x N row-major")
-            bias_ld = bias.stride(0)
-        elif tuple(bias.shape) != (N,) or (N > 1 and bias.stride(0) != 1):
-            raise ValueError("bias vector must have N contiguous entries")
-    return [_ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(bias), bias_ld, _ptr(C), C.stride(0), M, N, K]
+    bp, bias_ld = _bias_i8(bias, M, N)
+    return A.data_ptr(), lda, B.data_ptr(), ldb, bp, bias_ld, C.data_ptr(), ldc, M, N, K
 
 
 def ac_gemm_i8(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, workspace=None, stream=None):
     """C[M,N] int8 = stage(A[M,K] . B[K,N] + bias); bias is None, (N,) or (M,N) int32.  Returns C."""
     wp, wb = _ws(workspace)
-    st = lib().ac_gemm_i8(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, _stream(stream))
+    st = (_lib or lib()).ac_gemm_i8(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8")
     return C
@@ -191,7 +210,7 @@ AC_STATIC_SCRATCH_BYTES = 16 << 20
 
 def ac_gemm_i8_static(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, stream=None):
     """ac_gemm_i8 whose K-slice partial sums go through the buffer inside the library (no workspace, no allocation).  Returns C."""
-    st = lib().ac_gemm_i8_static(*_gemm_i8_args(A, B, bias, C), shift, act, _stream(stream))
+    st = (_lib or lib()).ac_gemm_i8_static(*_gemm_i8_args(A, B, bias, C), shift, act, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_static")
     return C
@@ -199,25 +218,18 @@ def ac_gemm_i8_static(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, stream=
 
 def ac_gemm_i8_t(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, trans_a: bool = False, trans_b: bool = False, stream=None):
     """ac_gemm_i8 with A given as A^T (K x M) when trans_a and B as B^T (N x K) when trans_b.  Returns C."""
-    _check2d(A, torch.int8, "A")
-    _check2d(B, torch.int8, "B")
-    _check2d(C, torch.int8, "C")
-    K, M = (A.shape if trans_a else A.shape[::-1])
-    N, K2 = (B.shape if trans_b else B.shape[::-1])
-    if K2 != K or tuple(C.shape) != (M, N):
+    M, K, lda = _matrix(A, torch.int8, "A")
+    K2, N, ldb = _matrix(B, torch.int8, "B")
+    M2, N2, ldc = _matrix(C, torch.int8, "C")
+    if trans_a:
+        M, K = K, M
+    if trans_b:
+        K2, N = N, K2
+    if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch")
-    bias_ld = 0
-    if bias is not None:
-        if bias.dtype != torch.int32 or not bias.is_cuda:
-            raise ValueError("bias: expected int32 device tensor")
-        if bias.dim() == 2:
-            if tuple(bias.shape) != (M, N) or bias.stride(1) != 1:
-                raise ValueError("bias matrix must be M x N row-major")
-            bias_ld = bias.stride(0)
-        elif tuple(bias.shape) != (N,) or (N > 1 and bias.stride(0) != 1):
-            raise ValueError("bias vector must have N contiguous entries")
-    st = lib().ac_gemm_i8_t(_ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(bias), bias_ld, _ptr(C), C.stride(0),
-                            M, N, K, shift, act, int(bool(trans_a)), int(bool(trans_b)), _stream(stream))
+    bp, bias_ld = _bias_i8(bias, M, N)
+    st = (_lib or lib()).ac_gemm_i8_t(A.data_ptr(), lda, B.data_ptr(), ldb, bp, bias_ld, C.data_ptr(), ldc,
+                                      M, N, K, shift, act, int(bool(trans_a)), int(bool(trans_b)), _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_t")
     return C
@@ -226,7 +238,7 @@ def ac_gemm_i8_t(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, trans_a: boo
 def ac_gemm_i8_planned(A, B, bias, C, shift: int, act: int, tile: int, splits: int, workspace=None, stream=None):
     """ac_gemm_i8 with the block tile code (64, 128, 192, 256; 320 / 160 = weight-stationary) and the K split named by the caller.  Returns C."""
     wp, wb = _ws(workspace)
-    st = lib().ac_gemm_i8_planned(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, tile, splits, _stream(stream))
+    st = (_lib or lib()).ac_gemm_i8_planned(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, tile, splits, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_planned")
     return C
@@ -237,49 +249,55 @@ def ac_conv2d_i8(x, w, bias, out, stride: int, pad: int, shift: int, act: int = 
     """out[Nb,OH,OW,Cout] int8 = stage(conv(x[Nb,H,W,Cin], w[KH,KW,Cin,Cout]) + bias[Cout]).  Returns out.
 
     plan = (tile, splits) goes through ac_conv2d_i8_planned."""
+    shapes = []
     for t, name in ((x, "x"), (w, "w"), (out, "out")):
-        if t.dtype != torch.int8 or t.dim() != 4 or not t.is_contiguous() or not t.is_cuda:
+        shape = t.shape
+        if t.dtype is not torch.int8 or len(shape) != 4 or not t.is_contiguous() or not t.is_cuda:
             raise ValueError(f"{name}: expected a dense 4-D int8 device tensor")
-    Nb, H, W, Cin = x.shape
-    KH, KW, Cin2, Cout = w.shape
+        shapes.append(shape)
+    Nb, H, W, Cin = shapes[0]
+    KH, KW, Cin2, Cout = shapes[1]
     if Cin2 != Cin:
         raise ValueError("channel mismatch")
-    if bias is not None and (bias.dtype != torch.int32 or tuple(bias.shape) != (Cout,) or not bias.is_contiguous()):
+    if bias is not None and (bias.dtype is not torch.int32 or tuple(bias.shape) != (Cout,) or not bias.is_contiguous()):
         raise ValueError("bias: expected (Cout,) int32")
     OH = (H + 2 * pad - KH) // stride + 1
     OW = (W + 2 * pad - KW) // stride + 1
-    if tuple(out.shape) != (Nb, OH, OW, Cout):
+    if tuple(shapes[2]) != (Nb, OH, OW, Cout):
         raise ValueError(f"out: expected shape {(Nb, OH, OW, Cout)}")
     wp, wb = _ws(workspace)
     if plan is not None:
-        st = lib().ac_conv2d_i8_planned(_ptr(x), _ptr(w), _ptr(bias), _ptr(out), Nb, H, W, Cin, Cout, KH, KW, stride, pad,
+        st = (_lib or lib()).ac_conv2d_i8_planned(_ptr(x), _ptr(w), _ptr(bias), _ptr(out), Nb, H, W, Cin, Cout, KH, KW, stride, pad,
                                         shift, act, wp, wb, int(plan[0]), int(plan[1]), _stream(stream))
         if st != AC_OK:
             raise AcError(st, "ac_conv2d_i8_planned")
         return out
-    st = lib().ac_conv2d_i8(_ptr(x), _ptr(w), _ptr(bias), _ptr(out), Nb, H, W, Cin, Cout, KH, KW, stride, pad,
+    st = (_lib or lib()).ac_conv2d_i8(_ptr(x), _ptr(w), _ptr(bias), _ptr(out), Nb, H, W, Cin, Cout, KH, KW, stride, pad,
                             shift, act, wp, wb, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_conv2d_i8")
     return out
 
 
+_BF16 = (torch.bfloat16, torch.int16, torch.uint16)
+
+
 def _gemm_bf16_args(A, B, C):
-    ok = (torch.bfloat16, torch.int16, torch.uint16)
+    dims = []
     for t, name in ((A, "A"), (B, "B")):
-        if t.dtype not in ok or t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1) or not t.is_cuda:
+        if t.dtype not in _BF16 or t.ndim != 2 or (t.shape[1] > 1 and t.stride(1) != 1) or not t.is_cuda:
             raise ValueError(f"{name}: expected a 2-D row-major bf16 device tensor")
-    _check2d(C, torch.float32, "C")
-    M, K = A.shape
-    N = B.shape[1]
-    if B.shape[0] != K or tuple(C.shape) != (M, N):
+        dims.append((*t.shape, t.stride(0)))
+    (M, K, lda), (K2, N, ldb) = dims
+    M2, N2, ldc = _matrix(C, torch.float32, "C")
+    if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch")
-    return [_ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(C), C.stride(0), M, N, K]
+    return A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, M, N, K
 
 
 def ac_gemm_bf16(A, B, C, alpha: float = 1.0, beta: float = 0.0, stream=None):
     """C[M,N] fp32 = alpha * A[M,K] . B[K,N] + beta * C; A, B are bf16 (torch.bfloat16, or int16/uint16 bit patterns)."""
-    st = lib().ac_gemm_bf16(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), _stream(stream))
+    st = (_lib or lib()).ac_gemm_bf16(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_bf16")
     return C
@@ -288,7 +306,7 @@ def ac_gemm_bf16(A, B, C, alpha: float = 1.0, beta: float = 0.0, stream=None):
 def ac_gemm_bf16_ws(A, B, C, alpha: float = 1.0, beta: float = 0.0, workspace=None, stream=None):
     """ac_gemm_bf16 that sums the slices of a cut K range through `workspace` (in a fixed order) when one is given.  Returns C."""
     wp, wb = _ws(workspace)
-    st = lib().ac_gemm_bf16_ws(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, _stream(stream))
+    st = (_lib or lib()).ac_gemm_bf16_ws(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_bf16_ws")
     return C
@@ -298,7 +316,7 @@ def ac_gemm_bf16_planned(A, B, C, alpha: float, beta: float, tile: int, splits: 
     """ac_gemm_bf16 with the block tile code (64, 128, 192, 256) and the K split named by the caller; a split sums through
     `workspace` when one is given, else with atomic adds into C.  Returns C."""
     wp, wb = _ws(workspace)
-    st = lib().ac_gemm_bf16_planned(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, tile, splits, _stream(stream))
+    st = (_lib or lib()).ac_gemm_bf16_planned(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, tile, splits, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_bf16_planned")
     return C
@@ -307,7 +325,7 @@ def ac_gemm_bf16_planned(A, B, C, alpha: float, beta: float, tile: int, splits: 
 def ac_batched_gemm_f32(A, B, C=None, x=None, d=None, y=None, stream=None):
     """Per item: C = A . B (n x n), y = C . x + d.  A, B, C: [batch,n,n]; x, d, y: [batch,n]; fp32 dense."""
     for t, name in ((A, "A"), (B, "B"), (C, "C"), (x, "x"), (d, "d"), (y, "y")):
-        if t is not None and (t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda):
+        if t is not None and (t.dtype is not torch.float32 or not t.is_contiguous() or not t.is_cuda):
             raise ValueError(f"{name}: expected a dense fp32 device tensor")
     batch, n, n2 = A.shape
     if n != n2 or tuple(B.shape) != (batch, n, n):
@@ -317,7 +335,7 @@ def ac_batched_gemm_f32(A, B, C=None, x=None, d=None, y=None, stream=None):
     for t, name in ((x, "x"), (d, "d"), (y, "y")):
         if t is not None and tuple(t.shape) != (batch, n):
             raise ValueError(f"{name} must be [batch, n]")
-    st = lib().ac_batched_gemm_f32(_ptr(A), _ptr(B), _ptr(C), _ptr(x), _ptr(d), _ptr(y), n, batch, _stream(stream))
+    st = (_lib or lib()).ac_batched_gemm_f32(_ptr(A), _ptr(B), _ptr(C), _ptr(x), _ptr(d), _ptr(y), n, batch, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_batched_gemm_f32")
     return C, y
@@ -328,7 +346,7 @@ def ac_tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out=None, stream=None):
 
     Adyn [nx,nx], Bdyn [nx,nu], Kinf [nu,nx], x0 [batch,nx], d and u [batch,horizon,nu], x_out [batch,horizon+1,nx] or None."""
     for t, name in ((Adyn, "Adyn"), (Bdyn, "Bdyn"), (Kinf, "Kinf"), (x0, "x0"), (d, "d"), (u, "u"), (x_out, "x_out")):
-        if t is not None and (t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda):
+        if t is not None and (t.dtype is not torch.float32 or not t.is_contiguous() or not t.is_cuda):
             raise ValueError(f"{name}: expected a dense fp32 device tensor")
     nx, nu = Bdyn.shape
     batch, horizon, nu2 = d.shape
@@ -336,7 +354,7 @@ def ac_tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out=None, stream=None):
         raise ValueError("shape mismatch")
     if tuple(u.shape) != (batch, horizon, nu) or (x_out is not None and tuple(x_out.shape) != (batch, horizon + 1, nx)):
         raise ValueError("output shape mismatch")
-    st = lib().ac_tinympc_forward_f32(_ptr(Adyn), _ptr(Bdyn), _ptr(Kinf), _ptr(x0), _ptr(d), _ptr(u), _ptr(x_out),
+    st = (_lib or lib()).ac_tinympc_forward_f32(_ptr(Adyn), _ptr(Bdyn), _ptr(Kinf), _ptr(x0), _ptr(d), _ptr(u), _ptr(x_out),
                                       nx, nu, horizon, batch, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_tinympc_forward_f32")
@@ -345,12 +363,10 @@ def ac_tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out=None, stream=None):
 
 def ac_gemm_i8_acc32(A, B, bias, C, stream=None):
     """C[M,N] int32 = A[M,K] . B[K,N] + bias (raw accumulator: no scaling, no activation).  Returns C."""
-    _check2d(A, torch.int8, "A")
-    _check2d(B, torch.int8, "B")
-    _check2d(C, torch.int32, "C")
-    M, K = A.shape
-    N = B.shape[1]
-    if B.shape[0] != K or tuple(C.shape) != (M, N):
+    M, K, lda = _matrix(A, torch.int8, "A")
+    K2, N, ldb = _matrix(B, torch.int8, "B")
+    M2, N2, ldc = _matrix(C, torch.int32, "C")
+    if K2 != K or M2 != M or N2 != N:
         raise ValueError("shape mismatch")
     bias_ld = 0
     if bias is not None:
@@ -358,8 +374,8 @@ def ac_gemm_i8_acc32(A, B, bias, C, stream=None):
             raise ValueError("bias: expected int32 device tensor")
         if bias.dim() == 2:
             bias_ld = bias.stride(0)
-    st = lib().ac_gemm_i8_acc32(_ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(bias), bias_ld, _ptr(C), C.stride(0),
-                                M, N, K, _stream(stream))
+    st = (_lib or lib()).ac_gemm_i8_acc32(A.data_ptr(), lda, B.data_ptr(), ldb, _ptr(bias), bias_ld, C.data_ptr(), ldc,
+                                          M, N, K, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_acc32")
     return C
