@@ -45,23 +45,6 @@ struct __attribute__((packed, aligned(4))) Dwords16 {
   v4i v;
 };
 
-// 16 consecutive int8 outputs of a row at any address, the first `valid` of them
-static __device__ __forceinline__ void store_run16(int8_t* dst, v4i o, int valid) {
-  if (valid >= 16) {
-    ((Unaligned16*)dst)->v = o;
-  } else if (valid > 0) {
-    uint64_t lo = (uint64_t)(unsigned)o[0] | ((uint64_t)(unsigned)o[1] << 32);
-    const uint64_t hi = (uint64_t)(unsigned)o[2] | ((uint64_t)(unsigned)o[3] << 32);
-    struct __attribute__((packed)) U8 { uint64_t v; };
-    struct __attribute__((packed)) U4 { uint32_t v; };
-    struct __attribute__((packed)) U2 { uint16_t v; };
-    if (valid & 8) ((U8*)dst)->v = lo, dst += 8, lo = hi;
-    if (valid & 4) ((U4*)dst)->v = (uint32_t)lo, dst += 4, lo >>= 32;
-    if (valid & 2) ((U2*)dst)->v = (uint16_t)lo, dst += 2, lo >>= 16;
-    if (valid & 1) *dst = (int8_t)lo;
-  }
-}
-
 template <int BM, int BN>
 __global__ void __launch_bounds__(2 * BM) __attribute__((amdgpu_waves_per_eu(4))) conv_i8_image_kernel(const GemmParams p, const ConvImageParams h, const int n_blocks) {
   using T = TypeI8;

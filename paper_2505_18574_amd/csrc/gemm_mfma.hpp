@@ -92,6 +92,29 @@ static __device__ __forceinline__ void for_each_unswapped(int mrow0, int ncol0, 
   for (int r = 0; r < 16; r++) f(r, mrow0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), ncol0 + (lane & 31));
 }
 
+// Stores f(r) for the 16 registers of an unswapped tile, `ld` elements between rows: sixteen plain stores where all 32
+// rows exist (wave-uniform; with a guard and an address of its own each they are some 25 instructions apiece).
+template <class V, class F>
+static __device__ __forceinline__ void store_unswapped(V* base, int64_t ld, int rows, int cols, int mrow0, int ncol0, int lane, F f) {
+  const int n = ncol0 + (lane & 31), mb = mrow0 + 4 * (lane >> 5);
+  if (n >= cols) return;
+  V* dst = base + (int64_t)mb * ld + n;
+  if (mrow0 + 32 <= rows) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) dst[e * ld] = f(4 * q + e);
+      dst += 8 * ld;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+      const int dm = 8 * (r >> 2) + (r & 3);
+      if (mb + dm < rows) dst[dm * ld] = f(r);
+    }
+  }
+}
+
 // An epilogue that can take a whole wave tile at once declares WAVE_TILE.
 template <class E, class = void>
 struct has_wave_tile : std::false_type {};
@@ -311,9 +334,31 @@ struct EpilogueI8 {
   }
 };
 
-// The same output stage for a C of any alignment and pitch (unswapped tiles: 32 lanes store 32 consecutive bytes).
+struct __attribute__((packed)) Unaligned16 {
+  v4i v;
+};
+// 16 consecutive int8 outputs of a row at any address, the first `valid` of them.
+static __device__ __forceinline__ void store_run16(int8_t* dst, v4i o, int valid) {
+  if (valid >= 16) {
+    ((Unaligned16*)dst)->v = o;
+  } else if (valid > 0) {
+    uint64_t lo = (uint64_t)(unsigned)o[0] | ((uint64_t)(unsigned)o[1] << 32);
+    const uint64_t hi = (uint64_t)(unsigned)o[2] | ((uint64_t)(unsigned)o[3] << 32);
+    struct __attribute__((packed)) U8 { uint64_t v; };
+    struct __attribute__((packed)) U4 { uint32_t v; };
+    struct __attribute__((packed)) U2 { uint16_t v; };
+    if (valid & 8) ((U8*)dst)->v = lo, dst += 8, lo = hi;
+    if (valid & 4) ((U4*)dst)->v = (uint32_t)lo, dst += 4, lo >>= 32;
+    if (valid & 2) ((U2*)dst)->v = (uint16_t)lo, dst += 2, lo >>= 16;
+    if (valid & 1) *dst = (int8_t)lo;
+  }
+}
+
+// The same output stage for a C of any alignment and pitch: after the exchange a lane holds 16 consecutive columns of
+// its row and stores them with one unaligned store (one byte per lane and store, on unswapped tiles, is sixteen stores
+// with their guards and addresses).
 struct EpilogueI8Any {
-  static constexpr bool SWAP = false;
+  static constexpr bool SWAP = true;
   struct Pre {};
   static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, int v) {
     if (p.bias) v += p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
@@ -321,28 +366,30 @@ struct EpilogueI8Any {
   }
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
-    const int n = ncol0 + (lane & 31), mb = mrow0 + 4 * (lane >> 5);
-    if (n >= p.N) return;
-    int8_t* C = (int8_t*)p.C + (int64_t)mb * p.ldc + n;
-    const int row_bias = p.bias && p.bias_ld == 0 ? p.bias[n] : 0;
-    const bool matrix_bias = p.bias && p.bias_ld != 0;
-    auto rows = [&](auto quant) {
+    if (ncol0 >= p.N) return;
+    const int m = mrow0 + (lane & 31), half = lane >> 5;
+    int v[16];
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int dm = 8 * (r >> 2) + (r & 3);
-        if (mb + dm < p.M) {
-          int v = acc[r] + row_bias;
-          if (matrix_bias) v += p.bias[(int64_t)(mb + dm) * p.bias_ld + n];
-          C[(int64_t)dm * p.ldc] = (int8_t)quant(v);
+    for (int r = 0; r < 16; r++) v[r] = acc[r];
+    if (p.bias) {
+      // a row is read through a bounds-checked buffer of N values, one of the rows of a matrix (or a row of more than
+      // 2^29 values) with a guard on every value: columns beyond N are not stored, whatever is added to them
+      if (p.bias_ld == 0 && p.N < (1 << 29)) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)p.bias, 0, p.N * 4, 0x00020000);
+#pragma unroll
+        for (int r = 0; r < 16; r++) v[r] += __builtin_amdgcn_raw_buffer_load_b32(rsrc, (ncol0 + 8 * (r >> 2) + 4 * half + (r & 3)) * 4, 0, 0);
+      } else {
+        const int32_t* const row = p.bias + (p.bias_ld != 0 ? (int64_t)(m < p.M ? m : p.M - 1) * p.bias_ld : 0);
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          const int n = ncol0 + 8 * (r >> 2) + 4 * half + (r & 3);
+          v[r] += row[n < p.N ? n : p.N - 1];
         }
       }
-    };
-    if (p.shift >= 1 && p.shift <= 17) {
-      const EpilogueI8::FastQuant f = EpilogueI8::fast_quant(p.shift, p.act);
-      rows([&](int v) { return EpilogueI8::requant_fast<true>(v, f); });
-    } else {
-      rows([&](int v) { return EpilogueI8::requant(v, p.shift, p.act); });
     }
+    const v4i o = p.shift >= 1 && p.shift <= 23 ? EpilogueI8::quant16_by_shift(v, EpilogueI8::fast_quant(p.shift, p.act)) : EpilogueI8::quant16(v, p.shift, p.act);
+    const int n = ncol0 + 16 * half;
+    if (m < p.M) store_run16((int8_t*)p.C + (int64_t)m * p.ldc + n, o, p.N - n);
   }
 };
 
@@ -360,9 +407,7 @@ struct EpiloguePartialI32 {
   static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int split, const Pre&) {
-    for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
-      if (m < p.M && n < p.N) p.partial[((int64_t)split * p.M + m) * p.N + n] = acc[r];
-    });
+    store_unswapped(p.partial + (int64_t)split * p.M * p.N, p.N, p.M, p.N, mrow0, ncol0, lane, [&](int r) { return acc[r]; });
   }
 };
 
@@ -388,9 +433,15 @@ struct EpilogueRawI32 {
   }
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
-    for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
-      if (m < p.M && n < p.N) one(p, m, n, acc[r]);
-    });
+    if (p.bias != nullptr && p.bias_ld != 0) {
+      for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
+        if (m < p.M && n < p.N) one(p, m, n, acc[r]);
+      });
+      return;
+    }
+    const int n = ncol0 + (lane & 31);
+    const int bias = p.bias && n < p.N ? p.bias[n] : 0;
+    store_unswapped((int32_t*)p.C, p.ldc, p.M, p.N, mrow0, ncol0, lane, [&](int r) { return acc[r] + bias; });
   }
 };
 
@@ -417,6 +468,10 @@ struct EpilogueF32 {
   }
   template <class ACC>
   static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+    if (p.beta == 0.f) {
+      store_unswapped((float*)p.C, p.ldc, p.M, p.N, mrow0, ncol0, lane, [&](int r) { return p.alpha * acc[r]; });
+      return;
+    }
     for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
       if (m < p.M && n < p.N) one(p, m, n, acc[r]);
     });

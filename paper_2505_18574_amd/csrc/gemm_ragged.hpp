@@ -16,23 +16,21 @@
 //     image bytes there are does not matter) and a chunk then lies in one image row: one load, plus a mask where the
 //     window hangs over the left or right edge.
 //
-// global (16 bytes per lane, R tiles ahead in registers) -> LDS (two stages, padded rows) -> MFMA, one barrier per
-// K tile.  The MFMA operands are not swapped: a half-wave then owns 32 consecutive columns of one output row, so even
-// byte stores leave as whole 32-byte pieces whatever the alignment of C.
+// global (16 bytes per lane, R tiles ahead in registers) -> LDS (two buffers, padded rows) -> MFMA, one barrier per K
+// tile; the LDS write of a tile runs under the reads and products of the one before.  Two tiles in registers are enough:
+// four lose what their longer code costs (bf16 1000 x 1000 x 1022 10.4 us with two, 11.4 with four before the trips
+// were overlapped, int8 1000^3 7.7 and 8.6 after).
 //
-// Bound: latency for the sizes that fill the chip once, LDS writes beyond (some 72 bytes per clock and compute unit).
-// Against the byte-guarded kernel, kernel time: bf16 1023 x 1537 x 1021 98.4 -> 18.6 us, int8 1000^3 21.5 -> 9.9,
-// 44 x 316 x 1992 (with a workspace: cut along K, which that kernel never was) 42.1 -> 6.8, both operands transposed
-// 888 x 1368 x 720 20.1 -> 11.1, 7 x 7, 51 -> 28 channels on three images of 19 x 19 (cut along K) 13.7.  Convolutions of
-// few channels or taps go to conv_image.hpp.
+// Bound: the chain of a trip (barrier, LDS reads, products) for the sizes that fill the chip once, 0.26 us a K tile
+// against 0.12 on the direct-to-LDS kernels, and some 1.3 us more set-up; LDS writes beyond (some 72 bytes per clock
+// and compute unit).  Overlapped trips, the partial tile ahead of the pipeline and 16-byte stores of int8 outputs,
+// before and after: int8 1000^3 10.0 -> 7.7, 72 x 252 x 100 5.2 -> 4.2, 364 x 20 x 920 8.8 -> 7.0, 1516 x 1764 x 56
+// 9.2 -> 6.1; bf16 1023 x 1537 x 1021 19.2 -> 15.0, 712 x 101 x 204 7.5 -> 6.1, 999 x 999 x 333 9.5 -> 7.8.
 #pragma once
 #include "gemm_dtl.hpp"
 
 namespace ac {
 
-struct __attribute__((packed)) Unaligned16 {
-  v4i v;
-};
 static __device__ __forceinline__ v4i load16_any(const unsigned char* p) { return ((const Unaligned16*)p)->v; }
 
 // What has to happen to a loaded chunk on its way into LDS: shift its bytes down by `s` (up when negative) and keep
@@ -112,8 +110,8 @@ struct RaggedMatrix {
   const unsigned char *base, *last;  // first byte of the matrix, last address with 16 bytes behind it (the launcher makes sure there is one)
   const unsigned char* ptr[IT];      // this thread's chunks of the next tile to load
   int64_t step;                      // bytes from one K tile to the next
-  int kb, kbytes;                    // KC: byte of K of this thread's chunk in the next tile; bytes of K
-  int k, K;                          // !KC: k-row of its first chunk in the next tile; K
+  int kb, kbytes;                    // KC: byte of K of this thread's chunk in the first tile; bytes of K
+  int k, K;                          // !KC: k-row of its first chunk in the first tile; K
   int edge;                          // !KC: the fix of this thread's column (the same for every k-row)
 
   __device__ __forceinline__ void init(const void* p, int64_t ld_elems, int origin, int extent, int K_, int kt0, int t) {
@@ -158,26 +156,22 @@ struct RaggedMatrix {
       reg[i] = load16_any(ptr[i]);
       ptr[i] += step;
     }
-    if constexpr (KC) kb += RAGGED_KTB;
-    else k += RAGGED_KTB / EB;
   }
-  // any tile
-  __device__ __forceinline__ void load(v4i (&reg)[IT], int (&fix)[IT]) {
+  // any tile: the one `ahead` tiles after the next whole one, which does not move on
+  __device__ __forceinline__ void load_any(v4i (&reg)[IT], int (&fix)[IT], int ahead) const {
+    const int64_t off = ahead * step;
 #pragma unroll
     for (int i = 0; i < IT; i++) {
       if constexpr (KC) {
-        const int valid = kbytes - kb;
-        reg[i] = guarded(valid > 0 ? ptr[i] : base, 0, valid < 0 ? 0 : (valid < 16 ? valid : 16), fix[i]);
+        const int valid = kbytes - (kb + ahead * RAGGED_KTB);
+        reg[i] = guarded(valid > 0 ? ptr[i] + off : base, 0, valid < 0 ? 0 : (valid < 16 ? valid : 16), fix[i]);
       } else {
-        const bool in = k + i * Tile::RPP < K;
-        reg[i] = guarded(in ? ptr[i] : base, 0, in ? 16 : 0, fix[i]);
+        const bool in = k + ahead * (RAGGED_KTB / EB) + i * Tile::RPP < K;
+        reg[i] = guarded(in ? ptr[i] + off : base, 0, in ? 16 : 0, fix[i]);
         // the shift of the row's last chunk; it was loaded 16 bytes before the row's end, which is never beyond `last`
         if (in && edge != CHUNK_AS_IS) fix[i] = edge;
       }
-      ptr[i] += step;
     }
-    if constexpr (KC) kb += RAGGED_KTB;
-    else k += RAGGED_KTB / EB;
   }
 };
 
@@ -284,7 +278,7 @@ struct RaggedWeights {
 // AKC / BKC: A (B) is K-contiguous in memory: plain A and B^T are, plain B and A^T are not.  CONV: A is the NHWC input
 // and B the weights of a convolution.  R: K tiles in flight in registers.
 template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV, int R>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(const GemmParams p, const int tiles_m, const int tiles_n) {
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const unsigned band_magic) {
   constexpr int THREADS = 64 * WAVES_M * WAVES_N;
   constexpr int EB = T::EB;
   using SA = std::conditional_t<CONV, RaggedImage<BM, THREADS>, RaggedMatrix<T, BM, THREADS, AKC>>;
@@ -302,11 +296,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   // tiles before this one lie inside K and (K-strided operands) have rows of 16 bytes and more: unconditional loads
   const bool long_rows = (AKC || (int64_t)p.M * EB >= 16) && (BKC || (int64_t)p.N * EB >= 16);
   const int nkt_whole = CONV || !long_rows ? 0 : kbytes / RAGGED_KTB;
+  const unsigned items = (unsigned)ntiles * (unsigned)p.splits;  // (K is cut only where tiles are few)
 
-  for (int64_t item = blockIdx.x; item < (int64_t)ntiles * p.splits; item += gridDim.x) {
-    const int split = (int)(item / ntiles);
+  for (unsigned item = blockIdx.x; item < items; item += gridDim.x) {
+    const int split = p.splits > 1 ? (int)(item / (unsigned)ntiles) : 0;
     int tm, tn;
-    tile_coords((int)(item - (int64_t)split * ntiles), ntiles, tiles_m, tiles_n, tm, tn);
+    tile_coords_mul((int)item - split * ntiles, ntiles, tiles_m, tiles_n, band_magic, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int kt0 = p.splits > 1 ? split * p.kt_per_split : 0;
     const int nkt = p.splits > 1 && nkt_total - kt0 > p.kt_per_split ? p.kt_per_split : nkt_total - kt0;
@@ -326,93 +321,162 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
 #pragma unroll
       for (int j = 0; j < TN; j++) acc[i][j] = T::zero();
 
-    v4i ra[R][SA::IT], rb[R][SB::IT];
-    int fa[R][SA::IT], fb[R][SB::IT];
-    auto stage_rt = [&](int buf, int s) {  // register set s (a constant after unrolling) -> LDS
-#pragma unroll
-      for (int i = 0; i < SA::IT; i++) ra[s][i] = chunk_apply<CONV>(ra[s][i], fa[s][i]);
-#pragma unroll
-      for (int i = 0; i < SB::IT; i++) rb[s][i] = chunk_apply<false>(rb[s][i], fb[s][i]);
-      TA::store(smem + buf * STAGE, t, ra[s]);
-      TB::store(smem + buf * STAGE + TA::BYTES, t, rb[s]);
+    auto store = [&](int buf, const v4i (&xa)[SA::IT], const v4i (&xb)[SB::IT]) {
+      TA::store(smem + buf * STAGE, t, xa);
+      TB::store(smem + buf * STAGE + TA::BYTES, t, xb);
     };
-    auto stage_whole = [&](int buf, auto sc) {  // a whole tile: only the last chunk of a K-strided row needs its shift
-      constexpr int S = decltype(sc)::value;
-      if constexpr (!CONV && !AKC) {
+    auto store_fixed = [&](int buf, v4i (&xa)[SA::IT], v4i (&xb)[SB::IT], const int (&fa)[SA::IT], const int (&fb)[SB::IT]) {
 #pragma unroll
-        for (int i = 0; i < SA::IT; i++) ra[S][i] = chunk_apply<false>(ra[S][i], a.edge);
-      }
-      if constexpr (!CONV && !BKC) {
+      for (int i = 0; i < SA::IT; i++) xa[i] = chunk_apply<CONV>(xa[i], fa[i]);
 #pragma unroll
-        for (int i = 0; i < SB::IT; i++) rb[S][i] = chunk_apply<false>(rb[S][i], b.edge);
-      }
-      TA::store(smem + buf * STAGE, t, ra[S]);
-      TB::store(smem + buf * STAGE + TA::BYTES, t, rb[S]);
+      for (int i = 0; i < SB::IT; i++) xb[i] = chunk_apply<false>(xb[i], fb[i]);
+      store(buf, xa, xb);
     };
-    auto multiply = [&](int buf) {
+    constexpr int KS = RAGGED_KTB / 32;
+    struct Frags {
+      v4i a[KS][TM], b[KS][TN];
+    };
+    auto read = [&](int buf, Frags& f) {
       const unsigned char* As = smem + buf * STAGE;
       const unsigned char* Bs = As + TA::BYTES;
 #pragma unroll
-      for (int ks = 0; ks < RAGGED_KTB / 32; ks++) {
+      for (int ks = 0; ks < KS; ks++) {
         const int kb = ks * 32 + (lane >> 5) * 16;
-        v4i af[TM], bf[TN];
 #pragma unroll
-        for (int i = 0; i < TM; i++) af[i] = TA::fragment(As, (wm * TM + i) * 32, kb, lane);
+        for (int i = 0; i < TM; i++) f.a[ks][i] = TA::fragment(As, (wm * TM + i) * 32, kb, lane);
 #pragma unroll
-        for (int j = 0; j < TN; j++) bf[j] = TB::fragment(Bs, (wn * TN + j) * 32, kb, lane);
+        for (int j = 0; j < TN; j++) f.b[ks][j] = TB::fragment(Bs, (wn * TN + j) * 32, kb, lane);
+      }
+    };
+    auto multiply = [&](const Frags& f) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++)
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
-          for (int j = 0; j < TN; j++) acc[i][j] = T::mfma(af[i], bf[j], acc[i][j]);
-      }
+          for (int j = 0; j < TN; j++) acc[i][j] = EPI::SWAP ? T::mfma(f.b[ks][j], f.a[ks][i], acc[i][j]) : T::mfma(f.a[ks][i], f.b[ks][j], acc[i][j]);
     };
-    int kt = 0, buf = 0;
-    const int whole = nkt_whole - kt0 < nkt ? nkt_whole - kt0 : nkt;  // whole tiles of this slice, from its first
-    auto fetch_whole = [&](auto sc) {
-      constexpr int S = decltype(sc)::value;
-      if constexpr (!CONV) {  // (a convolution has no whole tiles in this sense)
+    // The tiles' requests stay in tile order: a wait counts the younger ones, and where a path into a loop has issued
+    // them in another order the compiler waits for the worst of both.
+    auto in_order = [&]() { asm volatile("" ::: "memory"); };
+
+    if constexpr (CONV) {
+      v4i ra[R][SA::IT], rb[R][SB::IT];
+      int fa[R][SA::IT], fb[R][SB::IT];
+#pragma unroll
+      for (int s = 0; s < R; s++) {
+        a.load(ra[s], fa[s]);
+        b.load(rb[s], fb[s]);
+        in_order();
+      }
+      // Tiles beyond the last are requested like any other (nothing of them is kept): a request that depended on the
+      // tile would make every wait below drain all of them.
+      for (int kt = 0, buf = 0;;) {
+#pragma unroll
+        for (int s = 0; s < R; s++) {
+          if (kt >= nkt) goto multiplied;
+          store_fixed(buf, ra[s], rb[s], fa[s], fb[s]);
+          a.load(ra[s], fa[s]);
+          b.load(rb[s], fb[s]);
+          in_order();
+          block_sync();
+          Frags f;
+          read(buf, f);
+          multiply(f);
+          buf ^= 1;
+          kt++;
+        }
+      }
+    } else {
+      // Whole tiles w_0 .. w_(nw - 1) of the slice go through the pipeline: w_k waits in register set k % R, then in LDS
+      // buffer k % 2 (R is even).  Trip k reads w_k from LDS, moves w_(k+1) there, requests w_(k+1+R) and multiplies, so
+      // the LDS write of one tile runs under the reads and products of another and a tile costs one barrier.  The
+      // partial last tile, with its masks, is requested and multiplied ahead of them: no trip then asks what kind of
+      // tile it has.
+      static_assert(R % 2 == 0, "set and buffer of a trip are constants");
+      const int nw = nkt_whole - kt0 < nkt ? (nkt_whole > kt0 ? nkt_whole - kt0 : 0) : nkt;
+      v4i ra[R][SA::IT], rb[R][SB::IT];
+      auto fetch = [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
         a.load_whole(ra[S]);
         b.load_whole(rb[S]);
+        in_order();
+      };
+      auto stage = [&](int buf, auto sc) {  // of a whole tile, only the last chunk of a K-strided row needs its shift
+        constexpr int S = decltype(sc)::value;
+        if constexpr (!AKC) {
 #pragma unroll
-        for (int i = 0; i < SA::IT; i++) fa[S][i] = a.edge;
+          for (int i = 0; i < SA::IT; i++) ra[S][i] = chunk_apply<false>(ra[S][i], a.edge);
+        }
+        if constexpr (!BKC) {
 #pragma unroll
-        for (int i = 0; i < SB::IT; i++) fb[S][i] = b.edge;
+          for (int i = 0; i < SB::IT; i++) rb[S][i] = chunk_apply<false>(rb[S][i], b.edge);
+        }
+        store(buf, ra[S], rb[S]);
+      };
+      v4i xa[SA::IT], xb[SB::IT];
+      int fa[SA::IT], fb[SB::IT];
+      if (nw < nkt) {
+        a.load_any(xa, fa, nw);
+        b.load_any(xb, fb, nw);
+        in_order();
       }
-    };
-    if (whole >= R) {
-      for_each_stage(fetch_whole, std::make_integer_sequence<int, R>{});
-    } else {
-#pragma unroll
-      for (int s = 0; s < R; s++) {
-        a.load(ra[s], fa[s]);
-        b.load(rb[s], fb[s]);
-      }
-    }
-    // Steady trips: tile kt + R is whole too, so its loads are plain and the fixes are constants of the thread.
-    if constexpr (!CONV) {
-      for (; kt + 2 * R - 1 < whole; kt += R) {
-        for_each_stage([&](auto sc) {
-          stage_whole(buf, sc);
-          fetch_whole(sc);
-          block_sync();
-          multiply(buf);
-          buf ^= 1;
-        }, std::make_integer_sequence<int, R>{});
-      }
-    }
-    // The rest.  Tiles beyond the last are requested like any other (nothing of them is kept): a request that depended
-    // on the tile would make every wait below drain all of them.
-    for (;;) {
-#pragma unroll
-      for (int s = 0; s < R; s++) {
-        if (kt >= nkt) goto multiplied;
-        stage_rt(buf, s);
-        a.load(ra[s], fa[s]);
-        b.load(rb[s], fb[s]);
+      int k = 0;
+      Frags f;
+      // the partial tile, once its requests and those of w_0 .. w_(R - 1) are out
+      auto begin = [&](auto refill) {
+        if (nw < nkt) store_fixed(1, xa, xb, fa, fb);
+        if (refill.value || nw > 0) stage(0, std::integral_constant<int, 0>{});
+        if (refill.value || R < nw) fetch(std::integral_constant<int, 0>{});
         block_sync();
-        multiply(buf);
-        buf ^= 1;
-        kt++;
+        if (nw < nkt) {
+          read(1, f);
+          multiply(f);
+          block_sync();
+        }
+      };
+      if (nw > 2 * R) {  // requests without conditions from the first to the last steady trip, so that every wait is counted
+        for_each_stage(fetch, std::make_integer_sequence<int, R>{});
+        begin(std::true_type{});
+#pragma unroll 1
+        for (; k + 2 * R < nw; k += R) {
+          for_each_stage([&](auto sc) {
+            constexpr int S = decltype(sc)::value, N = (S + 1) % R;
+            read(S & 1, f);
+            stage(N & 1, std::integral_constant<int, N>{});
+            fetch(std::integral_constant<int, N>{});
+            multiply(f);
+            block_sync();
+          }, std::make_integer_sequence<int, R>{});
+        }
+      } else {
+        for_each_stage([&](auto sc) {
+          if (decltype(sc)::value < nw) fetch(sc);
+        }, std::make_integer_sequence<int, R>{});
+        begin(std::false_type{});
+        for (int g = nw + 1; g < nkt; g++) {  // rows of fewer than 16 bytes: no tile is whole
+          a.load_any(xa, fa, g);
+          b.load_any(xb, fb, g);
+          store_fixed(1, xa, xb, fa, fb);
+          block_sync();
+          read(1, f);
+          multiply(f);
+          block_sync();
+        }
+      }
+#pragma unroll 1
+      while (k < nw) {
+        for_each_stage([&](auto sc) {
+          constexpr int S = decltype(sc)::value, N = (S + 1) % R;
+          if (k < nw) {
+            read(S & 1, f);
+            if (k + 1 < nw) stage(N & 1, std::integral_constant<int, N>{});
+            if (k + 1 + R < nw) fetch(std::integral_constant<int, N>{});
+            multiply(f);
+            block_sync();
+          }
+          k++;
+        }, std::make_integer_sequence<int, R>{});
       }
     }
   multiplied:
@@ -427,9 +491,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   }
 }
 
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV>
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV, int R = 2>
 static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
-  constexpr int THREADS = 64 * WAVES_M * WAVES_N, R = CONV ? 2 : 3;
+  constexpr int THREADS = 64 * WAVES_M * WAVES_N;
   constexpr int LDS = 2 * (RaggedTile<T, BM, THREADS, AKC>::BYTES + RaggedTile<T, BN, THREADS, BKC>::BYTES);
   auto kern = gemm_ragged_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AKC, BKC, CONV, R>;
   static std::atomic<bool> configured{LDS <= 64 * 1024};
@@ -437,7 +501,9 @@ static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int64_t items = (int64_t)tiles_m * tiles_n * p.splits;
   const unsigned grid = (unsigned)(items < (1 << 20) ? items : (1 << 20));  // beyond that the workgroups walk over the items
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, p, tiles_m, tiles_n);
+  const uint64_t band = 4 * (uint64_t)tiles_n;  // tiles of a band (tile_coords_mul)
+  const unsigned band_magic = (uint64_t)tiles_m * tiles_n * band < (1ull << 32) ? FastDiv::make((unsigned)band).magic : 0u;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, p, tiles_m, tiles_n, band_magic);
   return hipGetLastError();
 }
 
@@ -470,9 +536,10 @@ static bool ragged_tiny(const GemmParams& p) {
   return p.K > 0 && ((CONV ? (int64_t)p.a_bytes : bytes(AKC, p.lda, p.M)) < 16 || bytes(BKC, p.ldb, p.N) < 16);
 }
 
-// Tile of the ragged kernel: 128 x 128 (eight waves) once such tiles fill half the chip, 64 x 64 otherwise.
+// Tile of the ragged kernel: 128 x 128 once such tiles fill half the chip, 64 x 64 otherwise (an edge of less than 192
+// wastes too much of the second tile: bf16 130 x 9001 x 301 10.6 us with 128, 9.0 with 64).
 static inline int ragged_tile(int32_t M, int32_t N) {
-  return M >= 96 && N >= 96 && (int64_t)((M + 127) / 128) * ((N + 127) / 128) >= 128 ? 128 : 64;
+  return M >= 192 && N >= 192 && (int64_t)((M + 127) / 128) * ((N + 127) / 128) >= 128 ? 128 : 64;
 }
 template <class T, class EPI, bool AKC, bool BKC, bool CONV = false>
 static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t stream) {
@@ -483,7 +550,17 @@ static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t strea
       return hipGetLastError();
     }
   }
-  return tile >= 128 ? launch_ragged_tile<T, EPI, 128, 128, 2, 4, AKC, BKC, CONV>(p, stream)
+  // 64 x 64 tiles that would leave some compute units with two and others with one become 128 x 64 tiles, one apiece
+  // and twice the waves: bf16 1023 x 1537 x 1021 (400 tiles of 64 x 64) 17.6 -> 15.0 us, int8 13.1 -> 10.8, int8
+  // 2047 x 800 x 333 6.5 -> 6.3; with one tile to a compute unit anyway the smaller tile wins (int8 1000^3 7.7, 8.1).
+  if (!CONV && tile == 64) {
+    const int64_t tn = (p.N + 63) / 64, tall = (int64_t)((p.M + 127) / 128) * tn;
+    if (p.splits == 1 && tall <= 256 && (int64_t)((p.M + 63) / 64) * tn > 256) return launch_ragged_tile<T, EPI, 128, 64, 4, 2, AKC, BKC, CONV>(p, stream);
+  }
+  // 128 x 128: sixteen waves of one MFMA tile each for int8, whose products are short beside a trip's other work
+  // (2047 x 2045 x 2041 23.2 -> 21.9 us, 1516 x 1764 x 56 6.9 -> 6.1), eight waves of two for bf16 (1500^3 24.0, 26.3)
+  constexpr int WAVES_M = T::EB == 1 && !CONV ? 4 : 2;
+  return tile >= 128 ? launch_ragged_tile<T, EPI, 128, 128, WAVES_M, 4, AKC, BKC, CONV>(p, stream)
                      : launch_ragged_tile<T, EPI, 64, 64, 2, 2, AKC, BKC, CONV>(p, stream);
 }
 

@@ -97,3 +97,26 @@ def test_convolutions(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
         out = torch.full(want.shape, 17, dtype=torch.int8, device="cuda")
         ops.ac_conv2d_i8(dev(x), dev(w), dev(b), out, stride, pad, 8, 1, workspace=ws)
         np.testing.assert_array_equal(host(out), want)
+
+
+# K tiles of 128 bytes against the pipeline of the whole tiles: none, 1 .. 2 R + 2 of them (steady trips start at 2 R + 1,
+# R = 2), with and without a partial tile; tiles of 64 x 64, 128 x 64 (more than 256 of the former) and 128 x 128
+@pytest.mark.parametrize("M,N", [(61, 67), (1030, 1027), (1985, 1410)])
+@pytest.mark.parametrize("K", [100, 128, 131, 256, 300, 384, 512, 520, 640, 641, 768, 896, 1000])
+def test_pipeline_edges(M, N, K):
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=M + 3 * N + 7 * K)
+    want = A.astype(np.float64) @ B.astype(np.float64) + bias  # (exact: sums below 2^53)
+    C = torch.full((M, N), 33, dtype=torch.int32, device="cuda")
+    ops.ac_gemm_i8_acc32(odd_view(A), odd_view(B), dev(bias), C)
+    np.testing.assert_array_equal(host(C), want.astype(np.int64))
+    q = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+    matrix = np.broadcast_to(bias, (M, N)).astype(np.int32)
+    for b in (dev(bias), dev(matrix)):
+        ops.ac_gemm_i8(odd_view(A), odd_view(B), b, q, 9, 0)
+        np.testing.assert_array_equal(host(q), np.clip(np.rint(want / 512), -128, 127).astype(np.int8))  # halves to even
+    if K % 2 == 0:
+        A2, B2 = inputs.gemm_bf16_inputs(M, N, K // 2, seed=K)
+        a, b = inputs.bf16_bits_to_f32(A2).astype(np.float64), inputs.bf16_bits_to_f32(B2).astype(np.float64)
+        Cf = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ops.ac_gemm_bf16(odd_view(A2), odd_view(B2), Cf)
+        assert (np.abs(host(Cf) - a @ b) <= 4.0 * (K // 2 + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)) + 1e-30).all()
