@@ -2,7 +2,7 @@
 //
 // The work is bound by HBM traffic (2 flop per byte), so the kernel is a
 // streaming one: a workgroup brings G consecutive items into LDS with fully
-// coalesced 16-byte loads, 16 lanes then own one item as a 4 x 4 grid of small
+// coalesced loads, 16 lanes then own one item as a 4 x 4 grid of small
 // register blocks of C, the matrix-vector partial sums are combined across the 4
 // lanes of a quad with DPP shuffles, and C goes back out through LDS so that the
 // stores are coalesced as well.
@@ -18,40 +18,17 @@ static __device__ __forceinline__ float quad_xor2(float v) {  // lane ^ 2 within
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
 }
 
-// Coalesced copy of `count` floats global -> LDS (VEC: 16-byte granules where whole).
-template <bool VEC>
+// Coalesced copies of `count` floats, global -> LDS and back.
 static __device__ __forceinline__ void copy_in(float* dst, const float* src, int count, int t) {
-  if (VEC) {
-    for (int i = t * 4; i < count; i += 256 * 4) {
-      if (i + 3 < count) {
-        *(v4f*)(dst + i) = *(const v4f*)(src + i);
-      } else {
-        for (int e = 0; i + e < count; e++) dst[i + e] = src[i + e];
-      }
-    }
-  } else {
-    for (int i = t; i < count; i += 256) dst[i] = src[i];
-  }
+  for (int i = t; i < count; i += 256) dst[i] = src[i];
 }
-
-template <bool VEC>
 static __device__ __forceinline__ void copy_out(float* dst, const float* src, int count, int t) {
-  if (VEC) {
-    for (int i = t * 4; i < count; i += 256 * 4) {
-      if (i + 3 < count) {
-        *(v4f*)(dst + i) = *(const v4f*)(src + i);
-      } else {
-        for (int e = 0; i + e < count; e++) dst[i + e] = src[i + e];
-      }
-    }
-  } else {
-    for (int i = t; i < count; i += 256) dst[i] = src[i];
-  }
+  for (int i = t; i < count; i += 256) dst[i] = src[i];
 }
 
 // NFIX > 0: n is the compile-time constant NFIX.  NFIX == 0: n = p.n at run time (1..16).
-// G items per workgroup (multiple of 16).  VEC: all pointers are 16-byte aligned.
-template <int NFIX, int G, bool VEC>
+// G items per workgroup (multiple of 16).  Pointers of any 4-byte alignment.
+template <int NFIX, int G>
 __global__ void __launch_bounds__(256) batched_f32_kernel(const BatchedParams p) {
   extern __shared__ __attribute__((aligned(16))) float lds_f[];
   const int n = NFIX ? NFIX : p.n;
@@ -67,10 +44,10 @@ __global__ void __launch_bounds__(256) batched_f32_kernel(const BatchedParams p)
   const int64_t left = p.batch - b0;
   const int cnt = left < G ? (int)left : G;
 
-  copy_in<VEC>(As, p.A + b0 * nn, cnt * nn, t);
-  copy_in<VEC>(Bs, p.B + b0 * nn, cnt * nn, t);
-  if (p.x) copy_in<VEC>(xs, p.x + b0 * n, cnt * n, t);
-  if (p.x && p.d) copy_in<VEC>(ds, p.d + b0 * n, cnt * n, t);
+  copy_in(As, p.A + b0 * nn, cnt * nn, t);
+  copy_in(Bs, p.B + b0 * nn, cnt * nn, t);
+  if (p.x) copy_in(xs, p.x + b0 * n, cnt * n, t);
+  if (p.x && p.d) copy_in(ds, p.d + b0 * n, cnt * n, t);
   __syncthreads();
 
   const int sub = t & 15;           // lane within the item's 4 x 4 grid
@@ -128,8 +105,159 @@ __global__ void __launch_bounds__(256) batched_f32_kernel(const BatchedParams p)
   }
   if (p.C) {
     __syncthreads();
-    copy_out<VEC>(p.C + b0 * nn, As, cnt * nn, t);
+    copy_out(p.C + b0 * nn, As, cnt * nn, t);
   }
+}
+
+// ---- other sizes, 16-byte aligned operands -----------------------------------------------------------------
+// The same plan with n a compile-time constant: the register blocks fit n (with n at run time every item took the
+// 16 x 16 grid, a quarter of whose lanes an 8 x 8 item uses), and all of a workgroup's loads are requested before
+// any of them is waited for (copied array by array, a small batch is a chain of four memory latencies).
+// Bound: HBM traffic for large batches, one memory latency and the launch for small ones.  Before and after: 120000
+// items of n = 2 17.6 -> 4.9 us, 5 23.9 -> 10.8, 8 38.5 -> 20.3, 11 50.4 -> 36.8, 16 115 -> 70.5 (5.4 TB/s); 262144 of
+// n = 16 without x 210 -> 138 (5.8 TB/s); 125 items of n = 9 5.6 -> 3.8, of 16 8.1 -> 5.2.
+//
+// Items of n = 8 and 16 are spread in LDS (RS floats from row to row, IS from item to item) so that the four row
+// blocks of four items fall on banks of their own; whole 16-byte chunks stay inside a row there.
+template <int N>
+struct BatchedFixed {
+  static constexpr int RS = N == 16 ? 20 : N, IS = N == 16 ? 324 : (N == 8 ? 68 : N * N);
+  static constexpr int G = N <= 3 ? 128 : (N <= 4 ? 64 : (N <= 8 ? 32 : 16));  // items per workgroup: 2 to 16 KB of A
+  static constexpr int MAT = G * N * N / 4, VEC = G * N / 4;                   // 16-byte chunks of A (B, C), of x (d)
+  static constexpr int CT = (MAT + 255) / 256, VT = (VEC + 255) / 256;         // ... per thread
+  static constexpr int LDS = (2 * G * IS + 2 * G * N) * 4;
+  static __device__ __forceinline__ int at(int chunk) {  // float index in LDS of a chunk of a matrix array
+    if constexpr (IS == N * N) return 4 * chunk;
+    const int item = chunk / (N * N / 4), r = chunk - item * (N * N / 4), row = r / (N / 4);
+    return item * IS + row * RS + 4 * (r - row * (N / 4));
+  }
+};
+
+template <int N>
+__global__ void __launch_bounds__(256) batched_fixed_kernel(const BatchedParams p) {
+  using F = BatchedFixed<N>;
+  constexpr int G = F::G, RB = (N + 3) / 4;  // the 4 x 4 lane grid covers 4 RB >= N
+  extern __shared__ __attribute__((aligned(16))) float lds_f[];
+  float* const As = lds_f;  // reused for C on the way out
+  float* const Bs = As + G * F::IS;
+  float* const xs = Bs + G * F::IS;
+  float* const ds = xs + G * N;
+  const int t = threadIdx.x;
+  const int64_t b0 = (int64_t)blockIdx.x * G;
+  const int cnt = p.batch - b0 < G ? (int)(p.batch - b0) : G;
+  const bool has_x = p.x != nullptr, has_d = has_x && p.d != nullptr;
+  const float *Ag = p.A + b0 * (N * N), *Bg = p.B + b0 * (N * N), *xg = p.x + b0 * N, *dg = p.d + b0 * N;
+
+  if (cnt == G) {
+    v4f a[F::CT], b[F::CT], x[F::VT], d[F::VT];
+    // a thread without a chunk of its own in a pass takes the last one again
+    auto chunk = [&](int i, int n) { return i * 256 + t < n ? i * 256 + t : n - 1; };
+#pragma unroll
+    for (int i = 0; i < F::CT; i++) a[i] = *(const v4f*)(Ag + 4 * chunk(i, F::MAT));
+#pragma unroll
+    for (int i = 0; i < F::CT; i++) b[i] = *(const v4f*)(Bg + 4 * chunk(i, F::MAT));
+#pragma unroll
+    for (int i = 0; i < F::VT; i++) {
+      if (has_x) x[i] = *(const v4f*)(xg + 4 * chunk(i, F::VEC));
+      if (has_d) d[i] = *(const v4f*)(dg + 4 * chunk(i, F::VEC));
+    }
+#pragma unroll
+    for (int i = 0; i < F::CT; i++) *(v4f*)(As + F::at(chunk(i, F::MAT))) = a[i];
+#pragma unroll
+    for (int i = 0; i < F::CT; i++) *(v4f*)(Bs + F::at(chunk(i, F::MAT))) = b[i];
+#pragma unroll
+    for (int i = 0; i < F::VT; i++) {
+      if (has_x) *(v4f*)(xs + 4 * chunk(i, F::VEC)) = x[i];
+      if (has_d) *(v4f*)(ds + 4 * chunk(i, F::VEC)) = d[i];
+    }
+  } else {  // the last workgroup: its arrays end anywhere
+    for (int i = t; i < cnt * N * N; i += 256) {
+      const int item = i / (N * N), r = i - item * (N * N), row = r / N;
+      As[item * F::IS + row * F::RS + r - row * N] = Ag[i];
+      Bs[item * F::IS + row * F::RS + r - row * N] = Bg[i];
+    }
+    for (int i = t; i < cnt * N; i += 256) {
+      if (has_x) xs[i] = xg[i];
+      if (has_d) ds[i] = dg[i];
+    }
+  }
+  __syncthreads();
+
+  const int sub = t & 15, bi = sub >> 2, bj = sub & 3;  // lane within the item's 4 x 4 grid
+  const int r0 = bi * RB, c0 = bj * RB;
+#pragma unroll 1
+  for (int item = t >> 4; item < cnt; item += 16) {
+    const float* Ai = As + item * F::IS;
+    const float* Bi = Bs + item * F::IS;
+    float c[RB][RB];
+#pragma unroll
+    for (int i = 0; i < RB; i++)
+#pragma unroll
+      for (int j = 0; j < RB; j++) c[i][j] = 0.f;
+    // rows and columns beyond N read the last one: their results are never used
+    int ra[RB], cb[RB];
+#pragma unroll
+    for (int i = 0; i < RB; i++) ra[i] = (r0 + i < N ? r0 + i : N - 1) * F::RS, cb[i] = c0 + i < N ? c0 + i : N - 1;
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+      float a[RB], b[RB];
+#pragma unroll
+      for (int i = 0; i < RB; i++) a[i] = Ai[ra[i] + k];
+#pragma unroll
+      for (int j = 0; j < RB; j++) b[j] = Bi[k * F::RS + cb[j]];
+#pragma unroll
+      for (int i = 0; i < RB; i++)
+#pragma unroll
+        for (int j = 0; j < RB; j++) c[i][j] = __builtin_fmaf(a[i], b[j], c[i][j]);
+    }
+    if (has_x) {
+      float xv[RB];
+#pragma unroll
+      for (int j = 0; j < RB; j++) xv[j] = xs[item * N + cb[j]];
+#pragma unroll
+      for (int i = 0; i < RB; i++) {
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < RB; j++) s = c0 + j < N ? __builtin_fmaf(c[i][j], xv[j], s) : s;
+        s += quad_xor1(s);  // sum over the 4 column blocks of this row
+        s += quad_xor2(s);
+        if (bj == 0 && r0 + i < N) p.y[(b0 + item) * N + r0 + i] = s + (has_d ? ds[item * N + r0 + i] : 0.f);
+      }
+    }
+    if (p.C) {
+      // all 16 lanes of this item sit in one wavefront and have finished reading Ai
+      float* Ci = As + item * F::IS;
+#pragma unroll
+      for (int i = 0; i < RB; i++)
+#pragma unroll
+        for (int j = 0; j < RB; j++)
+          if (r0 + i < N && c0 + j < N) Ci[(r0 + i) * F::RS + c0 + j] = c[i][j];
+    }
+  }
+  if (p.C) {
+    __syncthreads();
+    float* Cg = p.C + b0 * (N * N);
+    if (cnt == G) {
+#pragma unroll
+      for (int i = 0; i < F::CT; i++)
+        if (i * 256 + t < F::MAT) *(v4f*)(Cg + 4 * (i * 256 + t)) = *(const v4f*)(As + F::at(i * 256 + t));
+    } else {
+      for (int i = t; i < cnt * N * N; i += 256) {
+        const int item = i / (N * N), r = i - item * (N * N), row = r / N;
+        Cg[i] = As[item * F::IS + row * F::RS + r - row * N];
+      }
+    }
+  }
+}
+
+template <int N>
+static hipError_t launch_batched_fixed(const BatchedParams& p, hipStream_t stream) {
+  using F = BatchedFixed<N>;
+  static_assert(F::LDS <= 64 * 1024 && F::G * N % 4 == 0, "LDS and whole chunks");
+  const int64_t blocks = (p.batch + F::G - 1) / F::G;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(batched_fixed_kernel<N>, dim3((unsigned)blocks), dim3(256), F::LDS, stream, p);
+  return hipGetLastError();
 }
 
 // ---- 12 x 12 streaming kernel -----------------------------------------------------------------------------
@@ -291,18 +419,34 @@ hipError_t launch_batched_f32(const BatchedParams& p, hipStream_t stream) {
     hipLaunchKernelGGL(batched12_stream_kernel, dim3((unsigned)wgs), dim3(64 * B12_WAVES), B12_WAVES * 3 * B12_WIN, stream, p);
     return hipGetLastError();
   }
-  // LDS-staged kernel: 32 items per workgroup for unaligned 12 x 12 operands (39 KB of LDS), 16 for other n
+  if (vec) {
+    switch (n) {
+      case 1: return launch_batched_fixed<1>(p, stream);
+      case 2: return launch_batched_fixed<2>(p, stream);
+      case 3: return launch_batched_fixed<3>(p, stream);
+      case 4: return launch_batched_fixed<4>(p, stream);
+      case 5: return launch_batched_fixed<5>(p, stream);
+      case 6: return launch_batched_fixed<6>(p, stream);
+      case 7: return launch_batched_fixed<7>(p, stream);
+      case 8: return launch_batched_fixed<8>(p, stream);
+      case 9: return launch_batched_fixed<9>(p, stream);
+      case 10: return launch_batched_fixed<10>(p, stream);
+      case 11: return launch_batched_fixed<11>(p, stream);
+      case 13: return launch_batched_fixed<13>(p, stream);
+      case 14: return launch_batched_fixed<14>(p, stream);
+      case 15: return launch_batched_fixed<15>(p, stream);
+      case 16: return launch_batched_fixed<16>(p, stream);
+      default: return hipErrorInvalidValue;  // (the entry point takes 1 .. 16)
+    }
+  }
+  // LDS-staged kernel for unaligned operands: 32 items per workgroup for 12 x 12 (39 KB of LDS), 16 for other n
   const int G = n == 12 ? 32 : 16;
   const size_t lds = (size_t)G * (2 * n * n + 2 * n) * sizeof(float);
   const int64_t blocks = (p.batch + G - 1) / G;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks), block(256);
-  if (n == 12) {
-    hipLaunchKernelGGL((batched_f32_kernel<12, 32, false>), grid, block, lds, stream, p);
-  } else {
-    if (vec) hipLaunchKernelGGL((batched_f32_kernel<0, 16, true>), grid, block, lds, stream, p);
-    else hipLaunchKernelGGL((batched_f32_kernel<0, 16, false>), grid, block, lds, stream, p);
-  }
+  if (n == 12) hipLaunchKernelGGL((batched_f32_kernel<12, 32>), grid, block, lds, stream, p);
+  else hipLaunchKernelGGL((batched_f32_kernel<0, 16>), grid, block, lds, stream, p);
   return hipGetLastError();
 }
 

@@ -79,3 +79,21 @@ def test_empty_and_errors():
     assert L.ac_batched_gemm_f32(a, a + 1024, a + 2048, a + 3072, None, None, 12, 1, None) == ops.AC_ERR_NULL
     assert L.ac_batched_gemm_f32(a, a + 1024, a, None, None, None, 12, 1, None) == ops.AC_ERR_ALIAS
     assert L.ac_batched_gemm_f32(None, a + 1024, a + 2048, None, None, None, 12, 1, None) == ops.AC_ERR_NULL
+
+
+@pytest.mark.parametrize("n", range(1, 17))
+def test_every_size_at_workgroup_edges(n):
+    """Batches that end one under, at and one over a workgroup's items (16 to 128 of them), aligned and not, with NaN
+    behind the inputs and guard values behind the outputs."""
+    for batch in (1, 15, 16, 17, 31, 33, 64, 65, 127, 129, 260):
+        A, B, x, d = inputs.batched_f32_inputs(batch, n, seed=n * 1000 + batch)
+        Cw, yw = oracle.batched_gemm_f32(A, B, x, d)
+        for lead in (0, 1):  # one float off an aligned address: the kernel for unaligned operands
+            def put(a, fill=float("nan")):
+                buf = torch.full((a.size + lead + 64,), fill, dtype=torch.float32, device="cuda")
+                buf[lead:lead + a.size] = dev(a).reshape(-1)
+                return buf, buf[lead:lead + a.size].view(a.shape)
+            (bc, C), (by, y) = put(np.zeros_like(A), 7.0), put(np.zeros_like(x), 7.0)
+            ops.ac_batched_gemm_f32(put(A)[1], put(B)[1], C, put(x)[1], put(d)[1], y)
+            assert np.abs(host(C) - Cw).max() <= 4 * n * 2.0 ** -24 * n and np.abs(host(y) - yw).max() <= 4 * (2 * n + 1) * 2.0 ** -24 * n * n
+            assert (host(bc)[lead + A.size:] == 7.0).all() and (host(by)[lead + x.size:] == 7.0).all()
