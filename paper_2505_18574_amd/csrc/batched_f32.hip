@@ -18,6 +18,11 @@ static __device__ __forceinline__ float quad_xor2(float v) {  // lane ^ 2 within
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
 }
 
+template <int Q>
+static __device__ __forceinline__ float quad_bcast(float v) {  // lane Q of the quad
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), Q * 0x55, 0xF, 0xF, true));
+}
+
 // Coalesced copies of `count` floats, global -> LDS and back.
 static __device__ __forceinline__ void copy_in(float* dst, const float* src, int count, int t) {
   for (int i = t; i < count; i += 256) dst[i] = src[i];
@@ -211,17 +216,39 @@ __global__ void __launch_bounds__(256) batched_fixed_kernel(const BatchedParams 
         for (int j = 0; j < RB; j++) c[i][j] = __builtin_fmaf(a[i], b[j], c[i][j]);
     }
     if (has_x) {
-      float xv[RB];
+      if constexpr (RB <= 2) {
+        // blocks this narrow would cost the sum more roundings than its terms: every lane takes the whole row from its
+        // quad and adds it in runs of four
+        float xv[N];
 #pragma unroll
-      for (int j = 0; j < RB; j++) xv[j] = xs[item * N + cb[j]];
+        for (int j = 0; j < N; j++) xv[j] = xs[item * N + j];
 #pragma unroll
-      for (int i = 0; i < RB; i++) {
-        float s = 0.f;
+        for (int i = 0; i < RB; i++) {
+          float row[4 * RB];
 #pragma unroll
-        for (int j = 0; j < RB; j++) s = c0 + j < N ? __builtin_fmaf(c[i][j], xv[j], s) : s;
-        s += quad_xor1(s);  // sum over the 4 column blocks of this row
-        s += quad_xor2(s);
-        if (bj == 0 && r0 + i < N) p.y[(b0 + item) * N + r0 + i] = s + (has_d ? ds[item * N + r0 + i] : 0.f);
+          for (int j = 0; j < RB; j++) {
+            row[j] = quad_bcast<0>(c[i][j]), row[RB + j] = quad_bcast<1>(c[i][j]);
+            row[2 * RB + j] = quad_bcast<2>(c[i][j]), row[3 * RB + j] = quad_bcast<3>(c[i][j]);
+          }
+          float s[2] = {0.f, 0.f};
+#pragma unroll
+          for (int j = 0; j < N; j++) s[j / 4] = __builtin_fmaf(row[j], xv[j], s[j / 4]);
+          if (bj == 0 && r0 + i < N) p.y[(b0 + item) * N + r0 + i] = s[0] + s[1] + (has_d ? ds[item * N + r0 + i] : 0.f);
+        }
+      } else {
+        float xv[RB];
+#pragma unroll
+        for (int j = 0; j < RB; j++) xv[j] = xs[item * N + cb[j]];
+#pragma unroll
+        for (int i = 0; i < RB; i++) {
+          const int r = r0 + i < N ? r0 + i : N - 1;
+          float s = has_d && bj == 0 ? ds[item * N + r] : 0.f;  // (added first, where it costs no rounding of its own)
+#pragma unroll
+          for (int j = 0; j < RB; j++) s = c0 + j < N ? __builtin_fmaf(c[i][j], xv[j], s) : s;
+          s += quad_xor1(s);  // sum over the 4 column blocks of this row
+          s += quad_xor2(s);
+          if (bj == 0 && r0 + i < N) p.y[(b0 + item) * N + r] = s;
+        }
       }
     }
     if (p.C) {
