@@ -413,6 +413,15 @@ bool conv_i8_fast_path(const GemmParams& p) {
          ((int64_t)p.M / (p.OW > 0 ? p.OW : 1) + 1) * p.OH < lim && p.a_bytes > 0 && lane_offsets_fit(0, p.ldb);
 }
 
+// A convolution of at most 64 output channels on more than one 64 x 64 tile per compute unit: that tile, uncut.  The
+// planner's estimates, made for products, take wider tiles or K slices there, which compute or store columns that do not
+// exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of 55 x 55
+// 101 -> 77; level on the shapes where they agree).
+static bool narrow_conv_plan(const GemmParams& p, GemmPlan* plan) {
+  if (p.N > 64 || p.M <= 64 * PLAN_CUS || plan->tile == 32) return false;
+  return make_plan_i8(p.K, 64, 1, plan);
+}
+
 hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced) {
   const bool fast = conv_i8_fast_path(p);
   if (hipError_t e; !forced && !fast && launch_conv_image(p, stream, &e)) return e;  // channels that are not whole chunks
@@ -451,7 +460,8 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
       // 18.5 us on the best tiled kernel, 128 images 29.6 against 33.6)
       if (h.units * nblk >= 512) return launch_conv_halo<128>(q, h, lds, stream);
     } else if (p.KH * p.KW <= 32) {
-      return dispatch_i8<1>(p, stream, fast, forced);
+      GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0);
+      return narrow_conv_plan(p, &plan) ? dispatch_i8<1>(p, stream, fast, &plan) : dispatch_i8<1>(p, stream, fast, nullptr);
     }
     // a convolution the patch kernel could take but that is too small for it: the tiled kernels (or one wave per
     // tile, by the GEMM's rule: 56 x 56 x 64 -> 64, one image, 4.4 us against 5.4; K = 1152 gains 0.5 us with the
@@ -460,6 +470,7 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0);
     int ws_bm;
     if (wstat_tile_rows(plan.tile, &ws_bm)) make_plan_i8(p.K, choose_tile(p.M, p.N), 1, &plan);  // unsplit: no workspace needed
+    narrow_conv_plan(p, &plan);
     return dispatch_i8<1>(p, stream, fast, &plan);
   }
   return dispatch_i8<1>(p, stream, fast, forced);
