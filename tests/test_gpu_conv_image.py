@@ -1,7 +1,7 @@
 """GPU parity of the convolution kernel for channels that are not whole 16-byte chunks, bit for bit, where its forms
-change: channel counts of one to several dwords a pixel, runs of one chunk, two and more, odd and even K-steps, patches
-of one piece to a wave and of many, short rows that share a piece, units that end inside an image, column blocks of 32,
-64 and 96 with partial columns, weights that end inside a chunk, inputs whose last dword is cut, odd addresses."""
+change: windows that start on any byte of a dword, runs of one chunk, two and more, odd and even K-steps, patches of one
+piece to a wave and of many, short rows that share a piece, rows that end inside a chunk, units that end inside an image,
+column blocks of 32, 64 and 96 with partial columns, weights and inputs that end inside a chunk, odd addresses."""
 import numpy as np
 import pytest
 import torch
@@ -35,8 +35,11 @@ def check(Nb, H, W, Cin, Cout, KH, KW, stride, pad, shift=8, act=1, put=dev, bia
     (1, 30, 31, 2, 96, 2, 4, 1, 2),      # two runs of one chunk: one K-step
     (3, 1, 1, 3, 8, 5, 5, 1, 2),         # images of three bytes, all but one tap padding
     (5, 7, 7, 14, 27, 3, 3, 1, 1),       # short rows share a piece; 27 columns
-    (1, 5, 3, 1, 16, 3, 3, 1, 1),        # an input of 15 bytes
-    (2, 13, 11, 59, 57, 3, 3, 1, 1),     # 15 dwords a pixel
+    (1, 5, 3, 1, 16, 3, 3, 1, 1),        # an input of 15 bytes: not taken
+    (1, 4, 4, 1, 17, 3, 3, 1, 1),        # ... of 16
+    (1, 17, 1, 1, 17, 3, 1, 1, 0),       # ... of 17, rows of one byte
+    (2, 9, 1100, 2, 40, 3, 3, 2, 1),     # rows of more than 64 chunks
+    (2, 13, 11, 59, 57, 3, 3, 1, 1),     # runs of 177 bytes
     (1, 9, 200, 5, 130, 3, 3, 1, 1),     # several pieces to a row, two column blocks, the second partial
     (2, 33, 1, 3, 33, 3, 1, 2, 0),       # one column of pixels
     (1, 1, 300, 6, 70, 1, 5, 3, 1),      # one row
@@ -46,7 +49,7 @@ def check(Nb, H, W, Cin, Cout, KH, KW, stride, pad, shift=8, act=1, put=dev, bia
     (2, 17, 16, 65, 50, 1, 1, 2, 0),     # ... and the first not taken
     (1, 18, 18, 40, 20, 7, 7, 1, 3),     # 63 K-steps
     (1, 18, 18, 41, 20, 7, 7, 1, 3),     # beyond 64: the any-alignment kernel
-    (8, 100, 101, 3, 48, 7, 7, 2, 3),    # units of 256 pixels
+    (8, 100, 101, 3, 48, 7, 7, 2, 3),    # several units to a workgroup
     (13, 57, 59, 16, 32, 3, 3, 1, 1),    # sixteen channels, more than 512 tiles
     (1, 6, 6, 3, 16, 3, 3, 1, 20),       # windows of padding only
 ])
