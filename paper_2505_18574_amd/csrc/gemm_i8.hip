@@ -450,8 +450,8 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     // and the patch of a kernel of more than 32 taps is mostly halo
     const bool taps = p.KH * p.KW > 1 && p.KH * p.KW <= 32;
     // sixteen channels are half a K-step of the patch kernel, which does not take them: the same rule sends 3 x 3 kernels
-    // over them to the kernel that pads its runs (16 -> 64 on 32 images of 56 x 56 11.2 us tiled and 8.9 there, 16 -> 32
-    // on 64 of 28 x 28 7.4 and 5.3; 5 x 5 with stride 2, 16 -> 368 on 13 of 54 x 54 12.2 and 12.8)
+    // over them to the kernel that pads its runs (16 -> 64 on 32 images of 56 x 56 12.0 us tiled and 8.1 there, 16 -> 32
+    // on 64 of 28 x 28 7.5 and 5.4, 16 -> 320 on 50 of 50 x 50 39.9 and 21.1)
     if (hipError_t e; p.Cin == 16 && p.KH * p.KW > 1 && p.KH * p.KW <= 9 && tiles64 > 512 && launch_conv_image(p, stream, &e)) return e;
     if (taps && conv_halo_plan(p, 256, &h, &lds)) {
       if (h.units * nblk >= 256 || tiles64 > 512) return launch_conv_halo<256>(q, h, lds, stream);
