@@ -7,6 +7,7 @@
 // (tinympc_forward_mfma_kernel); any other size, and unaligned arrays, on the vector ALU with four lanes per problem
 // (tinympc_forward_quad_kernel).
 #include "common.hpp"
+#include "tinympc_window.hpp"
 
 #include <type_traits>
 
@@ -203,8 +204,8 @@ __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const 
 // them independent.
 //
 // d comes in and u and the trajectory leave as whole contiguous runs through a wave-private LDS window (u overwrites d
-// in place).  A horizon too long for the window goes through it `chunk` steps at a time, a run per problem.
-// WHOLE: chunk == horizon.
+// in place; tinympc_window.hpp).  A horizon too long for the window goes through it `chunk` steps at a time, a run per
+// problem.  WHOLE: all of it is in the window at once.
 template <int RX, int RU, bool WHOLE>
 __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpcParams p, const int window, const int chunk) {
   extern __shared__ __attribute__((aligned(16))) float tmpc_quad_lds[];
@@ -213,9 +214,10 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
   const int q = lane & 3, pr = lane >> 2;
   const int64_t nblk = (p.batch + 15) / 16, stride = (int64_t)gridDim.x * waves;
   const bool traj = p.x_out != nullptr;
-  const int dpitch = chunk * nu, xpitch = (WHOLE ? H + 1 : chunk) * nx;  // floats per problem; x[0] has no place in a chunk
+  const TmpcLayout at = tmpc_layout(nx, nu, H, chunk, WHOLE);
+  const int dpitch = at.dpitch, xpitch = at.xpitch;
   float* dwin = tmpc_quad_lds + wave * window;  // [16 problems][chunk][nu]: d, then u (before that: the matrices)
-  float* xwin = dwin + ((16 * dpitch + 3) & ~3);
+  float* xwin = dwin + at.xwin;
   float *dmine = dwin + pr * dpitch, *xmine = xwin + pr * xpitch;
 
   // The matrices pass through the wave's LDS window, padded with zeros to whole fours, so that a lane picks its rows up
@@ -337,23 +339,16 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
 
 template <int RX, int RU>
 static hipError_t launch_quad(const TinyMpcParams& p, hipStream_t stream) {
-  // Floats of a wave's window: the whole horizon of 16 problems up to 16 KB (ten waves to a compute unit), chunks of it
-  // beyond; never less than the 256 a matrix needs on its way in.
-  constexpr int64_t MOST = 4096;
-  const int per_step = 16 * (p.nu + (p.x_out ? p.nx : 0));
-  const int64_t all = (int64_t)p.horizon * per_step + (p.x_out ? 16 * p.nx : 0) + 3;
-  const int chunk = all <= MOST ? p.horizon : (int)((MOST - 3) / per_step);
-  int64_t window = all <= MOST ? all : MOST;
-  window = window < 256 ? 256 : (window + 3) & ~3ll;
+  const TmpcWindow w = tmpc_window(p.nx, p.nu, p.horizon, p.x_out != nullptr);
   const int64_t blocks16 = (p.batch + 15) / 16;
   // one-wave workgroups until every compute unit has four: a small batch then spreads over the chip
   const int waves = blocks16 >= 4 * (int64_t)compute_units() ? 4 : 1;
   const int64_t most = (int64_t)compute_units() * 16 / waves;  // persistent beyond that: the matrices are loaded once per wave
   const int64_t wgs = (blocks16 + waves - 1) / waves;
   const dim3 grid((unsigned)(wgs < most ? wgs : most)), block(64 * waves);
-  const size_t lds = (size_t)(waves * window * sizeof(float));
-  if (chunk == p.horizon) hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, true>), grid, block, lds, stream, p, (int)window, chunk);
-  else hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, false>), grid, block, lds, stream, p, (int)window, chunk);
+  const size_t lds = (size_t)waves * w.floats * sizeof(float);
+  if (w.whole) hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, true>), grid, block, lds, stream, p, w.floats, w.chunk);
+  else hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, false>), grid, block, lds, stream, p, w.floats, w.chunk);
   return hipGetLastError();
 }
 

@@ -61,6 +61,20 @@ def test_sizes_at_the_edges_of_the_kernels(nx, nu, horizon, batch):
     np.testing.assert_array_equal(u2, u)
 
 
+@pytest.mark.parametrize("batch", [35, 16421])  # one wave and four waves per workgroup
+@pytest.mark.parametrize("nx,nu,horizon", [(12, 5, 15), (12, 3, 17), (9, 16, 10), (7, 8, 17), (15, 15, 8), (16, 1, 15)])
+def test_horizons_of_one_chunk(nx, nu, horizon, batch):
+    """Horizons whose controls and states fit the LDS window and whose first state beside them does not (and one
+    length that just fits): one chunk, not the whole form."""
+    Adyn, Bdyn, Kinf, x0, d = inputs.tinympc_inputs(batch, seed=nx * 100 + horizon, nx=nx, nu=nu, horizon=horizon)
+    Adyn, Bdyn, Kinf = ((m / (1.5 * nx ** 0.5)).astype(np.float32) for m in (Adyn, Bdyn, Kinf))
+    uw, xw = oracle.tinympc_forward(Adyn, Bdyn, Kinf, x0, d, return_x=True)
+    u, xs = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=True)
+    assert rel_fro(u, uw) <= TOL and rel_fro(xs, xw) <= TOL
+    u2, _ = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
+    np.testing.assert_array_equal(u2, u)
+
+
 def test_paper_sizes_on_unaligned_arrays():
     """(12, 4, 5) with x0 and u four bytes off a 16-byte boundary: the vector-ALU kernel, same bar."""
     batch, horizon = 333, 5
