@@ -508,7 +508,9 @@ static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
 }
 
 // An operand of fewer than 16 bytes in all has no chunk to load: one output per thread.  (A matrix of that size has
-// K < 16, a convolution input that many values in all, so an output is a handful of products.)
+// K < 16, a convolution input that many values in all, so an output is a handful of products.)  A convolution without
+// input channels is one of them: its operands may be null, no loop below touches them, and the tiled kernel would
+// request its first tiles before it counts them.  (A product with K = 0 requests nothing there.)
 template <class T, class EPI, bool AKC, bool BKC, bool CONV>
 __global__ void __launch_bounds__(256) gemm_tiny_kernel(const GemmParams p) {
   typedef std::conditional_t<T::EB == 1, int, float> val;
@@ -533,7 +535,8 @@ __global__ void __launch_bounds__(256) gemm_tiny_kernel(const GemmParams p) {
 template <class T, bool AKC, bool BKC, bool CONV>
 static bool ragged_tiny(const GemmParams& p) {
   auto bytes = [&](bool kc, int64_t ld, int64_t extent) { return ((kc ? extent - 1 : p.K - 1) * ld + (kc ? p.K : extent)) * T::EB; };
-  return p.K > 0 && ((CONV ? (int64_t)p.a_bytes : bytes(AKC, p.lda, p.M)) < 16 || bytes(BKC, p.ldb, p.N) < 16);
+  if (p.K <= 0) return CONV;
+  return (CONV ? (int64_t)p.a_bytes : bytes(AKC, p.lda, p.M)) < 16 || bytes(BKC, p.ldb, p.N) < 16;
 }
 
 // Tile of the ragged kernel: 128 x 128 once such tiles fill half the chip, 64 x 64 otherwise (an edge of less than 192

@@ -99,6 +99,23 @@ def test_convolutions(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
         np.testing.assert_array_equal(host(out), want)
 
 
+@pytest.mark.parametrize("KH,KW,stride,pad", [(3, 3, 1, 1), (1, 1, 2, 0), (1, 1, 1, 1), (7, 7, 2, 3), (1, 1, 1, 0)])
+def test_convolutions_without_input_channels(KH, KW, stride, pad):
+    """Empty operands (null addresses): every output is the stage of its bias, with and without a workspace or a plan."""
+    Nb, H, W, Cout = 2, 9, 8, 37
+    x = torch.empty((Nb, H, W, 0), dtype=torch.int8, device="cuda")
+    w = torch.empty((KH, KW, 0, Cout), dtype=torch.int8, device="cuda")
+    assert x.data_ptr() == 0 and w.data_ptr() == 0
+    b = np.random.default_rng(3).integers(-40000, 40000, Cout).astype(np.int32)
+    shape = (Nb, (H + 2 * pad - KH) // stride + 1, (W + 2 * pad - KW) // stride + 1, Cout)
+    for bias, sums in ((dev(b), b), (None, np.zeros_like(b))):
+        want = np.broadcast_to(oracle.requantise_vec(sums, 8, 0), shape)
+        for ws, plan in ((None, None), (torch.empty(4096, dtype=torch.uint8, device="cuda"), None), (None, (64, 1)), (None, (128, 1))):
+            out = torch.full(shape, 17, dtype=torch.int8, device="cuda")
+            ops.ac_conv2d_i8(x, w, bias, out, stride, pad, 8, 0, workspace=ws, plan=plan)
+            np.testing.assert_array_equal(host(out), want, err_msg=f"{ws is not None} {plan}")
+
+
 # K tiles of 128 bytes against the pipeline of the whole tiles: none, 1 .. 2 R + 2 of them (steady trips start at 2 R + 1,
 # R = 2), with and without a partial tile; tiles of 64 x 64, 128 x 64 (more than 256 of the former) and 128 x 128
 @pytest.mark.parametrize("M,N", [(61, 67), (1030, 1027), (1985, 1410)])
