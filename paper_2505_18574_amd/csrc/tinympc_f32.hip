@@ -195,7 +195,8 @@ __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const 
 // problem and sixteen problems to a wave.  Lane q of a quad owns the state rows q + 4 i and the control rows q + 4 j and
 // keeps its rows of the three matrices in registers for the whole kernel (RX = ceil(nx / 4), RU = ceil(nu / 4): at most
 // 192 values); x[c] reaches the quad by a DPP quad broadcast, which all of the lane's row sums share.  Every sum is still
-// one fused multiply-add chain in ascending index order from zero; indices beyond nx / nu add 0 * 0.
+// one fused multiply-add chain in ascending index order from zero; indices beyond nx / nu add 0 * 0 (the rows there are set
+// to zero after every step).
 //
 // One lane per problem, which this replaces, keeps the matrices in LDS: one LDS read per multiply-add, and a chain of
 // nx (nx + 2 nu) of both per step that a small batch has nothing to hide behind.  With the trajectory, before -> now:
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
           }
 #pragma unroll
           for (int i = 0; i < RX; i++) {
-            x[i] = sx[i] + t[i];
+            x[i] = q + 4 * i < nx ? sx[i] + t[i] : 0.f;  // (rows beyond nx: 0 times an infinite state is no zero)
             if (traj && q + 4 * i < nx) xrow[step * nx + q + 4 * i] = x[i];
           }
         }

@@ -75,6 +75,45 @@ def test_horizons_of_one_chunk(nx, nu, horizon, batch):
     np.testing.assert_array_equal(u2, u)
 
 
+def recurrence_f32(Adyn, Bdyn, Kinf, x0, d):
+    """The recurrence as printed, sums in ascending order, every one rounded to fp32 (float64 in between)."""
+    def product(m, v):
+        s = np.zeros((v.shape[0], m.shape[0]), np.float32)
+        for c in range(m.shape[1]):
+            s = (s.astype(np.float64) + m[:, c].astype(np.float64) * v[:, c:c + 1].astype(np.float64)).astype(np.float32)
+        return s
+
+    x, us, xs = x0, [], [x0]
+    for i in range(d.shape[1]):
+        us.append(-product(Kinf, x) - d[:, i])
+        x = product(Adyn, x) + product(Bdyn, us[-1])
+        xs.append(x)
+    return np.stack(us, 1), np.stack(xs, 1)
+
+
+@pytest.mark.parametrize("nx,nu,horizon", [(2, 1, 4), (5, 3, 6), (13, 4, 3), (9, 5, 4), (8, 2, 4), (7, 1, 60), (12, 4, 7)])
+def test_infinite_and_overflowing_states(nx, nu, horizon):
+    """States that are infinite at the start or become so: infinities of the recurrence stay infinities, and a problem
+    leaves its neighbours alone.  (No sum here mixes signs, so the recurrence itself has no NaN.)"""
+    rng = np.random.default_rng(nx)
+    f = lambda *shape: rng.uniform(0.5, 1.5, shape).astype(np.float32)
+    Adyn, Bdyn, Kinf = f(nx, nx), f(nx, nu), -f(nu, nx)
+    batch = 40
+    x0, d = f(batch, nx), -f(batch, horizon, nu)
+    x0[1::4] *= np.float32(1e37)
+    x0[2::4, nx // 2] = np.inf
+    x0[3::8] = -np.inf
+    d[3::8] = 0
+    with np.errstate(over="ignore", invalid="ignore"):
+        uw, xw = recurrence_f32(Adyn, Bdyn, Kinf, x0, d)
+    assert np.isinf(uw).any() and np.isinf(xw[1::4, -1]).any() and not np.isnan(uw).any() and not np.isnan(xw).any()
+    u, xs = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=True)
+    np.testing.assert_allclose(u, uw, rtol=1e-5 * horizon)
+    np.testing.assert_allclose(xs, xw, rtol=1e-5 * horizon)
+    u2, _ = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
+    np.testing.assert_array_equal(u2, u)
+
+
 def test_paper_sizes_on_unaligned_arrays():
     """(12, 4, 5) with x0 and u four bytes off a 16-byte boundary: the vector-ALU kernel, same bar."""
     batch, horizon = 333, 5
