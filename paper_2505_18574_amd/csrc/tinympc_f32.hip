@@ -219,6 +219,7 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
   const int dpitch = at.dpitch, xpitch = at.xpitch;
   float* dwin = tmpc_quad_lds + wave * window;  // [16 problems][chunk][nu]: d, then u (before that: the matrices)
   float* xwin = dwin + at.xwin;
+  const int64_t drun = tmpc_pitch(H, nu), xrun = tmpc_pitch((int64_t)H + 1, nx);
   float *dmine = dwin + pr * dpitch, *xmine = xwin + pr * xpitch;
 
   // The matrices pass through the wave's LDS window, padded with zeros to whole fours, so that a lane picks its rows up
@@ -282,13 +283,13 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
       for (int i = 0; i < RX; i++)
         if (live && q + 4 * i < nx) {
           if constexpr (WHOLE) xmine[q + 4 * i] = x[i];
-          else p.x_out[prob * (H + 1) * nx + q + 4 * i] = x[i];
+          else p.x_out[prob * xrun + q + 4 * i] = x[i];
         }
     }
-    for (int s0 = 0; s0 < H; s0 += chunk) {
-      const int steps = H - s0 < chunk ? H - s0 : chunk;
-      if constexpr (WHOLE) copy(dwin, p.d + b0 * H * nu, nvalid * H * nu);
-      else copy_runs(dwin, dpitch, p.d + (b0 * H + s0) * nu, H * nu, nvalid, steps * nu);
+    for (int s0 = 0, steps = 0; s0 < H; s0 += steps) {
+      steps = H - s0 < chunk ? H - s0 : chunk;
+      if constexpr (WHOLE) copy(dwin, p.d + b0 * drun, nvalid * H * nu);
+      else copy_runs(dwin, dpitch, p.d + b0 * drun + (int64_t)s0 * nu, drun, nvalid, steps * nu);
       float* xrow = xmine + (WHOLE ? nx : 0);
       for (int step = 0; step < steps; step++) {
         float dv[RU], su[RU], sx[RX];
@@ -328,11 +329,11 @@ __global__ void __launch_bounds__(256) tinympc_forward_quad_kernel(const TinyMpc
         }
       }
       if constexpr (WHOLE) {
-        copy(p.u + b0 * H * nu, dwin, nvalid * H * nu);
-        if (traj) copy(p.x_out + b0 * (H + 1) * nx, xwin, nvalid * (H + 1) * nx);
+        copy(p.u + b0 * drun, dwin, nvalid * H * nu);
+        if (traj) copy(p.x_out + b0 * xrun, xwin, nvalid * (H + 1) * nx);
       } else {
-        copy_runs(p.u + (b0 * H + s0) * nu, H * nu, dwin, dpitch, nvalid, steps * nu);
-        if (traj) copy_runs(p.x_out + (b0 * (H + 1) + s0 + 1) * nx, (H + 1) * nx, xwin, xpitch, nvalid, steps * nx);
+        copy_runs(p.u + b0 * drun + (int64_t)s0 * nu, drun, dwin, dpitch, nvalid, steps * nu);
+        if (traj) copy_runs(p.x_out + b0 * xrun + (int64_t)(s0 + 1) * nx, xrun, xwin, xpitch, nvalid, steps * nx);
       }
     }
   }

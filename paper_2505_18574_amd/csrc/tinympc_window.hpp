@@ -18,6 +18,9 @@ constexpr TmpcLayout tmpc_layout(int nx, int nu, int horizon, int chunk, bool wh
   return {chunk * nu, (whole ? horizon + 1 : chunk) * nx, 16 * chunk * nu};
 }
 
+// From one problem to the next in memory: `steps` of `size` values each, more than 2^31 of them at long horizons.
+constexpr int64_t tmpc_pitch(int64_t steps, int size) { return steps * size; }
+
 struct TmpcWindow {
   bool whole;
   int chunk;   // steps that go through the window at a time (whole: the horizon)

@@ -14,6 +14,7 @@ extern "C" void window(int nx, int nu, int horizon, int trajectory, int* out) {
   const ac::TmpcLayout l = ac::tmpc_layout(nx, nu, horizon, w.chunk, w.whole);
   out[0] = w.whole, out[1] = w.chunk, out[2] = w.floats, out[3] = l.dpitch, out[4] = l.xpitch, out[5] = l.xwin;
 }
+extern "C" long long pitch(long long steps, int size) { return ac::tmpc_pitch(steps, size); }
 """
 
 
@@ -24,12 +25,14 @@ def window(tmp_path_factory):
     so = str(folder / "shim.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", so, str(folder / "shim.cpp")], check=True)
     L = ctypes.CDLL(so)
+    L.pitch.restype, L.pitch.argtypes = ctypes.c_longlong, [ctypes.c_longlong, ctypes.c_int]
 
     def call(nx, nu, horizon, trajectory):
         out = (ctypes.c_int * 6)()
         L.window(nx, nu, horizon, int(trajectory), out)
         return tuple(out)
 
+    call.pitch = L.pitch
     return call
 
 
@@ -50,3 +53,10 @@ def test_window_holds_what_the_kernel_addresses(window):
                         assert states <= xpitch and xwin + 15 * xpitch + states <= floats, where
                     if not whole:  # a run is divided by one multiply, exact for runs of up to 255 values
                         assert chunk * max(nu, nx if trajectory else 0) <= 255, where
+
+
+def test_pitch_of_long_horizons(window):
+    """Two problems of 2^31 values and more each lie apart by as many."""
+    for steps in (5, 2 ** 27, 2 ** 31 - 1, 2 ** 31):
+        for size in (1, 3, 16):
+            assert window.pitch(steps, size) == steps * size
