@@ -248,7 +248,7 @@ ac_status ac_batched_gemm_f32(const float* A, const float* B, float* C,
  *   x_out  device, fp32, [batch][horizon + 1][nx], or NULL: the state trajectory x[0..horizon]; when NULL the
  *          state after the last control, which the paper notes is never used, is not computed
  *   1 <= nx, nu <= 16 (the paper's problem has nx = 12, nu = 4, horizon = 5); horizon == 0 or batch == 0
- *   return AC_OK without a launch.  Arithmetic is fp32 throughout.  With nx = 12, nu = 4, horizon 5 and x0, d, u, x_out
+ *   return AC_OK without a launch.  Arithmetic is fp32 throughout.  With nx = 12, nu = 4, horizon 1 .. 5 and x0, d, u, x_out
  *   16-byte aligned the call runs on the matrix units: u[i] is substituted into the state update,
  *   [x[i+1]; u[i]] = [Adyn - Bdyn Kinf, -Bdyn; -Kinf, -I] . [x[i]; d[i]], with Adyn - Bdyn Kinf formed first (four
  *   fused multiply-adds per entry) and the sums of a product in the matrix unit's order; this equals the

@@ -3,9 +3,9 @@
 //   x[i+1] =  Adyn . x[i] + Bdyn . u[i]        i = 0 .. horizon-1
 // Per problem the operation moves nx + horizon * nu floats in and horizon * nu out (plus the optional state
 // trajectory): with the paper's sizes (12, 4, 5) that is 208 bytes (496 with the trajectory) for 2400 flop, so HBM
-// bounds it.  Two families: the paper's sizes run on the matrix units, sixteen problems to a 16 x 16 product
-// (tinympc_forward_mfma_kernel); any other size, and unaligned arrays, on the vector ALU with four lanes per problem
-// (tinympc_forward_quad_kernel).
+// bounds it.  Two families: the paper's sizes, at horizons up to its 5, run on the matrix units, sixteen problems to a
+// 16 x 16 product (tinympc_forward_mfma_kernel); any other size or horizon, and unaligned arrays, on the vector ALU with
+// four lanes per problem (tinympc_forward_quad_kernel).
 #include "common.hpp"
 #include "tinympc_window.hpp"
 
@@ -44,19 +44,19 @@ static __device__ __forceinline__ float quad_broadcast(float v, int k) {
 // with the results held in registers and stored back to back at the end).  d is therefore loaded, and u and the
 // trajectory are stored, as whole runs of 16 bytes per lane through a wave-private LDS window (u overwrites d in place,
 // step by step; the trajectory goes block by block through a second window).  The results of a block stay in registers
-// until then, which fixes the horizon at compile time: the paper's 5.
+// until then, which fixes the horizon H at compile time: the paper's 5 and the shorter ones.
 constexpr int TMPC_H = 5;
-constexpr int TMPC_XPITCH = 304;  // LDS bytes per problem of a trajectory block (288 + padding)
 
 // NB: column blocks (of sixteen problems) per wave; WAVES per workgroup.  Four blocks hide a block's chain of 20 MFMAs behind
 // three others and are right once every compute unit has work; a small batch is one such chain after three memory
 // latencies, and one block to a wave, one wave to a workgroup, shortens the chain and spreads it over the chip (100
 // problems 7.0 -> 4.1 us, 4000 7.6 -> 4.4, up to four such waves per compute unit: 16384 problems, 5.0 us).
-template <bool WITH_X, int NB, int WAVES>
+template <bool WITH_X, int H, int NB, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const TinyMpcParams p) {
-  constexpr int NX = 12, NU = 4, H = TMPC_H, PB = 16 * NB;      // PB: problems of a wave-block
-  constexpr int DN = (PB * H + 63) / 64;                        // 16-byte pieces of d per lane
-  constexpr int WAVE_LDS = DN * 1024 + 16 * TMPC_XPITCH;        // d / u window of PB problems + trajectory window of 16
+  constexpr int NX = 12, NU = 4, PB = 16 * NB;            // PB: problems of a wave-block
+  constexpr int DN = (PB * H + 63) / 64;                  // 16-byte pieces of d per lane
+  constexpr int XPITCH = 16 * (((H + 1) * NX / 4) | 1);   // LDS bytes per problem of a trajectory block, an odd number of pieces
+  constexpr int WAVE_LDS = DN * 1024 + 16 * XPITCH;       // d / u window of PB problems + trajectory window of 16
   __shared__ __attribute__((aligned(16))) unsigned char tmpc_lds[WAVES * WAVE_LDS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, g = lane >> 4;
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const 
   int64_t blk = (int64_t)blockIdx.x * WAVES + wave;
   if (blk >= nblk) return;  // whole waves leave; no wave waits for another
   unsigned char* dwin = tmpc_lds + wave * WAVE_LDS;  // [PB problems][H][4] floats: d, then u
-  unsigned char* xwin = dwin + DN * 1024;            // [16 problems][TMPC_XPITCH]
+  unsigned char* xwin = dwin + DN * 1024;            // [16 problems][XPITCH]
 
   // inputs of a block: d as one contiguous run, 16 bytes per lane and instruction, and per column block the
   // lane's 16 bytes of x0 (lanes past the end re-read the last problem and store nothing).  Every byte is read once
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const 
       for (int b = 0; b < NB; b++) {
         if (g < 3) {
 #pragma unroll
-          for (int i = 0; i <= H; i++) *(v4f*)(xwin + n * TMPC_XPITCH + i * (NX * 4) + g * 16) = hist[i][b];
+          for (int i = 0; i <= H; i++) *(v4f*)(xwin + n * XPITCH + i * (NX * 4) + g * 16) = hist[i][b];
         }
         v4f* dst = (v4f*)(p.x_out + (blk * PB + 16 * b) * (int64_t)(H + 1) * NX);
         const int left = nvalid - 16 * b;  // problems of this block that exist
@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(64 * WAVES) tinympc_forward_mfma_kernel(const 
 #pragma unroll
         for (int k = 0; k < (16 * PPB + 63) / 64; k++) {
           const int q = k * 64 + lane;  // piece q of the block: problem q / PPB, piece q % PPB of its rows
-          if (q < pieces) __builtin_nontemporal_store(*(const v4f*)(xwin + (q / PPB) * TMPC_XPITCH + (q % PPB) * 16), dst + q);
+          if (q < pieces) __builtin_nontemporal_store(*(const v4f*)(xwin + (q / PPB) * XPITCH + (q % PPB) * 16), dst + q);
         }
       }
     }
@@ -354,23 +354,39 @@ static hipError_t launch_quad(const TinyMpcParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int NB, int WAVES>
-static hipError_t launch_mfma(const TinyMpcParams& p, hipStream_t stream) {
+template <int H, int NB, int WAVES>
+static hipError_t launch_mfma_form(const TinyMpcParams& p, hipStream_t stream) {
   const int64_t blks = (p.batch + 16 * NB - 1) / (16 * NB), wgs = (blks + WAVES - 1) / WAVES;
   // one persistent workgroup of four waves per compute unit (27.3 us for 262144 problems; two, three, four: 31.1,
   // 33.0, 34.9 us)
   const int64_t slots = (int64_t)compute_units() * (4 / WAVES);
   const dim3 grid((unsigned)(wgs < slots ? wgs : slots)), block(64 * WAVES);
-  if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, NB, WAVES>), grid, block, 0, stream, p);
-  else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, NB, WAVES>), grid, block, 0, stream, p);
+  if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, H, NB, WAVES>), grid, block, 0, stream, p);
+  else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, H, NB, WAVES>), grid, block, 0, stream, p);
   return hipGetLastError();
+}
+
+template <int H>
+static hipError_t launch_mfma(const TinyMpcParams& p, hipStream_t stream) {
+  return p.batch <= 16 * 4 * (int64_t)compute_units() ? launch_mfma_form<H, 1, 1>(p, stream) : launch_mfma_form<H, 4, 4>(p, stream);
 }
 
 hipError_t launch_tinympc_forward(const TinyMpcParams& p, hipStream_t stream) {
   if ((p.batch + 255) / 256 > 0x7fffffffLL) return hipErrorInvalidValue;
   const bool aligned16 = ((((uintptr_t)p.x0) | ((uintptr_t)p.d) | ((uintptr_t)p.u) | ((uintptr_t)p.x_out)) & 15) == 0;
-  if (p.nx == 12 && p.nu == 4 && p.horizon == TMPC_H && aligned16)
-    return p.batch <= 16 * 4 * (int64_t)compute_units() ? launch_mfma<1, 1>(p, stream) : launch_mfma<4, 4>(p, stream);
+  // The paper's sizes up to its horizon, where a call is bound by the bytes it moves; 262144 problems on the vector ALU and
+  // here: horizon 1 12.3 and 6.7 us, 4 21.5 and 13.7, with the trajectory 19.7 and 11.2, 29.8 and 22.1.  (Beyond 5, where the
+  // registers of a block's states run out, the vector ALU is ahead of matrix units that store state by state: horizon 6
+  // without the trajectory 41 us so and 28.7.)
+  if (p.nx == 12 && p.nu == 4 && p.horizon <= TMPC_H && aligned16) {
+    switch (p.horizon) {
+      case 1: return launch_mfma<1>(p, stream);
+      case 2: return launch_mfma<2>(p, stream);
+      case 3: return launch_mfma<3>(p, stream);
+      case 4: return launch_mfma<4>(p, stream);
+      case TMPC_H: return launch_mfma<TMPC_H>(p, stream);
+    }
+  }
   switch (4 * ((p.nx - 1) / 4) + (p.nu - 1) / 4) {
 #define AC_QUAD(RX, RU) \
   case 4 * (RX - 1) + RU - 1: return launch_quad<RX, RU>(p, stream);

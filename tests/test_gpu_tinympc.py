@@ -3,8 +3,8 @@
 fp32 sums of at most nx + nu terms per element and `horizon` dependent steps (fused multiply-add chains, or for the
 paper's sizes 16 x 16 products on the matrix units with u substituted into the state update): rounding stays near
 1e-6 relative to the magnitudes involved, so the bar is the fp32 one of the library (relative Frobenius error
-<= 1e-5 over the batch).  Both kernel families are covered: (12, 4) at horizon 5 with aligned arrays takes the matrix
-units, everything else the vector ALU."""
+<= 1e-5 over the batch).  Both kernel families are covered: (12, 4) at horizons up to 5 with aligned arrays takes the
+matrix units, everything else the vector ALU."""
 import numpy as np
 import pytest
 import torch
@@ -56,6 +56,18 @@ def test_sizes_at_the_edges_of_the_kernels(nx, nu, horizon, batch):
     uw, xw = oracle.tinympc_forward(Adyn, Bdyn, Kinf, x0, d, return_x=True)
     u, xs = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=True)
     assert np.isfinite(u).all() and np.isfinite(xs).all()
+    assert rel_fro(u, uw) <= TOL and rel_fro(xs, xw) <= TOL
+    u2, _ = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
+    np.testing.assert_array_equal(u2, u)
+
+
+@pytest.mark.parametrize("batch", [1, 17, 77, 16384, 16449])  # part blocks of 16 and 64, both launch shapes
+@pytest.mark.parametrize("horizon", [1, 2, 3, 4])
+def test_paper_sizes_at_shorter_horizons(horizon, batch):
+    Adyn, Bdyn, Kinf, x0, d = inputs.tinympc_inputs(batch, seed=horizon, nx=12, nu=4, horizon=horizon)
+    Adyn = (Adyn / 2).astype(np.float32)
+    uw, xw = oracle.tinympc_forward(Adyn, Bdyn, Kinf, x0, d, return_x=True)
+    u, xs = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=True)
     assert rel_fro(u, uw) <= TOL and rel_fro(xs, xw) <= TOL
     u2, _ = run_gpu(Adyn, Bdyn, Kinf, x0, d, want_x=False)
     np.testing.assert_array_equal(u2, u)
