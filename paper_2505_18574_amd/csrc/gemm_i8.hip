@@ -416,9 +416,17 @@ bool conv_i8_fast_path(const GemmParams& p) {
 // A convolution of at most 64 output channels on more than one 64 x 64 tile per compute unit: that tile, uncut.  The
 // planner's estimates, made for products, take wider tiles or K slices there, which compute or store columns that do not
 // exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of 55 x 55
-// 101 -> 77; level on the shapes where they agree).
+// 101 -> 77; level on the shapes where they agree).  Where they take the weight-stationary kernel they are right as long
+// as K is short, and a single tap, a plain product but for its rows, always is (1 x 1 stride 2, 48 -> 16 on 185 images of
+// 65 x 65 13.5 us there and 22.6 on the tile, 64 -> 48 on 64 of 56 x 56 6.6 and 8.8); its gather loses from K = 800 on
+// where the columns are whole 32s, from 1200 on otherwise (3 x 3 stride 2, 96 -> 64 on 76800 pixels 20.8 and 14.3,
+// 5 x 5 stride 2, 64 -> 16 on 234484 92 and 57; 2 x 2 stride 2, 256 -> 16 on 113568, K = 1024, 24.2 and 26.6).  Sixty-four
+// columns fill half of a wide tile, which is the better one for K beyond 32768 (5 x 5, 1968 -> 64 on 51840 pixels 378 and
+// 410, 1520 -> 64 339 and 350; 1056 -> 64 on 39546, K = 26400, 182 and 147).
 static bool narrow_conv_plan(const GemmParams& p, GemmPlan* plan) {
-  if (p.N > 64 || p.M <= 64 * PLAN_CUS || plan->tile == 32) return false;
+  int bm;
+  if (p.N > 64 || p.M <= 64 * PLAN_CUS || plan->tile == 32 || (p.N > 48 && p.K > 32768)) return false;
+  if (wstat_tile_rows(plan->tile, &bm) && p.K < (p.N % 32 == 0 ? 800 : 1200)) return false;
   return make_plan_i8(p.K, 64, 1, plan);
 }
 

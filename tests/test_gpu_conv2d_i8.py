@@ -131,3 +131,17 @@ def test_sums_around_the_clamp_bounds(plan):
             ops.ac_conv2d_i8(dev(x), dev(w), dev(bias), out, 1, 1, shift, act, plan=plan)
             torch.cuda.synchronize()
             np.testing.assert_array_equal(host(out), want)
+
+
+@pytest.mark.parametrize("Nb,H,W,Cin,Cout,k,stride,pad", [
+    (70, 31, 31, 48, 16, 1, 2, 0),    # a single tap: weight-stationary
+    (80, 31, 31, 192, 64, 2, 2, 0),   # K = 768, 64 columns: weight-stationary
+    (70, 31, 31, 32, 32, 5, 2, 2),    # K = 800, whole 32s: the 64 x 64 tile
+    (80, 31, 31, 288, 48, 2, 2, 0),   # K = 1152: weight-stationary
+    (70, 31, 31, 48, 48, 5, 2, 2),    # K = 1200: the tile
+])
+def test_narrow_outputs_on_many_tiles(Nb, H, W, Cin, Cout, k, stride, pad):
+    """At most 64 columns on more than one 64 x 64 tile per compute unit, on both sides of the depths at which the kernel
+    changes."""
+    x, w, bias = inputs.conv_i8_inputs(Nb, H, W, Cin, Cout, k, k, seed=Cin + Cout)
+    check(x, w, bias, stride, pad, 9, 1)
