@@ -318,6 +318,22 @@ static hipError_t launch_conv_image_kernel(const GemmParams& p, const ConvImageP
   return dwords ? launch_conv_image_form<BN, true>(p, h, lds, stream) : launch_conv_image_form<BN, false>(p, h, lds, stream);
 }
 
+// Whether a convolution of sixteen channels, which the direct-to-LDS gather takes too, belongs here: it copies every input
+// row under a unit whole, so not where most of a row lies beside the unit's pixels or between its windows (1 x 3 on rows
+// of 1000 pixels 31.8 us on the gather and 34.9 here, 9 x 1 stride 3 on rows of 280 39 and 78: patches of 31 and 66 KB;
+// 2 x 2 stride 3 6.8 and 7.4), nor where less than half of a unit exists (16 -> 512 on 512 images of 7 x 7 12.5 and 15.1).
+// Elsewhere 3 x 3 kernels over 16 channels: 16 -> 64 on 32 images of 56 x 56 10.9 us tiled and 7.2 here, 16 -> 320 on 50 of
+// 50 x 50 35.9 and 19.5, stride 2, 16 -> 320 on 55 of 84 x 131 42 and 30.
+// Kernels between nine taps and more than 32 stay with the gather; beyond it has twice the rows and a few columns leave
+// it idle (7 x 7, 16 -> 16 on 64 images of 28 x 28 13.4 and 6.9, 6 x 6, 16 -> 48 on 4384 tiles 2.4 times its rate).
+static inline bool conv_image_takes_sixteen(const GemmParams& p) {
+  const int taps = p.KH * p.KW;
+  if (p.Cin != 16 || p.stride > 2 || taps < 2 || (taps > 9 && (taps <= 32 || p.N > 64))) return false;
+  ConvImageParams h;
+  size_t lds = 0;
+  return conv_image_plan(p, 32, &h, &lds) && h.patch <= 28 * 1024 && 2 * (int64_t)p.OH * p.OW >= (int64_t)h.U * CONV_IMAGE_BM;
+}
+
 // Launches the kernel when it takes the convolution and is the faster one; false otherwise.
 static inline bool launch_conv_image(const GemmParams& p, hipStream_t stream, hipError_t* e) {
   // the block width that computes the fewest columns beyond N

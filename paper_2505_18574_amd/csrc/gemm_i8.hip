@@ -457,10 +457,11 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     // is planned as one (64 -> 256 on 64 images of 56 x 56, stride 2: 13.1 us weight-stationary, 21.3 us patch kernel)
     // and the patch of a kernel of more than 32 taps is mostly halo
     const bool taps = p.KH * p.KW > 1 && p.KH * p.KW <= 32;
-    // sixteen channels are half a K-step of the patch kernel, which does not take them: the same rule sends 3 x 3 kernels
-    // over them to the kernel that pads its runs (16 -> 64 on 32 images of 56 x 56 12.0 us tiled and 8.1 there, 16 -> 32
-    // on 64 of 28 x 28 7.5 and 5.4, 16 -> 320 on 50 of 50 x 50 39.9 and 21.1)
-    if (hipError_t e; p.Cin == 16 && p.KH * p.KW > 1 && p.KH * p.KW <= 9 && tiles64 > 512 && launch_conv_image(p, stream, &e)) return e;
+    auto planned = [&] { return plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0); };
+    // sixteen channels are half a K-step of the patch kernel, which does not take them: on more than a round of tiles most of
+    // them go to the kernel that pads its runs (not those of one wave per tile: 2 x 4 stride 2, 16 -> 32 on 111 images of
+    // 14 x 148 4.1 us so and 5.5 there)
+    if (hipError_t e; tiles64 > 512 && conv_image_takes_sixteen(p) && planned().tile != 32 && launch_conv_image(p, stream, &e)) return e;
     if (taps && conv_halo_plan(p, 256, &h, &lds)) {
       if (h.units * nblk >= 256 || tiles64 > 512) return launch_conv_halo<256>(q, h, lds, stream);
     } else if (taps && conv_halo_plan(p, 128, &h, &lds)) {
@@ -468,14 +469,14 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
       // 18.5 us on the best tiled kernel, 128 images 29.6 against 33.6)
       if (h.units * nblk >= 512) return launch_conv_halo<128>(q, h, lds, stream);
     } else if (p.KH * p.KW <= 32) {
-      GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0);
+      GemmPlan plan = planned();
       return narrow_conv_plan(p, &plan) ? dispatch_i8<1>(p, stream, fast, &plan) : dispatch_i8<1>(p, stream, fast, nullptr);
     }
     // a convolution the patch kernel could take but that is too small for it: the tiled kernels (or one wave per
     // tile, by the GEMM's rule: 56 x 56 x 64 -> 64, one image, 4.4 us against 5.4; K = 1152 gains 0.5 us with the
     // input in the caches and loses up to 1 us with it in HBM, as for the GEMM), never the weight-stationary
     // kernel, whose gather loses to both (28 x 28 x 128 -> 128, 32 images: 13.9 us against 10.2)
-    GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, small_i8_eligible(p) ? 2 : 0);
+    GemmPlan plan = planned();
     int ws_bm;
     if (wstat_tile_rows(plan.tile, &ws_bm)) make_plan_i8(p.K, choose_tile(p.M, p.N), 1, &plan);  // unsplit: no workspace needed
     narrow_conv_plan(p, &plan);

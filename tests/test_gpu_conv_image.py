@@ -63,6 +63,24 @@ def test_shifts(shift, act):
     check(2, 15, 16, 3, 36, 3, 3, 1, 1, shift, act)
 
 
+@pytest.mark.parametrize("Nb,H,W,Cout,KH,KW,stride,pad", [
+    (13, 57, 59, 48, 3, 3, 2, 1),     # fewer than 512 tiles: the gather
+    (50, 57, 59, 48, 3, 3, 2, 1),     # ... more: here
+    (50, 57, 59, 48, 3, 3, 3, 1),     # stride 3: the gather
+    (700, 7, 7, 64, 3, 3, 1, 1),      # units less than half full: the gather
+    (500, 9, 9, 80, 3, 3, 1, 1),      # ... and more than half
+    (2, 40, 1000, 32, 1, 3, 1, 0),    # a patch of 32 KB: the gather
+    (2, 70, 500, 32, 1, 3, 1, 0),     # ... of 16: here
+    (36, 31, 33, 64, 7, 7, 1, 3),     # 49 taps and 64 columns: here
+    (36, 31, 33, 80, 7, 7, 1, 3),     # ... and 80: the gather
+    (40, 31, 33, 64, 2, 5, 1, 1),     # ten taps: the gather
+    (111, 14, 74, 32, 2, 4, 2, 0),    # one wave per tile
+])
+def test_sixteen_channels(Nb, H, W, Cout, KH, KW, stride, pad):
+    """Both sides of the rule that shares the convolutions of sixteen channels out."""
+    check(Nb, H, W, 16, Cout, KH, KW, stride, pad)
+
+
 def test_unit_order_and_many_units():
     """More units than workgroups: every workgroup walks over several, requesting the next one's rows early."""
     check(37, 50, 49, 3, 64, 3, 3, 1, 1)
