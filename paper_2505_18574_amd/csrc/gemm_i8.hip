@@ -478,7 +478,9 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     // kernel, whose gather loses to both (28 x 28 x 128 -> 128, 32 images: 13.9 us against 10.2)
     GemmPlan plan = planned();
     int ws_bm;
-    if (wstat_tile_rows(plan.tile, &ws_bm)) make_plan_i8(p.K, choose_tile(p.M, p.N), 1, &plan);  // unsplit: no workspace needed
+    // unsplit: no workspace needed.  More than 32 taps: K is deep, and tiles by the estimates beat those by count alone
+    // (6 x 6, 32 -> 144 on five images of 61 x 61 20.4 and 15.5 us).
+    if (wstat_tile_rows(plan.tile, &ws_bm)) make_plan_i8(p.K, p.KH * p.KW > 32 ? choose_tile_i8(p.M, p.N, p.K, false) : choose_tile(p.M, p.N), 1, &plan);
     narrow_conv_plan(p, &plan);
     return dispatch_i8<1>(p, stream, fast, &plan);
   }

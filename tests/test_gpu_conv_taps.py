@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     (1, 8, 60, 16, 32, 2, 33, 1, 0),     # a kernel column beyond the masks
     (2, 2, 2, 32, 16, 7, 7, 1, 3),       # an image smaller than the kernel
     (12, 40, 41, 16, 272, 7, 7, 1, 3),   # more tiles than one round
+    (5, 61, 61, 32, 144, 6, 6, 1, 3),    # ... whose plan is weight-stationary: the tile by the estimates
 ])
 def test_many_taps(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
     x, w, b = inputs.conv_i8_inputs(Nb, H, W, Cin, Cout, KH, KW, seed=H * W + Cin)
