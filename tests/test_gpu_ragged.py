@@ -116,6 +116,28 @@ def test_convolutions_without_input_channels(KH, KW, stride, pad):
             np.testing.assert_array_equal(host(out), want, err_msg=f"{ws is not None} {plan}")
 
 
+@pytest.mark.parametrize("M,N,K", [(32768, 32, 40), (32769, 32, 200), (32897, 33, 70), (33001, 1, 131), (40000, 15, 700), (32900, 31, 128)])
+def test_tall_and_narrow(M, N, K):
+    """Both sides of the rule that gives tall outputs of at most 32 columns tiles of 128 x 32, every layout."""
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=M + 3 * N + 7 * K)
+    sums = (A.astype(np.float64) @ B.astype(np.float64) + bias).astype(np.int64)
+    want = oracle.requantise_vec(sums, 9, 1)
+    At, Bt = np.zeros((K, M), np.int8) + A.T, np.zeros((N, K), np.int8) + B.T
+    for ta, tb in ((False, False), (True, False), (False, True), (True, True)):
+        C = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+        ops.ac_gemm_i8_t(odd_view(At if ta else A), odd_view(Bt if tb else B), dev(bias), C, 9, 1, trans_a=ta, trans_b=tb)
+        np.testing.assert_array_equal(host(C), want, err_msg=f"ta={ta} tb={tb}")
+    raw = torch.full((M, N), 33, dtype=torch.int32, device="cuda")
+    ops.ac_gemm_i8_acc32(odd_view(A), odd_view(B), dev(bias), raw)
+    np.testing.assert_array_equal(host(raw), sums)
+    if K % 2 == 0:
+        A2, B2 = inputs.gemm_bf16_inputs(M, N, K // 2, seed=K)
+        a, b = inputs.bf16_bits_to_f32(A2).astype(np.float64), inputs.bf16_bits_to_f32(B2).astype(np.float64)
+        Cf = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        ops.ac_gemm_bf16(odd_view(A2), odd_view(B2), Cf)
+        assert (np.abs(host(Cf) - a @ b) <= 4.0 * (K // 2 + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)) + 1e-30).all()
+
+
 # K tiles of 128 bytes against the pipeline of the whole tiles: none, 1 .. 2 R + 2 of them (steady trips start at 2 R + 1,
 # R = 2), with and without a partial tile; tiles of 64 x 64, 128 x 64 (more than 256 of the former) and 128 x 128
 @pytest.mark.parametrize("M,N", [(61, 67), (1030, 1027), (1985, 1410)])
