@@ -116,6 +116,32 @@ def test_convolutions_without_input_channels(KH, KW, stride, pad):
             np.testing.assert_array_equal(host(out), want, err_msg=f"{ws is not None} {plan}")
 
 
+@pytest.mark.parametrize("M,N,K", [(9000, 8, 16), (9000, 8, 17), (9000, 9, 16), (8, 9000, 16), (9, 9000, 16), (9000, 14, 15), (15, 9000, 3),
+                                   (9000, 15, 16), (16, 16, 16), (15, 16, 16), (1, 1, 16), (1, 70000, 16), (70000, 1, 16)])
+def test_short_products(M, N, K):
+    """Both sides of the rule that computes products of few terms one output to a thread, every layout and type."""
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=M + 3 * N + 7 * K)
+    sums = (A.astype(np.float64) @ B.astype(np.float64) + bias).astype(np.int64)
+    want = oracle.requantise_vec(sums, 7, 0)
+    At, Bt = np.zeros((K, M), np.int8) + A.T, np.zeros((N, K), np.int8) + B.T
+    matrix = np.broadcast_to(bias, (M, N)).astype(np.int32)
+    for put in (dev, odd_view):
+        for ta, tb in ((False, False), (True, False), (False, True), (True, True)):
+            C = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+            ops.ac_gemm_i8_t(put(At if ta else A), put(Bt if tb else B), dev(matrix if ta else bias), C, 7, 0, trans_a=ta, trans_b=tb)
+            np.testing.assert_array_equal(host(C), want, err_msg=f"{put.__name__} ta={ta} tb={tb}")
+        raw = torch.full((M, N), 33, dtype=torch.int32, device="cuda")
+        ops.ac_gemm_i8_acc32(put(A), put(B), dev(bias), raw)
+        np.testing.assert_array_equal(host(raw), sums)
+        A2, B2 = inputs.gemm_bf16_inputs(M, N, K, seed=K)
+        a, b = inputs.bf16_bits_to_f32(A2).astype(np.float64), inputs.bf16_bits_to_f32(B2).astype(np.float64)
+        C0 = torch.rand((M, N), dtype=torch.float32, device="cuda")
+        Cf = C0.clone()
+        ops.ac_gemm_bf16(put(A2), put(B2), Cf, alpha=0.5, beta=2.0)
+        c0 = host(C0).astype(np.float64)
+        assert (np.abs(host(Cf) - (0.5 * (a @ b) + 2 * c0)) <= 4.0 * (K + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b) + 2 * c0) + 1e-30).all(), put.__name__
+
+
 @pytest.mark.parametrize("M,N,K", [(32768, 32, 40), (32769, 32, 200), (32897, 33, 70), (33001, 1, 131), (40000, 15, 700), (32900, 31, 128)])
 def test_tall_and_narrow(M, N, K):
     """Both sides of the rule that gives tall outputs of at most 32 columns tiles of 128 x 32, every layout."""
