@@ -8,7 +8,6 @@
 // stores are coalesced as well.
 #include "common.hpp"
 
-
 namespace ac {
 
 static __device__ __forceinline__ float quad_xor1(float v) {  // lane ^ 1 within a quad
@@ -16,11 +15,6 @@ static __device__ __forceinline__ float quad_xor1(float v) {  // lane ^ 1 within
 }
 static __device__ __forceinline__ float quad_xor2(float v) {  // lane ^ 2 within a quad
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));
-}
-
-template <int Q>
-static __device__ __forceinline__ float quad_bcast(float v) {  // lane Q of the quad
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), Q * 0x55, 0xF, 0xF, true));
 }
 
 // Coalesced copies of `count` floats, global -> LDS and back.
@@ -227,8 +221,8 @@ __global__ void __launch_bounds__(256) batched_fixed_kernel(const BatchedParams 
           float row[4 * RB];
 #pragma unroll
           for (int j = 0; j < RB; j++) {
-            row[j] = quad_bcast<0>(c[i][j]), row[RB + j] = quad_bcast<1>(c[i][j]);
-            row[2 * RB + j] = quad_bcast<2>(c[i][j]), row[3 * RB + j] = quad_bcast<3>(c[i][j]);
+            row[j] = quad_broadcast(c[i][j], 0), row[RB + j] = quad_broadcast(c[i][j], 1);
+            row[2 * RB + j] = quad_broadcast(c[i][j], 2), row[3 * RB + j] = quad_broadcast(c[i][j], 3);
           }
           float s[2] = {0.f, 0.f};
 #pragma unroll

@@ -18,6 +18,17 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
+// v of lane k of every quad
+static __device__ __forceinline__ float quad_broadcast(float v, int k) {
+  const int i = __builtin_bit_cast(int, v);
+  switch (k) {  // constant after unrolling: the DPP control is an immediate
+    case 0: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x00, 0xF, 0xF, true));
+    case 1: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x55, 0xF, 0xF, true));
+    case 2: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xAA, 0xF, 0xF, true));
+    default: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xFF, 0xF, 0xF, true));
+  }
+}
+
 // x / d by one multiply, exact while x * d < 2^32 (the host checks the ranges it is used on).
 struct FastDiv {
   unsigned magic, d;

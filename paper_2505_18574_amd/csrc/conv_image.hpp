@@ -52,7 +52,7 @@ struct __attribute__((packed, aligned(4))) Dwords16 {
 template <int BN, bool DWORDS>
 __global__ void __launch_bounds__(2 * CONV_IMAGE_BM) __attribute__((amdgpu_waves_per_eu(BN == 96 ? 3 : 4))) conv_i8_image_kernel(const GemmParams p, const ConvImageParams h, const int n_blocks) {
   using T = TypeI8;
-  constexpr int BM = CONV_IMAGE_BM, THREADS = 2 * BM, WAVES = THREADS / 64, TN = BN / 32, B_STRIDE = BN + 16, CPR = BN / 16, WB = 1024 / THREADS, PB = 4;
+  constexpr int BM = CONV_IMAGE_BM, THREADS = 2 * BM, TN = BN / 32, B_STRIDE = BN + 16, CPR = BN / 16, WB = 1024 / THREADS, PB = 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(2 * CONV_IMAGE_BM) __attribute__((amdgpu_waves
     w.rin = (row_of(q_last) - oh0) * p.stride + p.KH;
     return w;
   };
-  // ---- the input rows of a unit.  A wave takes pieces wave, wave + WAVES, ...: 64 chunks of a row, or RPI short rows ----
+  // ---- the input rows of a unit.  A wave takes pieces wave, wave + 4, ...: 64 chunks of a row, or RPI short rows ----
   const int sub = h.RPI > 1 ? (int)h.dCH.div((unsigned)lane) : 0;
   const int j0 = lane - sub * h.CH;  // chunk of the row in piece 0
   const int row_bytes = p.W * p.Cin;

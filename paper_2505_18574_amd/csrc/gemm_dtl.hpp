@@ -166,7 +166,9 @@ struct DtlGeometry {
   static __device__ __forceinline__ int a_xor(int row) { return (row / A_RPW) & (A_SPR - 1); }
 };
 
-// tile_coords() (the XCD-aware tile order) without integer divisions: the band size is divided by with a
+// XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2), so workgroup b runs on
+// XCD b % 8.  Every XCD gets one contiguous run of logical tile ids, and those ids lie in bands of four tile rows, so that
+// a run is a compact rectangle sharing A rows and B columns.  No integer divisions: the band size is divided by with a
 // multiplier the host supplies, the band height (1 .. 4 tile rows) by a case split.  Two divisions are some sixty
 // scalar and vector instructions ahead of a kernel's first load: 0.07 us of a 4 us launch.
 static __device__ __forceinline__ void tile_coords_mul(int b, int nblocks, int tiles_m, int tiles_n, unsigned band_magic, int& tm, int& tn) {
@@ -490,7 +492,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   };
 
   // Persistent workgroups: each takes output tiles blockIdx.x, blockIdx.x + gridDim.x, ...  gridDim.x is a multiple
-  // of the number of XCDs (or equals ntiles), so a workgroup's tiles all map to its own XCD in tile_coords().
+  // of the number of XCDs (or equals ntiles), so a workgroup's tiles all map to its own XCD in tile_coords_mul().
   // With split-K a work item is (tile, K slice): slice s covers K tiles s * kt_per_split ...
   // The launcher never starts more workgroups than work items, so the first pass needs no test.
   int work = blockIdx.x;

@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(THREADS) splitk_reduce_i8_kernel(const GemmPar
   for (; k < p.splits; k++) s += *(const vec*)(part + k * slice);
   if constexpr (VEC == 4) {
     int a4[4] = {s[0], s[1], s[2], s[3]};
-    EpilogueI8::store4<true>(p, m, n, a4);
+    EpilogueI8::store4(p, m, n, a4);
   } else {
     EpilogueI8Any::one(p, m, n, s);
   }
@@ -316,7 +316,8 @@ static hipError_t launch_splitk_reduce_i8(const GemmParams& p, hipStream_t strea
 }
 
 // Operands that the direct-to-LDS kernels do not take.  The K slices are as many as the shape's own plan has (which is
-// what the workspace was sized for), but no more than fill the chip twice with this kernel's tiles.
+// what the workspace was sized for), but no more than give every compute unit four workgroups of this kernel (four of the
+// 64 x 64 tile are resident at once, two of the 128 x 128).
 template <int AMODE>
 static hipError_t launch_ragged_i8(GemmParams p, hipStream_t stream, const GemmPlan* forced) {
   const int tile = forced ? forced->tile : ragged_tile(p.M, p.N);

@@ -56,24 +56,6 @@ struct TypeBF16 {
   }
 };
 
-// XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs (each
-// with its own L2), so workgroup b runs on XCD b % 8.  Give every XCD one
-// contiguous run of logical tile ids, and lay those ids out in bands of GROUP_M
-// tile-rows so that a run is a compact rectangle sharing A rows and B columns.
-static __device__ __forceinline__ void tile_coords(int b, int nblocks, int tiles_m, int tiles_n, int& tm, int& tn) {
-  constexpr int XCDS = 8, GROUP_M = 4;
-  int q = nblocks / XCDS, r = nblocks % XCDS;
-  int xcd = b % XCDS, idx = b / XCDS;
-  int id = xcd * q + (xcd < r ? xcd : r) + idx;
-  int group_size = GROUP_M * tiles_n;
-  int group = id / group_size;
-  int first_m = group * GROUP_M;
-  int gsz = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
-  int in_group = id - group * group_size;
-  tm = first_m + in_group % gsz;
-  tn = in_group / gsz;
-}
-
 // Epilogue policies -----------------------------------------------------------
 // tile(): one 32x32 accumulator tile, whose operand order the policy chooses with SWAP:
 //   SWAP (B^T tile as the row operand): register r of lane l is row l % 32, column 8 (r/4) + 4 (l/32) + r % 4:
@@ -136,8 +118,9 @@ struct EpilogueI8 {
     if (act) q = q < 0 ? 0 : q;
     return q;
   }
-  template <bool VEC, bool ADD_BIAS = true>
-  static __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const int* a, int = 0) {
+  // Columns n .. n + 3 of row m, for a C whose rows are dword-aligned.
+  template <bool ADD_BIAS = true>
+  static __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const int* a) {
     if (m >= p.M || n >= p.N) return;
     int8_t* C = (int8_t*)p.C;
     int v[4];
@@ -149,7 +132,7 @@ struct EpilogueI8 {
       v[e] = requant(a[e] + b, p.shift, p.act);
     }
     int8_t* dst = C + (int64_t)m * p.ldc + n;
-    if (VEC && full) {
+    if (full) {
       unsigned int w = (unsigned int)(v[0] & 0xff) | ((unsigned int)(v[1] & 0xff) << 8) | ((unsigned int)(v[2] & 0xff) << 16) | ((unsigned int)(v[3] & 0xff) << 24);
       *(unsigned int*)dst = w;
     } else {
@@ -327,8 +310,8 @@ struct EpilogueI8 {
       for (int q = 0; q < 4; q++) {
         const int n = ncol0 + 8 * q + 4 * (lane >> 5);
         int a4[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        if constexpr (BIASED) store4<true, false>(p, m, n, a4);
-        else store4<true>(p, m, n, a4);
+        if constexpr (BIASED) store4<false>(p, m, n, a4);
+        else store4(p, m, n, a4);
       }
     }
   }

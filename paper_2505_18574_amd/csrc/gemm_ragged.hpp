@@ -558,18 +558,16 @@ static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t strea
       return hipGetLastError();
     }
   }
-  // Outputs of at most 32 columns on more 64 x 64 tiles than the chip holds at once: 128 x 32 tiles, whose waves all have
-  // columns (int8 100000 x 1 x 64 11.7 -> 8.2 us, x 32 x 100 12.5 -> 9.2, 10^6 x 4 x 64 83 -> 49, bf16 100000 x 1 x 64
-  // 8.1 -> 6.8; on one round the smaller tile is level or ahead, 30000 x 32 x 100 4.8 and 5.0, 8000 x 8 x 64 4.2 and 4.4).
-  if constexpr (!CONV && !std::is_same_v<EPI, EpiloguePartialI32>) {
+  if constexpr (!CONV && !std::is_same_v<EPI, EpiloguePartialI32>) {  // (slices: few tiles)
+    // Outputs of at most 32 columns on more 64 x 64 tiles than the chip holds at once: 128 x 32 tiles, whose waves all have
+    // columns (int8 100000 x 1 x 64 11.7 -> 8.2 us, x 32 x 100 12.5 -> 9.2, 10^6 x 4 x 64 83 -> 49, bf16 100000 x 1 x 64
+    // 8.1 -> 6.8; on one round the smaller tile is level or ahead, 30000 x 32 x 100 4.8 and 5.0, 8000 x 8 x 64 4.2 and 4.4).
     if (p.N <= 32 && p.M > 64 * 512) return launch_ragged_tile<T, EPI, 128, 32, 4, 1, AKC, BKC, CONV>(p, stream);
-  }
-  // 64 x 64 tiles that would leave some compute units with two and others with one become 128 x 64 tiles, one apiece
-  // and twice the waves: bf16 1023 x 1537 x 1021 (400 tiles of 64 x 64) 17.6 -> 15.0 us, int8 13.1 -> 10.8, int8
-  // 2047 x 800 x 333 6.5 -> 6.3; with one tile to a compute unit anyway the smaller tile wins (int8 1000^3 7.7, 8.1).
-  if (!CONV && tile == 64) {
+    // 64 x 64 tiles that would leave some compute units with two and others with one become 128 x 64 tiles, one apiece
+    // and twice the waves: bf16 1023 x 1537 x 1021 (400 tiles of 64 x 64) 17.6 -> 15.0 us, int8 13.1 -> 10.8, int8
+    // 2047 x 800 x 333 6.5 -> 6.3; with one tile to a compute unit anyway the smaller tile wins (int8 1000^3 7.7, 8.1).
     const int64_t tn = (p.N + 63) / 64, tall = (int64_t)((p.M + 127) / 128) * tn;
-    if (p.splits == 1 && tall <= 256 && (int64_t)((p.M + 63) / 64) * tn > 256) return launch_ragged_tile<T, EPI, 128, 64, 4, 2, AKC, BKC, CONV>(p, stream);
+    if (tile == 64 && tall <= 256 && (int64_t)((p.M + 63) / 64) * tn > 256) return launch_ragged_tile<T, EPI, 128, 64, 4, 2, AKC, BKC, CONV>(p, stream);
   }
   // 128 x 128: sixteen waves of one MFMA tile each for int8, whose products are short beside a trip's other work
   // (2047 x 2045 x 2041 23.2 -> 21.9 us, 1516 x 1764 x 56 6.9 -> 6.1), eight waves of two for bf16 (1500^3 24.0, 26.3)

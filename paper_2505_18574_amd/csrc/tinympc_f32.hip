@@ -13,17 +13,6 @@
 
 namespace ac {
 
-// v of lane k of every quad
-static __device__ __forceinline__ float quad_broadcast(float v, int k) {
-  const int i = __builtin_bit_cast(int, v);
-  switch (k) {  // constant after unrolling: the DPP control is an immediate
-    case 0: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x00, 0xF, 0xF, true));
-    case 1: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0x55, 0xF, 0xF, true));
-    case 2: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xAA, 0xF, 0xF, true));
-    default: return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, i, 0xFF, 0xF, 0xF, true));
-  }
-}
-
 // The paper's state and control sizes (12, 4) on the matrix units.  With u[i] substituted into the state update a
 // step is one 16 x 16 product on the stacked vector z = [x[i] (12); d[i] (4)] of each problem:
 //   [x[i + 1]; u[i]] = M . z,     M = [Adyn - Bdyn Kinf, -Bdyn; -Kinf, -I]

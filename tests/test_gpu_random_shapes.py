@@ -1,5 +1,5 @@
 """GPU parity on seeded random shapes: every kernel family (direct-to-LDS tiles of all three sizes, split-K,
-the generic fallback, the transposed-operand kernel) is reached by shapes the directed tests do not name."""
+the any-alignment kernel, the transposed operands) is reached by shapes the directed tests do not name."""
 import numpy as np
 import pytest
 import torch

@@ -101,7 +101,7 @@ def test_refusals_and_fallbacks():
     with pytest.raises(ops.AcError) as e:  # operands the direct-to-LDS kernels do not take (N = 60)
         ops.ac_gemm_i8_planned(dev(A), dev(B[:, :60].copy()), dev(bias[:60].copy()), C[:, :60].contiguous(), 8, 0, 32, 1)
     assert e.value.status == ops.AC_ERR_PLAN
-    # ac_gemm_i8 plans tile 32 for this size; with an unaligned A it must still run (on the generic kernel) and agree
+    # ac_gemm_i8 plans tile 32 for this size; with an unaligned A it must still run (on the any-alignment kernel) and agree
     assert ops.ac_gemm_i8_auto_plan(64, 64, 128) == (32, 1)
     Ap = torch.zeros((64, 129), dtype=torch.int8, device="cuda")
     Ap[:, :128] = dev(A)

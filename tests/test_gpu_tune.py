@@ -78,7 +78,7 @@ def test_split_refused_for_operands_off_the_fast_path():
     with pytest.raises(ops.AcError) as e:
         ops.ac_gemm_i8_planned(A, B, None, C, 0, 0, 64, 2, workspace=ws)
     assert e.value.status == ops.AC_ERR_PLAN
-    ops.ac_gemm_i8_planned(A, B, None, C, 0, 0, 64, 1)  # the unsplit plan runs on the generic kernel
+    ops.ac_gemm_i8_planned(A, B, None, C, 0, 0, 64, 1)  # the unsplit plan runs on the any-alignment kernel
     torch.cuda.synchronize()
 
 
