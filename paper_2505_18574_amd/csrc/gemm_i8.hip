@@ -420,14 +420,16 @@ bool conv_i8_fast_path(const GemmParams& p) {
 // 101 -> 77; level on the shapes where they agree).  Where they take the weight-stationary kernel they are right as long
 // as K is short, and a single tap, a plain product but for its rows, always is (1 x 1 stride 2, 48 -> 16 on 185 images of
 // 65 x 65 13.5 us there and 22.6 on the tile, 64 -> 48 on 64 of 56 x 56 6.6 and 8.8); its gather loses from K = 800 on
-// where the columns are whole 32s, from 1200 on otherwise (3 x 3 stride 2, 96 -> 64 on 76800 pixels 20.8 and 14.3,
-// 5 x 5 stride 2, 64 -> 16 on 234484 92 and 57; 2 x 2 stride 2, 256 -> 16 on 113568, K = 1024, 24.2 and 26.6).  Sixty-four
+// where the columns are whole 32s (from 400 with more than nine taps), from 1200 on otherwise (3 x 3 stride 2, 96 -> 64 on
+// 76800 pixels 20.8 and 14.3, 5 x 5 stride 2, 16 -> 64 on 39546 10.5 and 7.8, 64 -> 16 on 234484 92 and 57; 2 x 2
+// stride 2, 256 -> 16 on 113568, K = 1024, 24.2 and 26.6, 144 -> 64 on 285696, K = 576, 32.9 and 35.4).  Sixty-four
 // columns fill half of a wide tile, which is the better one for K beyond 32768 (5 x 5, 1968 -> 64 on 51840 pixels 378 and
 // 410, 1520 -> 64 339 and 350; 1056 -> 64 on 39546, K = 26400, 182 and 147).
 static bool narrow_conv_plan(const GemmParams& p, GemmPlan* plan) {
   int bm;
   if (p.N > 64 || p.M <= 64 * PLAN_CUS || plan->tile == 32 || (p.N > 48 && p.K > 32768)) return false;
-  if (wstat_tile_rows(plan->tile, &bm) && p.K < (p.N % 32 == 0 ? 800 : 1200)) return false;
+  const int32_t gather = p.N % 32 != 0 ? 1200 : p.KH * p.KW > 9 ? 400 : 800;
+  if (wstat_tile_rows(plan->tile, &bm) && p.K < gather) return false;
   return make_plan_i8(p.K, 64, 1, plan);
 }
 

@@ -136,7 +136,8 @@ def test_sums_around_the_clamp_bounds(plan):
 @pytest.mark.parametrize("Nb,H,W,Cin,Cout,k,stride,pad", [
     (70, 31, 31, 48, 16, 1, 2, 0),    # a single tap: weight-stationary
     (80, 31, 31, 192, 64, 2, 2, 0),   # K = 768, 64 columns: weight-stationary
-    (70, 31, 31, 32, 32, 5, 2, 2),    # K = 800, whole 32s: the 64 x 64 tile
+    (70, 31, 31, 96, 32, 3, 2, 1),    # K = 864, whole 32s: the 64 x 64 tile
+    (70, 31, 31, 16, 32, 5, 2, 2),    # ... and of 25 taps K = 400
     (80, 31, 31, 288, 48, 2, 2, 0),   # K = 1152: weight-stationary
     (70, 31, 31, 48, 48, 5, 2, 2),    # K = 1200: the tile
 ])
