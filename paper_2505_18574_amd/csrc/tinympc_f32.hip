@@ -366,7 +366,8 @@ hipError_t launch_tinympc_forward(const TinyMpcParams& p, hipStream_t stream) {
   // The paper's sizes up to its horizon, where a call is bound by the bytes it moves; 262144 problems on the vector ALU and
   // here: horizon 1 12.3 and 6.7 us, 4 21.5 and 13.7, with the trajectory 19.7 and 11.2, 29.8 and 22.1.  (Beyond 5, where the
   // registers of a block's states run out, the vector ALU is ahead of matrix units that store state by state: horizon 6
-  // without the trajectory 41 us so and 28.7.)
+  // without the trajectory 41 us so and 28.7, 40 322 and 126, with it in chunks 16 213 and 177, 40 596 and 398; 100 problems
+  // of horizon 8 11.2 and 5.2, of 100 with the trajectory 115 and 66.)
   if (p.nx == 12 && p.nu == 4 && p.horizon <= TMPC_H && aligned16) {
     switch (p.horizon) {
       case 1: return launch_mfma<1>(p, stream);
