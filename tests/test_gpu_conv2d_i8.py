@@ -39,7 +39,7 @@ def test_workload_configs(case):
     (1, 5, 5, 16, 16, 3, 3, 1, 1),      # one tile
     (2, 9, 7, 16, 32, 3, 3, 2, 1),      # stride 2, odd image
     (3, 12, 12, 32, 48, 3, 3, 1, 0),    # no padding
-    (1, 8, 8, 3, 8, 3, 3, 1, 1),        # Cin not a multiple of 16: element-wise gather path
+    (1, 8, 8, 3, 8, 3, 3, 1, 1),        # Cin not a multiple of 16: rows copied into LDS
     (2, 10, 6, 5, 7, 3, 2, 2, 1),       # nothing aligned, KH != KW
     (2, 14, 14, 64, 64, 1, 1, 1, 0),    # 1x1: a plain GEMM over pixels
     (1, 6, 6, 16, 16, 5, 5, 1, 2),      # 5x5
@@ -50,8 +50,8 @@ def test_workload_configs(case):
     (1, 14, 14, 256, 64, 3, 3, 1, 1),   # few tiles, deep K
     (2, 7, 7, 512, 128, 3, 3, 1, 1),
     (1, 7, 7, 1024, 64, 3, 3, 1, 1),    # one tile, 72 K tiles: split-K when a workspace is given
-    (1, 9, 9, 16, 16, 4, 8, 1, 3),      # 32 kernel taps: the most the tap bit mask of the tiled gather holds
-    (1, 10, 10, 16, 32, 6, 6, 1, 2),    # 36 taps: beyond the mask, the element-wise gather takes it
+    (1, 9, 9, 16, 16, 4, 8, 1, 3),      # 32 kernel taps: the most the patch kernel takes
+    (1, 10, 10, 16, 32, 6, 6, 1, 2),    # 36 taps: the gather, or rows copied into LDS
     (1, 12, 12, 16, 16, 7, 7, 2, 3),    # 7x7 stride 2
     (2, 5, 7, 48, 16, 3, 3, 1, 3),      # padding wider than the kernel: border outputs see no input at all
     (1, 6, 20, 32, 16, 1, 5, 1, 2),     # one kernel row
