@@ -1,7 +1,7 @@
 // bf16 GEMM, fp32 accumulate and output: tile selection, split-K and launch.
 #include <algorithm>
 
-#include "gemm_ragged.hpp"
+#include "gemm_kgroup.hpp"
 
 namespace ac {
 
@@ -77,8 +77,11 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
     if (forced && plan.splits > 1) return hipErrorInvalidValue;
     p.splits = 1;
     p.kt_per_split = 0;
+    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && kgroup_ragged_takes<TypeBF16, true, false>(p, false))
+      return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);
     return launch_ragged<TypeBF16, EpilogueF32, true, false>(forced ? plan.tile : ragged_tile(p.M, p.N), p, stream);
   }
+  if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits > 1)) return launch_kgroup<TypeBF16, KGroupF32, 0>(p, stream);
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
   if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order

@@ -135,6 +135,13 @@ static __device__ __forceinline__ void for_each_stage(F&& f, std::integer_sequen
   (f(std::integral_constant<int, I>{}), ...);
 }
 
+// Bits k = 0 .. n - 1 with 0 <= first + k < extent (kernel rows or columns of a convolution that fall inside the image).
+static __device__ __forceinline__ unsigned span_bits(int first, int n, int extent) {
+  const int lo = first < 0 ? -first : 0, hi = extent - first < n ? extent - first : n;
+  if (hi <= lo) return 0u;
+  return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
+}
+
 template <class T, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KTB_>
 struct DtlGeometry {
   static constexpr int EB = T::EB;
@@ -295,13 +302,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
         const int ow = (int)(mm - q * p.OW), oh = (int)(q - img * p.OH);
         const int ih0 = oh * p.stride - p.pad, iw0 = ow * p.stride - p.pad;
         g_base[i] = (((int)img * p.H + ih0) * p.W + iw0) * p.Cin;
-        auto span = [](int first, int n, int extent) {  // bits k = 0 .. n-1 with 0 <= first + k < extent
-          const int lo = first < 0 ? -first : 0, hi = extent - first < n ? extent - first : n;
-          if (hi <= lo) return 0u;
-          return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
-        };
-        g_rows[i] = m < p.M ? span(ih0, p.KH, p.H) : 0u;
-        g_cols[i] = span(iw0, p.KW, p.W);
+        g_rows[i] = m < p.M ? span_bits(ih0, p.KH, p.H) : 0u;
+        g_cols[i] = span_bits(iw0, p.KW, p.W);
       }
     }
 #pragma unroll

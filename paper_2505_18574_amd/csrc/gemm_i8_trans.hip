@@ -11,7 +11,7 @@
 // the ragged kernel.
 #include <algorithm>
 
-#include "gemm_ragged.hpp"
+#include "gemm_kgroup.hpp"
 
 namespace ac {
 
@@ -20,6 +20,7 @@ static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   GemmParams p = p0;
   p.splits = 1;
   p.kt_per_split = 0;
+  if (kgroup_takes<TypeI8, TB>(p, false, false)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB>(p, stream);
   switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // square tiles only: the 256 x 128 code falls to 128
     case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB>(p, stream);
     case 192:
@@ -47,9 +48,13 @@ hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b,
   GemmParams q = p;
   q.splits = 1;
   q.kt_per_split = 0;
-  if (trans_a && trans_b) return launch_ragged<TypeI8, EpilogueI8Any, false, true>(tile, q, stream);
-  if (trans_a) return launch_ragged<TypeI8, EpilogueI8Any, false, false>(tile, q, stream);
-  return launch_ragged<TypeI8, EpilogueI8Any, true, true>(tile, q, stream);
+  auto ragged = [&](auto ta, auto tb) {
+    constexpr bool AKC = !decltype(ta)::value, BKC = decltype(tb)::value;
+    if (!ragged_tiny<TypeI8, AKC, BKC, false>(q) && kgroup_ragged_takes<TypeI8, AKC, BKC>(q, false)) return launch_kgroup_ragged<TypeI8, KGroupI8, AKC, BKC>(q, stream);
+    return launch_ragged<TypeI8, EpilogueI8Any, AKC, BKC>(tile, q, stream);
+  };
+  if (trans_a && trans_b) return ragged(std::true_type{}, std::true_type{});
+  return trans_a ? ragged(std::true_type{}, std::false_type{}) : ragged(std::false_type{}, std::true_type{});
 }
 
 }  // namespace ac

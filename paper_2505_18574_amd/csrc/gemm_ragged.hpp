@@ -149,12 +149,13 @@ struct RaggedMatrix {
     fix = s >= 16 ? chunk_fix(0, 0, 0) : chunk_fix((int)s, lo, hi);
     return load16_any(q);
   }
-  // the next tile in order, which must lie inside K with every row of it at least 16 bytes long
-  __device__ __forceinline__ void load_whole(v4i (&reg)[IT]) {
+  // the next tile in order, which must lie inside K with every row of it at least 16 bytes long; the one after it lies
+  // `advance` bytes further on
+  __device__ __forceinline__ void load_whole(v4i (&reg)[IT], int64_t advance) {
 #pragma unroll
     for (int i = 0; i < IT; i++) {
       reg[i] = load16_any(ptr[i]);
-      ptr[i] += step;
+      ptr[i] += advance;
     }
   }
   // any tile: the one `ahead` tiles after the next whole one, which does not move on
@@ -179,13 +180,13 @@ struct RaggedMatrix {
 static __host__ __device__ __forceinline__ int conv_run(const GemmParams& p) { return p.KW * p.Cin; }
 static __host__ __device__ __forceinline__ int conv_run_padded(const GemmParams& p) { return p.Cin > 0 ? (p.KW * p.Cin + 15) & ~15 : 16; }
 
-// Position (kh, r) of a K index inside that walk, advanced by one K tile at a time without a division.
+// Position (kh, r) of a K index inside that walk, advanced by `tiles` K tiles at a time without a division.
 struct ConvWalk {
   int kh, r, dkh, dr, runp;
-  __device__ __forceinline__ void init(int kp, int runp_) {
+  __device__ __forceinline__ void init(int kp, int runp_, int tiles) {
     runp = runp_;
     kh = kp / runp, r = kp - kh * runp;
-    dkh = RAGGED_KTB / runp, dr = RAGGED_KTB - dkh * runp;
+    dkh = tiles * RAGGED_KTB / runp, dr = tiles * RAGGED_KTB - dkh * runp;
   }
   __device__ __forceinline__ void next() {
     kh += dkh, r += dr;
@@ -211,11 +212,11 @@ struct RaggedImage {
     const int64_t lim = 1 << 30;
     return (int)(d > lim ? lim : (d < -lim ? -lim : d));
   }
-  __device__ __forceinline__ void init(const GemmParams& p, int m0, int kt0, int t) {
+  __device__ __forceinline__ void init(const GemmParams& p, int m0, int kt0, int t, int tiles = 1) {
     in = (const unsigned char*)p.A;
     pitch = p.W * p.Cin, H = p.H, total = p.a_bytes, KH = p.KH;
     const int cc = t % Tile::CPR, r0 = t / Tile::CPR;
-    w.init(kt0 * RAGGED_KTB + cc * 16, conv_run_padded(p));
+    w.init(kt0 * RAGGED_KTB + cc * 16, conv_run_padded(p), tiles);
 #pragma unroll
     for (int i = 0; i < IT; i++) {
       const int m = m0 + r0 + i * Tile::RPP;
@@ -257,12 +258,12 @@ struct RaggedWeights {
   int64_t ld;
   int run, KH, col;
 
-  __device__ __forceinline__ void init(const GemmParams& p, int n0, int kt0, int t) {
+  __device__ __forceinline__ void init(const GemmParams& p, int n0, int kt0, int t, int tiles = 1) {
     m.init(p.B, p.ldb, n0, p.N, p.K, 0, t);
     ld = p.ldb, run = conv_run(p), KH = p.KH;
     col = (int)(m.ptr[0] - m.base - (int64_t)(t / Tile::CPR) * ld);  // this thread's column after clamping and shifting
 #pragma unroll
-    for (int i = 0; i < IT; i++) w[i].init(kt0 * RAGGED_KTB + t / Tile::CPR + i * Tile::RPP, conv_run_padded(p));
+    for (int i = 0; i < IT; i++) w[i].init(kt0 * RAGGED_KTB + t / Tile::CPR + i * Tile::RPP, conv_run_padded(p), tiles);
   }
   __device__ __forceinline__ void load(v4i (&reg)[IT], int (&fix)[IT]) {
 #pragma unroll
@@ -398,8 +399,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
       v4i ra[R][SA::IT], rb[R][SB::IT];
       auto fetch = [&](auto sc) {
         constexpr int S = decltype(sc)::value;
-        a.load_whole(ra[S]);
-        b.load_whole(rb[S]);
+        a.load_whole(ra[S], a.step);
+        b.load_whole(rb[S], b.step);
         in_order();
       };
       auto stage = [&](int buf, auto sc) {  // of a whole tile, only the last chunk of a K-strided row needs its shift

@@ -79,13 +79,8 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
       const int ow = (int)(mm - q * p.OW), oh = (int)(q - img * p.OH);
       const int ih0 = oh * p.stride - p.pad, iw0 = ow * p.stride - p.pad;
       g_base[i] = (((int)img * p.H + ih0) * p.W + iw0) * p.Cin;
-      auto span = [](int first, int n, int extent) {  // bits k = 0 .. n-1 with 0 <= first + k < extent
-        const int lo = first < 0 ? -first : 0, hi = extent - first < n ? extent - first : n;
-        if (hi <= lo) return 0u;
-        return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
-      };
-      g_rows[i] = m < p.M ? span(ih0, p.KH, p.H) : 0u;
-      g_cols[i] = span(iw0, p.KW, p.W);
+      g_rows[i] = m < p.M ? span_bits(ih0, p.KH, p.H) : 0u;
+      g_cols[i] = span_bits(iw0, p.KW, p.W);
     }
     const int brow = i * G::B_ROWS_PER_INSTR + lane / G::B_SPR;
     const int slot = lane % G::B_SPR;
