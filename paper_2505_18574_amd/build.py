@@ -1,14 +1,17 @@
-"""Build the HIP library in-tree: csrc/*.hip + api.cpp -> libac_mi355x.so (gfx950 only)."""
+"""Build in-tree: csrc/*.hip + api.cpp -> libac_mi355x.so (the HIP library, gfx950 only), csrc/binding.cpp -> _binding.so
+(the compiled side of ops.py, host code against this interpreter's torch)."""
 from __future__ import annotations
 
 import concurrent.futures
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libac_mi355x.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 SOURCES = ["api.cpp", "gemm_i8.hip", "gemm_i8_trans.hip", "gemm_bf16.hip", "batched_f32.hip", "tinympc_f32.hip"]
 
@@ -33,6 +36,21 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    """Needs LIB, which the binding finds beside itself; torch's own libraries are in the process before it is loaded."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + [f"-I{i}" for i in include]
+    cmd += [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, LIB, "-Wl,-rpath,$ORIGIN", "-L" + os.path.join(root, "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building the binding failed:\n{r.stderr}")
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
@@ -41,8 +59,9 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr}")
+    _build_binding()
     if verbose:
-        print("built", LIB)
+        print("built", LIB, BINDING)
     return LIB
 
 

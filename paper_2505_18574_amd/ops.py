@@ -31,6 +31,7 @@ EXPORTS = ("ac_gemm_i8", "ac_gemm_i8_workspace_bytes", "ac_conv2d_i8", "ac_gemm_
            "ac_status_string", "ac_version")
 
 _lib = None
+_native = None
 
 
 class AcError(RuntimeError):
@@ -94,6 +95,20 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def native():
+    """The compiled side of the functions below (csrc/binding.cpp)."""
+    global _native
+    if _native is None:
+        lib()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise ImportError(f"the compiled binding is missing or does not fit this torch ({e}): build it with "
+                              "`python -m paper_2505_18574_amd.build`; there is no fallback path") from e
+        _native = _binding
+    return _native
+
+
 def status_string(status: int) -> str:
     return lib().ac_status_string(int(status)).decode()
 
@@ -136,9 +151,9 @@ def ac_gemm_bf16_auto_plan(M: int, N: int, K: int):
 
 
 # The functions below run once per launch, and on this path a launch takes the GPU no longer than the checks take the
-# host: addresses go to ctypes as plain integers, a tensor's properties are read once, and the current stream's handle is
-# asked for without building a Stream object (2.8 of the 9.7 us that a call
-# took; now 6.0, of which the launch is 2.8).
+# host.  Each hands its arguments to its compiled namesake first, which takes plain ones (torch.Tensor itself, the right
+# types and shapes, ...) and returns a status; a positive one says that something was not plain, and the checks here
+# decide whether it is unusual or wrong.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -198,8 +213,10 @@ def _gemm_i8_args(A, B, bias, C):
 
 def ac_gemm_i8(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, workspace=None, stream=None):
     """C[M,N] int8 = stage(A[M,K] . B[K,N] + bias); bias is None, (N,) or (M,N) int32.  Returns C."""
-    wp, wb = _ws(workspace)
-    st = (_lib or lib()).ac_gemm_i8(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, _stream(stream))
+    st = (_native or native()).gemm_i8(A, B, bias, C, shift, act, workspace, stream)
+    if st > AC_OK:
+        wp, wb = _ws(workspace)
+        st = lib().ac_gemm_i8(*_gemm_i8_args(A, B, bias, C), shift, act, wp, wb, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8")
     return C
@@ -218,18 +235,20 @@ def ac_gemm_i8_static(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, stream=
 
 def ac_gemm_i8_t(A, B, bias, C, shift: int, act: int = AC_ACT_NONE, trans_a: bool = False, trans_b: bool = False, stream=None):
     """ac_gemm_i8 with A given as A^T (K x M) when trans_a and B as B^T (N x K) when trans_b.  Returns C."""
-    M, K, lda = _matrix(A, torch.int8, "A")
-    K2, N, ldb = _matrix(B, torch.int8, "B")
-    M2, N2, ldc = _matrix(C, torch.int8, "C")
-    if trans_a:
-        M, K = K, M
-    if trans_b:
-        K2, N = N, K2
-    if K2 != K or M2 != M or N2 != N:
-        raise ValueError("shape mismatch")
-    bp, bias_ld = _bias_i8(bias, M, N)
-    st = (_lib or lib()).ac_gemm_i8_t(A.data_ptr(), lda, B.data_ptr(), ldb, bp, bias_ld, C.data_ptr(), ldc,
-                                      M, N, K, shift, act, int(bool(trans_a)), int(bool(trans_b)), _stream(stream))
+    st = (_native or native()).gemm_i8_t(A, B, bias, C, shift, act, trans_a, trans_b, stream)
+    if st > AC_OK:
+        M, K, lda = _matrix(A, torch.int8, "A")
+        K2, N, ldb = _matrix(B, torch.int8, "B")
+        M2, N2, ldc = _matrix(C, torch.int8, "C")
+        if trans_a:
+            M, K = K, M
+        if trans_b:
+            K2, N = N, K2
+        if K2 != K or M2 != M or N2 != N:
+            raise ValueError("shape mismatch")
+        bp, bias_ld = _bias_i8(bias, M, N)
+        st = lib().ac_gemm_i8_t(A.data_ptr(), lda, B.data_ptr(), ldb, bp, bias_ld, C.data_ptr(), ldc,
+                                M, N, K, shift, act, int(bool(trans_a)), int(bool(trans_b)), _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_t")
     return C
@@ -249,6 +268,12 @@ def ac_conv2d_i8(x, w, bias, out, stride: int, pad: int, shift: int, act: int = 
     """out[Nb,OH,OW,Cout] int8 = stage(conv(x[Nb,H,W,Cin], w[KH,KW,Cin,Cout]) + bias[Cout]).  Returns out.
 
     plan = (tile, splits) goes through ac_conv2d_i8_planned."""
+    if plan is None:
+        st = (_native or native()).conv2d_i8(x, w, bias, out, stride, pad, shift, act, workspace, stream)
+        if st == AC_OK:
+            return out
+        if st < AC_OK:
+            raise AcError(st, "ac_conv2d_i8")
     shapes = []
     for t, name in ((x, "x"), (w, "w"), (out, "out")):
         shape = t.shape
@@ -297,7 +322,9 @@ def _gemm_bf16_args(A, B, C):
 
 def ac_gemm_bf16(A, B, C, alpha: float = 1.0, beta: float = 0.0, stream=None):
     """C[M,N] fp32 = alpha * A[M,K] . B[K,N] + beta * C; A, B are bf16 (torch.bfloat16, or int16/uint16 bit patterns)."""
-    st = (_lib or lib()).ac_gemm_bf16(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), _stream(stream))
+    st = (_native or native()).gemm_bf16_ws(A, B, C, alpha, beta, None, stream)
+    if st > AC_OK:
+        st = lib().ac_gemm_bf16(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_bf16")
     return C
@@ -305,8 +332,10 @@ def ac_gemm_bf16(A, B, C, alpha: float = 1.0, beta: float = 0.0, stream=None):
 
 def ac_gemm_bf16_ws(A, B, C, alpha: float = 1.0, beta: float = 0.0, workspace=None, stream=None):
     """ac_gemm_bf16 that sums the slices of a cut K range through `workspace` (in a fixed order) when one is given.  Returns C."""
-    wp, wb = _ws(workspace)
-    st = (_lib or lib()).ac_gemm_bf16_ws(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, _stream(stream))
+    st = (_native or native()).gemm_bf16_ws(A, B, C, alpha, beta, workspace, stream)
+    if st > AC_OK:
+        wp, wb = _ws(workspace)
+        st = lib().ac_gemm_bf16_ws(*_gemm_bf16_args(A, B, C), float(alpha), float(beta), wp, wb, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_bf16_ws")
     return C
@@ -324,6 +353,11 @@ def ac_gemm_bf16_planned(A, B, C, alpha: float, beta: float, tile: int, splits: 
 
 def ac_batched_gemm_f32(A, B, C=None, x=None, d=None, y=None, stream=None):
     """Per item: C = A . B (n x n), y = C . x + d.  A, B, C: [batch,n,n]; x, d, y: [batch,n]; fp32 dense."""
+    st = (_native or native()).batched_gemm_f32(A, B, C, x, d, y, stream)
+    if st == AC_OK:
+        return C, y
+    if st < AC_OK:
+        raise AcError(st, "ac_batched_gemm_f32")
     for t, name in ((A, "A"), (B, "B"), (C, "C"), (x, "x"), (d, "d"), (y, "y")):
         if t is not None and (t.dtype is not torch.float32 or not t.is_contiguous() or not t.is_cuda):
             raise ValueError(f"{name}: expected a dense fp32 device tensor")
@@ -345,6 +379,11 @@ def ac_tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out=None, stream=None):
     """Batched TinyMPC forward pass: u[b,i] = -Kinf x[b,i] - d[b,i]; x[b,i+1] = Adyn x[b,i] + Bdyn u[b,i].
 
     Adyn [nx,nx], Bdyn [nx,nu], Kinf [nu,nx], x0 [batch,nx], d and u [batch,horizon,nu], x_out [batch,horizon+1,nx] or None."""
+    st = (_native or native()).tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out, stream)
+    if st == AC_OK:
+        return u, x_out
+    if st < AC_OK:
+        raise AcError(st, "ac_tinympc_forward_f32")
     for t, name in ((Adyn, "Adyn"), (Bdyn, "Bdyn"), (Kinf, "Kinf"), (x0, "x0"), (d, "d"), (u, "u"), (x_out, "x_out")):
         if t is not None and (t.dtype is not torch.float32 or not t.is_contiguous() or not t.is_cuda):
             raise ValueError(f"{name}: expected a dense fp32 device tensor")
@@ -363,19 +402,21 @@ def ac_tinympc_forward_f32(Adyn, Bdyn, Kinf, x0, d, u, x_out=None, stream=None):
 
 def ac_gemm_i8_acc32(A, B, bias, C, stream=None):
     """C[M,N] int32 = A[M,K] . B[K,N] + bias (raw accumulator: no scaling, no activation).  Returns C."""
-    M, K, lda = _matrix(A, torch.int8, "A")
-    K2, N, ldb = _matrix(B, torch.int8, "B")
-    M2, N2, ldc = _matrix(C, torch.int32, "C")
-    if K2 != K or M2 != M or N2 != N:
-        raise ValueError("shape mismatch")
-    bias_ld = 0
-    if bias is not None:
-        if bias.dtype != torch.int32 or not bias.is_cuda:
-            raise ValueError("bias: expected int32 device tensor")
-        if bias.dim() == 2:
-            bias_ld = bias.stride(0)
-    st = (_lib or lib()).ac_gemm_i8_acc32(A.data_ptr(), lda, B.data_ptr(), ldb, _ptr(bias), bias_ld, C.data_ptr(), ldc,
-                                          M, N, K, _stream(stream))
+    st = (_native or native()).gemm_i8_acc32(A, B, bias, C, stream)
+    if st > AC_OK:
+        M, K, lda = _matrix(A, torch.int8, "A")
+        K2, N, ldb = _matrix(B, torch.int8, "B")
+        M2, N2, ldc = _matrix(C, torch.int32, "C")
+        if K2 != K or M2 != M or N2 != N:
+            raise ValueError("shape mismatch")
+        bias_ld = 0
+        if bias is not None:
+            if bias.dtype != torch.int32 or not bias.is_cuda:
+                raise ValueError("bias: expected int32 device tensor")
+            if bias.dim() == 2:
+                bias_ld = bias.stride(0)
+        st = lib().ac_gemm_i8_acc32(A.data_ptr(), lda, B.data_ptr(), ldb, _ptr(bias), bias_ld, C.data_ptr(), ldc,
+                                    M, N, K, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_acc32")
     return C

@@ -1,0 +1,81 @@
+"""The compiled binding takes plain arguments and leaves everything else to the checks of ops.py."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_18574_amd import ops
+
+PYTHON = 1
+
+
+def i8(*s):
+    return torch.zeros(s, dtype=torch.int8)
+
+
+def f32(*s):
+    return torch.zeros(s)
+
+
+def test_what_is_not_plain_is_left_to_python():
+    n = ops.native()
+    A, C, b = i8(4, 4), i8(4, 4), torch.zeros(4, dtype=torch.int32)
+    for args in ((A, A, b, C, 1, 0, None, None), (None,) * 8, ("A",) * 8, (A, A, b, C, 1.5, 0, None, None), (A,), (A,) * 9):
+        assert n.gemm_i8(*args) == PYTHON  # tensors on the host, no tensors, other counts
+    assert n.gemm_i8_t(A, A, b, C, 1, 0, False, 1, None) == PYTHON
+    assert n.gemm_i8_acc32(A, A, b, C, None) == PYTHON
+    assert n.conv2d_i8(i8(1, 4, 4, 2), i8(3, 3, 2, 4), None, i8(1, 4, 4, 4), 1, 1, 1, 0, None, None) == PYTHON
+    assert n.gemm_bf16_ws(A, A, C, 1.0, 0.0, None, None) == PYTHON
+    assert n.batched_gemm_f32(f32(2, 3, 3), f32(2, 3, 3), None, None, None, None, None) == PYTHON
+    assert n.tinympc_forward_f32(*[f32(2, 2)] * 7, None) == PYTHON
+
+
+def test_errors_are_those_of_the_python_checks():
+    A, C = i8(4, 4), i8(4, 4)
+    with pytest.raises(ValueError, match="A: expected a 2-D row-major device tensor"):
+        ops.ac_gemm_i8(A, A, None, C, 1)
+    with pytest.raises(ValueError, match="A: expected a 2-D row-major bf16 device tensor"):
+        ops.ac_gemm_bf16_ws(A, A, C)
+    with pytest.raises(ValueError, match="x: expected a dense 4-D int8 device tensor"):
+        ops.ac_conv2d_i8(A, A, None, C, 1, 0, 1)
+    with pytest.raises(ValueError, match="A: expected a dense fp32 device tensor"):
+        ops.ac_batched_gemm_f32(f32(1, 2, 2), f32(1, 2, 2), f32(1, 2, 2))
+    with pytest.raises(AttributeError):
+        ops.ac_gemm_i8(None, A, None, C, 1)
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.gpu
+def test_plain_and_unusual_arguments_give_the_same_result():
+    g = np.random.default_rng(3)
+    A, B = (torch.from_numpy(g.integers(-128, 128, s).astype(np.int8)).cuda() for s in ((40, 64), (64, 48)))
+    bias = torch.arange(48, dtype=torch.int32, device="cuda") * 300
+    new = lambda: torch.full((40, 48), 5, dtype=torch.int8, device="cuda")
+    n = ops.native()
+    C = new()
+    assert n.gemm_i8(A, B, bias, C, 9, 1, None, None) == ops.AC_OK
+    assert n.gemm_i8(A, B, bias, C, 99, 1, None, None) == ops.AC_ERR_SHIFT
+    assert n.gemm_i8(A, B.t(), bias, C, 9, 1, None, None) == PYTHON      # not row-major
+    assert n.gemm_i8(A, B, bias[:-1], C, 9, 1, None, None) == PYTHON     # a bias of another length
+    with pytest.raises(ops.AcError) as e:
+        ops.ac_gemm_i8(A, B, bias, C, 99)
+    assert e.value.status == ops.AC_ERR_SHIFT
+    with pytest.raises(ValueError, match="bias vector"):
+        ops.ac_gemm_i8(A, B, bias[:-1], C, 9)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    D, E, F = new(), new(), new()
+    with torch.cuda.stream(side):
+        ops.ac_gemm_i8(A, B, bias, D, np.int64(9), np.int32(1))            # integers of numpy
+    ops.ac_gemm_i8(A, B, bias, E, 9, act=1, stream=side)                   # a stream by name
+    side.synchronize()
+    ops.ac_gemm_i8(A.as_subclass(Sub), B, bias.expand(40, 48).contiguous(), F, True + 8, True)  # a subclass, a bias matrix, bools
+    for out in (D, E, F):
+        assert torch.equal(out, C)
+    P, Q = torch.randn(33, 16, device="cuda").bfloat16(), torch.randn(16, 24, device="cuda").bfloat16()
+    R, S = torch.zeros(33, 24, device="cuda"), torch.zeros(33, 24, device="cuda")
+    ops.ac_gemm_bf16(P, Q, R)
+    ops.ac_gemm_bf16(P.view(torch.int16), Q.view(torch.uint16), S, 1, 0)   # bit patterns, integer factors
+    assert torch.equal(R, S)
