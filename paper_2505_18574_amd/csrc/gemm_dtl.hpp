@@ -45,6 +45,15 @@ static __device__ __forceinline__ void load_to_lds16_so(const void* sbase, unsig
 static __device__ __forceinline__ void buffer_to_lds16(v4i rsrc, unsigned voff, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(voff), "s"(rsrc) : "memory");
 }
+// 4 bytes per lane: lane i's dword at offset voff (zero beyond the descriptor's size) to lds_base + 4 * i.
+static __device__ __forceinline__ void buffer_to_lds4(v4i rsrc, unsigned voff, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_base), "v"(voff), "s"(rsrc) : "memory");
+}
+// Descriptor of `bytes` bytes from a wave-uniform address, for raw dword access.
+static __device__ __forceinline__ v4i buffer_of(const void* base, unsigned bytes) {
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  return (v4i){__builtin_amdgcn_readfirstlane((int)(uint32_t)b), __builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)), __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
 // Workgroup barrier that waits for this wave's LDS traffic only.  __syncthreads() would also drain every
 // outstanding global store, which would serialise one tile's epilogue with the next tile's main loop.
 static __device__ __forceinline__ void block_sync() {
@@ -197,6 +206,10 @@ static __device__ __forceinline__ void tile_coords_mul(int b, int nblocks, int t
   tn = qn;
 }
 
+// Whether gemm_dtl_kernel keeps the bias row of its tile in LDS, behind the stages: BN * 4 bytes.
+template <class EPI, int BM, int AMODE, bool PINGPONG>
+constexpr bool has_bias_lds = BM >= 256 && !(PINGPONG && AMODE == 0) && std::is_same_v<EPI, EpilogueI8>;
+
 // TA / TB (int8 GEMM on square tiles): A is given as A^T (K x M, row pitch lda) / B as B^T (N x K, row pitch ldb).
 // A transposed operand takes the other operand's role in LDS: A^T is "K-strided" like B (k-rows of BM bytes, the
 // B swizzle, fragments through the transposing reads), B^T is "K-contiguous" like A (rows of KTB bytes, the A
@@ -229,6 +242,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   constexpr int EPI_VM = EPI::LDS_STAGED ? G::TM * 2 * (16 / (64 / (G::WTN / 4))) : G::TM * G::TN;
   static_assert(!XPF || (STAGES - 2) * (G::A_INSTR + G::B_INSTR) + EPI_VM <= 63, "vmcnt is a 6-bit counter");
 
+  // The bias of a wave's columns waits in LDS behind the stages, where the tile leaves no registers to hold it over the K
+  // loop: those went to scratch, 16 to 18 of a wave of the 256 x 128 tiles and 10 of the 256 x 256 convolution (4784 x 1600 x
+  // 2048 24.3 -> 21.8 us, 8192 x 1024 x 1024 14.5 -> 13.6, 3 x 3 stride 2, 256 -> 512 on 64 images of 28 x 28 24.9 -> 22.7, 3 x 3,
+  // 496 -> 304 on 29 of 27 x 27 47.4 -> 44.7).  The product of a 256 x 256 tile holds them without and is slower with it
+  // (5000 x 2560 x 320 12.1 and 13.6).  The request is the oldest of its wave, so the K loop's first wait covers it and the
+  // barrier behind that publishes it; the barrier at the end of the item frees it.
+  constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, AMODE, PINGPONG>;
+
   // ---- item-independent lane roles ---------------------------------------------------------------------
   constexpr int NVAR = G::KTB == 128 ? 2 : 1;
   int a_chunk[NVAR];
@@ -236,14 +257,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   for (int v = 0; v < NVAR; v++) a_chunk[v] = (lane % G::A_SPR) ^ G::a_xor(v * G::A_ROWS_PER_INSTR + lane / G::A_SPR);
   const int64_t b_step = (int64_t)G::BK * p.ldb * EB;
   const int64_t a_step_t = (int64_t)G::BK * p.lda * EB;  // A^T: one K tile further down
-  v4i a_rsrc = {0, 0, 0, 0};  // buffer descriptor of the input image: base, size in bytes, raw dword format
-  if constexpr (AMODE == 1) {
-    const uint64_t ab = (uint64_t)(uintptr_t)p.A;
-    a_rsrc[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)ab);
-    a_rsrc[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(ab >> 32));
-    a_rsrc[2] = __builtin_amdgcn_readfirstlane(p.a_bytes);
-    a_rsrc[3] = 0x00020000;
-  }
+  v4i a_rsrc = {0, 0, 0, 0};  // the input image
+  if constexpr (AMODE == 1) a_rsrc = buffer_of(p.A, (unsigned)p.a_bytes);
 
   // ---- state of the item whose loads are being issued: per-lane source addressing ------------------------
   // A: wave instruction j (j = wave * A_INSTR + i) fills A_ROWS_PER_INSTR tile rows; lane l -> row
@@ -511,8 +526,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 
   // operands of the output stage that do not depend on the product (bias) are requested before the K loop
   typename EPI::Pre pre[G::TN];
+  if constexpr (BIAS_LDS) {
+    // no row bias: a buffer of no bytes, which reads as zeros (N is at most 2^29)
+    const v4i rsrc = buffer_of(p.bias, p.bias != nullptr && p.bias_ld == 0 ? (unsigned)p.N * 4u : 0u);
+    if (wave < BN / 64) buffer_to_lds4(rsrc, (unsigned)(n0 + wave * 64 + lane) * 4u, lds0 + G::LDS_BYTES + wave * 256);
+  } else {
 #pragma unroll
-  for (int j = 0; j < G::TN; j++) EPI::prefetch(p, n0 + wn * G::WTN + j * 32, lane, pre[j]);
+    for (int j = 0; j < G::TN; j++) EPI::prefetch(p, n0 + wn * G::WTN + j * 32, lane, pre[j]);
+  }
 
   if constexpr (PINGPONG) {
     // ---- ping-pong main loop ---------------------------------------------------------------------------
@@ -609,6 +630,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     block_sync();
 #pragma unroll
     for (int ks = 0; ks < G::KSTEPS; ks++) read_frags(0, ks, fr[ks]);
+  } else if constexpr (BIAS_LDS) {
+    wait_vm<0>();
+    block_sync();
   }
   int buf = 0;
   int kt = 0;
@@ -712,6 +736,15 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     };
     if (XPF && efull) body(std::true_type{});
     else body(std::false_type{});
+  } else if constexpr (BIAS_LDS) {
+    const auto pre_of = [&](int j) {
+      asm volatile("" ::: "memory");  // read for each block anew: kept over the blocks they are registers again
+      typename EPI::Pre b;
+#pragma unroll
+      for (int q = 0; q < 4; q++) b.bias[q] = *(const v4i*)(smem + G::LDS_BYTES + (wn * G::WTN + j * 32 + 8 * q + 4 * (lane >> 5)) * 4);
+      return b;
+    };
+    EPI::template wave_blocks<false, G::TM, G::TN>(p, em0 + wm * G::WTM, en0 + wn * G::WTN, [&](int i, int j) -> const typename T::accv& { return acc[i][j]; }, lane, esplit, pre_of);
   } else if constexpr (has_wave_tile<EPI>::value) {
     EPI::wave_tile(p, em0 + wm * G::WTM, en0 + wn * G::WTN, acc, lane, esplit, pre);
   } else {
@@ -730,8 +763,9 @@ template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMOD
 static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
   auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, PINGPONG, TA, TB>;
-  static std::atomic<bool> configured{G::LDS_BYTES <= 64 * 1024};
-  if (const hipError_t e = allow_dynamic_lds_once(configured, kern, G::LDS_BYTES)) return e;
+  constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, AMODE, PINGPONG> ? BN * 4 : 0);
+  static std::atomic<bool> configured{LDS <= 64 * 1024};
+  if (const hipError_t e = allow_dynamic_lds_once(configured, kern, LDS)) return e;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int ntiles = tiles_m * tiles_n;
   // one persistent workgroup per LDS-limited slot of every compute unit
@@ -745,7 +779,7 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   // multiplier for the division by the band size of the tile order (0: too many tiles for it, divide)
   const unsigned band = 4u * (unsigned)tiles_n;
   const unsigned band_magic = (uint64_t)ntiles * band < (1ull << 32) ? FastDiv::make(band).magic : 0u;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), G::LDS_BYTES, stream, p, tiles_m, tiles_n, band_magic);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, p, tiles_m, tiles_n, band_magic);
   return hipGetLastError();
 }
 
