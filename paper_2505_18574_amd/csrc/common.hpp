@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 namespace ac {
 
@@ -31,9 +32,9 @@ static __device__ __forceinline__ float quad_broadcast(float v, int k) {
 
 // x / d by one multiply, exact while x * d < 2^32 (the host checks the ranges it is used on).
 struct FastDiv {
-  unsigned magic, d;
-  __host__ __device__ static FastDiv make(unsigned d) { return FastDiv{d > 1 ? (unsigned)(0x100000000ull / d) + 1u : 0u, d}; }
-  __device__ __forceinline__ unsigned div(unsigned x) const { return d == 1 ? x : __umulhi(x, magic); }
+  unsigned magic;  // 0: d == 1
+  __host__ __device__ static FastDiv make(unsigned d) { return FastDiv{d > 1 ? (unsigned)(0x100000000ull / d) + 1u : 0u}; }
+  __device__ __forceinline__ unsigned div(unsigned x) const { return magic == 0 ? x : __umulhi(x, magic); }
 };
 
 // Compute units of the device that was current at the first call (256 if the query fails).  A function-local
@@ -84,6 +85,78 @@ struct GemmParams {
   int32_t kt_per_split;  // K tiles (of the launched kernel's tile depth) per slice
   int32_t* partial;      // int8: [splits][M][N] int32 partial sums when splits > 1
 };
+
+// What the kernels of small launches receive.  Up to 112 bytes of kernel arguments a launch costs the host 2.8 us, beyond
+// 3.5 (measured from 60 to 512 bytes, in steps of 8 around the border): a fifth of a small call.  The same names as in
+// GemmParams; band_magic: multiplier of the kernel's tile order (0: divide).
+struct GemmArgs {
+  const void *A, *B;
+  void* C;
+  const int32_t* bias;
+  int32_t* partial;
+  int64_t lda, ldb, ldc, bias_ld;
+  int32_t M, N, K;
+  int32_t splits, kt_per_split;
+  union {
+    struct { int32_t shift, act; };  // int8
+    struct { float alpha, beta; };   // bf16
+  };
+  unsigned band_magic;
+};
+// A convolution is dense: the weights' and the output's pitch are its columns, its bias is a row.  The image's sizes with
+// their padding and the kernel's are below 2^16 (checked at the boundary).
+struct ConvArgs {
+  const void *A, *B;
+  void* C;
+  const int32_t* bias;
+  int32_t* partial;
+  union { int32_t N, ldb, ldc; };
+  static constexpr int64_t lda = 0, bias_ld = 0;
+  int32_t M, K;
+  int32_t splits, kt_per_split;
+  int32_t Cin, a_bytes, stride;
+  uint16_t H, W, OH, OW, KH, KW, pad;
+  uint8_t shift, act;
+  FastDiv dCin, dKW, dOW, dOH;
+  unsigned band_magic;
+};
+// Tiles that fill the registers take everything as it is: with ConvArgs the compiler spills 18 of them in the 256 x 128 kernel,
+// and its launches last too long for the difference in arguments to show.
+struct ConvArgsWide : GemmParams {
+  unsigned band_magic;
+};
+static_assert(sizeof(GemmArgs) <= 112 && sizeof(ConvArgs) <= 112, "beyond, a launch costs a fifth more");
+
+// The arguments of a kernel on operands of type T from the host's descriptor.
+template <class ARGS, class T>
+inline ARGS kernel_args(const GemmParams& p, unsigned band_magic = 0) {
+  ARGS a = {};
+  if constexpr (std::is_same_v<ARGS, ConvArgsWide>) {
+    (GemmParams&)a = p;
+  } else {
+    a.A = p.A, a.B = p.B, a.C = p.C, a.bias = p.bias, a.partial = p.partial;
+    a.M = p.M, a.N = p.N, a.K = p.K;
+    a.splits = p.splits, a.kt_per_split = p.kt_per_split;
+    if constexpr (std::is_same_v<ARGS, ConvArgs>) {
+      a.Cin = p.Cin, a.a_bytes = p.a_bytes, a.stride = p.stride;
+      a.H = (uint16_t)p.H, a.W = (uint16_t)p.W, a.OH = (uint16_t)p.OH, a.OW = (uint16_t)p.OW;
+      a.KH = (uint16_t)p.KH, a.KW = (uint16_t)p.KW, a.pad = (uint16_t)p.pad;
+      a.dCin = p.dCin, a.dKW = p.dKW, a.dOW = p.dOW, a.dOH = p.dOH;
+      a.shift = (uint8_t)p.shift, a.act = (uint8_t)p.act;
+    } else {
+      a.lda = p.lda, a.ldb = p.ldb, a.ldc = p.ldc, a.bias_ld = p.bias_ld;
+      if constexpr (T::EB == 1) a.shift = p.shift, a.act = p.act;
+      else a.alpha = p.alpha, a.beta = p.beta;
+    }
+  }
+  a.band_magic = band_magic;
+  return a;
+}
+// Multiplier of the division by the tiles of a band (tile_coords_mul): 0 where there are too many tiles for it.
+inline unsigned band_magic_of(int64_t tiles_m, int64_t tiles_n) {
+  const uint64_t band = 4 * (uint64_t)tiles_n;
+  return (uint64_t)tiles_m * (uint64_t)tiles_n * band < (1ull << 32) ? FastDiv::make((unsigned)band).magic : 0u;
+}
 
 struct BatchedParams {
   const float* A;

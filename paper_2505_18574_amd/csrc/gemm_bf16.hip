@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(256) scale_c_f32_kernel(float* C, int64_t ldc,
 
 // Output stage of a split-K launch through a workspace: C = alpha * (sum of the slices, in slice order) + beta * C.
 template <int THREADS>
-__global__ void __launch_bounds__(THREADS) splitk_reduce_f32_kernel(const GemmParams p) {
+__global__ void __launch_bounds__(THREADS) splitk_reduce_f32_kernel(const GemmArgs p) {
   const int64_t quads_per_row = p.N / 4;  // fast path: N is a multiple of 8
   const int64_t q = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   if (q >= (int64_t)p.M * quads_per_row) return;
@@ -89,8 +89,9 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
     if (e != hipSuccess) return e;
     // one-wave workgroups for small outputs, as for the int8 combine (64 x 64 x 65536 in 128 slices: 15.3 -> 13.5 us)
     const int64_t quads = (int64_t)p.M * (p.N / 4);
-    if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, p);
-    else hipLaunchKernelGGL(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, p);
+    const GemmArgs args = kernel_args<GemmArgs, TypeBF16>(p);
+    if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, args);
+    else hipLaunchKernelGGL(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, args);
     return hipGetLastError();
   }
   if (plan.splits > 1) {  // no workspace: slices add into C with fp32 atomics

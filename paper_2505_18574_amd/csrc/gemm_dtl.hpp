@@ -210,13 +210,16 @@ static __device__ __forceinline__ void tile_coords_mul(int b, int nblocks, int t
 template <class EPI, int BM, int AMODE, bool PINGPONG>
 constexpr bool has_bias_lds = BM >= 256 && !(PINGPONG && AMODE == 0) && std::is_same_v<EPI, EpilogueI8>;
 
+template <int BM, int AMODE>
+using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), ConvArgsWide, ConvArgs>, GemmArgs>;
+
 // TA / TB (int8 GEMM on square tiles): A is given as A^T (K x M, row pitch lda) / B as B^T (N x K, row pitch ldb).
 // A transposed operand takes the other operand's role in LDS: A^T is "K-strided" like B (k-rows of BM bytes, the
 // B swizzle, fragments through the transposing reads), B^T is "K-contiguous" like A (rows of KTB bytes, the A
 // swizzle, 16-byte fragment reads).  With BM == BN the tiles, the instruction counts and the lane roles of the two
 // forms coincide, so only the source offsets, the advance per K tile and the fragment addresses differ.
 template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_, bool PINGPONG, bool TA = false, bool TB = false>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const unsigned band_magic) {
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const dtl_args<BM, AMODE> p) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
   constexpr int EB = G::EB;
   static_assert(!(TA || TB) || (BM == BN && AMODE == 0 && EB == 1), "transposed operands: int8 GEMM on square tiles");
@@ -230,7 +233,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int kbytes = p.K * EB, nbytes = p.N * EB;
   const unsigned char* zero = (const unsigned char*)g_zero16;
-  const int ntiles = tiles_m * tiles_n;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
   const int nwork = ntiles * p.splits;
 
   // Cross-item prefetch (ping-pong GEMM only): a persistent workgroup requests the first STAGES-1 K tiles of its
@@ -295,7 +298,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     const int tile = w - split * ntiles;
     kt0 = split * p.kt_per_split;  // first K tile of this slice
     int tm, tn;
-    tile_coords_mul(tile, ntiles, tiles_m, tiles_n, band_magic, tm, tn);
+    tile_coords_mul(tile, ntiles, tiles_m, tiles_n, p.band_magic, tm, tn);
     m0 = tm * BM, n0 = tn * BN;
 #pragma unroll
     for (int i = 0; i < G::A_INSTR; i++) {
@@ -776,10 +779,8 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   const int64_t nwork = (int64_t)ntiles * (p.splits > 1 ? p.splits : 1);
   if (nwork > INT32_MAX) return hipErrorInvalidValue;  // the kernel counts (tile, K slice) items in 32 bits
   const int grid = nwork < slots ? (int)nwork : slots;
-  // multiplier for the division by the band size of the tile order (0: too many tiles for it, divide)
-  const unsigned band = 4u * (unsigned)tiles_n;
-  const unsigned band_magic = (uint64_t)ntiles * band < (1ull << 32) ? FastDiv::make(band).magic : 0u;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, p, tiles_m, tiles_n, band_magic);
+  const auto args = kernel_args<dtl_args<BM, AMODE>, T>(p, band_magic_of(tiles_m, tiles_n));
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, args);
   return hipGetLastError();
 }
 

@@ -277,7 +277,7 @@ void plan_few_tiles(int32_t M, int32_t N, int64_t kbytes, bool may_slice, const 
 // Output stage of a split-K launch: sum the K slices, then bias / shift / saturate / ReLU.  VEC outputs of a row per
 // thread: 4 where N is a multiple of 4 and C takes packed stores, otherwise 1.
 template <int THREADS, int VEC>
-__global__ void __launch_bounds__(THREADS) splitk_reduce_i8_kernel(const GemmParams p) {
+__global__ void __launch_bounds__(THREADS) splitk_reduce_i8_kernel(const GemmArgs p) {
   typedef std::conditional_t<VEC == 4, v4i, int> vec;
   const int64_t per_row = p.N / VEC;
   const int64_t q = (int64_t)blockIdx.x * THREADS + threadIdx.x;
@@ -310,8 +310,9 @@ __global__ void __launch_bounds__(THREADS) splitk_reduce_i8_kernel(const GemmPar
 template <int VEC>
 static hipError_t launch_splitk_reduce_i8(const GemmParams& p, hipStream_t stream) {
   const int64_t items = (int64_t)p.M * (p.N / VEC);
-  if (items <= 32768) hipLaunchKernelGGL((splitk_reduce_i8_kernel<64, VEC>), dim3((unsigned)((items + 63) / 64)), dim3(64), 0, stream, p);
-  else hipLaunchKernelGGL((splitk_reduce_i8_kernel<256, VEC>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, p);
+  const GemmArgs args = kernel_args<GemmArgs, TypeI8>(p);
+  if (items <= 32768) hipLaunchKernelGGL((splitk_reduce_i8_kernel<64, VEC>), dim3((unsigned)((items + 63) / 64)), dim3(64), 0, stream, args);
+  else hipLaunchKernelGGL((splitk_reduce_i8_kernel<256, VEC>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, args);
   return hipGetLastError();
 }
 

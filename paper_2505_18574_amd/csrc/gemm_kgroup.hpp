@@ -15,7 +15,8 @@ namespace ac {
 
 // Output stages of four columns n .. n + 3 of row m, or of those of them that exist.  `bias` is what prefetch() returned.
 struct KGroupBias {
-  static __device__ __forceinline__ v4i prefetch(const GemmParams& p, int m, int n) {
+  template <class P>
+  static __device__ __forceinline__ v4i prefetch(const P& p, int m, int n) {
     v4i b = {0, 0, 0, 0};
     if (p.bias != nullptr) {
       const int32_t* row = p.bias + (int64_t)m * p.bias_ld + n;  // bias_ld 0: one row for all
@@ -31,7 +32,8 @@ struct KGroupBias {
 };
 struct KGroupI8 : KGroupBias {
   typedef int val;
-  static __device__ __forceinline__ void store(const GemmParams& p, int m, int n, v4i s, v4i bias) {
+  template <class P>
+  static __device__ __forceinline__ void store(const P& p, int m, int n, v4i s, v4i bias) {
     s += bias;
     int q[4];
     if (p.shift >= 1 && p.shift <= 23) {
@@ -55,7 +57,8 @@ struct KGroupI8 : KGroupBias {
 };
 struct KGroupRawI32 : KGroupBias {
   typedef int val;
-  static __device__ __forceinline__ void store(const GemmParams& p, int m, int n, v4i s, v4i bias) {
+  template <class P>
+  static __device__ __forceinline__ void store(const P& p, int m, int n, v4i s, v4i bias) {
     s += bias;
     int32_t* dst = (int32_t*)p.C + (int64_t)m * p.ldc + n;
     if (n + 3 < p.N) {
@@ -69,8 +72,10 @@ struct KGroupRawI32 : KGroupBias {
 };
 struct KGroupF32 {
   typedef float val;
-  static __device__ __forceinline__ v4i prefetch(const GemmParams&, int, int) { return (v4i){0, 0, 0, 0}; }
-  static __device__ __forceinline__ void store(const GemmParams& p, int m, int n, v4f s, v4i) {
+  template <class P>
+  static __device__ __forceinline__ v4i prefetch(const P&, int, int) { return (v4i){0, 0, 0, 0}; }
+  template <class P>
+  static __device__ __forceinline__ void store(const P& p, int m, int n, v4f s, v4i) {
     struct __attribute__((packed)) U16 { v4f v; };
     float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
     if (n + 3 < p.N) {
@@ -88,8 +93,8 @@ struct KGroupF32 {
 // The waves' sums of a 32 x 32 tile (swapped operand order: a lane holds runs of four columns of its row) meet in LDS, one
 // region of 4 KB per wave, PITCH bytes apart: columns 4 c .. 4 c + 3 of row r in slot r ^ c of group c, so that the eight
 // threads of a row read different banks.  Threads 0 .. 255 sum them and own row t / 8, columns 4 (t % 8) + 0 .. 3.
-template <class OUT, int W, int PITCH, class ACC>
-static __device__ __forceinline__ void kgroup_finish(const GemmParams& p, unsigned char* smem, int wave, int t, const ACC& acc, int om, int on, bool out, v4i bias) {
+template <class OUT, int W, int PITCH, class ACC, class P>
+static __device__ __forceinline__ void kgroup_finish(const P& p, unsigned char* smem, int wave, int t, const ACC& acc, int om, int on, bool out, v4i bias) {
   typedef typename OUT::val val;
   typedef val v4 __attribute__((ext_vector_type(4)));
   const int lane = t & 63;
@@ -110,7 +115,7 @@ static __device__ __forceinline__ void kgroup_finish(const GemmParams& p, unsign
 
 // KTB: bytes of K per tile, S: stages of a wave's ring, W: waves of a workgroup; AMODE, TA, TB as for gemm_dtl_kernel.
 template <class T, class OUT, int KTB, int S, int W, int AMODE, bool TA, bool TB>
-__global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const unsigned band_magic) {
+__global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const std::conditional_t<AMODE == 1, ConvArgs, GemmArgs> p) {
   using G = DtlGeometry<T, 32, 32, 1, 1, S, KTB>;
   constexpr int EB = T::EB, NA = G::A_INSTR, NB = G::B_INSTR, KS = G::KSTEPS, PER_TILE = NA + NB;
   static_assert(G::STAGE == 64 * KTB && S >= 3 && S * G::STAGE >= 4096 && W >= 4, "geometry");
@@ -122,8 +127,9 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const GemmParams p,
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   unsigned char* win = smem + wave * (S * G::STAGE);
   const unsigned lds0 = (unsigned)(uintptr_t)AC_LDS(unsigned char, win);
+  const int tiles_m = (p.M + 31) / 32, tiles_n = (p.N + 31) / 32;
   int tm, tn;
-  tile_coords_mul(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, band_magic, tm, tn);
+  tile_coords_mul(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, p.band_magic, tm, tn);
   const int m0 = tm * 32, n0 = tn * 32;
   const int kbytes = p.K * EB;
   const unsigned char* zero = (const unsigned char*)g_zero16;
@@ -292,13 +298,11 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const GemmParams p,
 
 static inline int64_t kgroup_tiles(const GemmParams& p) { return (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32); }
 
-template <class KERN>
+template <class ARGS, class T, class KERN>
 static hipError_t launch_kgroup_grid(std::atomic<bool>& configured, KERN kern, int waves, int lds, const GemmParams& p, hipStream_t stream) {
   if (const hipError_t e = allow_dynamic_lds_once(configured, kern, lds)) return e;
-  const int tiles_m = (p.M + 31) / 32, tiles_n = (p.N + 31) / 32, ntiles = tiles_m * tiles_n;  // a few hundred at most
-  const unsigned band = 4u * (unsigned)tiles_n;
-  const unsigned band_magic = (uint64_t)ntiles * band < (1ull << 32) ? FastDiv::make(band).magic : 0u;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(64 * waves), lds, stream, p, tiles_m, tiles_n, band_magic);
+  const ARGS args = kernel_args<ARGS, T>(p, band_magic_of((p.M + 31) / 32, (p.N + 31) / 32));
+  hipLaunchKernelGGL(kern, dim3((unsigned)kgroup_tiles(p)), dim3(64 * waves), lds, stream, args);  // a few hundred tiles at most
   return hipGetLastError();
 }
 
@@ -307,7 +311,7 @@ static hipError_t launch_kgroup_cfg(const GemmParams& p, hipStream_t stream) {
   constexpr int S = 3, LDS = W * S * 64 * KTB;  // (rings of four and five stages: level)
   static_assert(LDS <= 160 * 1024, "LDS budget");
   static std::atomic<bool> configured{LDS <= 64 * 1024};
-  return launch_kgroup_grid(configured, gemm_kgroup_kernel<T, OUT, KTB, S, W, AMODE, TA, TB>, W, LDS, p, stream);
+  return launch_kgroup_grid<std::conditional_t<AMODE == 1, ConvArgs, GemmArgs>, T>(configured, gemm_kgroup_kernel<T, OUT, KTB, S, W, AMODE, TA, TB>, W, LDS, p, stream);
 }
 
 // Direct-to-LDS operands (checked by the caller).  Eight waves, a tile to a compute unit, where K keeps them busy; four
@@ -349,7 +353,7 @@ static bool kgroup_takes(const GemmParams& p, bool conv, bool sliced) {
 // Any size, pitch and alignment (at least 16 bytes to a row of a K-strided operand): 16-byte chunks through registers, two
 // tiles ahead, into one padded LDS buffer per wave.  AKC, BKC, CONV as for gemm_ragged_kernel.
 template <class T, class OUT, int W, bool AKC, bool BKC, bool CONV>
-__global__ void __launch_bounds__(64 * W) gemm_kgroup_ragged_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const unsigned band_magic) {
+__global__ void __launch_bounds__(64 * W) gemm_kgroup_ragged_kernel(const std::conditional_t<CONV, ConvArgs, GemmArgs> p) {
   using SA = std::conditional_t<CONV, RaggedImage<32, 64>, RaggedMatrix<T, 32, 64, AKC>>;
   using SB = std::conditional_t<CONV, RaggedWeights<32, 64>, RaggedMatrix<T, 32, 64, BKC>>;
   using TA = typename SA::Tile;
@@ -359,10 +363,11 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_ragged_kernel(const GemmPa
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int tiles_m = (p.M + 31) / 32, tiles_n = (p.N + 31) / 32;
   int tm, tn;
-  tile_coords_mul(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, band_magic, tm, tn);
+  tile_coords_mul(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, p.band_magic, tm, tn);
   const int m0 = tm * 32, n0 = tn * 32;
-  const int kbytes = CONV ? p.KH * conv_run_padded(p) : p.K * T::EB;
+  const int kbytes = walk_bytes<CONV, T::EB>(p);
   const int nkt_total = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB, nkt_whole = CONV ? nkt_total : kbytes / RAGGED_KTB;
 
   const int om = m0 + (t >> 3), on = n0 + 4 * (t & 7);
@@ -467,7 +472,7 @@ static hipError_t launch_kgroup_ragged_cfg(const GemmParams& p, hipStream_t stre
   constexpr int LDS = W * (RaggedTile<T, 32, 64, AKC>::BYTES + RaggedTile<T, 32, 64, BKC>::BYTES);
   static_assert(LDS <= 160 * 1024, "LDS budget");
   static std::atomic<bool> configured{LDS <= 64 * 1024};
-  return launch_kgroup_grid(configured, gemm_kgroup_ragged_kernel<T, OUT, W, AKC, BKC, CONV>, W, LDS, p, stream);
+  return launch_kgroup_grid<std::conditional_t<CONV, ConvArgs, GemmArgs>, T>(configured, gemm_kgroup_ragged_kernel<T, OUT, W, AKC, BKC, CONV>, W, LDS, p, stream);
 }
 template <class T, class OUT, bool AKC, bool BKC, bool CONV = false>
 static hipError_t launch_kgroup_ragged(const GemmParams& p, hipStream_t stream) {

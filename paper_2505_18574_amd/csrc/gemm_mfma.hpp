@@ -119,8 +119,8 @@ struct EpilogueI8 {
     return q;
   }
   // Columns n .. n + 3 of row m, for a C whose rows are dword-aligned.
-  template <bool ADD_BIAS = true>
-  static __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const int* a) {
+  template <bool ADD_BIAS = true, class P>
+  static __device__ __forceinline__ void store4(const P& p, int m, int n, const int* a) {
     if (m >= p.M || n >= p.N) return;
     int8_t* C = (int8_t*)p.C;
     int v[4];
@@ -150,7 +150,8 @@ struct EpilogueI8 {
   };
   // The bias row is read through a bounds-checked buffer of N int32 (no row bias: zero records), so the four
   // loads carry no branches: columns beyond N, and every column when there is no row bias, come back as zeros.
-  static __device__ __forceinline__ void prefetch(const GemmParams& p, int ncol0, int lane, Pre& pre) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P& p, int ncol0, int lane, Pre& pre) {
     const bool row_bias = p.bias != nullptr && p.bias_ld == 0;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)p.bias, 0, row_bias && p.N < (1 << 29) ? p.N * 4 : 0, 0x00020000);
     const int off = (ncol0 + 4 * (lane >> 5)) * 4;
@@ -241,8 +242,8 @@ struct EpilogueI8 {
   // tile ran through some 90 KB of code).  BIASED as in tile().
   static constexpr bool WAVE_TILE = true;
   // acc_of(i, j) and pre_of(j) give block (i, j)'s accumulators and column block j's prefetched bias.
-  template <bool BIASED, int TM, int TN, class ACC_OF, class PRE_OF>
-  static __device__ __forceinline__ void wave_blocks(const GemmParams& p, int mrow0, int ncol0, ACC_OF acc_of, int lane, int esplit, PRE_OF pre_of) {
+  template <bool BIASED, int TM, int TN, class ACC_OF, class PRE_OF, class P>
+  static __device__ __forceinline__ void wave_blocks(const P& p, int mrow0, int ncol0, ACC_OF acc_of, int lane, int esplit, PRE_OF pre_of) {
     int8_t* C = (int8_t*)p.C;
     const bool fast = ncol0 + 32 * TN <= p.N && (p.ldc & 15) == 0 && (((uintptr_t)C) & 15) == 0 && (p.bias == nullptr || p.bias_ld == 0) && p.shift >= 1 && p.shift <= 23;
     if (fast) {  // wave-uniform
@@ -271,18 +272,18 @@ struct EpilogueI8 {
         for (int j = 0; j < TN; j++) tile<BIASED>(p, mrow0 + 32 * i, ncol0 + 32 * j, acc_of(i, j), lane, esplit, pre_of(j));
     }
   }
-  template <bool BIASED = false, int TM, int TN, class ACC>
-  static __device__ __forceinline__ void wave_tile(const GemmParams& p, int mrow0, int ncol0, const ACC (&acc)[TM][TN], int lane, int esplit, const Pre (&pre)[TN]) {
+  template <bool BIASED = false, int TM, int TN, class ACC, class P>
+  static __device__ __forceinline__ void wave_tile(const P& p, int mrow0, int ncol0, const ACC (&acc)[TM][TN], int lane, int esplit, const Pre (&pre)[TN]) {
     wave_blocks<BIASED, TM, TN>(p, mrow0, ncol0, [&](int i, int j) -> const ACC& { return acc[i][j]; }, lane, esplit, [&](int j) -> const Pre& { return pre[j]; });
   }
   // A column of TM blocks with one bias block.
-  template <bool BIASED = false, int TM, class ACC>
-  static __device__ __forceinline__ void wave_column(const GemmParams& p, int mrow0, int ncol0, const ACC (&acc)[TM], int lane, const Pre& pre) {
+  template <bool BIASED = false, int TM, class ACC, class P>
+  static __device__ __forceinline__ void wave_column(const P& p, int mrow0, int ncol0, const ACC (&acc)[TM], int lane, const Pre& pre) {
     wave_blocks<BIASED, TM, 1>(p, mrow0, ncol0, [&](int i, int) -> const ACC& { return acc[i]; }, lane, 0, [&](int) -> const Pre& { return pre; });
   }
   // BIASED: the accumulators already hold the bias (a kernel that starts its sums from the bias row).
-  template <bool BIASED = false, class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre& pre) {
+  template <bool BIASED = false, class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre& pre) {
     const int m = mrow0 + (lane & 31);
     if (m >= p.M || ncol0 >= p.N) return;
     int8_t* C = (int8_t*)p.C;
@@ -343,12 +344,13 @@ static __device__ __forceinline__ void store_run16(int8_t* dst, v4i o, int valid
 struct EpilogueI8Any {
   static constexpr bool SWAP = true;
   struct Pre {};
-  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, int v) {
+  template <class P>
+  static __device__ __forceinline__ void one(const P& p, int m, int n, int v) {
     if (p.bias) v += p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
     ((int8_t*)p.C)[(int64_t)m * p.ldc + n] = (int8_t)EpilogueI8::requant(v, p.shift, p.act);
   }
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     if (ncol0 >= p.N) return;
     const int m = mrow0 + (lane & 31), half = lane >> 5;
     int v[16];
@@ -382,14 +384,17 @@ struct EpiloguePartialI32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // the workspace is 16-byte aligned and N a multiple of 16 on this path
   typedef int StagedValue;
-  static __device__ __forceinline__ int staged_in(const GemmParams&, int a) { return a; }
-  static __device__ __forceinline__ void staged_out(const GemmParams& p, int m, int n, v4i o, int split) {
+  template <class P>
+  static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
+  template <class P>
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int split) {
     *(v4i*)(p.partial + ((int64_t)split * p.M + m) * p.N + n) = o;
   }
   struct Pre {};
-  static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int split, const Pre&) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int split, const Pre&) {
     store_unswapped(p.partial + (int64_t)split * p.M * p.N, p.N, p.M, p.N, mrow0, ncol0, lane, [&](int r) { return acc[r]; });
   }
 };
@@ -400,8 +405,10 @@ struct EpilogueRawI32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // C is 16-byte aligned with ldc a multiple of 4 on this path
   typedef int StagedValue;
-  static __device__ __forceinline__ int staged_in(const GemmParams&, int a) { return a; }
-  static __device__ __forceinline__ void staged_out(const GemmParams& p, int m, int n, v4i o, int) {
+  template <class P>
+  static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
+  template <class P>
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int) {
     if (p.bias) {
       const int32_t* b = p.bias_ld == 0 ? p.bias + n : p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
       o += (v4i){b[0], b[1], b[2], b[3]};
@@ -409,13 +416,15 @@ struct EpilogueRawI32 {
     *(v4i*)((int32_t*)p.C + (int64_t)m * p.ldc + n) = o;
   }
   struct Pre {};
-  static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
-  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, int v) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
+  template <class P>
+  static __device__ __forceinline__ void one(const P& p, int m, int n, int v) {
     if (p.bias) v += p.bias_ld == 0 ? p.bias[n] : p.bias[(int64_t)m * p.bias_ld + n];
     ((int32_t*)p.C)[(int64_t)m * p.ldc + n] = v;
   }
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     if (p.bias != nullptr && p.bias_ld != 0) {
       for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
         if (m < p.M && n < p.N) one(p, m, n, acc[r]);
@@ -435,22 +444,26 @@ struct EpilogueF32 {
   // accumulator on its way into LDS, staged_out() receives four consecutive columns of one row.
   static constexpr bool LDS_STAGED = true;
   typedef float StagedValue;
-  static __device__ __forceinline__ float staged_in(const GemmParams& p, float a) { return p.alpha * a; }
-  static __device__ __forceinline__ void staged_out(const GemmParams& p, int m, int n, v4f o, int) {
+  template <class P>
+  static __device__ __forceinline__ float staged_in(const P& p, float a) { return p.alpha * a; }
+  template <class P>
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int) {
     float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
     if (p.beta != 0.f) o += p.beta * *(const v4f*)dst;
     *(v4f*)dst = o;
   }
   struct Pre {};
-  static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
-  static __device__ __forceinline__ void one(const GemmParams& p, int m, int n, float v) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
+  template <class P>
+  static __device__ __forceinline__ void one(const P& p, int m, int n, float v) {
     float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
     float o = p.alpha * v;
     if (p.beta != 0.f) o += p.beta * *dst;
     *dst = o;
   }
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     if (p.beta == 0.f) {
       store_unswapped((float*)p.C, p.ldc, p.M, p.N, mrow0, ncol0, lane, [&](int r) { return p.alpha * acc[r]; });
       return;
@@ -468,9 +481,10 @@ struct EpilogueAtomicF32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = false;
   struct Pre {};
-  static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int, const Pre&) {
     for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
       if (m < p.M && n < p.N) unsafeAtomicAdd((float*)p.C + (int64_t)m * p.ldc + n, p.alpha * acc[r]);
     });
@@ -484,14 +498,17 @@ struct EpiloguePartialF32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // the workspace is 16-byte aligned and N a multiple of 8 on this path
   typedef float StagedValue;
-  static __device__ __forceinline__ float staged_in(const GemmParams&, float a) { return a; }
-  static __device__ __forceinline__ void staged_out(const GemmParams& p, int m, int n, v4f o, int split) {
+  template <class P>
+  static __device__ __forceinline__ float staged_in(const P&, float a) { return a; }
+  template <class P>
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int split) {
     *(v4f*)((float*)p.partial + ((int64_t)split * p.M + m) * p.N + n) = o;
   }
   struct Pre {};
-  static __device__ __forceinline__ void prefetch(const GemmParams&, int, int, Pre&) {}
-  template <class ACC>
-  static __device__ __forceinline__ void tile(const GemmParams& p, int mrow0, int ncol0, const ACC& acc, int lane, int split, const Pre&) {
+  template <class P>
+  static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
+  template <class ACC, class P>
+  static __device__ __forceinline__ void tile(const P& p, int mrow0, int ncol0, const ACC& acc, int lane, int split, const Pre&) {
     for_each_unswapped(mrow0, ncol0, lane, [&](int r, int m, int n) {
       if (m < p.M && n < p.N) ((float*)p.partial)[((int64_t)split * p.M + m) * p.N + n] = acc[r];
     });

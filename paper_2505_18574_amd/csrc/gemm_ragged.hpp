@@ -177,8 +177,16 @@ struct RaggedMatrix {
 };
 
 // K of a convolution as the kernel walks it: KH runs of KW * Cin bytes, each padded to whole chunks.
-static __host__ __device__ __forceinline__ int conv_run(const GemmParams& p) { return p.KW * p.Cin; }
-static __host__ __device__ __forceinline__ int conv_run_padded(const GemmParams& p) { return p.Cin > 0 ? (p.KW * p.Cin + 15) & ~15 : 16; }
+template <class P>
+static __host__ __device__ __forceinline__ int conv_run(const P& p) { return p.KW * p.Cin; }
+template <class P>
+static __host__ __device__ __forceinline__ int conv_run_padded(const P& p) { return p.Cin > 0 ? (p.KW * p.Cin + 15) & ~15 : 16; }
+// bytes of K as the kernels below walk it
+template <bool CONV, int EB, class P>
+static __device__ __forceinline__ int walk_bytes(const P& p) {
+  if constexpr (CONV) return p.KH * conv_run_padded(p);
+  else return p.K * EB;
+}
 
 // Position (kh, r) of a K index inside that walk, advanced by `tiles` K tiles at a time without a division.
 struct ConvWalk {
@@ -212,7 +220,7 @@ struct RaggedImage {
     const int64_t lim = 1 << 30;
     return (int)(d > lim ? lim : (d < -lim ? -lim : d));
   }
-  __device__ __forceinline__ void init(const GemmParams& p, int m0, int kt0, int t, int tiles = 1) {
+  __device__ __forceinline__ void init(const ConvArgs& p, int m0, int kt0, int t, int tiles = 1) {
     in = (const unsigned char*)p.A;
     pitch = p.W * p.Cin, H = p.H, total = p.a_bytes, KH = p.KH;
     const int cc = t % Tile::CPR, r0 = t / Tile::CPR;
@@ -258,7 +266,7 @@ struct RaggedWeights {
   int64_t ld;
   int run, KH, col;
 
-  __device__ __forceinline__ void init(const GemmParams& p, int n0, int kt0, int t, int tiles = 1) {
+  __device__ __forceinline__ void init(const ConvArgs& p, int n0, int kt0, int t, int tiles = 1) {
     m.init(p.B, p.ldb, n0, p.N, p.K, 0, t);
     ld = p.ldb, run = conv_run(p), KH = p.KH;
     col = (int)(m.ptr[0] - m.base - (int64_t)(t / Tile::CPR) * ld);  // this thread's column after clamping and shifting
@@ -279,7 +287,7 @@ struct RaggedWeights {
 // AKC / BKC: A (B) is K-contiguous in memory: plain A and B^T are, plain B and A^T are not.  CONV: A is the NHWC input
 // and B the weights of a convolution.  R: K tiles in flight in registers.
 template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, bool AKC, bool BKC, bool CONV, int R>
-__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(const GemmParams p, const int tiles_m, const int tiles_n, const unsigned band_magic) {
+__global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(const std::conditional_t<CONV, ConvArgs, GemmArgs> p) {
   constexpr int THREADS = 64 * WAVES_M * WAVES_N;
   constexpr int EB = T::EB;
   using SA = std::conditional_t<CONV, RaggedImage<BM, THREADS>, RaggedMatrix<T, BM, THREADS, AKC>>;
@@ -291,8 +299,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int ntiles = tiles_m * tiles_n;
-  const int kbytes = CONV ? p.KH * conv_run_padded(p) : p.K * EB;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
+  const int kbytes = walk_bytes<CONV, EB>(p);
   const int nkt_total = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
   // tiles before this one lie inside K and (K-strided operands) have rows of 16 bytes and more: unconditional loads
   const bool long_rows = (AKC || (int64_t)p.M * EB >= 16) && (BKC || (int64_t)p.N * EB >= 16);
@@ -302,7 +310,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   for (unsigned item = blockIdx.x; item < items; item += gridDim.x) {
     const int split = p.splits > 1 ? (int)(item / (unsigned)ntiles) : 0;
     int tm, tn;
-    tile_coords_mul((int)item - split * ntiles, ntiles, tiles_m, tiles_n, band_magic, tm, tn);
+    tile_coords_mul((int)item - split * ntiles, ntiles, tiles_m, tiles_n, p.band_magic, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int kt0 = p.splits > 1 ? split * p.kt_per_split : 0;
     const int nkt = p.splits > 1 && nkt_total - kt0 > p.kt_per_split ? p.kt_per_split : nkt_total - kt0;
@@ -502,9 +510,8 @@ static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   const int64_t items = (int64_t)tiles_m * tiles_n * p.splits;
   const unsigned grid = (unsigned)(items < (1 << 20) ? items : (1 << 20));  // beyond that the workgroups walk over the items
-  const uint64_t band = 4 * (uint64_t)tiles_n;  // tiles of a band (tile_coords_mul)
-  const unsigned band_magic = (uint64_t)tiles_m * tiles_n * band < (1ull << 32) ? FastDiv::make((unsigned)band).magic : 0u;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, p, tiles_m, tiles_n, band_magic);
+  const auto args = kernel_args<std::conditional_t<CONV, ConvArgs, GemmArgs>, T>(p, band_magic_of(tiles_m, tiles_n));
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, args);
   return hipGetLastError();
 }
 
@@ -515,7 +522,7 @@ static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
 // may be null, no loop below touches them, and the tiled kernel would request its first tiles before it counts them.  (A
 // product with K = 0 requests nothing there.)
 template <class T, class EPI, bool AKC, bool BKC, bool CONV>
-__global__ void __launch_bounds__(256) gemm_tiny_kernel(const GemmParams p) {
+__global__ void __launch_bounds__(256) gemm_tiny_kernel(const std::conditional_t<CONV, ConvArgs, GemmArgs> p) {
   typedef std::conditional_t<T::EB == 1, int, float> val;
   typedef std::conditional_t<T::EB == 1, int8_t, __bf16> elem;
   const elem *A = (const elem*)p.A, *B = (const elem*)p.B;
@@ -555,7 +562,8 @@ static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t strea
   if constexpr (!std::is_same_v<EPI, EpiloguePartialI32>) {  // (K slices: K is deep)
     if (ragged_tiny<T, AKC, BKC, CONV>(p)) {
       const int64_t blocks = ((int64_t)p.M * p.N + 255) / 256;
-      hipLaunchKernelGGL((gemm_tiny_kernel<T, EPI, AKC, BKC, CONV>), dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((gemm_tiny_kernel<T, EPI, AKC, BKC, CONV>), dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, stream,
+                         (kernel_args<std::conditional_t<CONV, ConvArgs, GemmArgs>, T>(p)));
       return hipGetLastError();
     }
   }

@@ -28,7 +28,7 @@ constexpr int SMALL_KTB = 64;  // K bytes per stage at least; 128 where K is a m
 // covers K tiles s * kt_per_split ... and leaves its int32 sums in p.partial[s][M][N] for splitk_reduce_i8_kernel
 // (with few tiles and a deep K, slices are what puts enough loads in flight; ntiles then counts tiles, not items).
 template <int KTB, int S, int SMALL_WAVES, int AMODE, bool SPLIT>
-__global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const GemmParams p, const int tiles_n, const int ntiles, const unsigned tn_magic) {
+__global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const std::conditional_t<AMODE == 1, ConvArgs, GemmArgs> p) {
   using T = TypeI8;
   using EPI = EpilogueI8;
   using G = DtlGeometry<T, 32, 32, 1, 1, S, KTB>;
@@ -39,12 +39,13 @@ __global__ void __launch_bounds__(64 * SMALL_WAVES) gemm_i8_small_kernel(const G
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_n = (p.N + 31) / 32, ntiles = (p.M + 31) / 32 * tiles_n;
   const int item = blockIdx.x * SMALL_WAVES + wave;
   if (item >= (SPLIT ? ntiles * p.splits : ntiles)) return;  // whole waves leave; no wave of this kernel ever waits for another
   const int split = SPLIT ? item / ntiles : 0;
   const int tile = item - split * ntiles;
   const int kt0 = split * p.kt_per_split;  // first K tile of this slice
-  const int tm = tn_magic ? (int)__umulhi((unsigned)tile, tn_magic) : tile / tiles_n;
+  const int tm = p.band_magic ? (int)__umulhi((unsigned)tile, p.band_magic) : tile / tiles_n;  // (here the multiplier divides by the tiles of a row)
   const int tn = tile - tm * tiles_n;
   const int m0 = tm * 32, n0 = tn * 32;
   unsigned char* win = smem + wave * (S * G::STAGE);
@@ -211,8 +212,8 @@ static hipError_t launch_small_i8_cfg(const GemmParams& p, hipStream_t stream) {
   const int ntiles = tiles_m * tiles_n;
   const unsigned tn_magic = (uint64_t)ntiles * (unsigned)tiles_n < (1ull << 32) ? FastDiv::make((unsigned)tiles_n).magic : 0u;
   const int64_t items = (int64_t)ntiles * (SPLIT ? p.splits : 1);
-  hipLaunchKernelGGL((gemm_i8_small_kernel<KTB, S, SMALL_WAVES, AMODE, SPLIT>), dim3((unsigned)((items + SMALL_WAVES - 1) / SMALL_WAVES)), dim3(64 * SMALL_WAVES), LDS, stream, p,
-                     tiles_n, ntiles, tn_magic);
+  hipLaunchKernelGGL((gemm_i8_small_kernel<KTB, S, SMALL_WAVES, AMODE, SPLIT>), dim3((unsigned)((items + SMALL_WAVES - 1) / SMALL_WAVES)), dim3(64 * SMALL_WAVES), LDS, stream,
+                     (kernel_args<std::conditional_t<AMODE == 1, ConvArgs, GemmArgs>, TypeI8>(p, tn_magic)));
   return hipGetLastError();
 }
 
