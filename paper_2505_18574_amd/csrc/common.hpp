@@ -257,6 +257,17 @@ constexpr size_t STATIC_SCRATCH_BYTES = 16u << 20;
 hipError_t static_scratch(void** ptr);
 hipError_t launch_batched_f32(const BatchedParams& p, hipStream_t stream);
 bool gemm_i8_fast_path(const GemmParams& p);
+// Operands whose addresses, pitches and contiguous extents (at least 16 bytes) are multiples of 4 bytes, for the
+// direct-to-LDS kernels' DW form; `c_align`: what the output's rows must be aligned to.  Beside the any-alignment kernels,
+// which move such operands through registers (us there / here): up to 256 tiles of 32 x 32 4.0-4.4 / 3.1-3.4 for K up to some
+// 300, 60 x 608 x 1176 with A^T 5.0 / 3.8, bf16 184 x 84 x 572 4.7 / 3.7; beyond them 604 x 1276 x 1384 9.2 / 8.2, 1000^3
+// 7.3 / 6.7, 520 x 4224 x 320 with A^T and B^T 7.1 / 6.2, bf16 1000 x 436 x 596 6.9 / 5.9, 4792 x 384 x 64 with both 4.7 / 4.8.
+inline bool dword_operands(const GemmParams& p, int eb, bool trans_a, bool trans_b, int c_align, int c_bytes) {
+  const int64_t a_ext = (int64_t)(trans_a ? p.M : p.K) * eb, b_ext = (int64_t)(trans_b ? p.K : p.N) * eb;
+  return (((uintptr_t)p.A | (uintptr_t)p.B) & 3) == 0 && p.lda * eb % 4 == 0 && p.ldb * eb % 4 == 0 && a_ext % 4 == 0 && b_ext % 4 == 0 &&
+         a_ext >= 16 && b_ext >= 16 && p.K * (int64_t)eb >= 16 && p.N % 4 == 0 && ((uintptr_t)p.C & (c_align - 1)) == 0 && p.ldc * c_bytes % c_align == 0 &&
+         lane_offsets_fit((p.lda > p.ldb ? p.lda : p.ldb) * eb, p.ldb * eb);
+}
 bool conv_i8_fast_path(const GemmParams& p);
 bool gemm_bf16_fast_path(const GemmParams& p);
 

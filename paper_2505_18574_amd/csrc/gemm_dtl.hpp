@@ -182,6 +182,41 @@ struct DtlGeometry {
   static __device__ __forceinline__ int a_xor(int row) { return (row / A_RPW) & (A_SPR - 1); }
 };
 
+// Offsets of the dwords of a last K tile from the tile's origin, for a buffer of DW_REACH bytes (lane_offsets_fit keeps the
+// others below that): slot q of the rows from row0 on, byte dw of it; beyond the operand the offset nothing is read at.
+constexpr unsigned DW_REACH = 0xfffffff0u, DW_NOTHING = 0xffffffffu;
+template <int KTB>  // rows of KTB bytes of K, `rows` and `bytes` of them left
+static __device__ __forceinline__ unsigned dword_contiguous(int row0, int q, int dw, int rows, int bytes, int64_t pitch) {
+  constexpr int SPR = KTB / 16, RPW = 256 / KTB;
+  const int row = row0 + q / SPR, kb = ((q % SPR) ^ ((row / RPW) & (SPR - 1))) * 16 + dw;
+  return (row < rows) & (kb < bytes) ? (unsigned)row * (unsigned)pitch + (unsigned)kb : DW_NOTHING;
+}
+template <int EB, int ROW>  // k-rows of ROW bytes, `rows` and `bytes` of them left
+static __device__ __forceinline__ unsigned dword_strided(int row0, int q, int dw, int rows, int bytes, int64_t pitch) {
+  constexpr int SPR = ROW / 16;
+  const int row = row0 + q / SPR, col = BSwizzle<EB, ROW>::slot(q % SPR, row) * 16 + dw;
+  return (row < rows) & (col < bytes) ? (unsigned)row * (unsigned)pitch + (unsigned)col : DW_NOTHING;
+}
+
+// One wave instruction (1 KB of LDS) of a last K tile: 16 bytes per lane at voff, but dword by dword (offset_of(slot, byte)) for
+// the one that holds the operand's very last row, `last`, where that ends inside a chunk: no byte behind it is read.
+template <class F>
+static __device__ __forceinline__ void dw_load(v4i tile, int last, int row0, int rows, int row_bytes, unsigned voff, unsigned lds, int lane, F offset_of) {
+  if (row_bytes % 16 != 0 && last >= row0 && last < row0 + rows) {  // wave-uniform
+    // a quarter of the instruction's slots at a time: lane l has dword l % 4 of slot 16 s + l / 4
+#pragma unroll
+    for (int sub = 0; sub < 4; sub++) buffer_to_lds4(tile, offset_of(sub * 16 + (lane >> 2), (lane & 3) * 4), lds + sub * 256);
+  } else {
+    buffer_to_lds16(tile, voff, lds);
+  }
+}
+// The lane's 16 K-bytes of a fragment, of which `valid` lie inside K; the others are another row's.
+static __device__ __forceinline__ v4i dw_mask(v4i f, int valid) {
+#pragma unroll
+  for (int d = 0; d < 4; d++) f[d] = 4 * d < valid ? f[d] : 0;
+  return f;
+}
+
 // XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2), so workgroup b runs on
 // XCD b % 8.  Every XCD gets one contiguous run of logical tile ids, and those ids lie in bands of four tile rows, so that
 // a run is a compact rectangle sharing A rows and B columns.  No integer divisions: the band size is divided by with a
@@ -218,7 +253,14 @@ using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), 
 // B swizzle, fragments through the transposing reads), B^T is "K-contiguous" like A (rows of KTB bytes, the A
 // swizzle, 16-byte fragment reads).  With BM == BN the tiles, the instruction counts and the lane roles of the two
 // forms coincide, so only the source offsets, the advance per K tile and the fragment addresses differ.
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_, bool PINGPONG, bool TA = false, bool TB = false>
+//
+// DW (products): bases, pitches and the contiguous extents are multiples of 4 bytes, not of 16.  A 16-byte load takes any
+// dword address, so whole tiles load as before, and a chunk that crosses the end of a row holds the first bytes of the next
+// behind it: columns that are never stored or, of a K-contiguous operand, products with k-rows of zeros.  The last K tile reads
+// zeros beyond the operands, and its one chunk that could leave a buffer dword by dword; where no zeros face the bytes
+// behind K (both operands K-contiguous) or they could be infinite (bf16), A's fragments of that tile are masked.  A contiguous
+// extent is at least 16 bytes.
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_, bool PINGPONG, bool TA = false, bool TB = false, bool DW = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const dtl_args<BM, AMODE> p) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
   constexpr int EB = G::EB;
@@ -347,12 +389,47 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   };
 
   // Tiles are issued strictly in order 0, 1, 2, ...: the running bases and tap decode rely on it.
-  auto issue_loads = [&](int kt_local, int buf) {
+  auto issue_loads = [&](int kt_local, int buf) __attribute__((always_inline)) {
     const unsigned As = lds0 + buf * G::STAGE;
     const unsigned Bs = As + G::A_BYTES;
     const int kt = kt0 + kt_local;
     const int kbase = kt * G::KTB;
-    const bool full = kbase + G::KTB <= kbytes;  // wave-uniform
+    const bool full = kbase + G::KTB <= kbytes - (DW ? 1 : 0);  // wave-uniform; DW: the last tile never is
+    if constexpr (DW) {
+      if (!full) {
+        const v4i a_tile = buffer_of(a_base, DW_REACH), b_tile = buffer_of(b_base, DW_REACH);
+        int l = lane;  // opaque, or its offsets are kept in registers from the kernel's start
+        asm volatile("" : "+v"(l));
+        const int krows = p.K - kt * G::BK;  // k-rows left
+#pragma unroll
+        for (int i = 0; i < G::A_INSTR; i++) {
+          const int j = wave * G::A_INSTR + i, v = (wave * G::A_INSTR + i) & (NVAR - 1);
+          if constexpr (TA) {
+            dw_load(a_tile, krows - 1, j * AT_RPI, AT_RPI, p.M * EB, a_krow[i] < krows ? a_voff[i] : DW_NOTHING, As + j * 1024, l,
+                    [&](int q, int dw) { return dword_strided<EB, AT_ROW>(j * AT_RPI, q, dw, krows, p.M * EB - m0 * EB, p.lda * EB); });
+          } else {
+            const int row = j * G::A_ROWS_PER_INSTR + l / G::A_SPR;
+            dw_load(a_tile, p.M - 1 - m0, j * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
+                    (row < p.M - m0) & (kbase + a_chunk[v] * 16 < kbytes) ? a_voff[i] : DW_NOTHING, As + j * 1024, l,
+                    [&](int q, int dw) { return dword_contiguous<G::KTB>(j * G::A_ROWS_PER_INSTR, q, dw, p.M - m0, kbytes - kbase, p.lda * EB); });
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < G::B_INSTR; i++) {
+          const int j = wave * G::B_INSTR + i, v = (wave * G::B_INSTR + i) & (NVAR - 1);
+          if constexpr (TB) {
+            const int row = j * G::A_ROWS_PER_INSTR + l / G::A_SPR;
+            dw_load(b_tile, p.N - 1 - n0, j * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
+                    (row < p.N - n0) & (kbase + a_chunk[v] * 16 < kbytes) ? b_voff[i] : DW_NOTHING, Bs + j * 1024, l,
+                    [&](int q, int dw) { return dword_contiguous<G::KTB>(j * G::A_ROWS_PER_INSTR, q, dw, p.N - n0, kbytes - kbase, p.ldb * EB); });
+          } else {
+            dw_load(b_tile, krows - 1, j * G::B_ROWS_PER_INSTR, G::B_ROWS_PER_INSTR, nbytes, b_krow[i] < krows ? b_voff[i] : DW_NOTHING, Bs + j * 1024, l,
+                    [&](int q, int dw) { return dword_strided<EB, G::B_ROW>(j * G::B_ROWS_PER_INSTR, q, dw, krows, nbytes - n0 * EB, p.ldb * EB); });
+          }
+        }
+        return;  // the last tile: the running bases are not needed any more
+      }
+    }
     if constexpr (AMODE == 1) {
       unsigned g_off[NVAR], g_kh[NVAR], g_kw[NVAR], g_dead[NVAR];
 #pragma unroll
@@ -440,6 +517,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
       for (int j = 0; j < G::TN; j++) acc[i][j] = EPI::SWAP ? T::mfma(f.b[j], f.a[i], acc[i][j]) : T::mfma(f.a[i], f.b[j], acc[i][j]);
   };
   const int nkt_total = (kbytes + G::KTB - 1) / G::KTB;
+  constexpr bool DW_MASK = DW && !TA && (TB || EB == 2);
+  auto mask_last = [&](Frag& f, int ks) {
+#pragma unroll
+    for (int i = 0; i < G::TM; i++) f.a[i] = dw_mask(f.a[i], kbytes - (nkt_total - 1) * G::KTB - (2 * ks + (lane >> 5)) * 16);
+  };
   constexpr int PER_TILE = G::A_INSTR + G::B_INSTR;  // outstanding vector-memory ops per tile per wave
   static_assert((STAGES - 1) * PER_TILE <= 63, "vmcnt is a 6-bit counter");
   using SW = BSwizzle<EB, G::B_ROW>;
@@ -477,7 +559,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     if constexpr (HI_STAGES) asm volatile("" : "+v"(b_fo_hi[x]));
   }
   // K slices keep the general loops; the convolution gather handles a partial last tile itself
-  const int nkt_whole = p.splits > 1 ? 0 : (AMODE == 0 ? kbytes / G::KTB : nkt_total);
+  const int nkt_whole = p.splits > 1 ? 0 : (AMODE == 0 ? (DW ? kbytes - 1 : kbytes) / G::KTB : nkt_total);
   auto issue_whole = [&](auto lbufc) {  // the next tile in order, a whole one, into stage LBUF
     constexpr int LBUF = decltype(lbufc)::value;
 #pragma unroll
@@ -556,7 +638,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     const int grp = wave >> 2;
     Frag fr[G::KSTEPS];
     if (!started) {
-#pragma unroll
+#pragma unroll(DW ? 1 : STAGES)
       for (int s = 0; s < STAGES - 1; s++)
         if (s < nkt) issue_loads(s, s);
     }
@@ -606,6 +688,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
       for (int ks = 0; ks < G::KSTEPS; ks++) read_frags(buf, ks, fr[ks]);
       if (kt + STAGES - 1 < nkt) wait_vm<(STAGES - 2) * PER_TILE>();
       else wait_vm<0>();
+      if constexpr (DW_MASK) {
+        if (kbytes % 16 != 0 && kt0 + kt == nkt_total - 1) {
+#pragma unroll
+          for (int ks = 0; ks < G::KSTEPS; ks++) mask_last(fr[ks], ks);
+        }
+      }
       block_sync();
       // compute phase
       __builtin_amdgcn_s_setprio(1);
@@ -624,7 +712,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   // every wave has received its fragments of tile kt (block_sync waits for the wave's own LDS reads), so the
   // stage of tile kt can take tile kt + STAGES, and tile kt + 1 is visible to everyone.
   Frag fr[G::KSTEPS];
-#pragma unroll
+#pragma unroll(DW ? 1 : STAGES)  // one copy of a last tile's code (int8 1000^3 6.9 -> 6.7 us)
   for (int s = 0; s < STAGES; s++)
     if (s < nkt) issue_loads(s, s);
   if (nkt > 0) {
@@ -675,6 +763,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     buf = nbuf;
   }
   if (nkt > 0) {  // last tile
+    if constexpr (DW_MASK) {
+      if (kbytes % 16 != 0 && kt0 + nkt == nkt_total) {
+#pragma unroll
+        for (int ks = 0; ks < G::KSTEPS; ks++) mask_last(fr[ks], ks);
+      }
+    }
 #pragma unroll
     for (int ks = 0; ks < G::KSTEPS; ks++) mfma_rows(fr[ks], 0, G::TM);
   }
@@ -762,10 +856,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   } while ((work += gridDim.x) < nwork);  // tile loop
 }
 
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_ = 128, bool PINGPONG = false, bool TA = false, bool TB = false>
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_ = 128, bool PINGPONG = false, bool TA = false, bool TB = false, bool DW = false>
 static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
-  auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, PINGPONG, TA, TB>;
+  auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, PINGPONG, TA, TB, DW>;
   constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, AMODE, PINGPONG> ? BN * 4 : 0);
   static std::atomic<bool> configured{LDS <= 64 * 1024};
   if (const hipError_t e = allow_dynamic_lds_once(configured, kern, LDS)) return e;
@@ -788,13 +882,13 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
 // (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128), 128 and 64: the rolling-refill loop with 128 bytes of K per tile,
 // eight waves of 64 x 64 / 64 x 32 or four waves of 32 x 32 (four stages: six and eight were measured slower on
 // every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x 4608: those loops wait on the barrier, not on loads).
-template <class T, class EPI, int AMODE>
+template <class T, class EPI, int AMODE, bool DW = false>
 static hipError_t launch_dtl_tile(int tile, const GemmParams& p, hipStream_t stream) {
   switch (tile) {
-    case 256: return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, true>(p, stream);
-    case 192: return launch_dtl<T, EPI, 256, 128, 4, 2, AMODE, 3, 128>(p, stream);
-    case 128: return launch_dtl<T, EPI, 128, 128, 2, 4, AMODE, 3, 128>(p, stream);
-    default: return launch_dtl<T, EPI, 64, 64, 2, 2, AMODE, 4, 128>(p, stream);
+    case 256: return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, true, false, false, DW>(p, stream);
+    case 192: return launch_dtl<T, EPI, 256, 128, 4, 2, AMODE, 3, 128, false, false, false, DW>(p, stream);
+    case 128: return launch_dtl<T, EPI, 128, 128, 2, 4, AMODE, 3, 128, false, false, false, DW>(p, stream);
+    default: return launch_dtl<T, EPI, 64, 64, 2, 2, AMODE, 4, 128, false, false, false, DW>(p, stream);
   }
 }
 

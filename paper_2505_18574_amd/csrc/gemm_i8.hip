@@ -401,6 +401,9 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
   if (fast && kgroup_takes<TypeI8>(p, false, false)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
+  if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4))
+    return kgroup_takes<TypeI8>(p, false, false) ? launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream)
+                                                 : launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
   if (!ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, false)) return launch_kgroup_ragged<TypeI8, KGroupRawI32, true, false>(p, stream);
   return launch_ragged<TypeI8, EpilogueRawI32, true, false>(ragged_tile(p.M, p.N), p, stream);
 }
@@ -410,6 +413,18 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
   if (!forced && fast) {
     const GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 1);
     if ((plan.tile != 32 || kgroup_tiles(p) <= 256) && kgroup_takes<TypeI8>(p, false, plan.splits > 1)) return launch_kgroup<TypeI8, KGroupI8, 0>(p, stream);
+  }
+  if (!forced && !fast && !ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 4, 1)) {
+    GemmParams q = p;
+    GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 0);
+    if (kgroup_takes<TypeI8>(p, false, plan.splits > 1)) return launch_kgroup<TypeI8, KGroupI8, 0, false, false, true>(p, stream);
+    int ws_bm;
+    if (wstat_tile_rows(plan.tile, &ws_bm)) plan.tile = choose_tile_i8(p.M, p.N, p.K, false);
+    q.splits = plan.splits;
+    q.kt_per_split = plan.kt_per_split;
+    if (plan.splits <= 1) return launch_dtl_tile<TypeI8, EpilogueI8, 0, true>(plan.tile, q, stream);
+    if (const hipError_t e = launch_dtl_tile<TypeI8, EpiloguePartialI32, 0, true>(plan.tile, q, stream)) return e;
+    return launch_splitk_reduce_i8<4>(q, stream);
   }
   return dispatch_i8<0>(p, stream, fast, forced);
 }

@@ -15,17 +15,17 @@
 
 namespace ac {
 
-template <bool TA, bool TB>
+template <bool TA, bool TB, bool DW>
 static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   GemmParams p = p0;
   p.splits = 1;
   p.kt_per_split = 0;
-  if (kgroup_takes<TypeI8, TB>(p, false, false)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB>(p, stream);
+  if (kgroup_takes<TypeI8, TB>(p, false, false)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB, DW>(p, stream);
   switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // square tiles only: the 256 x 128 code falls to 128
-    case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB>(p, stream);
+    case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB, DW>(p, stream);
     case 192:
-    case 128: return launch_dtl<TypeI8, EpilogueI8, 128, 128, 2, 4, 0, 3, 128, false, TA, TB>(p, stream);
-    default: return launch_dtl<TypeI8, EpilogueI8, 64, 64, 2, 2, 0, 4, 128, false, TA, TB>(p, stream);
+    case 128: return launch_dtl<TypeI8, EpilogueI8, 128, 128, 2, 4, 0, 3, 128, false, TA, TB, DW>(p, stream);
+    default: return launch_dtl<TypeI8, EpilogueI8, 64, 64, 2, 2, 0, 4, 128, false, TA, TB, DW>(p, stream);
   }
 }
 
@@ -40,9 +40,18 @@ hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b,
                     p.ldc % 4 == 0 && p.K % 16 == 0 && p.N % 16 == 0 && (!trans_a || p.M % 16 == 0) && p.K > 0 &&
                     lane_offsets_fit(pitch_kc, pitch_ks);
   if (fast) {
-    if (trans_a && trans_b) return launch_trans_dtl<true, true>(p, stream);
-    if (trans_a) return launch_trans_dtl<true, false>(p, stream);
-    return launch_trans_dtl<false, true>(p, stream);
+    if (trans_a && trans_b) return launch_trans_dtl<true, true, false>(p, stream);
+    if (trans_a) return launch_trans_dtl<true, false, false>(p, stream);
+    return launch_trans_dtl<false, true, false>(p, stream);
+  }
+  if (dword_operands(p, 1, trans_a, trans_b, 4, 1)) {
+    if (trans_a && trans_b) {
+      if (!ragged_tiny<TypeI8, false, true, false>(p)) return launch_trans_dtl<true, true, true>(p, stream);
+    } else if (trans_a) {
+      if (!ragged_tiny<TypeI8, false, false, false>(p)) return launch_trans_dtl<true, false, true>(p, stream);
+    } else if (!ragged_tiny<TypeI8, true, true, false>(p)) {
+      return launch_trans_dtl<false, true, true>(p, stream);
+    }
   }
   const int tile = ragged_tile(p.M, p.N);
   GemmParams q = p;

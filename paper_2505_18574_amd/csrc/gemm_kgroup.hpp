@@ -113,8 +113,8 @@ static __device__ __forceinline__ void kgroup_finish(const P& p, unsigned char* 
   OUT::store(p, om, on, s, bias);
 }
 
-// KTB: bytes of K per tile, S: stages of a wave's ring, W: waves of a workgroup; AMODE, TA, TB as for gemm_dtl_kernel.
-template <class T, class OUT, int KTB, int S, int W, int AMODE, bool TA, bool TB>
+// KTB: bytes of K per tile, S: stages of a wave's ring, W: waves of a workgroup; AMODE, TA, TB, DW as for gemm_dtl_kernel.
+template <class T, class OUT, int KTB, int S, int W, int AMODE, bool TA, bool TB, bool DW>
 __global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const std::conditional_t<AMODE == 1, ConvArgs, GemmArgs> p) {
   using G = DtlGeometry<T, 32, 32, 1, 1, S, KTB>;
   constexpr int EB = T::EB, NA = G::A_INSTR, NB = G::B_INSTR, KS = G::KSTEPS, PER_TILE = NA + NB;
@@ -194,10 +194,42 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const std::conditio
   const int nkt = nkt_total > wave ? (nkt_total - wave + W - 1) / W : 0;
 
   int wr = 0, kt_issue = wave;  // stage and K tile of the next request
-  auto issue = [&]() {
+  auto issue = [&]() __attribute__((always_inline)) {
     const unsigned st = lds0 + wr * G::STAGE;
-    const bool full = (kt_issue + 1) * KTB <= kbytes;  // wave-uniform
+    const bool full = (kt_issue + 1) * KTB <= kbytes - (DW ? 1 : 0);  // wave-uniform
     const int kbase = kt_issue * KTB;
+    if constexpr (DW) {
+      if (!full) {  // the last tile
+        const v4i a_tile = buffer_of(a_base, DW_REACH), b_tile = buffer_of(b_base, DW_REACH);
+        const int krows = p.K - kbase / EB;  // k-rows left
+#pragma unroll
+        for (int i = 0; i < NA; i++) {
+          if constexpr (TA) {
+            dw_load(a_tile, krows - 1, i * AT_RPI, AT_RPI, p.M, i * AT_RPI + lane / AT_SPR < krows ? a_voff[i] : DW_NOTHING, st + i * 1024, lane,
+                    [&](int q, int dw) { return dword_strided<EB, AT_ROW>(i * AT_RPI, q, dw, krows, p.M - m0, p.lda); });
+          } else {
+            dw_load(a_tile, p.M - 1 - m0, i * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
+                    (i * G::A_ROWS_PER_INSTR + lane / G::A_SPR < p.M - m0) & (kbase + a_chunk[i & (NVAR - 1)] * 16 < kbytes) ? a_voff[i] : DW_NOTHING, st + i * 1024, lane,
+                    [&](int q, int dw) { return dword_contiguous<KTB>(i * G::A_ROWS_PER_INSTR, q, dw, p.M - m0, kbytes - kbase, p.lda * EB); });
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+          const unsigned to = st + G::A_BYTES + i * 1024;
+          if constexpr (TB) {
+            dw_load(b_tile, p.N - 1 - n0, i * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
+                    (i * G::A_ROWS_PER_INSTR + lane / G::A_SPR < p.N - n0) & (kbase + a_chunk[i & (NVAR - 1)] * 16 < kbytes) ? b_voff[i] : DW_NOTHING, to, lane,
+                    [&](int q, int dw) { return dword_contiguous<KTB>(i * G::A_ROWS_PER_INSTR, q, dw, p.N - n0, kbytes - kbase, p.ldb); });
+          } else {
+            dw_load(b_tile, krows - 1, i * G::B_ROWS_PER_INSTR, G::B_ROWS_PER_INSTR, p.N * EB,
+                    i * G::B_ROWS_PER_INSTR + lane / G::B_SPR < krows ? b_voff[i] : DW_NOTHING, to, lane,
+                    [&](int q, int dw) { return dword_strided<EB, G::B_ROW>(i * G::B_ROWS_PER_INSTR, q, dw, krows, (p.N - n0) * EB, p.ldb * EB); });
+          }
+        }
+        wr = wr + 1 == S ? 0 : wr + 1;
+        return;
+      }
+    }
     if constexpr (AMODE == 1) {
       unsigned g_off[NVAR], g_kh[NVAR], g_kw[NVAR], g_dead[NVAR];
 #pragma unroll
@@ -282,6 +314,12 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_kernel(const std::conditio
       }
       read_frags(nxt);
     }
+    if constexpr (DW && !TA && (TB || EB == 2)) {
+      if (kbytes % 16 != 0 && wave + kt * W == nkt_total - 1) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) cur.a[ks] = dw_mask(cur.a[ks], kbytes - (nkt_total - 1) * KTB - (2 * ks + (lane >> 5)) * 16);
+      }
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) acc = T::mfma(cur.b[ks], cur.a[ks], acc);  // swapped: a lane holds runs of four columns of a row
   };
@@ -306,25 +344,25 @@ static hipError_t launch_kgroup_grid(std::atomic<bool>& configured, KERN kern, i
   return hipGetLastError();
 }
 
-template <class T, class OUT, int KTB, int W, int AMODE, bool TA, bool TB>
+template <class T, class OUT, int KTB, int W, int AMODE, bool TA, bool TB, bool DW>
 static hipError_t launch_kgroup_cfg(const GemmParams& p, hipStream_t stream) {
   constexpr int S = 3, LDS = W * S * 64 * KTB;  // (rings of four and five stages: level)
   static_assert(LDS <= 160 * 1024, "LDS budget");
   static std::atomic<bool> configured{LDS <= 64 * 1024};
-  return launch_kgroup_grid<std::conditional_t<AMODE == 1, ConvArgs, GemmArgs>, T>(configured, gemm_kgroup_kernel<T, OUT, KTB, S, W, AMODE, TA, TB>, W, LDS, p, stream);
+  return launch_kgroup_grid<std::conditional_t<AMODE == 1, ConvArgs, GemmArgs>, T>(configured, gemm_kgroup_kernel<T, OUT, KTB, S, W, AMODE, TA, TB, DW>, W, LDS, p, stream);
 }
 
 // Direct-to-LDS operands (checked by the caller).  Eight waves, a tile to a compute unit, where K keeps them busy; four
 // waves, three workgroups to a compute unit, where it does not or where there are more tiles than compute units; and
 // 128-byte K tiles for long rows, whose 64-byte pieces two waves would fetch as two halves of a cache line (B^T
 // 588 x 128 x 5888 8.4 -> 6.9 us, 83 x 928 x 8048 12.2 -> 10.5).
-template <class T, class OUT, int AMODE, bool TA = false, bool TB = false>
+template <class T, class OUT, int AMODE, bool TA = false, bool TB = false, bool DW = false>
 static hipError_t launch_kgroup(const GemmParams& p, hipStream_t stream) {
   const int64_t kbytes = (int64_t)p.K * T::EB;
-  if (kgroup_tiles(p) > 256 || kbytes <= 512) return launch_kgroup_cfg<T, OUT, 64, 4, AMODE, TA, TB>(p, stream);
+  if (kgroup_tiles(p) > 256 || kbytes <= 512) return launch_kgroup_cfg<T, OUT, 64, 4, AMODE, TA, TB, DW>(p, stream);
   if constexpr (AMODE == 0)
-    if (kbytes >= 4864) return launch_kgroup_cfg<T, OUT, 128, 4, AMODE, TA, TB>(p, stream);
-  return launch_kgroup_cfg<T, OUT, 64, 8, AMODE, TA, TB>(p, stream);
+    if (kbytes >= 4864) return launch_kgroup_cfg<T, OUT, 128, 4, AMODE, TA, TB, DW>(p, stream);
+  return launch_kgroup_cfg<T, OUT, 64, 8, AMODE, TA, TB, DW>(p, stream);
 }
 
 // Whether the kernel above takes a product (or, `conv`, a convolution) from the others: `sliced` says that these would cut K

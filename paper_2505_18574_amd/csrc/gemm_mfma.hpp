@@ -103,6 +103,26 @@ struct has_wave_tile : std::false_type {};
 template <class E>
 struct has_wave_tile<E, std::void_t<decltype(E::WAVE_TILE)>> : std::true_type {};
 
+struct __attribute__((packed)) Unaligned16 {
+  v4i v;
+};
+// 16 consecutive int8 outputs of a row at any address, the first `valid` of them.
+static __device__ __forceinline__ void store_run16(int8_t* dst, v4i o, int valid) {
+  if (valid >= 16) {
+    ((Unaligned16*)dst)->v = o;
+  } else if (valid > 0) {
+    uint64_t lo = (uint64_t)(unsigned)o[0] | ((uint64_t)(unsigned)o[1] << 32);
+    const uint64_t hi = (uint64_t)(unsigned)o[2] | ((uint64_t)(unsigned)o[3] << 32);
+    struct __attribute__((packed)) U8 { uint64_t v; };
+    struct __attribute__((packed)) U4 { uint32_t v; };
+    struct __attribute__((packed)) U2 { uint16_t v; };
+    if (valid & 8) ((U8*)dst)->v = lo, dst += 8, lo = hi;
+    if (valid & 4) ((U4*)dst)->v = (uint32_t)lo, dst += 4, lo >>= 32;
+    if (valid & 2) ((U2*)dst)->v = (uint16_t)lo, dst += 2, lo >>= 16;
+    if (valid & 1) *dst = (int8_t)lo;
+  }
+}
+
 // int8 output stage: bias, v / 2^shift to nearest (halves to even), saturate, ReLU.
 struct EpilogueI8 {
   static constexpr bool SWAP = true;
@@ -119,7 +139,7 @@ struct EpilogueI8 {
     return q;
   }
   // Columns n .. n + 3 of row m, for a C whose rows are dword-aligned.
-  template <bool ADD_BIAS = true, class P>
+  template <class P>
   static __device__ __forceinline__ void store4(const P& p, int m, int n, const int* a) {
     if (m >= p.M || n >= p.N) return;
     int8_t* C = (int8_t*)p.C;
@@ -128,7 +148,7 @@ struct EpilogueI8 {
 #pragma unroll
     for (int e = 0; e < 4; e++) {
       int b = 0;
-      if (ADD_BIAS && p.bias && (full || n + e < p.N)) b = p.bias_ld == 0 ? p.bias[n + e] : p.bias[(int64_t)m * p.bias_ld + n + e];
+      if (p.bias && (full || n + e < p.N)) b = p.bias_ld == 0 ? p.bias[n + e] : p.bias[(int64_t)m * p.bias_ld + n + e];
       v[e] = requant(a[e] + b, p.shift, p.act);
     }
     int8_t* dst = C + (int64_t)m * p.ldc + n;
@@ -245,7 +265,7 @@ struct EpilogueI8 {
   template <bool BIASED, int TM, int TN, class ACC_OF, class PRE_OF, class P>
   static __device__ __forceinline__ void wave_blocks(const P& p, int mrow0, int ncol0, ACC_OF acc_of, int lane, int esplit, PRE_OF pre_of) {
     int8_t* C = (int8_t*)p.C;
-    const bool fast = ncol0 + 32 * TN <= p.N && (p.ldc & 15) == 0 && (((uintptr_t)C) & 15) == 0 && (p.bias == nullptr || p.bias_ld == 0) && p.shift >= 1 && p.shift <= 23;
+    const bool fast = ncol0 + 32 * TN <= p.N && (p.bias == nullptr || p.bias_ld == 0) && p.shift >= 1 && p.shift <= 23;
     if (fast) {  // wave-uniform
       const FastQuant f = fast_quant(p.shift, p.act);
       auto blocks = [&](auto float_round) {
@@ -259,7 +279,7 @@ struct EpilogueI8 {
 #pragma unroll
             for (int r = 0; r < 16; r++) t[r] = BIASED ? acc_of(i, j)[r] : acc_of(i, j)[r] + pre_of(j).bias[r >> 2][r & 3];  // no bias: the prefetch returned zeros
             const v4i o = quant16<decltype(float_round)::value>(t, f);
-            if (m < p.M) *(v4i*)(dst + 32 * j) = o;
+            if (m < p.M) ((Unaligned16*)(dst + 32 * j))->v = o;
           }
         }
       };
@@ -287,56 +307,26 @@ struct EpilogueI8 {
     const int m = mrow0 + (lane & 31);
     if (m >= p.M || ncol0 >= p.N) return;
     int8_t* C = (int8_t*)p.C;
-    const bool wide = ncol0 + 32 <= p.N && (p.ldc & 15) == 0 && (((uintptr_t)C) & 15) == 0;
     const bool row_bias = p.bias && p.bias_ld == 0;
-    if (wide) {
-      int t[16];
+    int t[16];
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const int n = ncol0 + 8 * q + 4 * (lane >> 5);
+    for (int q = 0; q < 4; q++) {
+      const int n = ncol0 + 8 * q + 4 * (lane >> 5);
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-          int b = 0;
-          if constexpr (!BIASED) {
-            b = row_bias ? pre.bias[q][e] : 0;
-            if (p.bias && !row_bias) b = p.bias[(int64_t)m * p.bias_ld + n + e];
-          }
-          t[4 * q + e] = acc[4 * q + e] + b;
+      for (int e = 0; e < 4; e++) {
+        int b = 0;
+        if constexpr (!BIASED) {
+          b = row_bias ? pre.bias[q][e] : 0;
+          if (p.bias && !row_bias) b = p.bias[(int64_t)m * p.bias_ld + (n + e < p.N ? n + e : p.N - 1)];
         }
-      }
-      const v4i o = p.shift >= 1 && p.shift <= 23 ? quant16_by_shift(t, fast_quant(p.shift, p.act)) : quant16(t, p.shift, p.act);
-      *(v4i*)(C + (int64_t)m * p.ldc + ncol0 + 16 * (lane >> 5)) = o;
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const int n = ncol0 + 8 * q + 4 * (lane >> 5);
-        int a4[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        if constexpr (BIASED) store4<false>(p, m, n, a4);
-        else store4(p, m, n, a4);
+        t[4 * q + e] = acc[4 * q + e] + b;
       }
     }
+    const v4i o = p.shift >= 1 && p.shift <= 23 ? quant16_by_shift(t, fast_quant(p.shift, p.act)) : quant16(t, p.shift, p.act);
+    const int n = ncol0 + 16 * (lane >> 5);
+    store_run16(C + (int64_t)m * p.ldc + n, o, p.N - n);
   }
 };
-
-struct __attribute__((packed)) Unaligned16 {
-  v4i v;
-};
-// 16 consecutive int8 outputs of a row at any address, the first `valid` of them.
-static __device__ __forceinline__ void store_run16(int8_t* dst, v4i o, int valid) {
-  if (valid >= 16) {
-    ((Unaligned16*)dst)->v = o;
-  } else if (valid > 0) {
-    uint64_t lo = (uint64_t)(unsigned)o[0] | ((uint64_t)(unsigned)o[1] << 32);
-    const uint64_t hi = (uint64_t)(unsigned)o[2] | ((uint64_t)(unsigned)o[3] << 32);
-    struct __attribute__((packed)) U8 { uint64_t v; };
-    struct __attribute__((packed)) U4 { uint32_t v; };
-    struct __attribute__((packed)) U2 { uint16_t v; };
-    if (valid & 8) ((U8*)dst)->v = lo, dst += 8, lo = hi;
-    if (valid & 4) ((U4*)dst)->v = (uint32_t)lo, dst += 4, lo >>= 32;
-    if (valid & 2) ((U2*)dst)->v = (uint16_t)lo, dst += 2, lo >>= 16;
-    if (valid & 1) *dst = (int8_t)lo;
-  }
-}
 
 // The same output stage for a C of any alignment and pitch: after the exchange a lane holds 16 consecutive columns of
 // its row and stores them with one unaligned store (one byte per lane and store, on unswapped tiles, is sixteen stores
