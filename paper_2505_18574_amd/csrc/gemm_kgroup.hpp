@@ -449,9 +449,12 @@ __global__ void __launch_bounds__(64 * W) gemm_kgroup_ragged_kernel(const std::c
   if constexpr (!CONV) {
     // the partial last tile, ahead of the others by the wave whose turn it is
     if (nkt_whole < nkt_total && nkt_whole % W == wave) {  // wave-uniform
-      a.load_any(ra[0], fa[0], nkt_whole - wave);
-      b.load_any(rb[0], fb[0], nkt_whole - wave);
-      fix(ra[0], rb[0], fa[0], fb[0]);
+      typename SA::Last la;
+      typename SB::Last lb;
+      a.load_last(ra[0], la, nkt_whole - wave);
+      b.load_last(rb[0], lb, nkt_whole - wave);
+      a.last_fix(ra[0], la);
+      b.last_fix(rb[0], lb);
       multiply(ra[0], rb[0]);
     }
   }
@@ -518,7 +521,7 @@ static hipError_t launch_kgroup_ragged(const GemmParams& p, hipStream_t stream) 
 }
 
 // The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
-// here): up to 256 tiles ahead from K = 64 on (106 x 360 x 1476 with A^T 10.1 / 5.9 us, 872 x 29 x 1397 8.9 / 5.9, bf16
+// here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16
 // 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 / 8.0), but for cut products of K beyond 3500
 // (35 x 750 x 5476 9.7 / 14.5) and convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1);
 // up to 448 with half the waves (204 x 2077 x 597 7.8 / 5.8, 3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0; 2287 x 206 x 1941
@@ -526,7 +529,7 @@ static hipError_t launch_kgroup_ragged(const GemmParams& p, hipStream_t stream) 
 template <class T, bool AKC, bool BKC, bool CONV = false>
 static bool kgroup_ragged_takes(const GemmParams& p, bool sliced) {
   const int64_t t = kgroup_tiles(p), kbytes = (int64_t)p.K * T::EB;
-  if (kbytes < (CONV ? 200 : 64) || (CONV && (p.Cin < 1 || p.a_bytes < 16 || p.N < 1))) return false;
+  if (kbytes < (CONV ? 200 : 16) || (CONV && (p.Cin < 1 || p.a_bytes < 16 || p.N < 1))) return false;
   if (!CONV && !((AKC || (int64_t)p.M * T::EB >= 16) && (BKC || (int64_t)p.N * T::EB >= 16))) return false;  // rows of K-strided operands hold a chunk
   if (t <= 256) return !sliced || kbytes <= 3500;
   return t <= 448 && (CONV ? kbytes >= 1200 : !sliced || kbytes <= 2048);

@@ -174,6 +174,50 @@ struct RaggedMatrix {
       }
     }
   }
+  // The partial last tile, `ahead` tiles after the next whole one, where every row is at least 16 bytes long: all chunks are
+  // requested, then brought into shape by last_fix().  A K-contiguous operand can leave the buffer in its last row only
+  // (the chunk is then loaded where 16 bytes exist and shifted), and its lanes' chunks all end at the same byte of K;
+  // a K-strided one has whole rows or rows of zeros.
+  struct Last {
+    int shift[KC ? IT : 1];  // KC: bytes the chunk was loaded too early
+    int ahead;
+  };
+  __device__ __forceinline__ void load_last(v4i (&reg)[IT], Last& l, int ahead) const {
+    const int64_t off = ahead * step;
+    l.ahead = ahead;
+#pragma unroll
+    for (int i = 0; i < IT; i++) {
+      if constexpr (KC) {
+        const unsigned char *p = ptr[i] + off, *q = p > last ? last : p;
+        l.shift[i] = (int)(p - q);
+        reg[i] = load16_any(q);
+      } else {
+        reg[i] = load16_any(k + ahead * (RAGGED_KTB / EB) + i * Tile::RPP < K ? ptr[i] + off : base);
+      }
+    }
+  }
+  __device__ __forceinline__ void last_fix(v4i (&reg)[IT], const Last& l) const {
+    if constexpr (KC) {
+      const int valid = kbytes - (kb + l.ahead * RAGGED_KTB);
+      int mask[4];
+#pragma unroll
+      for (int d = 0; d < 4; d++) mask[d] = valid >= 4 * d + 4 ? -1 : valid <= 4 * d ? 0 : (1 << 8 * (valid - 4 * d)) - 1;
+#pragma unroll
+      for (int i = 0; i < IT; i++) {
+        if (l.shift[i] != 0) reg[i] = chunk_apply<false>(reg[i], chunk_fix(l.shift[i] < 16 ? l.shift[i] : 0, 0, 16));
+#pragma unroll
+        for (int d = 0; d < 4; d++) reg[i][d] &= mask[d];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < IT; i++) {
+        reg[i] = chunk_apply<false>(reg[i], edge);
+        const bool in = k + l.ahead * (RAGGED_KTB / EB) + i * Tile::RPP < K;
+#pragma unroll
+        for (int d = 0; d < 4; d++) reg[i][d] = in ? reg[i][d] : 0;
+      }
+    }
+  }
 };
 
 // K of a convolution as the kernel walks it: KH runs of KW * Cin bytes, each padded to whole chunks.
@@ -303,7 +347,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   const int kbytes = walk_bytes<CONV, EB>(p);
   const int nkt_total = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
   // tiles before this one lie inside K and (K-strided operands) have rows of 16 bytes and more: unconditional loads
-  const bool long_rows = (AKC || (int64_t)p.M * EB >= 16) && (BKC || (int64_t)p.N * EB >= 16);
+  const bool long_rows = (AKC ? (int64_t)p.K : (int64_t)p.M) * EB >= 16 && (BKC ? (int64_t)p.K : (int64_t)p.N) * EB >= 16;
   const int nkt_whole = CONV || !long_rows ? 0 : kbytes / RAGGED_KTB;
   const unsigned items = (unsigned)ntiles * (unsigned)p.splits;  // (K is cut only where tiles are few)
 
@@ -425,16 +469,29 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
       };
       v4i xa[SA::IT], xb[SB::IT];
       int fa[SA::IT], fb[SB::IT];
+      typename SA::Last la;
+      typename SB::Last lb;
       if (nw < nkt) {
-        a.load_any(xa, fa, nw);
-        b.load_any(xb, fb, nw);
+        if (long_rows) {
+          a.load_last(xa, la, nw);
+          b.load_last(xb, lb, nw);
+        } else {
+          a.load_any(xa, fa, nw);
+          b.load_any(xb, fb, nw);
+        }
         in_order();
       }
       int k = 0;
       Frags f;
       // the partial tile, once its requests and those of w_0 .. w_(R - 1) are out
       auto begin = [&](auto refill) {
-        if (nw < nkt) store_fixed(1, xa, xb, fa, fb);
+        if (nw < nkt && long_rows) {
+          a.last_fix(xa, la);
+          b.last_fix(xb, lb);
+          store(1, xa, xb);
+        } else if (nw < nkt) {
+          store_fixed(1, xa, xb, fa, fb);
+        }
         if (refill.value || nw > 0) stage(0, std::integral_constant<int, 0>{});
         if (refill.value || R < nw) fetch(std::integral_constant<int, 0>{});
         block_sync();
