@@ -8,6 +8,8 @@
 // and B multiples of 16 bytes, K and N multiples of 16 bytes' worth of elements,
 // C suitably aligned for vector stores.  M, N, K need not be multiples of the
 // tile: out-of-range 16-byte chunks are fetched from a 16-byte block of zeros.
+// The DW form of a product asks for multiples of 4 bytes where this says 16
+// (dword_operands in common.hpp).
 //
 // LDS layouts (16-byte slots; a direct-to-LDS wave instruction fills 64
 // consecutive slots, the source address of each slot is free):
@@ -879,8 +881,8 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
 }
 
 // The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages
-// (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128), 128 and 64: the rolling-refill loop with 128 bytes of K per tile,
-// eight waves of 64 x 64 / 64 x 32 or four waves of 32 x 32 (four stages: six and eight were measured slower on
+// (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128),
+// 128 and 64: the rolling-refill loop with 128 bytes of K per tile, eight waves of 64 x 64 / 64 x 32 or four waves of 32 x 32 (four stages: six and eight were measured slower on
 // every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x 4608: those loops wait on the barrier, not on loads).
 template <class T, class EPI, int AMODE, bool DW = false>
 static hipError_t launch_dtl_tile(int tile, const GemmParams& p, hipStream_t stream) {

@@ -521,8 +521,8 @@ static hipError_t launch_kgroup_ragged(const GemmParams& p, hipStream_t stream) 
 }
 
 // The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
-// here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16
-// 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 / 8.0), but for cut products of K beyond 3500
+// here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x
+// 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 / 8.0), but for cut products of K beyond 3500
 // (35 x 750 x 5476 9.7 / 14.5) and convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1);
 // up to 448 with half the waves (204 x 2077 x 597 7.8 / 5.8, 3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0; 2287 x 206 x 1941
 // of 504 tiles 13.0 / 14.8), convolutions from K = 1200 on (12943 x 25 x 925 9.7 / 9.7).

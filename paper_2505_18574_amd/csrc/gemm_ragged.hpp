@@ -1,5 +1,5 @@
 // Tiled MFMA GEMM / implicit-GEMM convolution for operands of any size, pitch and alignment: whatever the
-// direct-to-LDS kernels (gemm_dtl.hpp) do not take.  int8 and bf16, either operand transposed in memory, and
+// direct-to-LDS kernels (gemm_dtl.hpp) do not take, beyond the few tiles that gemm_kgroup.hpp shares.  int8 and bf16, either operand transposed in memory, and
 // convolutions with any channel count.
 //
 // Every 16-byte chunk of an operand tile comes in with ONE vector load, wherever it starts (a vector load takes any
