@@ -244,8 +244,8 @@ static __device__ __forceinline__ void tile_coords_mul(int b, int nblocks, int t
 }
 
 // Whether gemm_dtl_kernel keeps the bias row of its tile in LDS, behind the stages: BN * 4 bytes.
-template <class EPI, int BM, int AMODE, bool PINGPONG>
-constexpr bool has_bias_lds = BM >= 256 && !(PINGPONG && AMODE == 0) && std::is_same_v<EPI, EpilogueI8>;
+template <class EPI, int BM, bool PINGPONG>
+constexpr bool has_bias_lds = BM >= 256 && !PINGPONG && std::is_same_v<EPI, EpilogueI8>;
 
 template <int BM, int AMODE>
 using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), ConvArgsWide, ConvArgs>, GemmArgs>;
@@ -290,12 +290,15 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   static_assert(!XPF || (STAGES - 2) * (G::A_INSTR + G::B_INSTR) + EPI_VM <= 63, "vmcnt is a 6-bit counter");
 
   // The bias of a wave's columns waits in LDS behind the stages, where the tile leaves no registers to hold it over the K
-  // loop: those went to scratch, 16 to 18 of a wave of the 256 x 128 tiles and 10 of the 256 x 256 convolution (4784 x 1600 x
-  // 2048 24.3 -> 21.8 us, 8192 x 1024 x 1024 14.5 -> 13.6, 3 x 3 stride 2, 256 -> 512 on 64 images of 28 x 28 24.9 -> 22.7, 3 x 3,
-  // 496 -> 304 on 29 of 27 x 27 47.4 -> 44.7).  The product of a 256 x 256 tile holds them without and is slower with it
-  // (5000 x 2560 x 320 12.1 and 13.6).  The request is the oldest of its wave, so the K loop's first wait covers it and the
+  // loop: 16 to 18 of a wave of the 256 x 128 tiles went to scratch (4784 x 1600 x 2048 24.3 -> 21.8 us, 8192 x 1024 x 1024
+  // 14.5 -> 13.6, 3 x 3, 496 -> 304 on 29 images of 27 x 27 47.4 -> 44.7).  The product of a 256 x 256 tile holds them without
+  // and is slower with it (5000 x 2560 x 320 12.1 and 13.6); the convolution of that tile spills 19 and still takes registers:
+  // its K loop is short more often than long (3 x 3, 64 -> 256 on 64 images of 56 x 56 39.2 us so and 41.7 from LDS, 128 -> 256
+  // stride 2 on 192 of 28 x 28 22.1 and 22.8, 5 x 5, 48 -> 224 on 90 of 41 x 41 58.5 and 62.1; 512 -> 512 on 64 of 28 x 28,
+  // K = 4608, 121.7 and 118.3; 20 such shapes 1.008 in the mean).  The
+  // request is the oldest of its wave, so the K loop's first wait covers it and the
   // barrier behind that publishes it; the barrier at the end of the item frees it.
-  constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, AMODE, PINGPONG>;
+  constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, PINGPONG>;
 
   // ---- item-independent lane roles ---------------------------------------------------------------------
   constexpr int NVAR = G::KTB == 128 ? 2 : 1;
@@ -862,7 +865,7 @@ template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMOD
 static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
   auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, PINGPONG, TA, TB, DW>;
-  constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, AMODE, PINGPONG> ? BN * 4 : 0);
+  constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, PINGPONG> ? BN * 4 : 0);
   static std::atomic<bool> configured{LDS <= 64 * 1024};
   if (const hipError_t e = allow_dynamic_lds_once(configured, kern, LDS)) return e;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;

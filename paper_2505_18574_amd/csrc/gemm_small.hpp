@@ -14,7 +14,7 @@
 //
 // Operands as for the direct-to-LDS kernels (16-byte aligned, K and N in whole 16-byte chunks), and K a multiple
 // of 64; anything else stays on the tiled kernels.  Up to 256 tiles, where three of a compute unit's four SIMDs would
-// idle, several waves share a tile instead (gemm_kgroup.hpp; 256^3 4.05 -> 3.0 us replayed from a graph).
+// idle, several waves share a tile instead (gemm_kgroup.hpp; 256^3 4.05 -> 3.4 us replayed from a graph).
 #pragma once
 #include "gemm_dtl.hpp"
 

@@ -1,4 +1,4 @@
-"""GPU parity of the 256 x 128 int8 tiles and the 256 x 256 convolution tile, whose bias row waits in LDS: no bias, a row at an
+"""GPU parity of the 256 x 128 int8 tiles, whose bias row waits in LDS, and the 256 x 256 convolution tile, whose does not: no bias, a row at an
 odd address, a matrix (products), columns beyond N, no K tile, one, fewer than the stages and many, several tiles to a
 workgroup; bit for bit."""
 import numpy as np
