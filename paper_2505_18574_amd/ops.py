@@ -201,6 +201,24 @@ def _bias_i8(bias, M, N):
     return bias.data_ptr(), 0
 
 
+def _bias_raw(bias, M, N):
+    """(address, row pitch) of the bias of an M x N accumulator: as for _bias_i8, but a vector or a matrix may be larger than
+    the output.  What the kernel reads must lie inside it."""
+    if bias is None:
+        return None, 0
+    if bias.dtype != torch.int32 or not bias.is_cuda:
+        raise ValueError("bias: expected int32 device tensor")
+    if bias.dim() != 2:
+        if bias.numel() < N or (N > 1 and not bias.is_contiguous()):
+            raise ValueError("bias vector must have N contiguous entries")
+        return bias.data_ptr(), 0
+    (rows, cols), (pitch, step) = bias.shape, bias.stride()
+    # (the library refuses a pitch shorter than a row)
+    if not 0 < pitch < N and ((rows < M and pitch != 0) or cols < N or (N > 1 and step != 1)):
+        raise ValueError("bias matrix must be M x N row-major")
+    return bias.data_ptr(), pitch
+
+
 def _gemm_i8_args(A, B, bias, C):
     M, K, lda = _matrix(A, torch.int8, "A")
     K2, N, ldb = _matrix(B, torch.int8, "B")
@@ -409,13 +427,8 @@ def ac_gemm_i8_acc32(A, B, bias, C, stream=None):
         M2, N2, ldc = _matrix(C, torch.int32, "C")
         if K2 != K or M2 != M or N2 != N:
             raise ValueError("shape mismatch")
-        bias_ld = 0
-        if bias is not None:
-            if bias.dtype != torch.int32 or not bias.is_cuda:
-                raise ValueError("bias: expected int32 device tensor")
-            if bias.dim() == 2:
-                bias_ld = bias.stride(0)
-        st = lib().ac_gemm_i8_acc32(A.data_ptr(), lda, B.data_ptr(), ldb, _ptr(bias), bias_ld, C.data_ptr(), ldc,
+        bp, bias_ld = _bias_raw(bias, M, N)
+        st = lib().ac_gemm_i8_acc32(A.data_ptr(), lda, B.data_ptr(), ldb, bp, bias_ld, C.data_ptr(), ldc,
                                     M, N, K, _stream(stream))
     if st != AC_OK:
         raise AcError(st, "ac_gemm_i8_acc32")

@@ -43,6 +43,51 @@ def test_errors_are_those_of_the_python_checks():
         ops.ac_gemm_i8(None, A, None, C, 1)
 
 
+class OnDevice(torch.Tensor):
+    """A host tensor that says it is on the device, for the checks of ops.py."""
+    is_cuda = property(lambda self: True)
+
+
+class Launches:
+    """A library that notes what would have been launched."""
+
+    def __init__(self, monkeypatch):
+        self.calls = []
+        monkeypatch.setattr(ops, "lib", lambda: self)
+        monkeypatch.setattr(ops, "_lib", self)
+
+    def __getattr__(self, name):
+        return lambda *args: self.calls.append((name, args)) or ops.AC_OK
+
+
+class NullStream:
+    cuda_stream = 0
+
+
+def test_raw_accumulator_refuses_a_bias_it_would_read_beyond(monkeypatch):
+    """What the kernel reads (row m at data + m * pitch, N values in a row) lies inside the bias, and is what it holds."""
+    ops.native()
+    lib = Launches(monkeypatch)
+    A, B, C = (i8(5, 8).as_subclass(OnDevice), i8(8, 6).as_subclass(OnDevice), torch.zeros((5, 6), dtype=torch.int32).as_subclass(OnDevice))
+    i32 = lambda *s: torch.zeros(s, dtype=torch.int32)
+    call = lambda b: ops.ac_gemm_i8_acc32(A, B, b.as_subclass(OnDevice), C, stream=NullStream)
+    for bad in (i32(5), i32(0), i32(1, 6), i32(4, 6), i32(5, 9)[:, :5], i32(12)[::2], i32(5, 12)[:, ::2], i32(1, 1, 5)):
+        with pytest.raises(ValueError, match="bias"):
+            call(bad)
+    assert lib.calls == []
+    pitches = []
+    for good in (i32(6), i32(9), i32(5, 6), i32(7, 9), i32(5, 9)[:, 2:8], i32(6).expand(5, 6), i32(1, 1, 6)):
+        call(good)
+        name, args = lib.calls.pop()
+        assert name == "ac_gemm_i8_acc32" and args[4] == good.data_ptr()
+        pitches.append(args[5])
+    assert pitches == [0, 0, 6, 9, 9, 0, 0]
+    A, B, C = i8(5, 8).as_subclass(OnDevice), i8(8, 1).as_subclass(OnDevice), torch.zeros((5, 1), dtype=torch.int32).as_subclass(OnDevice)
+    for good, pitch in ((i32(2)[::2], 0), (i32(5, 1), 1), (i32(5, 3)[:, 1:2], 3), (i32(1, 5).t(), 1)):  # one column: rows of one value
+        call(good)
+        assert lib.calls.pop()[1][5] == pitch
+
+
 class Sub(torch.Tensor):
     pass
 
