@@ -304,6 +304,8 @@ def ac_conv2d_i8(x, w, bias, out, stride: int, pad: int, shift: int, act: int = 
         raise ValueError("channel mismatch")
     if bias is not None and (bias.dtype is not torch.int32 or tuple(bias.shape) != (Cout,) or not bias.is_contiguous()):
         raise ValueError("bias: expected (Cout,) int32")
+    if bias is not None and not bias.is_cuda and not bias.is_pinned():
+        raise ValueError("bias: expected int32 device tensor")
     OH = (H + 2 * pad - KH) // stride + 1
     OW = (W + 2 * pad - KW) // stride + 1
     if tuple(shapes[2]) != (Nb, OH, OW, Cout):

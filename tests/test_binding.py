@@ -48,6 +48,10 @@ class OnDevice(torch.Tensor):
     is_cuda = property(lambda self: True)
 
 
+class Pinned(torch.Tensor):
+    is_pinned = lambda self: True
+
+
 class Launches:
     """A library that notes what would have been launched."""
 
@@ -86,6 +90,20 @@ def test_raw_accumulator_refuses_a_bias_it_would_read_beyond(monkeypatch):
     for good, pitch in ((i32(2)[::2], 0), (i32(5, 1), 1), (i32(5, 3)[:, 1:2], 3), (i32(1, 5).t(), 1)):  # one column: rows of one value
         call(good)
         assert lib.calls.pop()[1][5] == pitch
+
+
+def test_convolution_refuses_a_bias_in_pageable_host_memory(monkeypatch):
+    ops.native()
+    lib = Launches(monkeypatch)
+    x, w, out = (i8(*s).as_subclass(OnDevice) for s in ((1, 4, 4, 2), (3, 3, 2, 4), (1, 4, 4, 4)))
+    bias = torch.zeros(4, dtype=torch.int32)
+    for plan in (None, (64, 1)):
+        with pytest.raises(ValueError, match="bias"):
+            ops.ac_conv2d_i8(x, w, bias, out, 1, 1, 1, stream=NullStream, plan=plan)
+        assert lib.calls == []
+        for there in (bias.as_subclass(OnDevice), bias.as_subclass(Pinned)):  # the GPU reads pinned memory
+            ops.ac_conv2d_i8(x, w, there, out, 1, 1, 1, stream=NullStream, plan=plan)
+            assert lib.calls.pop()[1][2] == bias.data_ptr()
 
 
 class Sub(torch.Tensor):
