@@ -37,14 +37,15 @@ def _compile(src: str) -> str:
 
 
 def _build_binding() -> None:
-    """Needs LIB, which the binding finds beside itself; torch's own libraries are in the process before it is loaded."""
+    """Needs LIB, which the binding finds beside itself, before any in LD_LIBRARY_PATH.  It is linked by name: a path would be
+    recorded, and followed from a copy of the package too.  torch's own libraries are in the process before it is loaded."""
     import torch
 
     root = os.path.dirname(torch.__file__)
     include = [os.path.join(root, "include"), sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + [f"-I{i}" for i in include]
-    cmd += [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, LIB, "-Wl,-rpath,$ORIGIN", "-L" + os.path.join(root, "lib"),
+    cmd += [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN,--disable-new-dtags", "-L" + os.path.join(root, "lib"),
             "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

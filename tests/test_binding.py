@@ -1,4 +1,9 @@
 """The compiled binding takes plain arguments and leaves everything else to the checks of ops.py."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -104,6 +109,21 @@ def test_convolution_refuses_a_bias_in_pageable_host_memory(monkeypatch):
         for there in (bias.as_subclass(OnDevice), bias.as_subclass(Pinned)):  # the GPU reads pinned memory
             ops.ac_conv2d_i8(x, w, there, out, 1, 1, 1, stream=NullStream, plan=plan)
             assert lib.calls.pop()[1][2] == bias.data_ptr()
+
+
+def test_a_copied_package_loads_its_own_library(tmp_path):
+    """One library in the process, the one beside the binding: not also that of the tree it was built in."""
+    here = os.path.dirname(ops.LIB_PATH)
+    copy = tmp_path / os.path.basename(here)
+    copy.mkdir()
+    for name in os.listdir(here):
+        if name.endswith((".py", ".so")):
+            shutil.copy(os.path.join(here, name), copy)
+    code = f"from {copy.name} import ops; ops.native(); print(*{{l.split()[-1] for l in open('/proc/self/maps') if 'libac_mi355x' in l}})"
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True,
+                       env={**os.environ, "PYTHONPATH": str(tmp_path), "LD_LIBRARY_PATH": here + ":" + os.environ.get("LD_LIBRARY_PATH", "")})
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.split() == [str(copy / os.path.basename(ops.LIB_PATH))]
 
 
 class Sub(torch.Tensor):
