@@ -185,3 +185,24 @@ def test_pipeline_edges(M, N, K):
         Cf = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
         ops.ac_gemm_bf16(odd_view(A2), odd_view(B2), Cf)
         assert (np.abs(host(Cf) - a @ b) <= 4.0 * (K // 2 + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)) + 1e-30).all()
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (15, 40, 300), (16, 40, 300), (17, 15, 300), (40, 15, 129), (40, 16, 300), (70, 33, 15), (70, 33, 16), (9, 9, 700),  # one tile and a few
+    (210, 1200, 13), (1200, 210, 15), (40000, 9, 100), (33000, 7, 15), (1441, 1003, 15), (15, 66000, 17)])                # each tile shape
+def test_rows_of_about_a_chunk(M, N, K):
+    """Rows of a K-strided operand, and K itself, on both sides of the 16 bytes from which whole tiles need no guard."""
+    A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=M + N + K)
+    want = oracle.gemm_i8(A, B, bias, 7, 1)
+    At, Bt = np.ascontiguousarray(A.T), np.ascontiguousarray(B.T)
+    for put in (dev, odd_view):
+        for ta, tb in ((False, False), (True, False), (False, True), (True, True)):
+            C = torch.full((M, N), 33, dtype=torch.int8, device="cuda")
+            ops.ac_gemm_i8_t(put(At if ta else A), put(Bt if tb else B), dev(bias), C, 7, 1, trans_a=ta, trans_b=tb)
+            np.testing.assert_array_equal(host(C), want, err_msg=f"{put.__name__} ta={ta} tb={tb}")
+    for K2 in (7, 8, 9):  # bf16: rows of 14, 16 and 18 bytes
+        A, B = inputs.gemm_bf16_inputs(min(M, 700), min(N, 700), K2, seed=K2)
+        C = torch.full((A.shape[0], B.shape[1]), float("nan"), dtype=torch.float32, device="cuda")
+        ops.ac_gemm_bf16(odd_view(A), odd_view(B), C)
+        mag = np.abs(inputs.bf16_bits_to_f32(A).astype(np.float64)) @ np.abs(inputs.bf16_bits_to_f32(B).astype(np.float64))
+        assert (np.abs(host(C) - oracle.gemm_bf16(A, B)) <= 4.0 * (K2 + 2) * 2.0 ** -24 * mag + 1e-30).all()
