@@ -70,7 +70,7 @@ bool gemm_bf16_fast_path(const GemmParams& p) {
 
 template <bool DW>
 static hipError_t launch_gemm_bf16_dtl(GemmParams p, hipStream_t stream, const GemmPlan& plan, bool forced) {
-  if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits > 1)) return launch_kgroup<TypeBF16, KGroupF32, 0, false, false, DW>(p, stream);
+  if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits)) return launch_kgroup<TypeBF16, KGroupF32, 0, false, false, DW>(p, stream);
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
   if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order
@@ -106,7 +106,7 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
       if (plan.splits > 1) make_plan_bf16(p.K, 64, 1, &plan);
       return launch_gemm_bf16_dtl<true>(p, stream, plan, false);
     }
-    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && kgroup_ragged_takes<TypeBF16, true, false>(p, false))
+    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && kgroup_ragged_takes<TypeBF16, true, false>(p, 1))
       return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);
     return launch_ragged<TypeBF16, EpilogueF32, true, false>(forced ? plan.tile : ragged_tile(p.M, p.N), p, stream);
   }

@@ -304,7 +304,7 @@ static hipError_t launch_ragged_i8(GemmParams p, hipStream_t stream, const GemmP
   p.splits = 1;
   p.kt_per_split = 0;
   if (!forced && !ragged_tiny<TypeI8, true, false, AMODE == 1>(p) &&
-      kgroup_ragged_takes<TypeI8, true, false, AMODE == 1>(p, p.partial != nullptr && plan_gemm_i8(p.M, p.N, p.K, true, 0).splits > 1))
+      kgroup_ragged_takes<TypeI8, true, false, AMODE == 1>(p, p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1))
     return launch_kgroup_ragged<TypeI8, KGroupI8, true, false, AMODE == 1>(p, stream);
   if (!forced && p.partial != nullptr && !ragged_tiny<TypeI8, true, false, AMODE == 1>(p)) {
     const int64_t kbytes = AMODE == 1 ? (int64_t)p.KH * conv_run_padded(p) : p.K, nkt = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
@@ -382,12 +382,12 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   p.splits = 1;
   p.kt_per_split = 0;
   const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
-  if (fast && kgroup_takes<TypeI8>(p, false, false)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
+  if (fast && kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
   if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4))
-    return kgroup_takes<TypeI8>(p, false, false) ? launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream)
+    return kgroup_takes<TypeI8>(p, false, 1) ? launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream)
                                                  : launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
-  if (!ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, false)) return launch_kgroup_ragged<TypeI8, KGroupRawI32, true, false>(p, stream);
+  if (!ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, 1)) return launch_kgroup_ragged<TypeI8, KGroupRawI32, true, false>(p, stream);
   return launch_ragged<TypeI8, EpilogueRawI32, true, false>(ragged_tile(p.M, p.N), p, stream);
 }
 
@@ -395,12 +395,12 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
   const bool fast = gemm_i8_fast_path(p);
   if (!forced && fast) {
     const GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 1);
-    if ((plan.tile != 32 || kgroup_tiles(p) <= 256) && kgroup_takes<TypeI8>(p, false, plan.splits > 1)) return launch_kgroup<TypeI8, KGroupI8, 0>(p, stream);
+    if ((plan.tile != 32 || kgroup_tiles(p) <= 256) && kgroup_takes<TypeI8>(p, false, plan.splits)) return launch_kgroup<TypeI8, KGroupI8, 0>(p, stream);
   }
   if (!forced && !fast && !ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 4, 1)) {
     GemmParams q = p;
     GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 0);
-    if (kgroup_takes<TypeI8>(p, false, plan.splits > 1)) return launch_kgroup<TypeI8, KGroupI8, 0, false, false, true>(p, stream);
+    if (kgroup_takes<TypeI8>(p, false, plan.splits)) return launch_kgroup<TypeI8, KGroupI8, 0, false, false, true>(p, stream);
     int ws_bm;
     if (wstat_tile_rows(plan.tile, &ws_bm)) plan.tile = choose_tile_i8(p.M, p.N, p.K, false);
     q.splits = plan.splits;
@@ -446,9 +446,9 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
   const bool fast = conv_i8_fast_path(p);
   const bool product = p.KH == 1 && p.KW == 1 && p.stride == 1 && p.pad == 0;
   if (!forced && !product) {  // few tiles
-    const bool sliced = p.partial != nullptr && plan_gemm_i8(p.M, p.N, p.K, true, 0).splits > 1;
-    if (fast && kgroup_takes<TypeI8>(p, true, sliced)) return launch_kgroup<TypeI8, KGroupI8, 1>(p, stream);
-    if (!fast && kgroup_ragged_takes<TypeI8, true, false, true>(p, sliced)) return launch_kgroup_ragged<TypeI8, KGroupI8, true, false, true>(p, stream);
+    const int splits = p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1;
+    if (fast && kgroup_takes<TypeI8>(p, true, splits)) return launch_kgroup<TypeI8, KGroupI8, 1>(p, stream);
+    if (!fast && kgroup_ragged_takes<TypeI8, true, false, true>(p, splits)) return launch_kgroup_ragged<TypeI8, KGroupI8, true, false, true>(p, stream);
   }
   if (hipError_t e; !forced && !fast && launch_conv_image(p, stream, &e)) return e;  // channels that are not whole chunks
   if (!forced && product) {

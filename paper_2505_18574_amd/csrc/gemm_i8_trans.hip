@@ -20,7 +20,7 @@ static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   GemmParams p = p0;
   p.splits = 1;
   p.kt_per_split = 0;
-  if (kgroup_takes<TypeI8, TB>(p, false, false)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB, DW>(p, stream);
+  if (kgroup_takes<TypeI8, TA, TB>(p, false, 1)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB, DW>(p, stream);
   switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // square tiles only: the 256 x 128 code falls to 128
     case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB, DW>(p, stream);
     case 192:
@@ -59,7 +59,7 @@ hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b,
   q.kt_per_split = 0;
   auto ragged = [&](auto ta, auto tb) {
     constexpr bool AKC = !decltype(ta)::value, BKC = decltype(tb)::value;
-    if (!ragged_tiny<TypeI8, AKC, BKC, false>(q) && kgroup_ragged_takes<TypeI8, AKC, BKC>(q, false)) return launch_kgroup_ragged<TypeI8, KGroupI8, AKC, BKC>(q, stream);
+    if (!ragged_tiny<TypeI8, AKC, BKC, false>(q) && kgroup_ragged_takes<TypeI8, AKC, BKC>(q, 1)) return launch_kgroup_ragged<TypeI8, KGroupI8, AKC, BKC>(q, stream);
     return launch_ragged<TypeI8, EpilogueI8Any, AKC, BKC>(tile, q, stream);
   };
   if (trans_a && trans_b) return ragged(std::true_type{}, std::true_type{});

@@ -10,6 +10,7 @@
 // through registers (gemm_ragged.hpp).
 #pragma once
 #include "gemm_ragged.hpp"
+#include "gemm_rules.hpp"
 
 namespace ac {
 
@@ -365,27 +366,10 @@ static hipError_t launch_kgroup(const GemmParams& p, hipStream_t stream) {
   return launch_kgroup_cfg<T, OUT, 64, 8, AMODE, TA, TB, DW>(p, stream);
 }
 
-// Whether the kernel above takes a product (or, `conv`, a convolution) from the others: `sliced` says that these would cut K
-// over workgroups.  Measured on 430 random shapes per form, warm and from HBM, in us (there / here):
-//   up to 256 tiles, a round of eight-wave workgroups, it is ahead for every K the others do not cut (128 x 1024 x 3072
-//   8.9 / 5.2, 16 x 2048 x 2304 6.6 / 4.1, int32 128 x 128 x 2048 5.9 / 3.8, bf16 256 x 256 x 1024 7.0 / 3.6, 3 x 3, 256 -> 256
-//   on one 14 x 14 image 8.3 / 4.4, 256 x 64 x 128 one wave to a tile 2.8 / 2.7), and of those they do cut up to K of some 4000
-//   bytes: beyond, a compute unit's share of B is the limit, which a cut over workgroups halves (49 x 2048 x 4608 9.1 / 8.9
-//   warm, 10.7 / 14.7 from HBM, 309 x 240 x 5984 9.6 / 12.8), unless B is narrow and its lines are used whole (1750 x 16 x 4640
-//   7.8 / 4.9, 121 x 64 x 7744 7.7 / 6.2); a gather costs the others more (2 us at K = 4176, level at 9600);
-//   up to 512 tiles, two rounds of four waves each, only where K is short (2350 x 256 x 176 4.4 / 3.4, 608 x 576 x 256
-//   3.5 / 3.5, A^T 2992 x 128 x 688 4.6 / 5.1) or both operands' rows run along K (B^T 256 x 1072 x 1280 5.8 / 4.0), and not
-//   against the kernel of one wave to a tile.
-template <class T, bool TB = false>
-static bool kgroup_takes(const GemmParams& p, bool conv, bool sliced) {
-  const int64_t t = kgroup_tiles(p), kbytes = (int64_t)p.K * T::EB;
-  if (p.K < 16 || p.N < 1) return false;
-  if (t <= 256) {
-    if (!sliced) return true;
-    if (conv) return kbytes <= (p.N <= 32 ? 9600 : 7200);
-    return kbytes <= (p.N * T::EB <= 64 ? 7168 : T::EB == 2 ? 5120 : 4096);
-  }
-  return t <= 512 && kbytes <= (conv ? 2400 : TB || T::EB == 2 ? 1280 : 640);
+// Whether the kernel above takes a product (or, `conv`, a convolution) from the others, which would cut K into `splits`.
+template <class T, bool TA = false, bool TB = false>
+static bool kgroup_takes(const GemmParams& p, bool conv, int splits) {
+  return kgroup_rule({p.M, p.N, p.K, T::EB, conv, !TA, TB, p.ldb * T::EB, splits, p.partial != nullptr, p.Cin});
 }
 
 // Any size, pitch and alignment (at least 16 bytes to a row of a K-strided operand): 16-byte chunks through registers, two
@@ -520,19 +504,12 @@ static hipError_t launch_kgroup_ragged(const GemmParams& p, hipStream_t stream) 
   return kgroup_tiles(p) <= 256 ? launch_kgroup_ragged_cfg<T, OUT, 8, AKC, BKC, CONV>(p, stream) : launch_kgroup_ragged_cfg<T, OUT, 4, AKC, BKC, CONV>(p, stream);
 }
 
-// The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
-// here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x
-// 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 / 8.0), but for cut products of K beyond 3500
-// (35 x 750 x 5476 9.7 / 14.5) and convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1);
-// up to 448 with half the waves (204 x 2077 x 597 7.8 / 5.8, 3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0; 2287 x 206 x 1941
-// of 504 tiles 13.0 / 14.8), convolutions from K = 1200 on (12943 x 25 x 925 9.7 / 9.7).
+// The same question for operands of any alignment.
 template <class T, bool AKC, bool BKC, bool CONV = false>
-static bool kgroup_ragged_takes(const GemmParams& p, bool sliced) {
-  const int64_t t = kgroup_tiles(p), kbytes = (int64_t)p.K * T::EB;
-  if (kbytes < (CONV ? 200 : 16) || (CONV && (p.Cin < 1 || p.a_bytes < 16 || p.N < 1))) return false;
+static bool kgroup_ragged_takes(const GemmParams& p, int splits) {
+  if (CONV && (p.Cin < 1 || p.a_bytes < 16 || p.N < 1)) return false;
   if (!CONV && !((AKC || (int64_t)p.M * T::EB >= 16) && (BKC || (int64_t)p.N * T::EB >= 16))) return false;  // rows of K-strided operands hold a chunk
-  if (t <= 256) return !sliced || kbytes <= 3500;
-  return t <= 448 && (CONV ? kbytes >= 1200 : !sliced || kbytes <= 2048);
+  return kgroup_ragged_rule({p.M, p.N, p.K, T::EB, CONV, AKC, BKC, p.ldb * T::EB, splits, p.partial != nullptr, p.Cin});
 }
 
 }  // namespace ac

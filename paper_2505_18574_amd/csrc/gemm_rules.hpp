@@ -63,4 +63,67 @@ inline int choose_product_tile_i8(int32_t M, int32_t N, int32_t K, bool st160_ru
   return best;
 }
 
+// ---- gemm_kgroup.hpp: which calls its kernels take from the others ------------------------------------------------------
+inline int64_t tiles_of(int32_t M, int32_t N, int bm, int bn) { return (((int64_t)M + bm - 1) / bm) * (((int64_t)N + bn - 1) / bn); }
+// A product (or, `conv`, a convolution as its implicit product) and how the other kernels would run it.
+struct KGroupCall {
+  int32_t M, N, K;
+  int eb;  // bytes of an element
+  bool conv;
+  bool a_along_k, b_along_k;  // the operand's rows run along K in memory (a plain A and a B^T do)
+  int64_t b_pitch;            // bytes
+  int splits;                 // pieces that the others would cut K into over workgroups (1: none)
+  bool workspace;             // ... through a workspace; without one bf16 slices meet in atomics
+  int32_t Cin;                // conv
+};
+
+// The kernel on direct-to-LDS operands.  On 430 random shapes per form, warm and from HBM, in us (there / here):
+//   up to 256 tiles, a round of eight-wave workgroups, it is ahead for every K the others do not cut (128 x 1024 x 3072
+//   without a workspace 8.9 / 5.2, 16 x 2048 x 2304 6.6 / 4.1, int32 128 x 128 x 2048 5.9 / 3.8, bf16 256 x 256 x 1024 7.0 /
+//   3.6, 3 x 3, 256 -> 256 on one 14 x 14 image 8.3 / 4.4, 256 x 64 x 128 one wave to a tile 2.8 / 2.7);
+//   up to 512 tiles, two rounds of four waves each, only where K is short (2350 x 256 x 176 4.4 / 3.4, 608 x 576 x 256
+//   3.5 / 3.5, A^T 2992 x 128 x 688 4.6 / 5.1) or both operands' rows run along K (B^T 256 x 1072 x 1280 5.8 / 4.0), and not
+//   against the kernel of one wave to a tile.
+// Where the others would cut K, slices have more of B in flight, and what decides is where the weights come from: from HBM a
+// compute unit's whole share of B in 32-byte pieces is the limit.  The line lies where two shapes of 430 are more than a tenth
+// behind from HBM, and none is when they come from the last-level cache (slices / here, warm and from HBM: 344 x 480 x
+// 3136 9.0 / 5.9 and 11.5 / 9.1, 58 x 512 x 2144 7.1 / 3.9 and 9.7 / 8.3; given back: 16 x 4096 x 4096 8.6 / 6.0 and 11.8 /
+// 15.7, 26 x 896 x 3520 7.7 / 4.7 and 9.8 / 11.6, bf16 16 x 896 x 2432 5.8 / 4.8 and 7.2 / 9.8, 3 x 3, 512 -> 512 on a 7 x 7
+// image 7.3 / 5.7 and 9.1 / 13.1).  More tiles move it up (the slices' sums are more), eight slices down (they share B
+// further), and rows of B a multiple of 2 KB apart (bf16: 1 KB) are left to the slices (16 x 2048 x 2048 from HBM 8.3 / 9.4,
+// 16 x 2064 x 2048 9.2 / 7.9).  Where B is narrow its lines are used whole (1400 x 32 x 4352 8.6 / 4.4 and 10.1 / 8.8).
+inline bool kgroup_rule(const KGroupCall& c) {
+  const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
+  if (c.K < 16 || c.N < 1) return false;
+  if (t > 256) return t <= 512 && kbytes <= (c.conv ? 2400 : c.b_along_k || c.eb == 2 ? 1280 : 640);
+  if (c.splits <= 1) return true;
+  if (!c.workspace) return kbytes <= (row <= 64 ? 7168 : 5120);  // atomics, whose sums differ from run to run
+  if (c.conv && row <= 64) return kbytes <= (row <= 32 && t <= 4 ? 9600 : 4800);
+  if (row <= 64) return kbytes <= (t <= 2 ? 7168 : 4480);
+  if (c.splits >= 8) return false;
+  if (c.conv) return kbytes <= 7200 && kbytes <= 3392 + 10 * t;
+  if (c.b_pitch % (2048 / c.eb) == 0) return false;
+  return c.eb == 2 ? kbytes <= 5120 && kbytes <= 4288 + 8 * t : kbytes <= 4096 && kbytes <= 2912 + 8 * t;
+}
+
+// The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
+// here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x
+// 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 /
+// 8.0), but for convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1),
+// and for cut products on the line above, drawn lower here (slices / here, warm and from HBM: 25 x 1000 x 2557 8.2 / 5.7
+// and 10.5 / 10.5, 20 x 485 x 3244 8.8 / 8.2 and 11.0 / 12.9, 317 x 262 x 3123 9.7 / 10.6 and 11.9 / 12.5).
+// Up to 448 tiles with half the waves (204 x 2077 x 597 7.8 / 5.8), for convolutions from K = 1200 on (3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0, 12943 x 25 x 925 9.7 / 9.7),
+// which their slices beat where the columns are many (5 x 5, 226 -> 126 on 2160 pixels 21.4 / 31.8; 169 -> 23 on 8712 30.5 / 25.2).
+inline bool kgroup_ragged_rule(const KGroupCall& c) {
+  const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
+  if (c.conv) {
+    if (kbytes < 200) return false;
+    if (t <= 256) return c.splits <= 1 || kbytes <= 3500;
+    return t <= 448 && kbytes >= 1200 && (c.splits <= 1 || row <= 32 || kbytes <= 2400);
+  }
+  if (kbytes < 16) return false;
+  if (t <= 256) return c.splits <= 1 || (kbytes <= 3500 && (row <= 64 || kbytes <= 2432 + 6 * t));
+  return t <= 448 && (c.splits <= 1 || kbytes <= 2048);
+}
+
 }  // namespace ac

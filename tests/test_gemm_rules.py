@@ -12,6 +12,10 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = """
 #include "gemm_rules.hpp"
 extern "C" int product_tile(int M, int N, int K, int st160, int st320) { return ac::choose_product_tile_i8(M, N, K, st160, st320); }
+extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_along_k, int b_along_k, int splits, int workspace, int Cin) {
+  const ac::KGroupCall c = {M, N, K, eb, conv != 0, a_along_k != 0, b_along_k != 0, (int64_t)N * eb, splits, workspace != 0, Cin};
+  return ragged ? ac::kgroup_ragged_rule(c) : ac::kgroup_rule(c);
+}
 """
 TILE_128X256 = 129
 
@@ -40,3 +44,33 @@ def test_product_tile_shapes(rules):
         for M, N, K in product_tile.SEVERAL_TO_A_WORKGROUP:
             assert product_tile_of(rules, M, N, K, matrix) == TILE_128X256 and -(-M // 128) * -(-N // 256) > 512, (M, N, K)
     assert [product_tile_of(rules, *shape, False) for shape in product_tile.OTHER_CODES] == [320, 128]
+
+
+def shared_tile(rules, M, N, K, eb=1, conv=False, ragged=False, workspace=True, Cin=0, a_along_k=True, b_along_k=False):
+    """Whether the waves of a workgroup share the call's tiles (dense operands)."""
+    need = (ops.ac_gemm_i8_workspace_bytes if eb == 1 else ops.ac_gemm_bf16_workspace_bytes)(M, N, K)
+    splits = need // (4 * M * N) if need and (workspace or eb == 2) else 1
+    if ragged and eb == 2:
+        splits = 1  # never cut
+    return bool(rules.kgroup(ragged, M, N, K, eb, conv, a_along_k, b_along_k, splits, workspace, Cin))
+
+
+def test_shared_tiles_leave_cut_products_that_they_would_slow_down(rules):
+    """Products and convolutions that the other kernels cut over workgroups and run faster, from HBM or at all."""
+    for M, N, K in [(16, 4096, 4096), (31, 1792, 2896 + 512), (16, 2048, 2048), (128, 128, 4096), (26, 896, 3520), (235, 64, 5568), (264, 64, 6856)]:
+        assert not shared_tile(rules, M, N, K), (M, N, K)
+        assert shared_tile(rules, M, N, K, workspace=False)
+    for M, N, K in [(16, 2064, 2048), (344, 480, 3136), (58, 512, 2144), (128, 1024, 3072), (1400, 32, 4352), (49, 512, 2304)]:
+        assert shared_tile(rules, M, N, K), (M, N, K)
+    for M, N, K in [(16, 896, 2432), (60, 512, 1984), (80, 4720, 2176)]:
+        assert not shared_tile(rules, M, N, K, eb=2), (M, N, K)
+    assert shared_tile(rules, 150, 576, 1184, eb=2) and shared_tile(rules, 64, 96, 2400, eb=2, workspace=False)
+    for M, N, K in [(49, 512, 4608), (64, 256, 6272), (200, 576, 6400), (100, 64, 5040)]:
+        assert not shared_tile(rules, M, N, K, conv=True), (M, N, K)
+    assert shared_tile(rules, 196, 256, 2304, conv=True) and shared_tile(rules, 338, 64, 4176, conv=True)
+    for M, N, K in [(20, 485, 3244), (317, 262, 3123), (14, 3779, 3482)]:
+        assert not shared_tile(rules, M, N, K, ragged=True), (M, N, K)
+    assert shared_tile(rules, 25, 1000, 2557, ragged=True) and shared_tile(rules, 20, 39, 3064, ragged=True)
+    for M, N, K, Cin in [(2048, 148, 13965, 285), (1764, 237, 8624, 176), (2160, 126, 5650, 226), (5600, 36, 7007, 143)]:
+        assert not shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin), (M, N, K)
+        assert shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin, workspace=False)

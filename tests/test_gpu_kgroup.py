@@ -68,10 +68,10 @@ def test_output_stage(shift, act):
         check_i8("plain", 40, 48, K, put, shift, act, bias_matrix=True)
 
 
-@pytest.mark.parametrize("K", [3488, 4096, 4112, 7168, 7184])
+@pytest.mark.parametrize("K", [2592, 2608, 3168, 3184, 3488, 3504, 4096, 4112, 4480, 4496, 7168, 7184])
 def test_beside_a_workspace(K):
     """Products that the other kernels would cut over workgroups: both sides of the rule, same bytes."""
-    for M, N in ((40, 512), (70, 48), (35, 51)):
+    for M, N in ((40, 512), (70, 48), (17, 48), (35, 51), (40, 515)):
         A, B, bias = inputs.gemm_i8_inputs(M, N, K, seed=K + M)
         ws = torch.empty(max(16, ops.ac_gemm_i8_workspace_bytes(M, N, K)), dtype=torch.uint8, device="cuda")
         C = torch.full((M, N), 3, dtype=torch.int8, device="cuda")
