@@ -112,7 +112,9 @@ inline bool kgroup_rule(const KGroupCall& c) {
 // 8.0), but for convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1),
 // and for cut products on the line above, drawn lower here (slices / here, warm and from HBM: 25 x 1000 x 2557 8.2 / 5.7
 // and 10.5 / 10.5, 20 x 485 x 3244 8.8 / 8.2 and 11.0 / 12.9, 317 x 262 x 3123 9.7 / 10.6 and 11.9 / 12.5).
-// Up to 448 tiles with half the waves (204 x 2077 x 597 7.8 / 5.8), for convolutions from K = 1200 on (3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0, 12943 x 25 x 925 9.7 / 9.7),
+// Up to 448 tiles with half the waves, as long as two rounds of them keep up with the wider tiles there (195 x 1599 x 233 5.1 /
+// 4.3, 621 x 509 x 2394 11.7 / 13.9, A^T 361 x 1101 x 1542 11.1 / 12.7, B^T 465 x 733 x 3258 11.2 / 10.5, bf16 1383 x 293 x
+// 6769 41.5 / 44.6), for convolutions from K = 1200 on (3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0, 12943 x 25 x 925 9.7 / 9.7),
 // which their slices beat where the columns are many (5 x 5, 226 -> 126 on 2160 pixels 21.4 / 31.8; 169 -> 23 on 8712 30.5 / 25.2).
 inline bool kgroup_ragged_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
@@ -123,7 +125,10 @@ inline bool kgroup_ragged_rule(const KGroupCall& c) {
   }
   if (kbytes < 16) return false;
   if (t <= 256) return c.splits <= 1 || (kbytes <= 3500 && (row <= 64 || kbytes <= 2432 + 6 * t));
-  return t <= 448 && (c.splits <= 1 || kbytes <= 2048);
+  if (t > 448 || (c.splits > 1 && kbytes > 2048)) return false;
+  if (c.eb == 2) return kbytes <= 8192;
+  if (c.b_along_k) return c.a_along_k || kbytes <= 3500;
+  return kbytes <= (c.a_along_k ? 2200 : 1408);
 }
 
 }  // namespace ac

@@ -74,3 +74,14 @@ def test_shared_tiles_leave_cut_products_that_they_would_slow_down(rules):
     for M, N, K, Cin in [(2048, 148, 13965, 285), (1764, 237, 8624, 176), (2160, 126, 5650, 226), (5600, 36, 7007, 143)]:
         assert not shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin), (M, N, K)
         assert shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin, workspace=False)
+
+
+def test_two_rounds_of_shared_tiles_end_where_wider_tiles_are_ahead(rules):
+    """257 to 448 tiles of any alignment, K uncut: which operands' rows run along K decides how deep."""
+    forms = {"plain": (True, False), "ta": (False, False), "tb": (True, True), "tab": (False, True)}
+    for M, N, K, form, takes in [(621, 509, 2394, "plain", False), (361, 871, 8134, "plain", False), (195, 1599, 233, "plain", True),
+                                 (361, 1101, 1542, "ta", False), (387, 623, 3283, "ta", False), (194, 1737, 203, "ta", True),
+                                 (156, 1897, 6132, "tab", False), (915, 349, 3444, "tab", True), (2294, 127, 7027, "tb", True)]:
+        a, b = forms[form]
+        assert shared_tile(rules, M, N, K, ragged=True, workspace=False, a_along_k=a, b_along_k=b) == takes, (M, N, K, form)
+    assert not shared_tile(rules, 1383, 293, 6769, eb=2, ragged=True) and shared_tile(rules, 2526, 105, 3140, eb=2, ragged=True)
