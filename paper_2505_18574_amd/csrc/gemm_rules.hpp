@@ -109,7 +109,8 @@ inline bool kgroup_rule(const KGroupCall& c) {
 // The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
 // here): up to 256 tiles ahead from K of 16 bytes on (91 x 54 x 19 4.3 / 3.7 us, int32 18 x 35 x 32 4.5 / 3.3, 106 x 360 x
 // 1476 with A^T 10.1 / 5.9, 872 x 29 x 1397 8.9 / 5.9, bf16 478 x 485 x 536 7.2 / 5.5, 5 x 5, 59 -> 57 on one 13 x 13 image 15.7 /
-// 8.0), but for convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1),
+// 8.0), but for convolutions of K below 200, which conv_image.hpp does as well (64 x 22 x 153 4.9 / 5.1), up to 320 or 800 where
+// its loads are whole dwords or chunks and the columns few (3 x 3, 32 -> 6 on 6728 pixels 4.5 / 5.2, 64 -> 20 on 300 5.6 / 6.0);
 // and for cut products on the line above, drawn lower here (slices / here, warm and from HBM: 25 x 1000 x 2557 8.2 / 5.7
 // and 10.5 / 10.5, 20 x 485 x 3244 8.8 / 8.2 and 11.0 / 12.9, 317 x 262 x 3123 9.7 / 10.6 and 11.9 / 12.5).
 // Up to 448 tiles with half the waves, as long as two rounds of them keep up with the wider tiles there (195 x 1599 x 233 5.1 /
@@ -119,7 +120,7 @@ inline bool kgroup_rule(const KGroupCall& c) {
 inline bool kgroup_ragged_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.conv) {
-    if (kbytes < 200) return false;
+    if (kbytes < (row > 32 ? 200 : c.Cin % 16 == 0 ? 800 : c.Cin % 4 == 0 ? 320 : 200)) return false;
     if (t <= 256) return c.splits <= 1 || kbytes <= 3500;
     return t <= 448 && kbytes >= 1200 && (c.splits <= 1 || row <= 32 || kbytes <= 2400);
   }

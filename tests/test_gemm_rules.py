@@ -85,3 +85,9 @@ def test_two_rounds_of_shared_tiles_end_where_wider_tiles_are_ahead(rules):
         a, b = forms[form]
         assert shared_tile(rules, M, N, K, ragged=True, workspace=False, a_along_k=a, b_along_k=b) == takes, (M, N, K, form)
     assert not shared_tile(rules, 1383, 293, 6769, eb=2, ragged=True) and shared_tile(rules, 2526, 105, 3140, eb=2, ragged=True)
+
+
+def test_small_convolutions_of_few_columns_keep_the_row_copying_kernel(rules):
+    for M, N, K, Cin, takes in [(6728, 6, 288, 32, False), (640, 11, 200, 8, False), (576, 15, 300, 12, False), (300, 20, 576, 64, False),
+                                (363, 174, 245, 5, True), (1058, 21, 700, 28, True), (1863, 20, 392, 8, True), (169, 51, 600, 24, True)]:
+        assert shared_tile(rules, M, N, K, conv=True, ragged=True, workspace=False, Cin=Cin) == takes, (M, N, K)
