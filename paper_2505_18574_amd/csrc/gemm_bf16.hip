@@ -104,7 +104,7 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
     p.kt_per_split = 0;
     if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && dword_operands(p, 2, false, false, 16, 4)) {
       if (plan.splits > 1) make_plan_bf16(p.K, 64, 1, &plan);
-      return launch_gemm_bf16_dtl<true>(p, stream, plan, false);
+      if (dword_tiles(p, 2, false, false) || kgroup_takes<TypeBF16>(p, false, 1)) return launch_gemm_bf16_dtl<true>(p, stream, plan, false);
     }
     if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && kgroup_ragged_takes<TypeBF16, true, false>(p, 1))
       return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);

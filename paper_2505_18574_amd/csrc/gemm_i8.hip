@@ -384,9 +384,10 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
   if (fast && kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
-  if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4))
-    return kgroup_takes<TypeI8>(p, false, 1) ? launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream)
-                                                 : launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
+  if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4)) {
+    if (kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream);
+    if (dword_tiles(p, 1, false, false)) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
+  }
   if (!ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, 1)) return launch_kgroup_ragged<TypeI8, KGroupRawI32, true, false>(p, stream);
   return launch_ragged<TypeI8, EpilogueRawI32, true, false>(ragged_tile(p.M, p.N), p, stream);
 }
@@ -405,9 +406,11 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
     if (wstat_tile_rows(plan.tile, &ws_bm)) plan.tile = choose_tile_i8(p.M, p.N, p.K, false);
     q.splits = plan.splits;
     q.kt_per_split = plan.kt_per_split;
-    if (plan.splits <= 1) return launch_dtl_tile<TypeI8, EpilogueI8, 0, true>(plan.tile, q, stream);
-    if (const hipError_t e = launch_dtl_tile<TypeI8, EpiloguePartialI32, 0, true>(plan.tile, q, stream)) return e;
-    return launch_splitk_reduce_i8<4>(q, stream);
+    if (plan.splits > 1) {
+      if (const hipError_t e = launch_dtl_tile<TypeI8, EpiloguePartialI32, 0, true>(plan.tile, q, stream)) return e;
+      return launch_splitk_reduce_i8<4>(q, stream);
+    }
+    if (dword_tiles(p, 1, false, false)) return launch_dtl_tile<TypeI8, EpilogueI8, 0, true>(plan.tile, q, stream);
   }
   return dispatch_i8<0>(p, stream, fast, forced);
 }

@@ -44,7 +44,7 @@ hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b,
     if (trans_a) return launch_trans_dtl<true, false, false>(p, stream);
     return launch_trans_dtl<false, true, false>(p, stream);
   }
-  if (dword_operands(p, 1, trans_a, trans_b, 4, 1)) {
+  if (dword_operands(p, 1, trans_a, trans_b, 4, 1) && (dword_tiles(p, 1, trans_a, trans_b) || kgroup_rule({p.M, p.N, p.K, 1, false, !trans_a, trans_b, p.ldb, 1, false, 0}))) {
     if (trans_a && trans_b) {
       if (!ragged_tiny<TypeI8, false, true, false>(p)) return launch_trans_dtl<true, true, true>(p, stream);
     } else if (trans_a) {

@@ -372,6 +372,9 @@ static bool kgroup_takes(const GemmParams& p, bool conv, int splits) {
   return kgroup_rule({p.M, p.N, p.K, T::EB, conv, !TA, TB, p.ldb * T::EB, splits, p.partial != nullptr, p.Cin});
 }
 
+// Whether an uncut product that meets dword_operands takes gemm_dtl_kernel's DW form.
+static inline bool dword_tiles(const GemmParams& p, int eb, bool trans_a, bool trans_b) { return dword_tiles_rule(p.M, p.N, (int64_t)p.K * eb, !trans_a && trans_b); }
+
 // Any size, pitch and alignment (at least 16 bytes to a row of a K-strided operand): 16-byte chunks through registers, two
 // tiles ahead, into one padded LDS buffer per wave.  AKC, BKC, CONV as for gemm_ragged_kernel.
 template <class T, class OUT, int W, bool AKC, bool BKC, bool CONV>

@@ -132,4 +132,17 @@ inline bool kgroup_ragged_rule(const KGroupCall& c) {
   return kbytes <= (c.a_along_k ? 2200 : 1408);
 }
 
+// Whether an uncut product on operands aligned to 4 bytes (dword_operands) that the shared tiles leave takes the direct-to-LDS
+// tiles; otherwise the any-alignment kernels, in us (there / here).  Between one and two rounds of 64 x 64 tiles those have a
+// tile of 128 x 64, one to a compute unit (828 x 2276 x 4028 21.1 / 26.4, int32 904 x 1380 x 2668 13.4 / 16.6, bf16 1184 x
+// 1364 x 1610 15.7 / 18.4, A^T 816 x 1516 x 2808 14.8 / 18.3, B^T 1600 x 980 x 940 6.7 / 7.8).  Up to three rounds, the last K
+// tile of these costs more than its products (2639 x 212 x 64 3.9 / 4.2, bf16 2107 x 1120 x 36 5.8 / 6.5; 1146 x 2564 x 2076
+// 15.8 / 14.7), longest where both operands end inside a chunk (B^T 535 x 1672 x 28 3.9 / 4.4, 1564 x 536 x 772 5.5 / 6.0,
+// 3513 x 788 x 1032 level).
+inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_along_k) {
+  const int64_t t64 = tiles_of(M, N, 64, 64);
+  if (t64 > PLAN_CUS && tiles_of(M, N, 128, 64) <= PLAN_CUS) return false;
+  return t64 > 3 * PLAN_CUS || kbytes >= (both_along_k ? 1024 : 192);
+}
+
 }  // namespace ac

@@ -5,6 +5,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_dword as dword
 import test_gpu_product_tile as product_tile
 from paper_2505_18574_amd import ops
 
@@ -16,6 +17,7 @@ extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_a
   const ac::KGroupCall c = {M, N, K, eb, conv != 0, a_along_k != 0, b_along_k != 0, (int64_t)N * eb, splits, workspace != 0, Cin};
   return ragged ? ac::kgroup_ragged_rule(c) : ac::kgroup_rule(c);
 }
+extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
 
@@ -91,3 +93,20 @@ def test_small_convolutions_of_few_columns_keep_the_row_copying_kernel(rules):
     for M, N, K, Cin, takes in [(6728, 6, 288, 32, False), (640, 11, 200, 8, False), (576, 15, 300, 12, False), (300, 20, 576, 64, False),
                                 (363, 174, 245, 5, True), (1058, 21, 700, 28, True), (1863, 20, 392, 8, True), (169, 51, 600, 24, True)]:
         assert shared_tile(rules, M, N, K, conv=True, ragged=True, workspace=False, Cin=Cin) == takes, (M, N, K)
+
+
+def test_dword_products_leave_the_direct_tiles_where_the_unaligned_ones_are_ahead(rules):
+    """(M, N, bytes of K, both operands' rows along K)"""
+    for M, N, kb, both, takes in [(828, 2276, 4028, 0, False), (904, 1380, 2668, 0, False), (1420, 1032, 2560, 0, False), (1600, 980, 940, 1, False),
+                                  (2639, 212, 64, 0, False), (2107, 1120, 72, 0, False), (535, 1672, 28, 1, False), (1564, 536, 772, 1, False),
+                                  (1000, 1000, 1000, 0, True), (2584, 2040, 160, 0, True), (1146, 2564, 2076, 0, True), (5426, 4740, 148, 1, True),
+                                  (3513, 788, 1032, 1, True), (935, 2092, 3968, 1, True)]:
+        assert bool(rules.dword_tiles(M, N, kb, both)) == takes, (M, N, kb)
+
+
+def test_dword_shapes(rules):
+    for tile, shapes in dword.DIRECT_TILES.items():
+        for M, N, K in shapes:
+            assert ops.ac_gemm_i8_auto_plan(M, N, K, False) == (tile, 1), (M, N, K)
+            assert all(rules.dword_tiles(M, N, K, both) for both in (0, 1)) and not shared_tile(rules, M, N, K, workspace=False), (M, N, K)
+            assert (K % 16 or N % 16) and M % 16  # each form meets the rule's operands

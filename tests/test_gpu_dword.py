@@ -51,6 +51,18 @@ def test_forms(form, M, N, K):
     check_i8(form, M, N, K, shift=4)
 
 
+# what the product's plan and the rule for these operands choose: test_gemm_rules.py holds each shape to its tile (transposed
+# operands take 128 for 192)
+DIRECT_TILES = {64: [(556, 6560, 132), (1548, 2472, 160)], 128: [(520, 5452, 136), (5448, 328, 2088)], 192: [(708, 8900, 136), (708, 8908, 388)],
+                256: [(916, 8908, 132), (796, 9500, 292)]}
+
+
+@pytest.mark.parametrize("form", ["plain", "ta", "tb", "tab"])
+@pytest.mark.parametrize("M,N,K", [shape for shapes in DIRECT_TILES.values() for shape in shapes])
+def test_direct_tiles(form, M, N, K):
+    check_i8(form, M, N, K, shift=4)
+
+
 @pytest.mark.parametrize("form", ["plain", "tab", "i32"])
 @pytest.mark.parametrize("M,N,K", [(4100, 4108, 60), (4100, 4108, 256), (3076, 3588, 324), (12292, 1028, 260)])
 def test_wide_tiles(form, M, N, K):
