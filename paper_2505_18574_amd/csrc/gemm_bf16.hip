@@ -68,13 +68,12 @@ bool gemm_bf16_fast_path(const GemmParams& p) {
          lane_offsets_fit(2 * (int64_t)p.lda, 2 * (int64_t)p.ldb);
 }
 
-template <bool DW>
 static hipError_t launch_gemm_bf16_dtl(GemmParams p, hipStream_t stream, const GemmPlan& plan, bool forced) {
-  if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits)) return launch_kgroup<TypeBF16, KGroupF32, 0, false, false, DW>(p, stream);
+  if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits)) return launch_kgroup<TypeBF16, KGroupF32, 0>(p, stream);
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
   if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order
-    const hipError_t e = launch_dtl_tile<TypeBF16, EpiloguePartialF32, 0, DW>(plan.tile, p, stream);
+    const hipError_t e = launch_dtl_tile<TypeBF16, EpiloguePartialF32, 0>(plan.tile, p, stream);
     if (e != hipSuccess) return e;
     // one-wave workgroups for small outputs, as for the int8 combine (64 x 64 x 65536 in 128 slices: 15.3 -> 13.5 us)
     const int64_t quads = (int64_t)p.M * (p.N / 4);
@@ -88,9 +87,9 @@ static hipError_t launch_gemm_bf16_dtl(GemmParams p, hipStream_t stream, const G
     hipLaunchKernelGGL(scale_c_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (float*)p.C, p.ldc, p.M, p.N, p.beta);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_dtl_tile<TypeBF16, EpilogueAtomicF32, 0, DW>(plan.tile, p, stream);
+    return launch_dtl_tile<TypeBF16, EpilogueAtomicF32, 0>(plan.tile, p, stream);
   }
-  return launch_dtl_tile<TypeBF16, EpilogueF32, 0, DW>(plan.tile, p, stream);
+  return launch_dtl_tile<TypeBF16, EpilogueF32, 0>(plan.tile, p, stream);
 }
 
 hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const GemmPlan* forced) {
@@ -102,15 +101,16 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
     if (forced && plan.splits > 1) return hipErrorInvalidValue;
     p.splits = 1;
     p.kt_per_split = 0;
-    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && dword_operands(p, 2, false, false, 16, 4)) {
-      if (plan.splits > 1) make_plan_bf16(p.K, 64, 1, &plan);
-      if (dword_tiles(p, 2, false, false) || kgroup_takes<TypeBF16>(p, false, 1)) return launch_gemm_bf16_dtl<true>(p, stream, plan, false);
+    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p)) {
+      if (dword_operands(p, 2, false, false, 16, 4)) {
+        if (kgroup_takes<TypeBF16>(p, false, 1)) return launch_kgroup<TypeBF16, KGroupF32, 0, false, false, true>(p, stream);
+        if (dword_tiles(p, 2, false, false)) return launch_dtl_tile<TypeBF16, EpilogueF32, 0, true>(plan.splits > 1 ? 64 : plan.tile, p, stream);
+      }
+      if (kgroup_ragged_takes<TypeBF16, true, false>(p, 1)) return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);
     }
-    if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p) && kgroup_ragged_takes<TypeBF16, true, false>(p, 1))
-      return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);
     return launch_ragged<TypeBF16, EpilogueF32, true, false>(forced ? plan.tile : ragged_tile(p.M, p.N), p, stream);
   }
-  return launch_gemm_bf16_dtl<false>(p, stream, plan, forced != nullptr);
+  return launch_gemm_bf16_dtl(p, stream, plan, forced != nullptr);
 }
 
 }  // namespace ac

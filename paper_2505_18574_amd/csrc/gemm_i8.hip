@@ -303,9 +303,9 @@ static hipError_t launch_ragged_i8(GemmParams p, hipStream_t stream, const GemmP
   const int tile = forced ? forced->tile : ragged_tile(p.M, p.N);
   p.splits = 1;
   p.kt_per_split = 0;
-  if (!forced && !ragged_tiny<TypeI8, true, false, AMODE == 1>(p) &&
-      kgroup_ragged_takes<TypeI8, true, false, AMODE == 1>(p, p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1))
-    return launch_kgroup_ragged<TypeI8, KGroupI8, true, false, AMODE == 1>(p, stream);
+  if constexpr (AMODE == 0)  // (a convolution has been asked in launch_conv2d_i8)
+    if (!forced && !ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1))
+      return launch_kgroup_ragged<TypeI8, KGroupI8, true, false>(p, stream);
   if (!forced && p.partial != nullptr && !ragged_tiny<TypeI8, true, false, AMODE == 1>(p)) {
     const int64_t kbytes = AMODE == 1 ? (int64_t)p.KH * conv_run_padded(p) : p.K, nkt = (kbytes + RAGGED_KTB - 1) / RAGGED_KTB;
     const int edge = tile >= 128 ? 128 : 64;
