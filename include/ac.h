@@ -189,7 +189,8 @@ ac_status ac_conv2d_i8(const int8_t* in, const int8_t* w, const int32_t* bias, i
  * order.  Shapes with few output tiles and a deep K are cut along K (see the
  * planned launches below) where the library's estimate, the cost of the
  * combining atomic adds included, is at least a fifth below that of the best
- * uncut plan: the slices then add into C with fp32 atomic adds, and the sums
+ * uncut plan and K is beyond 2560 (operands that do not qualify for the
+ * direct-to-LDS kernels are never cut): the slices then add into C with fp32 atomic adds, and the sums
  * may differ in the last bits from run to run (ac_gemm_bf16_ws with a
  * workspace gives the same bits every run).  C must be ordinary device memory
  * as the conventions above say: the atomic adds are the hardware's own.
@@ -277,7 +278,7 @@ ac_status ac_tinympc_forward_f32(const float* Adyn, const float* Bdyn, const flo
  *           no barrier anywhere, for the accelerator-sized layers of Sections 4.4.1 and 4.4.2 whose whole
  *           launch lasts a few microseconds.  It takes operands that qualify for the direct-to-LDS kernels and
  *           K a multiple of 64, at least 64 (K slices, splits > 1, are whole 64-byte K tiles; every (tile,
- *           slice) is then a wave of its own).  ac_gemm_i8 and ac_conv2d_i8 pick it, uncut, for such operands
+ *           slice) is then a wave of its own).  ac_gemm_i8_auto_plan names it, uncut, for such operands
  *           where it measured ahead of every tiled plan: the fewer the tiles of 32 x 32, the deeper the K (up
  *           to 512 tiles K <= 1024, up to 1024 K <= 384, up to 2048 K <= 192, for a convolution K <= 640).
  *           ac_conv2d_i8_planned only: 321 / 161 = the convolution patch kernel with units of 256 / 128 output
@@ -303,7 +304,9 @@ ac_status ac_tinympc_forward_f32(const float* Adyn, const float* Bdyn, const flo
  * ac_conv2d_i8_planned is ac_conv2d_i8 with the tile and K split of its implicit GEMM (M = Nb OH OW, N = Cout,
  *           K = KH KW Cin) named by the caller; "qualify" there means 16-byte aligned in / w, Cin and Cout
  *           multiples of 16, out 4-byte aligned; workspace size from ac_gemm_i8_planned_workspace_bytes(M, N, K, ...).
- * ac_gemm_*_auto_plan report what the unplanned call would choose for a shape (pure host arithmetic).
+ * ac_gemm_*_auto_plan report a plan for a shape to start a search from (pure host arithmetic): the one the unplanned call
+ * runs, unless a kernel that no code names is ahead of it there (few output tiles: the waves of a workgroup share a
+ * 32 x 32 tile; many, int8: tiles of 128 rows x 256 columns and estimates of their own).
  * Operands that do not qualify for the direct-to-LDS kernels run on a kernel for any alignment with tiles of 64 x 64
  * and 128 x 128, which takes codes 192 and 256 as 128.
  */

@@ -137,14 +137,14 @@ def ac_gemm_bf16_planned_workspace_bytes(M: int, N: int, K: int, tile: int, spli
 
 
 def ac_gemm_i8_auto_plan(M: int, N: int, K: int, have_workspace: bool = True):
-    """(tile, splits) that ac_gemm_i8 chooses for this shape."""
+    """A (tile, splits) of ac_gemm_i8_planned for this shape, to start a search from.  ac_gemm_i8 runs it where no kernel without a code is ahead."""
     tile, splits = ctypes.c_int32(0), ctypes.c_int32(0)
     lib().ac_gemm_i8_auto_plan(M, N, K, int(bool(have_workspace)), ctypes.byref(tile), ctypes.byref(splits))
     return tile.value, splits.value
 
 
 def ac_gemm_bf16_auto_plan(M: int, N: int, K: int):
-    """(tile, splits) that ac_gemm_bf16 chooses for this shape."""
+    """A (tile, splits) of ac_gemm_bf16_planned for this shape, to start a search from.  ac_gemm_bf16 runs it where no kernel without a code is ahead."""
     tile, splits = ctypes.c_int32(0), ctypes.c_int32(0)
     lib().ac_gemm_bf16_auto_plan(M, N, K, ctypes.byref(tile), ctypes.byref(splits))
     return tile.value, splits.value

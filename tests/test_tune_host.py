@@ -108,6 +108,17 @@ def test_finalists_are_measured_again_before_the_best_is_named():
     assert res.best == (128, 1) and res.best_us == true((128, 1))
 
 
+def test_the_call_without_a_plan_is_timed_beside_the_finalists():
+    """It is no candidate, and may be faster than every one of them."""
+    prob = FakeProblem(lambda p: 3.0 if p is None else 10.0 + abs(p[0] - 128) + p[1])
+    fill = prob.reference
+    prob.reference = lambda: (prob.launched.append(None), fill())
+    prob.confirm = lambda fn: (fn(), 3.0 if prob.launched[-1] is None else 10.0 + abs(prob.launched[-1][0] - 128) + prob.launched[-1][1])[1]
+    res = tune._search(prob, None, [(64, 1)], beam=3, iterations=5, exhaustive=False)
+    assert res.best == (128, 1) and res.best_us == 11.0 and res.unplanned_us == 3.0
+    assert None not in [t.plan for t in res.trials]
+
+
 def test_beam_stops_when_no_child_improves():
     prob = FakeProblem(lambda p: 10.0 + abs(p[0] - 128) + p[1])  # (128, 1) is a strict local and global minimum
     res = tune._search(prob, None, [(128, 1)], beam=3, iterations=5, exhaustive=False)
