@@ -189,9 +189,10 @@ ac_status ac_conv2d_i8(const int8_t* in, const int8_t* w, const int32_t* bias, i
  * order.  Shapes with few output tiles and a deep K are cut along K (see the
  * planned launches below) where the library's estimate, the cost of the
  * combining atomic adds included, is at least a fifth below that of the best
- * uncut plan and K is beyond 2560 (operands that do not qualify for the
- * direct-to-LDS kernels are never cut): the slices then add into C with fp32 atomic adds, and the sums
- * may differ in the last bits from run to run (ac_gemm_bf16_ws with a
+ * uncut plan and the waves of a workgroup do not share the tiles (they do on
+ * up to 256 tiles of 32 x 32 to K = 2560; operands that do not qualify for the
+ * direct-to-LDS kernels are never cut): the slices then add into C with fp32
+ * atomic adds, and the sums may differ in the last bits from run to run (ac_gemm_bf16_ws with a
  * workspace gives the same bits every run).  C must be ordinary device memory
  * as the conventions above say: the atomic adds are the hardware's own.
  */
