@@ -103,7 +103,7 @@ inline bool kgroup_rule(const KGroupCall& c) {
   if (c.splits >= 8) return false;
   if (c.conv) return kbytes <= 7200 && kbytes <= 3392 + 10 * t;
   if (c.b_pitch % (2048 / c.eb) == 0) return false;
-  return c.eb == 2 ? kbytes <= 5120 && kbytes <= 4288 + 8 * t : kbytes <= 4096 && kbytes <= 2912 + 8 * t;
+  return c.eb == 2 ? kbytes <= 5120 && kbytes <= 3712 + 8 * t : kbytes <= 4096 && kbytes <= 2912 + 8 * t;
 }
 
 // The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /
@@ -116,13 +116,14 @@ inline bool kgroup_rule(const KGroupCall& c) {
 // Up to 448 tiles with half the waves, as long as two rounds of them keep up with the wider tiles there (195 x 1599 x 233 5.1 /
 // 4.3, 621 x 509 x 2394 11.7 / 13.9, A^T 361 x 1101 x 1542 11.1 / 12.7, B^T 465 x 733 x 3258 11.2 / 10.5, bf16 1383 x 293 x
 // 6769 41.5 / 44.6), for convolutions from K = 1200 on (3 x 3, 54 -> 54 on 6075 pixels 15.0 / 12.0, 12943 x 25 x 925 9.7 / 9.7),
-// which their slices beat where the columns are many (5 x 5, 226 -> 126 on 2160 pixels 21.4 / 31.8; 169 -> 23 on 8712 30.5 / 25.2).
+// 2400 with whole chunks (5 x 5, 48 -> 198 on 1600 9.2 / 11.9), which their slices beat where the columns are many or K is deep (5 x
+// 5, 226 -> 126 on 2160 pixels 21.4 / 31.8; 169 -> 23 on 8712 30.5 / 25.2; 7 x 7, 193 -> 15 on 11236, K = 9457, 35.4 / 40.5).
 inline bool kgroup_ragged_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.conv) {
     if (kbytes < (row > 32 ? 200 : c.Cin % 16 == 0 ? 800 : c.Cin % 4 == 0 ? 320 : 200)) return false;
     if (t <= 256) return c.splits <= 1 || kbytes <= 3500;
-    return t <= 448 && kbytes >= 1200 && (c.splits <= 1 || row <= 32 || kbytes <= 2400);
+    return t <= 448 && kbytes >= (c.Cin % 16 == 0 ? 2400 : 1200) && (c.splits <= 1 || kbytes <= (row <= 32 ? 4500 : 2400));
   }
   if (kbytes < 16) return false;
   if (t <= 256) return c.splits <= 1 || (kbytes <= 3500 && (row <= 64 || kbytes <= 2432 + 6 * t));
@@ -135,14 +136,14 @@ inline bool kgroup_ragged_rule(const KGroupCall& c) {
 // Whether an uncut product on operands aligned to 4 bytes (dword_operands) that the shared tiles leave takes the direct-to-LDS
 // tiles; otherwise the any-alignment kernels, in us (there / here).  Between one and two rounds of 64 x 64 tiles those have a
 // tile of 128 x 64, one to a compute unit (828 x 2276 x 4028 21.1 / 26.4, int32 904 x 1380 x 2668 13.4 / 16.6, bf16 1184 x
-// 1364 x 1610 15.7 / 18.4, A^T 816 x 1516 x 2808 14.8 / 18.3, B^T 1600 x 980 x 940 6.7 / 7.8).  Up to three rounds, the last K
-// tile of these costs more than its products (2639 x 212 x 64 3.9 / 4.2, bf16 2107 x 1120 x 36 5.8 / 6.5; 1146 x 2564 x 2076
-// 15.8 / 14.7), longest where both operands end inside a chunk (B^T 535 x 1672 x 28 3.9 / 4.4, 1564 x 536 x 772 5.5 / 6.0,
-// 3513 x 788 x 1032 level).
+// 1364 x 1610 15.7 / 18.4, A^T 816 x 1516 x 2808 14.8 / 18.3, B^T 1600 x 980 x 940 6.7 / 7.8).  Up to three tiles to a compute
+// unit, the last K tile of these costs more than its products (2639 x 212 x 64 3.9 / 4.2, bf16 2107 x 1120 x 36 5.8 / 6.5; 1146 x
+// 2564 x 2076 15.8 / 14.7), and longer, up to four, where both operands end inside a chunk (B^T 535 x 1672 x 28 3.9 / 4.4,
+// 1564 x 536 x 772 5.5 / 6.0, 7077 x 460 x 156 6.1 / 6.7, 3513 x 788 x 1032 level).
 inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_along_k) {
   const int64_t t64 = tiles_of(M, N, 64, 64);
   if (t64 > PLAN_CUS && tiles_of(M, N, 128, 64) <= PLAN_CUS) return false;
-  return t64 > 3 * PLAN_CUS || kbytes >= (both_along_k ? 1024 : 192);
+  return both_along_k ? t64 > 4 * PLAN_CUS || kbytes >= 1024 : t64 > 3 * PLAN_CUS || kbytes >= 192;
 }
 
 }  // namespace ac

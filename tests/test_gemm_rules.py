@@ -64,7 +64,7 @@ def test_shared_tiles_leave_cut_products_that_they_would_slow_down(rules):
         assert shared_tile(rules, M, N, K, workspace=False)
     for M, N, K in [(16, 2064, 2048), (344, 480, 3136), (58, 512, 2144), (128, 1024, 3072), (1400, 32, 4352), (49, 512, 2304)]:
         assert shared_tile(rules, M, N, K), (M, N, K)
-    for M, N, K in [(16, 896, 2432), (60, 512, 1984), (80, 4720, 2176)]:
+    for M, N, K in [(16, 896, 2432), (60, 512, 1984), (23, 336, 2176), (93, 208, 2064)]:
         assert not shared_tile(rules, M, N, K, eb=2), (M, N, K)
     assert shared_tile(rules, 150, 576, 1184, eb=2) and shared_tile(rules, 64, 96, 2400, eb=2, workspace=False)
     for M, N, K in [(49, 512, 4608), (64, 256, 6272), (200, 576, 6400), (100, 64, 5040)]:
@@ -73,7 +73,7 @@ def test_shared_tiles_leave_cut_products_that_they_would_slow_down(rules):
     for M, N, K in [(20, 485, 3244), (317, 262, 3123), (14, 3779, 3482)]:
         assert not shared_tile(rules, M, N, K, ragged=True), (M, N, K)
     assert shared_tile(rules, 25, 1000, 2557, ragged=True) and shared_tile(rules, 20, 39, 3064, ragged=True)
-    for M, N, K, Cin in [(2048, 148, 13965, 285), (1764, 237, 8624, 176), (2160, 126, 5650, 226), (5600, 36, 7007, 143)]:
+    for M, N, K, Cin in [(2048, 148, 13965, 285), (1764, 237, 8624, 176), (2160, 126, 5650, 226), (5600, 36, 7007, 143), (11236, 15, 9457, 193)]:
         assert not shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin), (M, N, K)
         assert shared_tile(rules, M, N, K, conv=True, ragged=True, Cin=Cin, workspace=False)
 
@@ -91,14 +91,14 @@ def test_two_rounds_of_shared_tiles_end_where_wider_tiles_are_ahead(rules):
 
 def test_small_convolutions_of_few_columns_keep_the_row_copying_kernel(rules):
     for M, N, K, Cin, takes in [(6728, 6, 288, 32, False), (640, 11, 200, 8, False), (576, 15, 300, 12, False), (300, 20, 576, 64, False),
-                                (363, 174, 245, 5, True), (1058, 21, 700, 28, True), (1863, 20, 392, 8, True), (169, 51, 600, 24, True)]:
+                                (363, 174, 245, 5, True), (1058, 21, 700, 28, True), (1863, 20, 392, 8, True), (169, 51, 600, 24, True), (1600, 198, 1200, 48, False), (6075, 54, 1210, 54, True)]:
         assert shared_tile(rules, M, N, K, conv=True, ragged=True, workspace=False, Cin=Cin) == takes, (M, N, K)
 
 
 def test_dword_products_leave_the_direct_tiles_where_the_unaligned_ones_are_ahead(rules):
     """(M, N, bytes of K, both operands' rows along K)"""
     for M, N, kb, both, takes in [(828, 2276, 4028, 0, False), (904, 1380, 2668, 0, False), (1420, 1032, 2560, 0, False), (1600, 980, 940, 1, False),
-                                  (2639, 212, 64, 0, False), (2107, 1120, 72, 0, False), (535, 1672, 28, 1, False), (1564, 536, 772, 1, False),
+                                  (2639, 212, 64, 0, False), (2107, 1120, 72, 0, False), (535, 1672, 28, 1, False), (1564, 536, 772, 1, False), (7077, 460, 156, 1, False),
                                   (1000, 1000, 1000, 0, True), (2584, 2040, 160, 0, True), (1146, 2564, 2076, 0, True), (5426, 4740, 148, 1, True),
                                   (3513, 788, 1032, 1, True), (935, 2092, 3968, 1, True)]:
         assert bool(rules.dword_tiles(M, N, kb, both)) == takes, (M, N, kb)

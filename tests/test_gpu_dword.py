@@ -53,7 +53,7 @@ def test_forms(form, M, N, K):
 
 # what the product's plan and the rule for these operands choose: test_gemm_rules.py holds each shape to its tile (transposed
 # operands take 128 for 192)
-DIRECT_TILES = {64: [(556, 6560, 132), (1548, 2472, 160)], 128: [(520, 5452, 136), (5448, 328, 2088)], 192: [(708, 8900, 136), (708, 8908, 388)],
+DIRECT_TILES = {64: [(556, 8284, 128), (524, 8372, 152)], 128: [(788, 8432, 140), (5448, 328, 2088)], 192: [(708, 8900, 136), (708, 8908, 388)],
                 256: [(916, 8908, 132), (796, 9500, 292)]}
 
 
