@@ -1,7 +1,7 @@
 // Native side of ops.py: reads the tensors and calls the C ABI (include/ac.h) in one step.
 //
-// On this path a launch takes the GPU no longer than argument checks in Python take the host: of the 6.2 us that a call
-// of a few-microsecond kernel cost there, 2.4 are the runtime's launch; through these functions a call is 3.1 us.
+// On this path a launch takes the GPU no longer than argument checks in Python take the host: of the 6.6 us that a call
+// of a few-microsecond kernel cost there, 2.6 are the runtime's launch; through these functions a call is 3.4 us.
 //
 // Every function takes the arguments of its namesake in ops.py, all of them, in order, and returns the ac_status of the
 // call, or PYTHON where an argument is not of the plain kind that is read here (an exact torch.Tensor of the right type,

@@ -86,9 +86,9 @@ struct GemmParams {
   int32_t* partial;      // int8: [splits][M][N] int32 partial sums when splits > 1
 };
 
-// What the kernels of small launches receive.  Up to 112 bytes of kernel arguments a launch costs the host 2.8 us, beyond
-// 3.5 (measured from 60 to 512 bytes, in steps of 8 around the border): a fifth of a small call.  The same names as in
-// GemmParams; band_magic: multiplier of the kernel's tile order (0: divide).
+// What the kernels of small launches receive.  Up to 112 bytes of kernel arguments a launch costs the host 2.6 to 2.7 us,
+// 2.8 to 3.0 to 208 and 3.1 to 3.2 at 256 (an empty kernel, one host thread, the HIP runtime that torch loads; ROCm 7.2's
+// own 2.4 and 2.5): a tenth of a small call.  The same names as in GemmParams; band_magic: multiplier of the kernel's tile order (0: divide).
 struct GemmArgs {
   const void *A, *B;
   void* C;
@@ -125,7 +125,7 @@ struct ConvArgs {
 struct ConvArgsWide : GemmParams {
   unsigned band_magic;
 };
-static_assert(sizeof(GemmArgs) <= 112 && sizeof(ConvArgs) <= 112, "beyond, a launch costs a fifth more");
+static_assert(sizeof(GemmArgs) <= 112 && sizeof(ConvArgs) <= 112, "beyond, a launch costs more");
 
 // The arguments of a kernel on operands of type T from the host's descriptor.
 template <class ARGS, class T>
@@ -199,8 +199,9 @@ GemmPlan plan_gemm_bf16(int32_t M, int32_t N, int32_t K);
 bool tile_dims(int32_t tile, int* bm, int* bn);
 // Tile code the library picks for an M x N output when nothing else is known (convolutions, fallbacks).
 int choose_tile(int32_t M, int32_t N);
-// Kernel / tile code for a GEMM with more than 256 tiles of 64 x 64 (more than the chip holds at once), from
-// per-code time estimates  t = c0 + rounds * (c1 + c2 * k)  with k = K bytes / 128 and rounds = the number of
+// Kernel / tile code for a GEMM with more than 256 tiles of 64 x 64 (more than the chip holds at once): of a plan, of
+// transposed operands, of products on dwords and of bf16 (an int8 product without a plan has estimates of its own,
+// choose_product_tile_i8).  From per-code time estimates  t = c0 + rounds * (c1 + c2 * k)  with k = K bytes / 128 and rounds = the number of
 // times the code's workgroups fill the chip (tiled codes), or  t = c0 + rounds * (c1 k + c2 r + c3 r k)  with r =
 // row tiles per workgroup (the weight-stationary codes, int8 only, where K and the bias layout admit them).  The
 // coefficients are least-squares fits to the measured times of every code on some 300 int8 and 200 bf16 shapes
@@ -261,7 +262,7 @@ bool gemm_i8_fast_path(const GemmParams& p);
 // direct-to-LDS kernels' DW form; `c_align`: what the output's rows must be aligned to.  Beside the any-alignment kernels,
 // which move such operands through registers (us there / here): up to 256 tiles of 32 x 32 4.0-4.4 / 3.1-3.4 for K up to some
 // 300, 60 x 608 x 1176 with A^T 5.0 / 3.8, bf16 184 x 84 x 572 4.7 / 3.7; beyond them 604 x 1276 x 1384 9.2 / 8.2, 1000^3
-// 7.3 / 6.7, 520 x 4224 x 320 with A^T and B^T 7.1 / 6.2, bf16 1000 x 436 x 596 6.9 / 5.9, 4792 x 384 x 64 with both 4.7 / 4.8.
+// 7.3 / 6.7, 520 x 4224 x 320 with A^T and B^T 7.1 / 6.2, bf16 1000 x 436 x 596 6.9 / 5.9, where dword_tiles_rule says so.
 inline bool dword_operands(const GemmParams& p, int eb, bool trans_a, bool trans_b, int c_align, int c_bytes) {
   const int64_t a_ext = (int64_t)(trans_a ? p.M : p.K) * eb, b_ext = (int64_t)(trans_b ? p.K : p.N) * eb;
   return (((uintptr_t)p.A | (uintptr_t)p.B) & 3) == 0 && p.lda * eb % 4 == 0 && p.ldb * eb % 4 == 0 && a_ext % 4 == 0 && b_ext % 4 == 0 &&

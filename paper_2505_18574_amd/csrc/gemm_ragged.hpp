@@ -1,6 +1,6 @@
 // Tiled MFMA GEMM / implicit-GEMM convolution for operands of any size, pitch and alignment: whatever the
-// direct-to-LDS kernels (gemm_dtl.hpp) do not take, beyond the few tiles that gemm_kgroup.hpp shares.  int8 and bf16, either operand transposed in memory, and
-// convolutions with any channel count.
+// direct-to-LDS kernels (gemm_dtl.hpp) do not take, beyond the few tiles that gemm_kgroup.hpp shares.  int8 and bf16, either
+// operand transposed in memory, and convolutions with any channel count.
 //
 // Every 16-byte chunk of an operand tile comes in with ONE vector load, wherever it starts (a vector load takes any
 // byte address; a chunk fetched byte by byte is sixteen loads and as many waits on the address unit, which is what
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_ragged_kernel(con
   }
 }
 
-// (with K contiguous in both operands that is K; of a convolution, nothing is asked)
+// Whether a row of either operand in memory is at least 16 bytes (where K is contiguous, that is K).
 template <class T, bool AKC, bool BKC>
 static bool ragged_long_rows(const GemmParams& p) {
   return (int64_t)(AKC ? p.K : p.M) * T::EB >= 16 && (int64_t)(BKC ? p.K : p.N) * T::EB >= 16;

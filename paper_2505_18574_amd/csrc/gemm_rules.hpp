@@ -36,8 +36,10 @@ inline double stationary_estimate(const StationaryCost& c, int bm, int32_t M, in
 // half held out of a fit the choice is 0.8 % over the best code).  Three stages of 64 bytes of K leave the 128 x 256 tile
 // its 72 KB, and rows of C twice as long; the older estimates also put K = 350 .. 800 too low on the weight-stationary
 // kernel.  3302 x 1296 x 496 12.3 -> 7.9 us (stationary before), 5676 x 640 x 512 8.7 -> 5.8 (128 x 128 now), 5788 x 960 x
-// 192 8.0 -> 6.0, 8192 x 100000 x 80 466 -> 376; over 70 shapes of those ranges outside the fit 0.953 of the time (worst 1776 x
-// 4560 x 5248 46.6 -> 48.5), over 80 of 8192 .. 900000 rows or columns 0.966 (worst 40811 x 128 x 864 13.7 -> 14.8).
+// 192 8.0 -> 6.0, 8192 x 100000 x 80 466 -> 376; over 70 shapes of those ranges outside the fit 0.953 of the time, over 80 of
+// 8192 .. 900000 rows or columns 0.966.  Against the kernels and estimates before both, the worst of 114 shapes are 5823 x
+// 5696 x 128 19.2 -> 19.9 and 7522 x 3680 x 96 15.2 -> 15.4; the 256 x 128 tile it gave up would still be 2 to 5 % ahead on
+// 40811 x 128 x 864 (12.2 and 12.8) and 1776 x 4560 x 5248 (43.0 and 44.0).
 // st160_runs, st320_runs: whether the weight-stationary codes may run it (wstat_eligible).
 constexpr int TILE_128X256 = 129;  // not a plan's code: this choice alone makes it
 inline int choose_product_tile_i8(int32_t M, int32_t N, int32_t K, bool st160_runs, bool st320_runs) {
