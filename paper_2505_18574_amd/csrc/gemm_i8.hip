@@ -396,7 +396,7 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
   const bool fast = gemm_i8_fast_path(p);
   if (!forced && fast) {
     const GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 1);
-    if ((plan.tile != 32 || kgroup_tiles(p) <= 256) && kgroup_takes<TypeI8>(p, false, plan.splits)) return launch_kgroup<TypeI8, KGroupI8, 0>(p, stream);
+    if ((plan.tile != 32 || kgroup_instead_of_one_wave(p.M, p.N, p.K)) && kgroup_takes<TypeI8>(p, false, plan.splits)) return launch_kgroup<TypeI8, KGroupI8, 0>(p, stream);
   }
   if (!forced && !fast && !ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 4, 1)) {
     GemmParams q = p;

@@ -84,8 +84,10 @@ struct KGroupCall {
 //   without a workspace 8.9 / 5.2, 16 x 2048 x 2304 6.6 / 4.1, int32 128 x 128 x 2048 5.9 / 3.8, bf16 256 x 256 x 1024 7.0 /
 //   3.6, 3 x 3, 256 -> 256 on one 14 x 14 image 8.3 / 4.4, 256 x 64 x 128 one wave to a tile 2.8 / 2.7);
 //   up to 512 tiles, two rounds of four waves each, only where K is short (2350 x 256 x 176 4.4 / 3.4, 608 x 576 x 256
-//   3.5 / 3.5, A^T 2992 x 128 x 688 4.6 / 5.1) or both operands' rows run along K (B^T 256 x 1072 x 1280 5.8 / 4.0), and not
-//   against the kernel of one wave to a tile.
+//   3.5 / 3.5, 224 x 1920 x 624 4.3 / 4.5), shorter where no operand's rows run along it (A^T 64 x 5584 x 336 3.8 / 3.7, 1328 x
+//   352 x 448 4.0 / 4.6), longer where both operands' do (B^T 256 x 1072 x 1280 5.8 / 4.0);
+//   against the kernel of one wave to a tile up to 256 tiles, but for a few tiles of one K tile, where one wave has all the work
+//   (57 x 64 x 64 2.5 / 2.65, 30 x 64 x 256 2.7 / 2.5, 100 x 256 x 64 3.0 / 2.7).
 // Where the others would cut K, slices have more of B in flight, and what decides is where the weights come from: from HBM a
 // compute unit's whole share of B in 32-byte pieces is the limit.  The line lies where two shapes of 430 are more than a tenth
 // behind from HBM, and none is when they come from the last-level cache (slices / here, warm and from HBM: 344 x 480 x
@@ -97,7 +99,7 @@ struct KGroupCall {
 inline bool kgroup_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.K < 16 || c.N < 1) return false;
-  if (t > 256) return t <= 512 && kbytes <= (c.conv ? 2400 : c.b_along_k || c.eb == 2 ? 1280 : 640);
+  if (t > 256) return t <= 512 && kbytes <= (c.conv ? 2400 : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
   if (c.splits <= 1) return true;
   if (!c.workspace) return kbytes <= (row <= 64 ? 7168 : 5120);  // atomics, whose sums differ from run to run
   if (c.conv && row <= 64) return kbytes <= (row <= 32 && t <= 4 ? 9600 : 4800);
@@ -106,6 +108,11 @@ inline bool kgroup_rule(const KGroupCall& c) {
   if (c.conv) return kbytes <= 7200 && kbytes <= 3392 + 10 * t;
   if (c.b_pitch % (2048 / c.eb) == 0) return false;
   return c.eb == 2 ? kbytes <= 5120 && kbytes <= 3712 + 8 * t : kbytes <= 4096 && kbytes <= 2912 + 8 * t;
+}
+
+inline bool kgroup_instead_of_one_wave(int32_t M, int32_t N, int32_t K) {
+  const int64_t t = tiles_of(M, N, 32, 32);
+  return t <= 256 && (K > 64 || t > 16);
 }
 
 // The same question for operands of any alignment, whose other kernels cost a K tile 0.26 us.  On 200 random shapes (there /

@@ -17,6 +17,7 @@ extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_a
   const ac::KGroupCall c = {M, N, K, eb, conv != 0, a_along_k != 0, b_along_k != 0, (int64_t)N * eb, splits, workspace != 0, Cin};
   return ragged ? ac::kgroup_ragged_rule(c) : ac::kgroup_rule(c);
 }
+extern "C" int one_wave(int M, int N, int K) { return !ac::kgroup_instead_of_one_wave(M, N, K); }
 extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
@@ -87,6 +88,12 @@ def test_two_rounds_of_shared_tiles_end_where_wider_tiles_are_ahead(rules):
         a, b = forms[form]
         assert shared_tile(rules, M, N, K, ragged=True, workspace=False, a_along_k=a, b_along_k=b) == takes, (M, N, K, form)
     assert not shared_tile(rules, 1383, 293, 6769, eb=2, ragged=True) and shared_tile(rules, 2526, 105, 3140, eb=2, ragged=True)
+
+
+def test_shared_tiles_where_k_is_short(rules):
+    assert [rules.one_wave(*s) for s in [(57, 64, 64), (190, 64, 64), (30, 64, 256), (100, 256, 64), (256, 256, 256), (700, 400, 64)]] == [1, 1, 0, 0, 0, 1]
+    assert shared_tile(rules, 64, 5584, 336, a_along_k=False) and not shared_tile(rules, 1328, 352, 448, a_along_k=False)
+    assert shared_tile(rules, 528, 736, 432) and not shared_tile(rules, 224, 1920, 624)
 
 
 def test_small_convolutions_of_few_columns_keep_the_row_copying_kernel(rules):

@@ -47,7 +47,8 @@ def check_i8(form, M, N, K, put=dev, shift=9, act=1, bias_matrix=False):
     (64, 32, 512), (80, 16, 528),                              # four waves, then eight
     (48, 48, 1040), (32, 16, 1600), (16, 64, 3264),            # K tiles per wave: two and three, and a partial one
     (32, 48, 4848), (32, 48, 4864), (16, 32, 5008),            # 64- and 128-byte K tiles
-    (512, 512, 576), (528, 512, 576), (544, 512, 640), (544, 512, 656)])  # 256 and 272 tiles
+    (512, 512, 576), (528, 512, 576), (544, 512, 640), (544, 512, 656),  # 256 and 272 tiles
+    (528, 512, 352), (528, 512, 368), (528, 512, 608), (528, 512, 624), (57, 64, 64), (128, 128, 64), (160, 128, 64)])
 def test_aligned(form, M, N, K):
     check_i8(form, M, N, K)
 
