@@ -115,7 +115,8 @@ ac_status gemm_i8_entry(const int8_t* A, int64_t lda, const int8_t* B, int64_t l
   ac::GemmPlan plan;
   if (planned && !ac::make_plan_i8(K, tile, splits, &plan)) return AC_ERR_PLAN;
   if ((workspace == nullptr) != (workspace_bytes == 0)) return AC_ERR_WORKSPACE;
-  const size_t need = planned ? ac_gemm_i8_planned_workspace_bytes(M, N, K, tile, splits) : ac_gemm_i8_workspace_bytes(M, N, K);
+  // the library's plan is asked for its partial sums only where there is, or has to be, room for them (0.1 us of a call)
+  const size_t need = planned ? ac_gemm_i8_planned_workspace_bytes(M, N, K, tile, splits) : workspace || static_workspace ? ac_gemm_i8_workspace_bytes(M, N, K) : 0;
   if (workspace && (((uintptr_t)workspace & 15) != 0 || workspace_bytes < need)) return AC_ERR_WORKSPACE;
   if (planned && need > 0 && !workspace) return AC_ERR_WORKSPACE;
   if (static_workspace && need > AC_STATIC_SCRATCH_BYTES) return AC_ERR_WORKSPACE;  // partial sums beyond the library's own buffer
@@ -152,7 +153,7 @@ ac_status gemm_bf16_entry(const uint16_t* A, int64_t lda, const uint16_t* B, int
   ac::GemmPlan plan;
   if (planned && !ac::make_plan_bf16(K, tile, splits, &plan)) return AC_ERR_PLAN;
   if ((workspace == nullptr) != (workspace_bytes == 0)) return AC_ERR_WORKSPACE;
-  const size_t need = planned ? ac_gemm_bf16_planned_workspace_bytes(M, N, K, tile, splits) : ac_gemm_bf16_workspace_bytes(M, N, K);
+  const size_t need = planned ? ac_gemm_bf16_planned_workspace_bytes(M, N, K, tile, splits) : workspace ? ac_gemm_bf16_workspace_bytes(M, N, K) : 0;
   if (workspace && (((uintptr_t)workspace & 15) != 0 || workspace_bytes < need)) return AC_ERR_WORKSPACE;
   ac::GemmParams p = {};
   p.A = A; p.B = B; p.C = C;
@@ -253,7 +254,7 @@ static ac_status conv2d_i8_entry(const int8_t* in, const int8_t* w, const int32_
   if (planned && !ac::make_plan_i8((int32_t)K, tile, splits, &plan)) return AC_ERR_PLAN;
   if ((workspace == nullptr) != (workspace_bytes == 0)) return AC_ERR_WORKSPACE;
   const size_t need = planned ? ac_gemm_i8_planned_workspace_bytes((int32_t)M, Cout, (int32_t)K, tile, splits)
-                              : ac_gemm_i8_workspace_bytes((int32_t)M, Cout, (int32_t)K);
+                              : workspace ? ac_gemm_i8_workspace_bytes((int32_t)M, Cout, (int32_t)K) : 0;
   if (workspace && (((uintptr_t)workspace & 15) != 0 || workspace_bytes < need)) return AC_ERR_WORKSPACE;
   if (planned && need > 0 && !workspace) return AC_ERR_WORKSPACE;
   if (M == 0 || Cout == 0) return AC_OK;

@@ -277,8 +277,7 @@ static hipError_t launch_batched_fixed(const BatchedParams& p, hipStream_t strea
   static_assert(F::LDS <= 64 * 1024 && F::G * N % 4 == 0, "LDS and whole chunks");
   const int64_t blocks = (p.batch + F::G - 1) / F::G;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(batched_fixed_kernel<N>, dim3((unsigned)blocks), dim3(256), F::LDS, stream, p);
-  return hipGetLastError();
+  return launch_kernel(batched_fixed_kernel<N>, dim3((unsigned)blocks), dim3(256), F::LDS, stream, p);
 }
 
 // ---- 12 x 12 streaming kernel -----------------------------------------------------------------------------
@@ -437,8 +436,7 @@ hipError_t launch_batched_f32(const BatchedParams& p, hipStream_t stream) {
     const int64_t ngroups = (p.batch + B12_GROUP - 1) / B12_GROUP;
     int64_t wgs = (ngroups + B12_WAVES - 1) / B12_WAVES;
     if (wgs > (int64_t)cus * WGS_PER_CU) wgs = (int64_t)cus * WGS_PER_CU;
-    hipLaunchKernelGGL(batched12_stream_kernel, dim3((unsigned)wgs), dim3(64 * B12_WAVES), B12_WAVES * 3 * B12_WIN, stream, p);
-    return hipGetLastError();
+    return launch_kernel(batched12_stream_kernel, dim3((unsigned)wgs), dim3(64 * B12_WAVES), B12_WAVES * 3 * B12_WIN, stream, p);
   }
   if (vec) {
     switch (n) {
@@ -466,9 +464,8 @@ hipError_t launch_batched_f32(const BatchedParams& p, hipStream_t stream) {
   const int64_t blocks = (p.batch + G - 1) / G;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   dim3 grid((unsigned)blocks), block(256);
-  if (n == 12) hipLaunchKernelGGL((batched_f32_kernel<12, 32>), grid, block, lds, stream, p);
-  else hipLaunchKernelGGL((batched_f32_kernel<0, 16>), grid, block, lds, stream, p);
-  return hipGetLastError();
+  if (n == 12) return launch_kernel(batched_f32_kernel<12, 32>, grid, block, lds, stream, p);
+  return launch_kernel(batched_f32_kernel<0, 16>, grid, block, lds, stream, p);
 }
 
 }  // namespace ac

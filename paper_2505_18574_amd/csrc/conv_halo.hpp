@@ -406,8 +406,7 @@ static hipError_t launch_conv_halo_nks(const GemmParams& p, const ConvHaloParams
   int wgs = cus / n_blocks;
   if (wgs < 1) wgs = 1;
   if (wgs > h.units) wgs = h.units;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(wgs * n_blocks)), dim3(512), lds, stream, p, h, n_blocks);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)(wgs * n_blocks)), dim3(512), lds, stream, p, h, n_blocks);
 }
 
 // K depths with a register-resident-weights instantiation: 3 x 3 taps of 32 / 64 channels, 1 x 1 of 64 .. 256.

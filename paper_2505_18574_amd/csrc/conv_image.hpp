@@ -308,8 +308,7 @@ static hipError_t launch_conv_image_form(const GemmParams& p, const ConvImagePar
   int64_t wgs = per_cu * compute_units() / n_blocks;
   if (wgs < 1) wgs = 1;
   if (wgs > h.units) wgs = h.units;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(wgs * n_blocks)), dim3(2 * CONV_IMAGE_BM), lds, stream, p, h, n_blocks);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)(wgs * n_blocks)), dim3(2 * CONV_IMAGE_BM), lds, stream, p, h, n_blocks);
 }
 
 template <int BN>

@@ -78,14 +78,12 @@ static hipError_t launch_gemm_bf16_dtl(GemmParams p, hipStream_t stream, const G
     // one-wave workgroups for small outputs, as for the int8 combine (64 x 64 x 65536 in 128 slices: 15.3 -> 13.5 us)
     const int64_t quads = (int64_t)p.M * (p.N / 4);
     const GemmArgs args = kernel_args<GemmArgs, TypeBF16>(p);
-    if (quads <= 32768) hipLaunchKernelGGL(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, args);
-    else hipLaunchKernelGGL(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, args);
-    return hipGetLastError();
+    if (quads <= 32768) return launch_kernel(splitk_reduce_f32_kernel<64>, dim3((unsigned)((quads + 63) / 64)), dim3(64), 0, stream, args);
+    return launch_kernel(splitk_reduce_f32_kernel<256>, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, args);
   }
   if (plan.splits > 1) {  // no workspace: slices add into C with fp32 atomics
     const int64_t n = (int64_t)p.M * p.N;
-    hipLaunchKernelGGL(scale_c_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (float*)p.C, p.ldc, p.M, p.N, p.beta);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(scale_c_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, (float*)p.C, p.ldc, p.M, p.N, p.beta);
     if (e != hipSuccess) return e;
     return launch_dtl_tile<TypeBF16, EpilogueAtomicF32, 0>(plan.tile, p, stream);
   }

@@ -879,8 +879,7 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   if (nwork > INT32_MAX) return hipErrorInvalidValue;  // the kernel counts (tile, K slice) items in 32 bits
   const int grid = nwork < slots ? (int)nwork : slots;
   const auto args = kernel_args<dtl_args<BM, AMODE>, T>(p, band_magic_of(tiles_m, tiles_n));
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, args);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, args);
 }
 
 // The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages

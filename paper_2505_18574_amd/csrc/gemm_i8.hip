@@ -290,9 +290,8 @@ template <int VEC>
 static hipError_t launch_splitk_reduce_i8(const GemmParams& p, hipStream_t stream) {
   const int64_t items = (int64_t)p.M * (p.N / VEC);
   const GemmArgs args = kernel_args<GemmArgs, TypeI8>(p);
-  if (items <= 32768) hipLaunchKernelGGL((splitk_reduce_i8_kernel<64, VEC>), dim3((unsigned)((items + 63) / 64)), dim3(64), 0, stream, args);
-  else hipLaunchKernelGGL((splitk_reduce_i8_kernel<256, VEC>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, args);
-  return hipGetLastError();
+  if (items <= 32768) return launch_kernel(splitk_reduce_i8_kernel<64, VEC>, dim3((unsigned)((items + 63) / 64)), dim3(64), 0, stream, args);
+  return launch_kernel(splitk_reduce_i8_kernel<256, VEC>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, args);
 }
 
 // Operands that the direct-to-LDS kernels do not take.  The K slices are as many as the shape's own plan has (which is

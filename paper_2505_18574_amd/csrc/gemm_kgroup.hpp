@@ -341,8 +341,7 @@ template <class ARGS, class T, class KERN>
 static hipError_t launch_kgroup_grid(std::atomic<bool>& configured, KERN kern, int waves, int lds, const GemmParams& p, hipStream_t stream) {
   if (const hipError_t e = allow_dynamic_lds_once(configured, kern, lds)) return e;
   const ARGS args = kernel_args<ARGS, T>(p, band_magic_of((p.M + 31) / 32, (p.N + 31) / 32));
-  hipLaunchKernelGGL(kern, dim3((unsigned)kgroup_tiles(p)), dim3(64 * waves), lds, stream, args);  // a few hundred tiles at most
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)kgroup_tiles(p)), dim3(64 * waves), lds, stream, args);  // a few hundred tiles at most
 }
 
 template <class T, class OUT, int KTB, int W, int AMODE, bool TA, bool TB, bool DW>

@@ -572,8 +572,7 @@ static hipError_t launch_ragged_tile(const GemmParams& p, hipStream_t stream) {
   const int64_t items = (int64_t)tiles_m * tiles_n * p.splits;
   const unsigned grid = (unsigned)(items < (1 << 20) ? items : (1 << 20));  // beyond that the workgroups walk over the items
   const auto args = kernel_args<std::conditional_t<CONV, ConvArgs, GemmArgs>, T>(p, band_magic_of(tiles_m, tiles_n));
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), LDS, stream, args);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3(grid), dim3(THREADS), LDS, stream, args);
 }
 
 // One output per thread.  For operands of fewer than 16 bytes in all, which have no chunk to load (a matrix of that size has
@@ -623,9 +622,8 @@ static hipError_t launch_ragged(int tile, const GemmParams& p, hipStream_t strea
   if constexpr (!std::is_same_v<EPI, EpiloguePartialI32>) {  // (K slices: K is deep)
     if (ragged_tiny<T, AKC, BKC, CONV>(p)) {
       const int64_t blocks = ((int64_t)p.M * p.N + 255) / 256;
-      hipLaunchKernelGGL((gemm_tiny_kernel<T, EPI, AKC, BKC, CONV>), dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, stream,
+      return launch_kernel(gemm_tiny_kernel<T, EPI, AKC, BKC, CONV>, dim3((unsigned)(blocks < (1 << 20) ? blocks : (1 << 20))), dim3(256), 0, stream,
                          (kernel_args<std::conditional_t<CONV, ConvArgs, GemmArgs>, T>(p)));
-      return hipGetLastError();
     }
   }
   if constexpr (!CONV && !std::is_same_v<EPI, EpiloguePartialI32>) {  // (slices: few tiles)

@@ -213,9 +213,8 @@ static hipError_t launch_small_i8_cfg(const GemmParams& p, hipStream_t stream) {
   const int ntiles = tiles_m * tiles_n;
   const unsigned tn_magic = (uint64_t)ntiles * (unsigned)tiles_n < (1ull << 32) ? FastDiv::make((unsigned)tiles_n).magic : 0u;
   const int64_t items = (int64_t)ntiles * (SPLIT ? p.splits : 1);
-  hipLaunchKernelGGL((gemm_i8_small_kernel<KTB, S, SMALL_WAVES, AMODE, SPLIT>), dim3((unsigned)((items + SMALL_WAVES - 1) / SMALL_WAVES)), dim3(64 * SMALL_WAVES), LDS, stream,
+  return launch_kernel(gemm_i8_small_kernel<KTB, S, SMALL_WAVES, AMODE, SPLIT>, dim3((unsigned)((items + SMALL_WAVES - 1) / SMALL_WAVES)), dim3(64 * SMALL_WAVES), LDS, stream,
                      (kernel_args<std::conditional_t<AMODE == 1, ConvArgs, GemmArgs>, TypeI8>(p, tn_magic)));
-  return hipGetLastError();
 }
 
 // Measured (us, warm, per launch; four waves per workgroup over 24 KB rings first, then the choice below):

@@ -293,8 +293,7 @@ static hipError_t launch_wstat(const GemmParams& p, hipStream_t stream) {
   if (wgs < 1) wgs = 1;
   if (wgs > tiles_m) wgs = tiles_m;
   const size_t lds = (size_t)nkt * G::B_TILE + G::RING;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(wgs * n_blocks)), dim3(G::THREADS), lds, stream, p, tiles_m, n_blocks);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3((unsigned)(wgs * n_blocks)), dim3(G::THREADS), lds, stream, p, tiles_m, n_blocks);
 }
 
 // Tile codes of the weight-stationary kernel: 320 = 256-row tiles, 160 = 128-row tiles (both 64 columns wide).

@@ -338,9 +338,8 @@ static hipError_t launch_quad(const TinyMpcParams& p, hipStream_t stream) {
   const int64_t wgs = (blocks16 + waves - 1) / waves;
   const dim3 grid((unsigned)(wgs < most ? wgs : most)), block(64 * waves);
   const size_t lds = (size_t)waves * w.floats * sizeof(float);
-  if (w.whole) hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, true>), grid, block, lds, stream, p, w.floats, w.chunk);
-  else hipLaunchKernelGGL((tinympc_forward_quad_kernel<RX, RU, false>), grid, block, lds, stream, p, w.floats, w.chunk);
-  return hipGetLastError();
+  if (w.whole) return launch_kernel(tinympc_forward_quad_kernel<RX, RU, true>, grid, block, lds, stream, p, w.floats, w.chunk);
+  return launch_kernel(tinympc_forward_quad_kernel<RX, RU, false>, grid, block, lds, stream, p, w.floats, w.chunk);
 }
 
 template <int H, int NB, int WAVES>
@@ -350,9 +349,8 @@ static hipError_t launch_mfma_form(const TinyMpcParams& p, hipStream_t stream) {
   // 33.0, 34.9 us)
   const int64_t slots = (int64_t)compute_units() * (4 / WAVES);
   const dim3 grid((unsigned)(wgs < slots ? wgs : slots)), block(64 * WAVES);
-  if (p.x_out) hipLaunchKernelGGL((tinympc_forward_mfma_kernel<true, H, NB, WAVES>), grid, block, 0, stream, p);
-  else hipLaunchKernelGGL((tinympc_forward_mfma_kernel<false, H, NB, WAVES>), grid, block, 0, stream, p);
-  return hipGetLastError();
+  if (p.x_out) return launch_kernel(tinympc_forward_mfma_kernel<true, H, NB, WAVES>, grid, block, 0, stream, p);
+  return launch_kernel(tinympc_forward_mfma_kernel<false, H, NB, WAVES>, grid, block, 0, stream, p);
 }
 
 template <int H>
