@@ -70,6 +70,10 @@ bool gemm_bf16_fast_path(const GemmParams& p) {
 
 static hipError_t launch_gemm_bf16_dtl(GemmParams p, hipStream_t stream, const GemmPlan& plan, bool forced) {
   if (!forced && kgroup_takes<TypeBF16>(p, false, plan.splits)) return launch_kgroup<TypeBF16, KGroupF32, 0>(p, stream);
+  if (!forced && wide_product_rule(p.M, p.N, (int64_t)p.K * 2, 2, false, plan.splits)) {
+    p.splits = 1;
+    return launch_dtl_wide<TypeBF16, EpilogueF32, 0>(p, stream);
+  }
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
   if (plan.splits > 1 && p.partial != nullptr) {  // slices through the caller's workspace, summed in a fixed order
@@ -102,6 +106,7 @@ hipError_t launch_gemm_bf16(const GemmParams& p0, hipStream_t stream, const Gemm
     if (!forced && !ragged_tiny<TypeBF16, true, false, false>(p)) {
       if (dword_operands(p, 2, false, false, 16, 4)) {
         if (kgroup_takes<TypeBF16>(p, false, 1)) return launch_kgroup<TypeBF16, KGroupF32, 0, false, false, true>(p, stream);
+        if (wide_product_rule(p.M, p.N, (int64_t)p.K * 2, 2, true, 1)) return launch_dtl_wide<TypeBF16, EpilogueF32, 0, true>(p, stream);
         if (dword_tiles(p, 2, false, false)) return launch_dtl_tile<TypeBF16, EpilogueF32, 0, true>(plan.splits > 1 ? 64 : plan.tile, p, stream);
       }
       if (kgroup_ragged_takes<TypeBF16, true, false>(p, 1)) return launch_kgroup_ragged<TypeBF16, KGroupF32, true, false>(p, stream);

@@ -250,11 +250,11 @@ constexpr bool has_bias_lds = BM >= 256 && !PINGPONG && std::is_same_v<EPI, Epil
 template <int BM, int AMODE>
 using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), ConvArgsWide, ConvArgs>, GemmArgs>;
 
-// TA / TB (int8 GEMM on square tiles): A is given as A^T (K x M, row pitch lda) / B as B^T (N x K, row pitch ldb).
+// TA / TB (int8 GEMM): A is given as A^T (K x M, row pitch lda) / B as B^T (N x K, row pitch ldb).
 // A transposed operand takes the other operand's role in LDS: A^T is "K-strided" like B (k-rows of BM bytes, the
 // B swizzle, fragments through the transposing reads), B^T is "K-contiguous" like A (rows of KTB bytes, the A
-// swizzle, 16-byte fragment reads).  With BM == BN the tiles, the instruction counts and the lane roles of the two
-// forms coincide, so only the source offsets, the advance per K tile and the fragment addresses differ.
+// swizzle, 16-byte fragment reads).  The bytes of a tile and the instructions that fill it are the same in either
+// role, so only the source offsets, the advance per K tile and the fragment addresses differ.
 //
 // DW (products): bases, pitches and the contiguous extents are multiples of 4 bytes, not of 16.  A 16-byte load takes any
 // dword address, so whole tiles load as before, and a chunk that crosses the end of a row holds the first bytes of the next
@@ -266,9 +266,9 @@ template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMOD
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const dtl_args<BM, AMODE> p) {
   using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
   constexpr int EB = G::EB;
-  static_assert(!(TA || TB) || (BM == BN && AMODE == 0 && EB == 1), "transposed operands: int8 GEMM on square tiles");
+  static_assert(!(TA || TB) || (AMODE == 0 && EB == 1), "transposed operands: int8 GEMM");
   constexpr int AT_ROW = BM * EB, AT_SPR = AT_ROW / 16, AT_RPI = 64 / AT_SPR;  // A^T tile: bytes, slots per k-row, k-rows per instruction
-  static_assert(!(TA || TB) || AT_ROW == G::B_ROW, "a transposed operand reuses the other operand's LDS geometry");
+  static_assert(AT_SPR <= 64 && 64 % AT_SPR == 0, "a k-row of A^T must divide a wave load");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned lds0 = (unsigned)(uintptr_t)AC_LDS(unsigned char, smem);
 
@@ -886,6 +886,13 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
 // (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128),
 // 128 and 64: the rolling-refill loop with 128 bytes of K per tile, eight waves of 64 x 64 / 64 x 32 or four waves of 32 x 32 (four stages: six and eight were measured slower on
 // every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x 4608: those loops wait on the barrier, not on loads).
+// One round of 64 x 128 tiles (gemm_rules.hpp says which calls): three stages of 24 KB, eight waves of 32 x 32.
+template <class T, class EPI, int AMODE, bool DW = false, bool TA = false, bool TB = false>
+static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
+  if constexpr (TA && TB) return launch_dtl<T, EPI, 128, 64, 4, 2, AMODE, 3, 128, false, TA, TB, DW>(p, stream);
+  else return launch_dtl<T, EPI, 64, 128, 2, 4, AMODE, 3, 128, false, TA, TB, DW>(p, stream);
+}
+
 template <class T, class EPI, int AMODE, bool DW = false>
 static hipError_t launch_dtl_tile(int tile, const GemmParams& p, hipStream_t stream) {
   switch (tile) {

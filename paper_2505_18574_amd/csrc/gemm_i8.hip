@@ -338,6 +338,10 @@ hipError_t dispatch_i8(GemmParams p, hipStream_t stream, bool fast, const GemmPl
   }
   p.splits = plan.splits;
   p.kt_per_split = plan.kt_per_split;
+  if (AMODE == 0 && !forced && plan.tile != 32 && wide_product_rule(p.M, p.N, p.K, 1, false, plan.splits)) {
+    p.splits = 1;
+    return launch_dtl_wide<TypeI8, EpilogueI8, 0>(p, stream);
+  }
   if (AMODE == 0 && !forced && plan.tile != 32 && many_tiles(p.M, p.N, p.K)) {
     plan.tile = choose_product_tile_i8(p.M, p.N, p.K, wstat_eligible(p, 160), wstat_eligible(p, 320));
     if (plan.tile == TILE_128X256) return launch_dtl<TypeI8, EpilogueI8, 128, 256, 2, 4, 0, 3, 64>(p, stream);
@@ -382,9 +386,11 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   p.kt_per_split = 0;
   const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
   if (fast && kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
+  if (fast && wide_product_rule(p.M, p.N, p.K, 1, false, 1)) return launch_dtl_wide<TypeI8, EpilogueRawI32, 0>(p, stream);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
   if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4)) {
     if (kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream);
+    if (wide_product_rule(p.M, p.N, p.K, 1, true, 1)) return launch_dtl_wide<TypeI8, EpilogueRawI32, 0, true>(p, stream);
     if (dword_tiles(p, 1, false, false)) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
   }
   if (!ragged_tiny<TypeI8, true, false, false>(p) && kgroup_ragged_takes<TypeI8, true, false>(p, 1)) return launch_kgroup_ragged<TypeI8, KGroupRawI32, true, false>(p, stream);
@@ -401,6 +407,7 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
     GemmParams q = p;
     GemmPlan plan = plan_gemm_i8(p.M, p.N, p.K, p.partial != nullptr, 0);
     if (kgroup_takes<TypeI8>(p, false, plan.splits)) return launch_kgroup<TypeI8, KGroupI8, 0, false, false, true>(p, stream);
+    if (wide_product_rule(p.M, p.N, p.K, 1, true, plan.splits)) return launch_dtl_wide<TypeI8, EpilogueI8, 0, true>(p, stream);
     int ws_bm;
     if (wstat_tile_rows(plan.tile, &ws_bm)) plan.tile = choose_tile_i8(p.M, p.N, p.K, false);
     q.splits = plan.splits;
@@ -451,6 +458,11 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     const int splits = p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1;
     if (fast && kgroup_takes<TypeI8>(p, true, splits)) return launch_kgroup<TypeI8, KGroupI8, 1>(p, stream);
     if (!fast && kgroup_ragged_takes<TypeI8, true, false, true>(p, splits)) return launch_kgroup_ragged<TypeI8, KGroupI8, true, false, true>(p, stream);
+  }
+  if (!forced && fast && !product && wide_conv_rule(p.M, p.N, p.K, p.KH * p.KW, p.stride, (int64_t)p.a_bytes + (int64_t)p.K * p.N)) {
+    GemmParams q = p;
+    q.splits = 1;
+    return launch_dtl_wide<TypeI8, EpilogueI8, 1>(q, stream);
   }
   if (hipError_t e; !forced && !fast && launch_conv_image(p, stream, &e)) return e;  // channels that are not whole chunks
   if (!forced && product) {

@@ -21,7 +21,9 @@ static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   p.splits = 1;
   p.kt_per_split = 0;
   if (kgroup_takes<TypeI8, TA, TB>(p, false, 1)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB, DW>(p, stream);
-  switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // square tiles only: the 256 x 128 code falls to 128
+  if constexpr (TA || !DW)  // (B^T on dwords never does)
+    if (wide_trans_rule(p.M, p.N, p.K, TA, TB, DW)) return launch_dtl_wide<TypeI8, EpilogueI8, 0, DW, TA, TB>(p, stream);
+  switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // no tile but the wide ones is other than square: the 256 x 128 code falls to 128
     case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB, DW>(p, stream);
     case 192:
     case 128: return launch_dtl<TypeI8, EpilogueI8, 128, 128, 2, 4, 0, 3, 128, false, TA, TB, DW>(p, stream);
@@ -44,7 +46,7 @@ hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b,
     if (trans_a) return launch_trans_dtl<true, false, false>(p, stream);
     return launch_trans_dtl<false, true, false>(p, stream);
   }
-  if (dword_operands(p, 1, trans_a, trans_b, 4, 1) && (dword_tiles(p, 1, trans_a, trans_b) || kgroup_rule({p.M, p.N, p.K, 1, false, !trans_a, trans_b, p.ldb, 1, false, 0}))) {
+  if (dword_operands(p, 1, trans_a, trans_b, 4, 1) && (dword_tiles(p, 1, trans_a, trans_b) || wide_trans_rule(p.M, p.N, p.K, trans_a, trans_b, true) || kgroup_rule({p.M, p.N, p.K, 1, false, !trans_a, trans_b, p.ldb, 1, false, 0}))) {
     if (trans_a && trans_b) {
       if (!ragged_tiny<TypeI8, false, true, false>(p)) return launch_trans_dtl<true, true, true>(p, stream);
     } else if (trans_a) {

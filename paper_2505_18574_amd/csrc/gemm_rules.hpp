@@ -65,8 +65,46 @@ inline int choose_product_tile_i8(int32_t M, int32_t N, int32_t K, bool st160_ru
   return best;
 }
 
-// ---- gemm_kgroup.hpp: which calls its kernels take from the others ------------------------------------------------------
 inline int64_t tiles_of(int32_t M, int32_t N, int bm, int bn) { return (((int64_t)M + bm - 1) / bm) * (((int64_t)N + bn - 1) / bn); }
+// ---- one round of 64 x 128 tiles ---------------------------------------------------------------------------------------
+// Outputs of more 64 x 64 tiles than compute units (where some of them get two) of which 64 x 128 tiles make at most one to a
+// unit.  What a unit fetches is counted in lines of 128 bytes, one per 1.8 clocks whatever part of it is used (direct-to-LDS
+// streams from L2: 147 to 177 KB/us a unit in pieces of 128 bytes, 67 to 78 in pieces of 64), and a k-row of a 64-column int8
+// tile is half a line: 64 rows of A and 128 half lines of B are 192 for 64 x 64 outputs, and 192 for 64 x 128.  Eight waves of
+// 32 x 32, three stages (four: 1 to 3 % slower below K = 4096; four waves of 32 x 64: 3 to 8).  Measured on 5800 random shapes,
+// warm, and 2000 from HBM (before / here, us): 2936 x 384 x 1024 6.3 / 5.5, x 2240 11.5 / 9.0, 1536 x 1024 x 2240 12.9 / 10.1,
+// int32 by K 256 .. 8192 1.07 to 1.40 of the time before, A^T 1.08 to 1.44, A^T B^T on 128 x 64 tiles 1.06 to 1.3.
+constexpr int TILE_64X128 = 65;  // no plan's code either
+inline bool one_round_of_wide_tiles(int32_t M, int32_t N, int bm, int bn) { return tiles_of(M, N, 64, 64) > PLAN_CUS && tiles_of(M, N, bm, bn) <= PLAN_CUS; }
+// A product that the others would cut into `splits` pieces (1: none); dw: on dwords; raw: int32 outputs.
+// Below K = 256 (on dwords 320) the set-up of the wider tile shows (K = 64 3.5 / 3.8); cut products keep their slices beyond
+// K = 5000, which are ahead with the weights in HBM (936 x 1200 x 7808 29.0 / 37.3, 436 x 3968 x 3952 28.4 / 19.2).  bf16 rows
+// of 64 columns are whole lines: from 640 bytes of K (on dwords 704), on more than 144 tiles (129 of them 16.7 / 18.7 from HBM at
+// 2717 x 384 x 2240), and uncut only, so that the sums keep their order.
+inline bool wide_product_rule(int32_t M, int32_t N, int64_t kbytes, int eb, bool dw, int splits) {
+  if (!one_round_of_wide_tiles(M, N, 64, 128)) return false;
+  if (eb == 2) return splits <= 1 && kbytes >= (dw ? 704 : 640) && tiles_of(M, N, 64, 128) > 144;
+  return kbytes >= (dw ? 320 : 256) && (splits <= 1 || kbytes <= 5000);
+}
+// An int8 product with transposed operands, never cut.  B^T has whole lines on either tile; its products on dwords stay (1.00
+// in the mean), and those of A^T B^T beyond K = 3000 (0.92 to 1.01).  A^T B^T is wide in M.
+inline bool wide_trans_rule(int32_t M, int32_t N, int32_t K, bool trans_a, bool trans_b, bool dw) {
+  if (!one_round_of_wide_tiles(M, N, trans_a && trans_b ? 128 : 64, trans_a && trans_b ? 64 : 128)) return false;
+  if (!trans_a) return !dw && K >= 640;
+  return K >= 256 && !(trans_b && dw && K > 3000);
+}
+// A convolution of `taps` kernel positions over `bytes` of input and weights.  Its gather issues an address per 16 bytes, and two
+// workgroups of 64 x 64 to a unit cover that better than one where the lines come from near by: kernels whose positions
+// overlap more than ten times on 2.5 MB and less stay (7 x 7, 64 -> 128 on 11264 pixels 12.1 / 12.9).  336 -> 112, 3 x 3 stride 2 on
+// 9522 pixels 16.0 / 12.5, 416 -> 336 on 3872 20.0 / 15.3, 128 -> 272 on 61 images of 8 x 8, taken from the patch kernel, 12.9 / 7.1.
+// K of some 500 to 640 stays with the kernel of one wave to a tile (64 -> 144 on 5832 pixels 5.1 / 6.0), K beyond 8192 with its
+// slices (496 -> 240 on 5746 pixels, K = 24304, 56.8 / 70.7).
+inline bool wide_conv_rule(int32_t M, int32_t N, int32_t K, int32_t taps, int32_t stride, int64_t bytes) {
+  if (!one_round_of_wide_tiles(M, N, 64, 128) || K < 256 || (K > 500 && K < 640) || K > 8192) return false;
+  return taps <= 10 * (int64_t)stride * stride || bytes > 2500000;
+}
+
+// ---- gemm_kgroup.hpp: which calls its kernels take from the others ------------------------------------------------------
 // A product (or, `conv`, a convolution as its implicit product) and how the other kernels would run it.
 struct KGroupCall {
   int32_t M, N, K;
