@@ -256,6 +256,8 @@ hipError_t launch_gemm_i8(const GemmParams& p, hipStream_t stream, const GemmPla
 hipError_t launch_gemm_i8_acc32(const GemmParams& p, hipStream_t stream);
 hipError_t launch_gemm_i8_trans(const GemmParams& p, bool trans_a, bool trans_b, hipStream_t stream);
 hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced = nullptr);
+// Convolutions of few channels (conv_direct.hip): launched, with its status in *e, or not taken.
+bool launch_conv_direct(const GemmParams& p, hipStream_t stream, hipError_t* e);
 // The direct-to-LDS loaders address a lane's 16-byte chunk as a wave-uniform 64-bit base plus a 32-bit byte offset
 // that spans up to 320 rows of A or 128 rows of B.  Row pitches beyond these limits (rows of 13 MB and more) take the
 // ragged kernel, whose lanes carry 64-bit addresses.

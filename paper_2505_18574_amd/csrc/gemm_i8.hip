@@ -454,6 +454,7 @@ static bool narrow_conv_plan(const GemmParams& p, GemmPlan* plan) {
 hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced) {
   const bool fast = conv_i8_fast_path(p);
   const bool product = p.KH == 1 && p.KW == 1 && p.stride == 1 && p.pad == 0;
+  if (hipError_t e; !forced && !fast && launch_conv_direct(p, stream, &e)) return e;  // few channels
   if (!forced && !product) {  // few tiles
     const int splits = p.partial != nullptr ? plan_gemm_i8(p.M, p.N, p.K, true, 0).splits : 1;
     if (fast && kgroup_takes<TypeI8>(p, true, splits)) return launch_kgroup<TypeI8, KGroupI8, 1>(p, stream);
