@@ -93,6 +93,11 @@ inline bool wide_trans_rule(int32_t M, int32_t N, int32_t K, bool trans_a, bool 
   if (!trans_a) return !dw && K >= 640;
   return K >= 256 && !(trans_b && dw && K > 3000);
 }
+// An int8 product of at most 32 columns on more rows than the shared tiles take (gemm_i8.hip, launch_narrow), us (the
+// weight-stationary kernel or the 64 x 64 tile / here): 50176 x 32 x 1024 11.6 / 9.8, 200704 x 32 x 256 13.3 / 11.5, 41876 x 32 x 208
+// 5.0 / 4.1, 27225 x 16 x 32 3.6 / 3.4.  From a few thousand tiles on a short K stays with the resident weights (401408 x 16 x 80
+// 13.5 / 14.1, 200704 x 16 x 64 8.4 / 8.6).
+inline bool narrow_product_rule(int32_t M, int32_t N, int32_t K) { return N <= 32 && M > 64 * PLAN_CUS && (K >= 128 || M <= 512 * PLAN_CUS); }
 // A convolution of `taps` kernel positions over `bytes` of input and weights.  Its gather issues an address per 16 bytes, and two
 // workgroups of 64 x 64 to a unit cover that better than one where the lines come from near by: kernels whose positions
 // overlap more than ten times on 2.5 MB and less stay (7 x 7, 64 -> 128 on 11264 pixels 12.1 / 12.9).  336 -> 112, 3 x 3 stride 2 on
