@@ -139,13 +139,29 @@ struct KGroupCall {
 // image 7.3 / 5.7 and 9.1 / 13.1).  More tiles move it up (the slices' sums are more), eight slices down (they share B
 // further), and rows of B a multiple of 2 KB apart (bf16: 1 KB) are left to the slices (16 x 2048 x 2048 from HBM 8.3 / 9.4,
 // 16 x 2064 x 2048 9.2 / 7.9).  Where B is narrow its lines are used whole (1400 x 32 x 4352 8.6 / 4.4 and 10.1 / 8.8).
+// Convolutions whose weights are few, up to 128 columns, come from the slices to a K that grows with the tiles: their images,
+// not their weights, are what a compute unit streams, and each pixel's chunks serve all columns of a tile.  On 160 random ones
+// (slices / here, warm and from HBM): 304 -> 16, 5 x 5 on 4232 pixels 13.1 / 6.7 and 14.0 / 8.1; 256 -> 32, 7 x 7 on 5618 23.3 / 8.8
+// and 22.6 / 11.7; 240 -> 48, 5 x 5 on 700 8.0 / 5.9 and 8.3 / 6.6; 256 -> 80 on 1980 13.2 / 7.6 and 13.7 / 11.1; none within the line
+// is more than a tenth behind from HBM, and the fewest tiles keep the line of the products (100 x 64 x 5040); left to the slices 320 -> 80 on 512 8.9 / 6.8 and 9.7 / 12.4, 480 -> 32 on 450, K =
+// 12000, 8.2 / 8.3 and 9.2 / 14.3.
+// Two rounds of four waves (t > 256) are ahead of the 64 x 64 tiles and their slices on these as well (448 -> 32, 3 x 3 on 11264 pixels
+// 12.6 / 7.7 and 12.7 / 9.9, 112 -> 48, 5 x 5 stride 1 on 5476, K = 6000, 13.9 / 9.9 and 14.4 / 11.9; given back: 432 -> 64, K = 10800, 18.8 /
+// 17.6 and 18.2 / 21.5), with more columns as long as K is some 4000 on up to 384 tiles (144 -> 240 on 1372 13.3 / 10.7 and 14.6 /
+// 12.5, 368 -> 160 on 2124 14.5 / 10.4 and 15.3 / 13.3; beyond, 288 -> 448 on 960, K = 2592, 8.9 / 9.6).
+inline int64_t kgroup_cut_conv_limit(int row, int64_t t) {
+  if (row <= 16) return t <= 81 ? 9600 + 128 * t : 20000;
+  if (row <= 32) return t <= 4 ? 9600 : 8800 + 40 * t;
+  if (row <= 64) return t <= 8 ? 4800 : 6400 + 22 * t;
+  return 3900 + 28 * t;
+}
 inline bool kgroup_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.K < 16 || c.N < 1) return false;
-  if (t > 256) return t <= 512 && kbytes <= (c.conv ? 2400 : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
+  if (t > 256) return t <= 512 && kbytes <= (c.conv ? (c.N <= 128 ? 8000 : t <= 384 ? 4000 : 2400) : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
   if (c.splits <= 1) return true;
   if (!c.workspace) return kbytes <= (row <= 64 ? 7168 : 5120);  // atomics, whose sums differ from run to run
-  if (c.conv && row <= 64) return kbytes <= (row <= 32 && t <= 4 ? 9600 : 4800);
+  if (c.conv && row <= 128) return kbytes <= kgroup_cut_conv_limit((int)row, t);
   if (row <= 64) return kbytes <= (t <= 2 ? 7168 : 4480);
   if (c.splits >= 8) return false;
   if (c.conv) return kbytes <= 7200 && kbytes <= 3392 + 10 * t;

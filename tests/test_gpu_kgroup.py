@@ -109,6 +109,21 @@ def test_convolutions(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
     np.testing.assert_array_equal(host(out), want)
 
 
+# images, edge, input and output channels, kernel edge, stride: both sides of each line, and the most tiles of two rounds
+@pytest.mark.parametrize("Nb,edge,Cin,Cout,k,stride", [
+    (1, 40, 384, 16, 5, 1), (2, 9, 400, 16, 5, 1), (2, 9, 432, 16, 5, 1), (1, 14, 352, 32, 5, 1), (1, 14, 384, 32, 5, 1), (1, 20, 128, 48, 7, 1), (1, 20, 160, 64, 7, 1),
+    (3, 19, 208, 80, 5, 2), (3, 19, 176, 80, 5, 2), (3, 19, 176, 128, 5, 2), (1, 7, 208, 144, 5, 1), (15, 33, 304, 32, 5, 1), (4, 37, 320, 48, 5, 1), (4, 37, 336, 48, 5, 1),
+    (7, 14, 160, 240, 5, 1), (7, 14, 176, 240, 5, 1), (33, 9, 256, 160, 3, 1), (33, 9, 272, 160, 3, 1)])
+def test_convolutions_beside_a_workspace(Nb, edge, Cin, Cout, k, stride):
+    x, w, b = inputs.conv_i8_inputs(Nb, edge, edge, Cin, Cout, k, k, seed=edge + Cin + Cout)
+    want = oracle.conv2d_i8(x, w, b, stride, k // 2, 11, 1)
+    ws = torch.empty(max(16, ops.ac_gemm_i8_workspace_bytes(want.size // Cout, Cout, k * k * Cin)), dtype=torch.uint8, device="cuda")
+    for workspace in (ws, None):
+        out = torch.full(want.shape, 17, dtype=torch.int8, device="cuda")
+        ops.ac_conv2d_i8(dev(x), dev(w), dev(b), out, stride, k // 2, 11, 1, workspace=workspace)
+        np.testing.assert_array_equal(host(out), want)
+
+
 def test_same_bits_on_every_run():
     """The waves' sums are added in one order (with no workspace, the kernels that cut K add them as they come)."""
     A, B = inputs.gemm_bf16_inputs(64, 96, 2400, seed=5)
