@@ -396,11 +396,11 @@ hipError_t launch_gemm_i8_acc32(const GemmParams& p0, hipStream_t stream) {
   p.splits = 1;
   p.kt_per_split = 0;
   const bool fast = aligned16(p.A) && aligned16(p.B) && (p.lda % 16 == 0) && (p.ldb % 16 == 0) && aligned16(p.C) && (p.ldc % 4 == 0) && (p.K % 16 == 0) && (p.N % 16 == 0) && lane_offsets_fit(p.lda, p.ldb);
-  if (fast && kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
+  if (fast && kgroup_takes<TypeI8>(p, false, 1, true)) return launch_kgroup<TypeI8, KGroupRawI32, 0>(p, stream);
   if (fast && wide_product_rule(p.M, p.N, p.K, 1, false, 1)) return launch_dtl_wide<TypeI8, EpilogueRawI32, 0>(p, stream);
   if (fast) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0>(choose_tile(p.M, p.N), p, stream);  // 4-byte output: its own regime, thresholds kept
   if (!ragged_tiny<TypeI8, true, false, false>(p) && dword_operands(p, 1, false, false, 16, 4)) {
-    if (kgroup_takes<TypeI8>(p, false, 1)) return launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream);
+    if (kgroup_takes<TypeI8>(p, false, 1, true)) return launch_kgroup<TypeI8, KGroupRawI32, 0, false, false, true>(p, stream);
     if (wide_product_rule(p.M, p.N, p.K, 1, true, 1)) return launch_dtl_wide<TypeI8, EpilogueRawI32, 0, true>(p, stream);
     if (dword_tiles(p, 1, false, false)) return launch_dtl_tile<TypeI8, EpilogueRawI32, 0, true>(choose_tile(p.M, p.N), p, stream);
   }

@@ -367,8 +367,8 @@ static hipError_t launch_kgroup(const GemmParams& p, hipStream_t stream) {
 
 // Whether the kernel above takes a product (or, `conv`, a convolution) from the others, which would cut K into `splits`.
 template <class T, bool TA = false, bool TB = false>
-static bool kgroup_takes(const GemmParams& p, bool conv, int splits) {
-  return kgroup_rule({p.M, p.N, p.K, T::EB, conv, !TA, TB, p.ldb * T::EB, splits, p.partial != nullptr, p.Cin});
+static bool kgroup_takes(const GemmParams& p, bool conv, int splits, bool raw = false) {
+  return kgroup_rule({p.M, p.N, p.K, T::EB, conv, !TA, TB, p.ldb * T::EB, splits, p.partial != nullptr, p.Cin, raw});
 }
 
 // Whether an uncut product that meets dword_operands takes gemm_dtl_kernel's DW form.

@@ -120,6 +120,7 @@ struct KGroupCall {
   int splits;                 // pieces that the others would cut K into over workgroups (1: none)
   bool workspace;             // ... through a workspace; without one bf16 slices meet in atomics
   int32_t Cin;                // conv
+  bool raw = false;           // int32 outputs, whose other tile is the 64 x 64 one whatever K
 };
 
 // The kernel on direct-to-LDS operands.  On 430 random shapes per form, warm and from HBM, in us (there / here):
@@ -129,6 +130,8 @@ struct KGroupCall {
 //   up to 512 tiles, two rounds of four waves each, only where K is short (2350 x 256 x 176 4.4 / 3.4, 608 x 576 x 256
 //   3.5 / 3.5, 224 x 1920 x 624 4.3 / 4.5), shorter where no operand's rows run along it (A^T 64 x 5584 x 336 3.8 / 3.7, 1328 x
 //   352 x 448 4.0 / 4.6), longer where both operands' do (B^T 256 x 1072 x 1280 5.8 / 4.0);
+//   longer for int32 outputs (7468 x 44 x 640 5.3 / 4.0, 700 x 532 x 904 6.2 / 5.3, from HBM 8.0 / 6.9; 4672 x 64 x 896 5.1 / 3.7; given
+//   back: 560 x 784 x 1024 5.1 / 5.6);
 //   against the kernel of one wave to a tile up to 256 tiles, but for a few tiles of one K tile, where one wave has all the work
 //   (57 x 64 x 64 2.5 / 2.65, 30 x 64 x 256 2.7 / 2.5, 100 x 256 x 64 3.0 / 2.7).
 // Where the others would cut K, slices have more of B in flight, and what decides is where the weights come from: from HBM a
@@ -158,7 +161,7 @@ inline int64_t kgroup_cut_conv_limit(int row, int64_t t) {
 inline bool kgroup_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.K < 16 || c.N < 1) return false;
-  if (t > 256) return t <= 512 && kbytes <= (c.conv ? (c.N <= 128 ? 8000 : t <= 384 ? 4000 : 2400) : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
+  if (t > 256) return t <= 512 && kbytes <= (c.conv ? (c.N <= 128 ? 8000 : t <= 384 ? 4000 : 2400) : c.raw ? (c.N <= 64 ? 1408 : 960) : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
   if (c.splits <= 1) return true;
   if (!c.workspace) return kbytes <= (row <= 64 ? 7168 : 5120);  // atomics, whose sums differ from run to run
   if (c.conv && row <= 128) return kbytes <= kgroup_cut_conv_limit((int)row, t);

@@ -109,6 +109,15 @@ def test_convolutions(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
     np.testing.assert_array_equal(host(out), want)
 
 
+@pytest.mark.parametrize("M,N,K", [(8193, 32, 624), (16384, 16, 1408), (16383, 32, 1424), (288, 928, 960), (511, 1008, 944), (511, 1008, 976), (300, 932, 956), (4099, 60, 1404)])
+def test_int32_on_two_rounds(M, N, K):
+    A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=M + N + K)
+    for bias in (b, None):
+        C = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+        ops.ac_gemm_i8_acc32(dev(A), dev(B), None if bias is None else dev(bias), C)
+        np.testing.assert_array_equal(host(C), (A.astype(np.float64) @ B.astype(np.float64) + (0 if bias is None else bias)).astype(np.int32))  # sums below 2^53
+
+
 # images, edge, input and output channels, kernel edge, stride: both sides of each line, and the most tiles of two rounds
 @pytest.mark.parametrize("Nb,edge,Cin,Cout,k,stride", [
     (1, 40, 384, 16, 5, 1), (2, 9, 400, 16, 5, 1), (2, 9, 432, 16, 5, 1), (1, 14, 352, 32, 5, 1), (1, 14, 384, 32, 5, 1), (1, 20, 128, 48, 7, 1), (1, 20, 160, 64, 7, 1),
