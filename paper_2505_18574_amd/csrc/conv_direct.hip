@@ -9,7 +9,8 @@
 //
 // Padding: rows outside the image are dropped lane by lane, and the bytes of a chunk that hang over the row's left or right
 // edge are the same for every kernel row, one mask per tile.  Most tiles touch no edge and skip both (a wave-uniform
-// test).  Chunks that would leave the input itself, at its first and last pixels, are loaded where 16 bytes exist and shifted.
+// test).  Where a chunk, or the dword behind it that some forms load too, would leave the input itself, at its first and last
+// pixels, the tile's chunks are loaded where 16 bytes exist and shifted.
 // Bytes behind a run meet weight rows of zeros.
 //
 // A wave takes tiles of 32 consecutive pixels, a run of them per XCD, whose L2 then holds its part of the image; the next
@@ -21,6 +22,7 @@
 // 224 x 224 10.2 / 7.3, on 32 23.4 / 15.3; 3 x 3, 4 -> 16 on 20 of 228 x 228 18.6 / 11.9; 5 x 5, 3 -> 32 on eight of 197 x 197
 // 11.1 / 7.1; 1 x 1, 3 -> 64 on ten of 200 x 200 12.4 / 9.5; 3 x 3, 3 -> 16 on one of 32 x 32 4.0 / 3.2.  With loads from any byte the
 // first of them 8.5.
+#include "conv_direct_rules.hpp"
 #include "conv_image.hpp"
 
 namespace ac {
@@ -38,19 +40,11 @@ struct ConvDirectArgs {
 };
 static_assert(sizeof(ConvDirectArgs) <= 112, "beyond, a launch costs more");
 
-// A load of 16 bytes a lane from any address costs a compute unit 65 clocks, from a dword 17 (from the L1, whatever the distance
-// between lanes up to 32 bytes): a chunk comes from the dword its first byte lies in and is shifted into place.
-enum ConvDirectShift {
-  DIRECT_NONE,   // every chunk starts on a dword
-  DIRECT_13,     // the dwords loaded hold 13 bytes of a chunk at least: that many of the run go to a chunk
-  DIRECT_TAIL,   // 16, with the dword that follows
-};
-
 // NKS: K-steps of 32 bytes.  NARROW: a kernel row is one chunk, two rows to a K-step; otherwise two chunks.
 template <int NKS, int TN, bool NARROW, ConvDirectShift SHIFT, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(TN == 3 ? 3 : 4))) conv_i8_direct_kernel(const ConvDirectArgs p) {
   using T = TypeI8;
-  constexpr int BN = 32 * TN, B_STRIDE = BN + 16, CPR = BN / 16, THREADS = 64 * WAVES, NROW = 32 * NKS, PAYLOAD = SHIFT == DIRECT_13 ? 13 : 16;
+  constexpr int BN = 32 * TN, B_STRIDE = BN + 16, CPR = BN / 16, THREADS = 64 * WAVES, NROW = 32 * NKS, PAYLOAD = conv_direct_payload(SHIFT);
   constexpr int WB = (NROW * CPR + THREADS - 1) / THREADS;  // chunks of the weights per thread
   constexpr bool RESIDENT = NKS * TN <= 6;                  // the weights' fragments stay in registers
   __shared__ __attribute__((aligned(16))) int bias[BN];
@@ -68,7 +62,7 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
   tile += wave;
 
   // ---- one tile's pixels: position, what of its chunks lies in the image, and the loads ----
-  constexpr int READ = SHIFT == DIRECT_TAIL ? 20 : 16;  // bytes from a chunk's first on that may be read
+  constexpr int READ = conv_direct_read(SHIFT);
   v4i a[NKS];
   int tail[SHIFT == DIRECT_TAIL ? NKS : 1];
   int m, ih0;   // the lane's pixel and the first image row under it
@@ -85,8 +79,8 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
     ih0 = oh * p.stride - p.pad;
     const int col = (ow * p.stride - p.pad) * p.Cin, b = col + (NARROW ? 0 : PAYLOAD * half);
     base = ((int)img * p.H + ih0) * row_bytes + b;
-    const bool inside = (ih0 >= 0) & (ih0 + p.KH <= p.H) & (col >= 0) & (col + p.RUN <= row_bytes) & (base + (p.KH - 1) * row_bytes + READ <= p.a_bytes);
-    whole = __all(inside);
+    const ConvDirectWindow window = {ih0, col, base};
+    whole = __all(conv_direct_whole(window, p.H, p.KH, p.RUN, row_bytes, p.a_bytes, READ));
     auto row_of = [&](int ks) { return NARROW ? 2 * ks + half : ks; };
     auto load = [&](int ks, int g) {
       if constexpr (SHIFT != DIRECT_NONE) g &= ~3;
@@ -105,8 +99,7 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
       hi = hi < 0 ? 0 : hi > 16 ? 16 : hi;  // (a chunk's bytes beyond its payload meet zeros)
       lo = lo > 16 ? 16 : lo;
       const int first = ih0 < 0 ? -ih0 : 0, last = p.H - 1 - ih0 < p.KH - 1 ? p.H - 1 - ih0 : p.KH - 1;  // kernel rows inside the image
-      const bool fits = (first > last) | ((base + first * row_bytes >= 0) & (base + last * row_bytes + 16 <= p.a_bytes));
-      near = !__all(fits);
+      near = !__all(conv_direct_fits(window, first, last, row_bytes, p.a_bytes, READ));
 #pragma unroll
       for (int ks = 0; ks < NKS; ks++) {
         const int kh = row_of(ks);
@@ -262,34 +255,18 @@ static hipError_t launch_conv_direct_shift(ConvDirectShift shift, int bn, int nk
 
 // Launches the kernel when it takes the convolution; false otherwise.
 bool launch_conv_direct(const GemmParams& p, hipStream_t stream, hipError_t* e) {
-  const int64_t run = (int64_t)p.KW * p.Cin, w_bytes = (int64_t)p.K * p.N, lim = 1ll << 32;
-  const bool dwords = (int64_t)p.stride * p.Cin % 4 == 0 && (int64_t)p.pad * p.Cin % 4 == 0 && (int64_t)p.W * p.Cin % 4 == 0;
-  const bool narrow = run <= 16;
-  const ConvDirectShift shift = dwords ? DIRECT_NONE : run <= 13 || (run > 16 && run <= 26) ? DIRECT_13 : DIRECT_TAIL;
-  const int nks = narrow ? (p.KH + 1) / 2 : p.KH;
-  if (run < 1 || run > 32 || nks < 1 || nks > (narrow ? 4 : 7) || p.a_bytes < 16 || w_bytes < 16 || w_bytes >= (1ll << 31) || p.N >= (1 << 29) || ((uintptr_t)p.A & 3) != 0) return false;
-  if ((p.bias != nullptr && p.bias_ld != 0) || p.shift < 1 || p.shift > 17) return false;  // (the rounding of the other shifts is not built into it)
-  // Outputs beyond the caches are written in one moving window (3 x 3, 1 -> 96 channels on 31 images of 183 x 183, 100 MB, 33.9 us in
-  // a run per XCD, 26.8 so; level below 40 MB), which the image kernel's workgroups in step do best where a pixel is one chunk
-  // (1 x 1, 3 -> 96 on 22 of 222 x 222, 104 MB, 32.9 there and 39.1, on 20 of 176 x 176, 59 MB, 20.1 and 15.7).
-  const int64_t out_bytes = (int64_t)p.M * p.N;
-  if (p.KH * p.KW == 1 && out_bytes > 90000000) return false;
-  if (p.OW < 1 || (int64_t)p.M * p.OW >= lim || ((int64_t)p.M / p.OW + 1) * p.OH >= lim) return false;  // divisions by one multiply
-  if ((int64_t)p.a_bytes + ((int64_t)p.KH + p.pad + 1) * ((int64_t)p.W + p.pad) * p.Cin >= 1ll << 31) return false;  // positions outside the image
-  // the block width that computes the fewest columns beyond N
-  auto cost = [&](int bn) { return (int64_t)((p.N + bn - 1) / bn) * (bn + 16); };
-  const int bn = cost(96) <= cost(64) && cost(96) <= cost(32) ? 96 : (cost(64) <= cost(32) ? 64 : 32);
-  const int64_t n_blocks = ((int64_t)p.N + bn - 1) / bn;
-  if (n_blocks > 65535) return false;
+  if (p.bias != nullptr && p.bias_ld != 0) return false;
+  const ConvDirectForm f = conv_direct_form({p.M, p.N, p.K, p.H, p.W, p.Cin, p.KH, p.KW, p.OH, p.OW, p.stride, p.pad, p.a_bytes, p.shift, ((uintptr_t)p.A & 3) == 0});
+  if (!f.takes) return false;
   ConvDirectArgs a = {};
   a.A = p.A, a.B = p.B, a.C = p.C, a.bias = p.bias;
-  a.M = p.M, a.N = p.N, a.a_bytes = p.a_bytes, a.w_bytes = (int32_t)w_bytes;
-  a.tiles = (int32_t)(((int64_t)p.M + 31) / 32), a.per_xcd = out_bytes <= 32 << 20 ? (a.tiles + 7) / 8 : 0;
+  a.M = p.M, a.N = p.N, a.a_bytes = p.a_bytes, a.w_bytes = p.K * p.N;
+  a.tiles = (int32_t)(((int64_t)p.M + 31) / 32), a.per_xcd = (int64_t)p.M * p.N <= 32 << 20 ? (a.tiles + 7) / 8 : 0;
   a.Cin = p.Cin, a.stride = p.stride;
-  a.H = (uint16_t)p.H, a.W = (uint16_t)p.W, a.OH = (uint16_t)p.OH, a.OW = (uint16_t)p.OW, a.KH = (uint16_t)p.KH, a.RUN = (uint16_t)run, a.pad = (uint16_t)p.pad;
+  a.H = (uint16_t)p.H, a.W = (uint16_t)p.W, a.OH = (uint16_t)p.OH, a.OW = (uint16_t)p.OW, a.KH = (uint16_t)p.KH, a.RUN = (uint16_t)(p.KW * p.Cin), a.pad = (uint16_t)p.pad;
   a.shift = (uint8_t)p.shift, a.act = (uint8_t)p.act;
   a.dOW = p.dOW, a.dOH = p.dOH;
-  *e = narrow ? launch_conv_direct_shift<true, 4>(shift, bn, nks, a, (int)n_blocks, stream) : launch_conv_direct_shift<false, 4>(shift, bn, nks, a, (int)n_blocks, stream);
+  *e = f.narrow ? launch_conv_direct_shift<true, 4>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream) : launch_conv_direct_shift<false, 4>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream);
   return true;
 }
 

@@ -50,6 +50,12 @@ def check(Nb, H, W, Cin, Cout, KH, KW, stride, pad, shift=8, act=1, offset=0, bi
     (1, 6, 6, 3, 16, 3, 3, 1, 20),      # windows of padding only
     (11, 100, 101, 3, 48, 3, 3, 1, 1),  # several tiles to a wave
     (40, 61, 63, 3, 100, 1, 1, 1, 0),   # ... and two column blocks
+    (1, 64, 64, 1, 16, 1, 16, 1, 0),    # the last window ends with the input, with and without the dword behind it
+    (1, 16, 16, 2, 16, 8, 8, 1, 0),
+    (1, 38, 38, 2, 16, 7, 7, 1, 3),     # ... in a tile that pads, the last but one of its rows
+    (1, 2048, 15, 2, 16, 8, 7, 1, 3),
+    (1, 1, 19, 1, 16, 1, 16, 1, 0),     # 19 and 20 bytes in all
+    (1, 1, 20, 1, 16, 1, 15, 1, 1),
 ])
 def test_forms(Nb, H, W, Cin, Cout, KH, KW, stride, pad):
     check(Nb, H, W, Cin, Cout, KH, KW, stride, pad)
