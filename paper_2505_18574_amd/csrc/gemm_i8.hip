@@ -322,7 +322,7 @@ static hipError_t launch_ragged_i8(GemmParams p, hipStream_t stream, const GemmP
   return launch_ragged<TypeI8, EpilogueI8Any, true, false, AMODE == 1>(tile, p, stream);
 }
 
-// At most 32 columns on many rows (narrow_product_rule, narrow_conv_plan): tiles of 128 x 32, four waves of 32 x 32, three stages of
+// At most 32 columns on many rows (narrow_product_rule, narrow_conv_rule): tiles of 128 x 32, four waves of 32 x 32, three stages of
 // 20 KB, two workgroups to a compute unit.  The 64 x 64 tile fetches, stages and multiplies as many columns that do not
 // exist.  Four stages are 2 % behind, tiles of 64 x 32 (two waves) 11 %.
 template <int AMODE>
@@ -443,31 +443,14 @@ bool conv_i8_fast_path(const GemmParams& p) {
          ((int64_t)p.M / (p.OW > 0 ? p.OW : 1) + 1) * p.OH < lim && p.a_bytes > 0 && lane_offsets_fit(0, p.ldb);
 }
 
-// A convolution of at most 64 output channels on more than one 64 x 64 tile per compute unit: that tile, uncut, or up to 32
-// channels the 128 x 32 one (launch_narrow).  The planner's estimates, made for products, take wider tiles or K slices there, which compute or store columns that do not
-// exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of 55 x 55
-// 101 -> 77; level on the shapes where they agree).  Where they take the weight-stationary kernel they are right as long
-// as K is short, and a single tap, a plain product but for its rows, always is (1 x 1 stride 2, 48 -> 16 on 185 images of
-// 65 x 65 13.5 us there and 22.6 on the tile, 64 -> 48 on 64 of 56 x 56 6.6 and 8.8); its gather loses from K = 800 on
-// where the columns are whole 32s (from 400 with more than nine taps), from 1200 on otherwise (3 x 3 stride 2, 96 -> 64 on
-// 76800 pixels 20.8 and 14.3, 5 x 5 stride 2, 16 -> 64 on 39546 10.5 and 7.8, 64 -> 16 on 234484 92 and 57; 2 x 2
-// stride 2, 256 -> 16 on 113568, K = 1024, 24.2 and 26.6, 144 -> 64 on 285696, K = 576, 32.9 and 35.4).  Sixty-four
-// columns fill half of a wide tile, which is the better one for K beyond 32768 (5 x 5, 1968 -> 64 on 51840 pixels 378 and
-// 410, 1520 -> 64 339 and 350; 1056 -> 64 on 39546, K = 26400, 182 and 147).
-// The narrow tile is ahead of the 64 x 64 one on all of 60 such convolutions, 1.2 times in the mean (3 x 3, 512 -> 32 on 50176 pixels
-// 29.8 -> 19.2 us, 5 x 5, 112 -> 16 on 290238 83.6 -> 47.4, 7 x 7, 128 -> 32 on 145119 85 -> 57), and of the
-// weight-stationary kernel at every K (3 x 3, 48 -> 32 on 139240 pixels 18.6 -> 10.5, 80 -> 16 on 40768 10.6 -> 6.5; 1 x 1 stride 2,
-// 32 -> 32 on 66240 6.8 -> 5.4).
+// The tile of a convolution of few columns (narrow_conv_rule), in place of the planned one.
 static bool narrow_conv_plan(const GemmParams& p, GemmPlan* plan) {
   int bm;
-  if (p.N > 64 || p.M <= 64 * PLAN_CUS || plan->tile == 32 || (p.N > 48 && p.K > 32768)) return false;
-  const int32_t gather = p.N <= 32 ? 0 : p.N % 32 != 0 ? 1200 : p.KH * p.KW > 9 ? 400 : 800;
-  if (wstat_tile_rows(plan->tile, &bm) && p.K < gather) return false;
-  return make_plan_i8(p.K, 64, 1, plan);
+  return narrow_conv_rule(p.M, p.N, p.K, p.KH * p.KW, p.stride, plan->tile == 32, wstat_tile_rows(plan->tile, &bm)) && make_plan_i8(p.K, 64, 1, plan);
 }
 
 static hipError_t launch_narrow_conv(const GemmParams& p, hipStream_t stream, const GemmPlan& plan) {
-  return p.N <= 32 ? launch_narrow<1>(p, stream) : dispatch_i8<1>(p, stream, true, &plan);
+  return narrow_conv_tile(p.M, p.N, p.K, p.KH * p.KW, p.stride) ? launch_narrow<1>(p, stream) : dispatch_i8<1>(p, stream, true, &plan);
 }
 
 hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmPlan* forced) {
@@ -514,13 +497,11 @@ hipError_t launch_conv2d_i8(const GemmParams& p, hipStream_t stream, const GemmP
     // them go to the kernel that pads its runs (not those of one wave per tile: 2 x 4 stride 2, 16 -> 32 on 111 images of
     // 14 x 148 4.1 us so and 5.5 there)
     if (hipError_t e; tiles64 > 512 && conv_image_takes_sixteen(p) && planned().tile != 32 && launch_conv_image(p, stream, &e)) return e;
-    // At most 32 columns and a stride: the patch, of which few pixels meet, gives way to the narrow tile (5 x 5 stride 2, 32 -> 32
-    // on 89 images of 59 x 59 12.6 -> 9.5 us, 3 x 3 stride 2, 64 -> 16 on 83 of 64 x 64 12.9 -> 10.1; at stride 1 it is
-    // ahead on most, 64 -> 32 on 94 of 55 x 55 16.0 and 18.6).
-    if (GemmPlan plan; p.stride > 1 && p.N <= 32 && (plan = planned(), narrow_conv_plan(p, &plan))) return launch_narrow<1>(p, stream);
-    if (taps && conv_halo_plan(p, 256, &h, &lds)) {
+    const bool patch_256 = taps && conv_halo_plan(p, 256, &h, &lds), patch_128 = !patch_256 && taps && conv_halo_plan(p, 128, &h, &lds);
+    if ((patch_256 || patch_128) && narrow_conv_instead_of_patch(p.M, p.N, p.stride) && planned().tile != 32) return launch_narrow<1>(p, stream);
+    if (patch_256) {
       if (h.units * nblk >= 256 || tiles64 > 512) return launch_conv_halo<256>(q, h, lds, stream);
-    } else if (taps && conv_halo_plan(p, 128, &h, &lds)) {
+    } else if (patch_128) {
       // the patch of 256 pixels does not fit, that of 128 does (28 x 28 x 128 -> 128: 64 images 18.7 us against
       // 18.5 us on the best tiled kernel, 128 images 29.6 against 33.6)
       if (h.units * nblk >= 512) return launch_conv_halo<128>(q, h, lds, stream);

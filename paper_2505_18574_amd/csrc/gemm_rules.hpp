@@ -93,11 +93,47 @@ inline bool wide_trans_rule(int32_t M, int32_t N, int32_t K, bool trans_a, bool 
   if (!trans_a) return !dw && K >= 640;
   return K >= 256 && !(trans_b && dw && K > 3000);
 }
-// An int8 product of at most 32 columns on more rows than the shared tiles take (gemm_i8.hip, launch_narrow), us (the
-// weight-stationary kernel or the 64 x 64 tile / here): 50176 x 32 x 1024 11.6 / 9.8, 200704 x 32 x 256 13.3 / 11.5, 41876 x 32 x 208
-// 5.0 / 4.1, 27225 x 16 x 32 3.6 / 3.4.  From a few thousand tiles on a short K stays with the resident weights (401408 x 16 x 80
-// 13.5 / 14.1, 200704 x 16 x 64 8.4 / 8.6).
-inline bool narrow_product_rule(int32_t M, int32_t N, int32_t K) { return N <= 32 && M > 64 * PLAN_CUS && (K >= 128 || M <= 512 * PLAN_CUS); }
+// ---- at most 32 columns on more rows than the shared tiles take: 128 x 32 tiles (gemm_i8.hip, launch_narrow) --------------
+// Rows that are read once, beside the weight-stationary kernel, which keeps more loads in flight where the rows are many (us there /
+// here): 137103 x 32 x 128 8.7 / 7.4, 282133 x 32 x 208 16.5 / 14.0, 290715 x 32 x 544 38.4 / 38.0, but 753035 x 16 x 128 24.3 / 27.9,
+// 574609 x 32 x 352 47.3 / 50.5, 1837930 x 16 x 176 73.5 / 81.9; a short K earlier: 96366 x 32 x 16 5.3 / 4.7 and 401408 x 16 x 80 13.5 /
+// 14.1; 1 x 1 stride 2, 48 -> 16 on 100719 pixels 7.4 / 7.0, on 164836 9.3 / 9.8, on 1052025 34.0 / 45.5; 2 x 2 stride 2, 176 -> 32 on
+// 960000 142 / 162.  Beside the 64 x 64 tile as well: 2 x 2 stride 2, 352 -> 16 on 349856 pixels 107 / 118.
+inline bool narrow_rows_rule(int32_t M, int32_t K) { return M <= 512 * PLAN_CUS || (K >= 128 && M <= 1152 * PLAN_CUS); }
+// Such rows beside the 64 x 64 tile: a deep K is all waiting for them, and the compute unit with the most counts.  Where tiles of 64
+// rows deal them more evenly those stay (48529 x 32 x 2192, 256 rows and 192, 24.8 / 27.3, 36048 x 32 x 2960 28.9 / 33.8, 70643 x 16 x
+// 2288, 384 and 320, 37.6 / 40.7, 3 x 3 stride 3, 368 -> 16 on 35525 pixels 30.6 / 36.8; 38235 x 32 x 160 4.4 / 4.0, 40867 x 16 x 1088
+// 12.1 / 10.7, 87408 x 32 x 2304, 384 and 384, 42.7 / 40.4).
+inline int64_t busiest_unit_rows(int32_t M, int bm) { return (((int64_t)M + bm - 1) / bm + PLAN_CUS - 1) / PLAN_CUS * bm; }
+inline bool narrow_rows_even(int32_t M, int32_t K) { return K < 1100 || 20 * busiest_unit_rows(M, 128) <= 23 * busiest_unit_rows(M, 64); }
+// An int8 product, against the stationary kernel or the 64 x 64 tile: 50176 x 32 x 1024 11.6 / 9.8, 200704 x 32 x 256 13.3 / 11.5, 41876 x
+// 32 x 208 5.0 / 4.1, 27225 x 16 x 32 3.6 / 3.4.
+inline bool narrow_product_rule(int32_t M, int32_t N, int32_t K) { return N <= 32 && M > 64 * PLAN_CUS && narrow_rows_rule(M, K) && narrow_rows_even(M, K); }
+// A convolution of at most 64 output channels on more than one 64 x 64 tile per compute unit: that tile, uncut, or up to 32
+// channels the 128 x 32 one (narrow_conv_tile).  The planner's estimates, made for products, take wider tiles or K slices there, which compute or
+// store columns that do not exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of
+// 55 x 55 101 -> 77; level on the shapes where they agree).  Where they take the weight-stationary kernel (`stationary`) they are
+// right as long as K is short, and a single tap, a plain product but for its rows, always is (1 x 1 stride 2, 64 -> 48 on 64
+// images of 56 x 56 6.6 us there and 8.8 on the tile); its gather loses from K = 800 on where the columns are whole 32s (from
+// 400 with more than nine taps), from 1200 on otherwise (3 x 3 stride 2, 96 -> 64 on 76800 pixels 20.8 and 14.3, 5 x 5 stride 2,
+// 16 -> 64 on 39546 10.5 and 7.8; 144 -> 64 on 285696, K = 576, 32.9 and 35.4).  Sixty-four columns fill half of a wide tile, which is
+// the better one for K beyond 32768 (5 x 5, 1968 -> 64 on 51840 pixels 378 and 410, 1520 -> 64 339 and 350; 1056 -> 64 on 39546, K =
+// 26400, 182 and 147).
+// The 128 x 32 tile is ahead of the 64 x 64 one on all of 60 such convolutions, 1.2 times in the mean (3 x 3, 512 -> 32 on 50176 pixels
+// 29.8 -> 19.2 us, 5 x 5, 112 -> 16 on 290238 83.6 -> 47.4, 7 x 7, 128 -> 32 on 145119 85 -> 57), and of the weight-stationary kernel
+// wherever windows overlap (3 x 3, 48 -> 32 on 139240 pixels 18.6 -> 10.5, 80 -> 16 on 40768 10.6 -> 6.5; 5 x 5 stride 2, 48 -> 32 on 1802493
+// 295 -> 200); where they do not, rows are read once, as a product's are.
+inline bool narrow_conv_tile(int32_t M, int32_t N, int32_t K, int32_t taps, int32_t stride) {
+  return N <= 32 && (taps > (int64_t)stride * stride || (narrow_rows_rule(M, K) && narrow_rows_even(M, K)));
+}
+inline bool narrow_conv_rule(int32_t M, int32_t N, int32_t K, int32_t taps, int32_t stride, bool one_wave, bool stationary) {
+  if (N > 64 || M <= 64 * PLAN_CUS || one_wave || (N > 48 && K > 32768)) return false;
+  return !stationary || narrow_conv_tile(M, N, K, taps, stride) || K >= (N % 32 != 0 ? 1200 : taps > 9 ? 400 : 800);
+}
+// Beside the patch kernel, few of whose pixels meet at a stride: 5 x 5 stride 2, 32 -> 32 on 89 images of 59 x 59 12.6 -> 9.5 us, 3 x 3
+// stride 2, 64 -> 16 on 83 of 64 x 64 12.9 -> 10.1, 2 x 2 stride 2, 32 -> 16 on 1441557 pixels 113 -> 63; at stride 1 it is ahead on
+// most (64 -> 32 on 94 of 55 x 55 16.0 and 18.6).
+inline bool narrow_conv_instead_of_patch(int32_t M, int32_t N, int32_t stride) { return stride > 1 && N <= 32 && M > 64 * PLAN_CUS; }
 // A convolution of `taps` kernel positions over `bytes` of input and weights.  Its gather issues an address per 16 bytes, and two
 // workgroups of 64 x 64 to a unit cover that better than one where the lines come from near by: kernels whose positions
 // overlap more than ten times on 2.5 MB and less stay (7 x 7, 64 -> 128 on 11264 pixels 12.1 / 12.9).  336 -> 112, 3 x 3 stride 2 on

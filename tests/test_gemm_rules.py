@@ -18,6 +18,10 @@ extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_a
   return ragged ? ac::kgroup_ragged_rule(c) : ac::kgroup_rule(c);
 }
 extern "C" int one_wave(int M, int N, int K) { return !ac::kgroup_instead_of_one_wave(M, N, K); }
+extern "C" int narrow_product(int M, int N, int K) { return ac::narrow_product_rule(M, N, K); }
+extern "C" int narrow_conv(int M, int N, int K, int taps, int stride, int one_wave, int stationary) { return ac::narrow_conv_rule(M, N, K, taps, stride, one_wave, stationary); }
+extern "C" int narrow_tile(int M, int N, int K, int taps, int stride) { return ac::narrow_conv_tile(M, N, K, taps, stride); }
+extern "C" int narrow_not_patch(int M, int N, int stride) { return ac::narrow_conv_instead_of_patch(M, N, stride); }
 extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
@@ -117,3 +121,19 @@ def test_dword_shapes(rules):
             assert ops.ac_gemm_i8_auto_plan(M, N, K, False) == (tile, 1), (M, N, K)
             assert all(rules.dword_tiles(M, N, K, both) for both in (0, 1)) and not shared_tile(rules, M, N, K, workspace=False), (M, N, K)
             assert (K % 16 or N % 16) and M % 16  # each form meets the rule's operands
+
+
+def test_narrow_tiles_leave_what_they_would_slow_down(rules):
+    for M, N, K, takes in [(753035, 16, 128, False), (902968, 16, 128, False), (574609, 32, 352, False), (1837930, 16, 176, False), (401408, 16, 80, False),
+                           (48529, 32, 2192, False), (36048, 32, 2960, False), (38364, 16, 3792, False), (70643, 16, 2288, False), (39018, 32, 1184, False),
+                           (137103, 32, 128, True), (282133, 32, 208, True), (290715, 32, 544, True), (96366, 32, 16, True), (38235, 32, 160, True),
+                           (40867, 16, 1088, True), (87408, 32, 2304, True), (153392, 16, 1280, True), (51937, 32, 1600, True), (50176, 48, 1024, False), (16384, 32, 1024, False)]:
+        assert bool(rules.narrow_product(M, N, K)) == takes, (M, N, K)
+    # beside the weight-stationary kernel: pixels, columns, K, taps, stride
+    for M, N, K, taps, stride, takes in [(1052025, 16, 48, 1, 2, False), (625931, 16, 128, 1, 2, False), (1018464, 32, 16, 1, 2, False), (811008, 32, 64, 4, 2, False),
+                                         (1177254, 16, 256, 4, 2, False), (960000, 32, 704, 4, 2, False), (835200, 16, 720, 9, 3, False), (349856, 16, 1008, 4, 2, False), (349856, 16, 1408, 4, 2, True),
+                                         (1802493, 32, 1200, 25, 2, True), (578654, 32, 432, 9, 1, True), (137275, 32, 352, 1, 3, True), (100719, 16, 48, 1, 2, True)]:
+        assert bool(rules.narrow_conv(M, N, K, taps, stride, 0, 1)) == takes, (M, N, K, taps, stride)
+        assert rules.narrow_conv(M, N, K, taps, stride, 0, 0) and not rules.narrow_conv(M, N, K, taps, stride, 1, 0)
+    assert not rules.narrow_tile(35525, 16, 3312, 9, 3) and rules.narrow_tile(35525, 16, 3312, 9, 2) and rules.narrow_tile(35525, 16, 1008, 9, 3) and not rules.narrow_tile(50176, 48, 4608, 9, 1) and not rules.narrow_tile(349856, 16, 1408, 4, 2)
+    assert rules.narrow_not_patch(1441557, 16, 2) and not rules.narrow_not_patch(284350, 32, 1)

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bias", ["row", "none", "matrix"])
-@pytest.mark.parametrize("M,N,K", [(16385, 16, 16), (16512, 32, 128), (16511, 32, 144), (33025, 16, 384), (20001, 32, 400), (131072, 16, 112), (131073, 16, 128), (131073, 16, 112), (40000, 32, 2064)])
+@pytest.mark.parametrize("M,N,K", [(16385, 16, 16), (16512, 32, 128), (16511, 32, 144), (33025, 16, 384), (20001, 32, 400), (131072, 16, 112), (131073, 16, 128), (131073, 16, 112), (40000, 32, 2064), (50000, 32, 2064)])
 def test_products(M, N, K, bias):
     A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=M + 2 * N + 3 * K, bias_matrix=bias == "matrix")
     if bias == "none":
