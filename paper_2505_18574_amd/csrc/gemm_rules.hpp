@@ -186,18 +186,26 @@ struct KGroupCall {
 // 12000, 8.2 / 8.3 and 9.2 / 14.3.
 // Two rounds of four waves (t > 256) are ahead of the 64 x 64 tiles and their slices on these as well (448 -> 32, 3 x 3 on 11264 pixels
 // 12.6 / 7.7 and 12.7 / 9.9, 112 -> 48, 5 x 5 stride 1 on 5476, K = 6000, 13.9 / 9.9 and 14.4 / 11.9; given back: 432 -> 64, K = 10800, 18.8 /
-// 17.6 and 18.2 / 21.5), with more columns as long as K is some 4000 on up to 384 tiles (144 -> 240 on 1372 13.3 / 10.7 and 14.6 /
-// 12.5, 368 -> 160 on 2124 14.5 / 10.4 and 15.3 / 13.3; beyond, 288 -> 448 on 960, K = 2592, 8.9 / 9.6).
+// 17.6 and 18.2 / 21.5) while the weights, which every second tile streams again, are some 600 KB (208 -> 112, 5 x 5 on 3211 14.8 / 13.0 and
+// 16.3 / 14.7, 192 -> 96 on 4056 15.2 / 11.0; 272 -> 128, 5 x 5 stride 2 on 2448 14.1 / 18.6 and 17.1 / 21.1, 816 -> 128, 3 x 3 on 3072 15.0 /
+// 20.9, 144 -> 112, 7 x 7 stride 2 on 3200 14.5 / 17.1) and, of more than 80 columns, some units have one tile left (144 -> 128, 5 x 5
+// stride 2 on 3920, 492 tiles, 11.7 / 13.1).  With up to 400 columns as long as K is some 4000 on up to 384 tiles (144 ->
+// 240 on 1372 13.3 / 10.7 and 14.6 / 12.5, 368 -> 160 on 2124 14.5 / 10.4 and 15.3 / 13.3; beyond, 288 -> 448 on 960, K = 2592, 8.9 / 9.6, 352 ->
+// 464, 3 x 3 stride 2 on 722 10.8 / 12.9, 320 -> 512 on 588 9.9 / 11.3).
 inline int64_t kgroup_cut_conv_limit(int row, int64_t t) {
   if (row <= 16) return t <= 81 ? 9600 + 128 * t : 20000;
   if (row <= 32) return t <= 4 ? 9600 : 8800 + 40 * t;
   if (row <= 64) return t <= 8 ? 4800 : 6400 + 22 * t;
   return 3900 + 28 * t;
 }
+inline int64_t kgroup_two_rounds_conv_limit(int32_t N, int64_t t) {
+  if (N <= 128) return N > 80 && t > 480 ? 2400 : N <= 76 ? 8000 : 615000 / N;
+  return N <= 400 && t <= 384 ? 4000 : 2400;
+}
 inline bool kgroup_rule(const KGroupCall& c) {
   const int64_t t = tiles_of(c.M, c.N, 32, 32), kbytes = (int64_t)c.K * c.eb, row = (int64_t)c.N * c.eb;
   if (c.K < 16 || c.N < 1) return false;
-  if (t > 256) return t <= 512 && kbytes <= (c.conv ? (c.N <= 128 ? 8000 : t <= 384 ? 4000 : 2400) : c.raw ? (c.N <= 64 ? 1408 : 960) : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
+  if (t > 256) return t <= 512 && kbytes <= (c.conv ? kgroup_two_rounds_conv_limit(c.N, t) : c.raw ? (c.N <= 64 ? 1408 : 960) : c.b_along_k || c.eb == 2 ? 1280 : c.a_along_k ? 608 : 352);
   if (c.splits <= 1) return true;
   if (!c.workspace) return kbytes <= (row <= 64 ? 7168 : 5120);  // atomics, whose sums differ from run to run
   if (c.conv && row <= 128) return kbytes <= kgroup_cut_conv_limit((int)row, t);

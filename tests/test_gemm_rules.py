@@ -94,6 +94,15 @@ def test_two_rounds_of_shared_tiles_end_where_wider_tiles_are_ahead(rules):
     assert not shared_tile(rules, 1383, 293, 6769, eb=2, ragged=True) and shared_tile(rules, 2526, 105, 3140, eb=2, ragged=True)
 
 
+def test_two_rounds_of_shared_tiles_of_convolutions_end_where_their_weights_are_many(rules):
+    for M, N, K, takes in [(2448, 128, 6800, False), (3072, 128, 7344, False), (3757, 128, 7344, False), (3024, 128, 6192, False), (3200, 112, 7056, False), (3179, 112, 6768, False),
+                           (2304, 112, 5616, False), (3456, 96, 7056, False), (3520, 96, 6800, False), (3920, 128, 3600, False), (3888, 128, 2448, False), (722, 464, 3168, False), (576, 496, 3920, False),
+                           (960, 448, 2592, False), (588, 512, 2880, False), (3528, 112, 5488, True), (3211, 112, 5200, True), (4056, 96, 4800, True), (3528, 128, 4704, True), (2800, 128, 3136, True), (4608, 96, 5488, True),
+                           (5200, 80, 6272, True), (4800, 64, 7840, True), (12167, 32, 7840, True), (1100, 320, 2880, True), (648, 400, 2800, True)]:
+        assert 256 < -(-M // 32) * -(-N // 32) <= 512
+        assert shared_tile(rules, M, N, K, conv=True) == takes, (M, N, K)
+
+
 def test_shared_tiles_where_k_is_short(rules):
     assert [rules.one_wave(*s) for s in [(57, 64, 64), (190, 64, 64), (30, 64, 256), (100, 256, 64), (256, 256, 256), (700, 400, 64)]] == [1, 1, 0, 0, 0, 1]
     assert shared_tile(rules, 64, 5584, 336, a_along_k=False) and not shared_tile(rules, 1328, 352, 448, a_along_k=False)
