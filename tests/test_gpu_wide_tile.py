@@ -21,7 +21,7 @@ DWORD_BF16 = [(2113, 532, 352), (1500, 1000, 502), (8161, 132, 388)]
 TRANSPOSED = [("ta", 2128, 528, 272), ("ta", 8160, 160, 1168), ("tb", 2113, 528, 640), ("tb", 8161, 160, 1040), ("tab", 528, 2128, 272), ("tab", 160, 8161 // 16 * 16, 1168),
               ("ta", 2116, 532, 324), ("ta", 1004, 1500, 1004), ("tab", 532, 2116, 256), ("tab", 2052, 812, 1004)]
 # images, edge, input and output channels, kernel edge, stride
-CONVOLUTIONS = [(8, 29, 80, 176, 3, 1), (1, 90, 32, 144, 3, 1), (16, 41, 96, 208, 3, 2), (60, 25, 336, 80, 1, 2), (5, 75, 112, 192, 5, 2), (12, 32, 240, 80, 5, 1)]
+CONVOLUTIONS = [(8, 29, 80, 176, 3, 1), (51, 24, 544, 192, 1, 2), (110, 19, 576, 128, 1, 2), (3, 83, 64, 352, 3, 2), (9, 22, 128, 384, 2, 1), (23, 27, 128, 256, 2, 2), (1, 90, 32, 144, 3, 1), (16, 41, 96, 208, 3, 2), (60, 25, 336, 80, 1, 2), (5, 75, 112, 192, 5, 2), (12, 32, 240, 80, 5, 1)]
 
 SHIM = """
 #include "gemm_rules.hpp"
@@ -60,6 +60,10 @@ def test_rule(tmp_path):
     assert rules.product(16384, 128, 512, 1, 0, 1)  # 256 tiles: one to each unit
     assert not rules.product(16385, 128, 512, 1, 0, 1) and not rules.product(1024, 1024, 1024, 1, 0, 1)
     assert not rules.product(2113, 528, 240, 1, 0, 1) and not rules.product(936, 1200, 7808, 1, 0, 2) and rules.product(936, 1200, 7808, 1, 0, 1)
+    # tiles of one wave: few of 64 bytes of K whose windows overlap; their other K, more tiles, no overlap, and K that is not theirs
+    for M, N, K, taps, stride, takes in [(6348, 160, 576, 9, 1, 0), (6156, 144, 576, 9, 2, 0), (5832, 176, 320, 4, 1, 0), (5887, 176, 448, 4, 1, 0),
+                                         (5239, 352, 576, 9, 2, 1), (4225, 384, 512, 4, 1, 1), (13068, 112, 576, 1, 2, 1), (7344, 192, 544, 1, 2, 1), (5480, 208, 608, 1, 2, 1), (5832, 208, 640, 4, 1, 1)]:
+        assert rules.conv(M, N, K, taps, stride, 5000000) == takes, (M, N, K, taps, stride)
     assert not rules.trans(2113, 532, 1004, 0, 1, 1) and not rules.conv(11264, 128, 3136, 49, 1, 1 << 20)
 
 
