@@ -23,9 +23,11 @@
 // 11.1 / 7.1; 1 x 1, 3 -> 64 on ten of 200 x 200 12.4 / 9.5; 3 x 3, 3 -> 16 on one of 32 x 32 4.0 / 3.2.  With loads from any byte the
 // first of them 8.5.
 #include "conv_direct_rules.hpp"
-#include "conv_image.hpp"
+#include "gemm_ragged.hpp"
 
 namespace ac {
+
+constexpr int CONV_DIRECT_WAVES = 4;
 
 struct ConvDirectArgs {
   const void *A, *B;
@@ -41,10 +43,10 @@ struct ConvDirectArgs {
 static_assert(sizeof(ConvDirectArgs) <= 112, "beyond, a launch costs more");
 
 // NKS: K-steps of 32 bytes.  NARROW: a kernel row is one chunk, two rows to a K-step; otherwise two chunks.
-template <int NKS, int TN, bool NARROW, ConvDirectShift SHIFT, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(TN == 3 ? 3 : 4))) conv_i8_direct_kernel(const ConvDirectArgs p) {
+template <int NKS, int TN, bool NARROW, ConvDirectShift SHIFT>
+__global__ void __launch_bounds__(64 * CONV_DIRECT_WAVES) __attribute__((amdgpu_waves_per_eu(TN == 3 ? 3 : 4))) conv_i8_direct_kernel(const ConvDirectArgs p) {
   using T = TypeI8;
-  constexpr int BN = 32 * TN, B_STRIDE = BN + 16, CPR = BN / 16, THREADS = 64 * WAVES, NROW = 32 * NKS, PAYLOAD = conv_direct_payload(SHIFT);
+  constexpr int WAVES = CONV_DIRECT_WAVES, BN = 32 * TN, B_STRIDE = BN + 16, CPR = BN / 16, THREADS = 64 * WAVES, NROW = 32 * NKS, PAYLOAD = conv_direct_payload(SHIFT);
   constexpr int WB = (NROW * CPR + THREADS - 1) / THREADS;  // chunks of the weights per thread
   constexpr bool RESIDENT = NKS * TN <= 6;                  // the weights' fragments stay in registers
   __shared__ __attribute__((aligned(16))) int bias[BN];
@@ -219,38 +221,39 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
   }
 }
 
-template <int NKS, int TN, bool NARROW, ConvDirectShift SHIFT, int WAVES>
+template <int NKS, int TN, bool NARROW, ConvDirectShift SHIFT>
 static hipError_t launch_conv_direct_cfg(ConvDirectArgs& a, int n_blocks, hipStream_t stream) {
+  constexpr int WAVES = CONV_DIRECT_WAVES;
   const int64_t wgs = (((int64_t)a.tiles + 7) / 8 + WAVES - 1) / WAVES * 8, most = (int64_t)compute_units() * ((TN == 3 ? 12 : 16) / WAVES) / n_blocks / 8 * 8;
   const int64_t grid = wgs < most ? wgs : most < 8 ? 8 : most;
-  return launch_kernel(conv_i8_direct_kernel<NKS, TN, NARROW, SHIFT, WAVES>, dim3((unsigned)grid, (unsigned)n_blocks), dim3(64 * WAVES), 0, stream, a);
+  return launch_kernel(conv_i8_direct_kernel<NKS, TN, NARROW, SHIFT>, dim3((unsigned)grid, (unsigned)n_blocks), dim3(64 * WAVES), 0, stream, a);
 }
-template <int TN, bool NARROW, ConvDirectShift SHIFT, int WAVES>
+template <int TN, bool NARROW, ConvDirectShift SHIFT>
 static hipError_t launch_conv_direct_steps(int nks, ConvDirectArgs& a, int n_blocks, hipStream_t stream) {
   switch (nks) {
-    case 1: return launch_conv_direct_cfg<1, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
-    case 2: return launch_conv_direct_cfg<2, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
-    case 3: return launch_conv_direct_cfg<3, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
-    case 4: return launch_conv_direct_cfg<4, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
+    case 1: return launch_conv_direct_cfg<1, TN, NARROW, SHIFT>(a, n_blocks, stream);
+    case 2: return launch_conv_direct_cfg<2, TN, NARROW, SHIFT>(a, n_blocks, stream);
+    case 3: return launch_conv_direct_cfg<3, TN, NARROW, SHIFT>(a, n_blocks, stream);
+    case 4: return launch_conv_direct_cfg<4, TN, NARROW, SHIFT>(a, n_blocks, stream);
   }
   if constexpr (!NARROW) {
     switch (nks) {
-      case 5: return launch_conv_direct_cfg<5, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
-      case 6: return launch_conv_direct_cfg<6, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
-      case 7: return launch_conv_direct_cfg<7, TN, NARROW, SHIFT, WAVES>(a, n_blocks, stream);
+      case 5: return launch_conv_direct_cfg<5, TN, NARROW, SHIFT>(a, n_blocks, stream);
+      case 6: return launch_conv_direct_cfg<6, TN, NARROW, SHIFT>(a, n_blocks, stream);
+      case 7: return launch_conv_direct_cfg<7, TN, NARROW, SHIFT>(a, n_blocks, stream);
     }
   }
   return hipErrorInvalidValue;
 }
-template <bool NARROW, ConvDirectShift SHIFT, int WAVES>
+template <bool NARROW, ConvDirectShift SHIFT>
 static hipError_t launch_conv_direct_columns(int bn, int nks, ConvDirectArgs& a, int n_blocks, hipStream_t stream) {
-  return bn == 96 ? launch_conv_direct_steps<3, NARROW, SHIFT, WAVES>(nks, a, n_blocks, stream)
-       : bn == 64 ? launch_conv_direct_steps<2, NARROW, SHIFT, WAVES>(nks, a, n_blocks, stream) : launch_conv_direct_steps<1, NARROW, SHIFT, WAVES>(nks, a, n_blocks, stream);
+  return bn == 96 ? launch_conv_direct_steps<3, NARROW, SHIFT>(nks, a, n_blocks, stream)
+       : bn == 64 ? launch_conv_direct_steps<2, NARROW, SHIFT>(nks, a, n_blocks, stream) : launch_conv_direct_steps<1, NARROW, SHIFT>(nks, a, n_blocks, stream);
 }
-template <bool NARROW, int WAVES>
+template <bool NARROW>
 static hipError_t launch_conv_direct_shift(ConvDirectShift shift, int bn, int nks, ConvDirectArgs& a, int n_blocks, hipStream_t stream) {
-  return shift == DIRECT_NONE ? launch_conv_direct_columns<NARROW, DIRECT_NONE, WAVES>(bn, nks, a, n_blocks, stream)
-       : shift == DIRECT_13 ? launch_conv_direct_columns<NARROW, DIRECT_13, WAVES>(bn, nks, a, n_blocks, stream) : launch_conv_direct_columns<NARROW, DIRECT_TAIL, WAVES>(bn, nks, a, n_blocks, stream);
+  return shift == DIRECT_NONE ? launch_conv_direct_columns<NARROW, DIRECT_NONE>(bn, nks, a, n_blocks, stream)
+       : shift == DIRECT_13 ? launch_conv_direct_columns<NARROW, DIRECT_13>(bn, nks, a, n_blocks, stream) : launch_conv_direct_columns<NARROW, DIRECT_TAIL>(bn, nks, a, n_blocks, stream);
 }
 
 // Launches the kernel when it takes the convolution; false otherwise.
@@ -266,7 +269,7 @@ bool launch_conv_direct(const GemmParams& p, hipStream_t stream, hipError_t* e) 
   a.H = (uint16_t)p.H, a.W = (uint16_t)p.W, a.OH = (uint16_t)p.OH, a.OW = (uint16_t)p.OW, a.KH = (uint16_t)p.KH, a.RUN = (uint16_t)(p.KW * p.Cin), a.pad = (uint16_t)p.pad;
   a.shift = (uint8_t)p.shift, a.act = (uint8_t)p.act;
   a.dOW = p.dOW, a.dOH = p.dOH;
-  *e = f.narrow ? launch_conv_direct_shift<true, 4>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream) : launch_conv_direct_shift<false, 4>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream);
+  *e = f.narrow ? launch_conv_direct_shift<true>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream) : launch_conv_direct_shift<false>(f.shift, f.bn, f.nks, a, (int)f.n_blocks, stream);
   return true;
 }
 

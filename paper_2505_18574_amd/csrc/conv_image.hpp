@@ -44,10 +44,6 @@ struct ConvImageParams {
   unsigned u_magic, ow_magic;  // x / U and x / OW for units and pixels of an image by one multiply; 0: by a division
 };
 
-struct __attribute__((packed, aligned(4))) Dwords16 {
-  v4i v;
-};
-
 // DWORDS: every window starts on a dword of LDS.
 template <int BN, bool DWORDS>
 __global__ void __launch_bounds__(2 * CONV_IMAGE_BM) __attribute__((amdgpu_waves_per_eu(BN == 96 ? 3 : 4))) conv_i8_image_kernel(const GemmParams p, const ConvImageParams h, const int n_blocks) {

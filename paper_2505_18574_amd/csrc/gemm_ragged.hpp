@@ -31,6 +31,9 @@
 
 namespace ac {
 
+struct __attribute__((packed, aligned(4))) Dwords16 {
+  v4i v;
+};
 static __device__ __forceinline__ v4i load16_any(const unsigned char* p) { return ((const Unaligned16*)p)->v; }
 
 // What has to happen to a loaded chunk on its way into LDS: shift its bytes down by `s` (up when negative) and keep

@@ -74,7 +74,6 @@ inline int64_t tiles_of(int32_t M, int32_t N, int bm, int bn) { return (((int64_
 // 32 x 32, three stages (four: 1 to 3 % slower below K = 4096; four waves of 32 x 64: 3 to 8).  Measured on 5800 random shapes,
 // warm, and 2000 from HBM (before / here, us): 2936 x 384 x 1024 6.3 / 5.5, x 2240 11.5 / 9.0, 1536 x 1024 x 2240 12.9 / 10.1,
 // int32 by K 256 .. 8192 1.07 to 1.40 of the time before, A^T 1.08 to 1.44, A^T B^T on 128 x 64 tiles 1.06 to 1.3.
-constexpr int TILE_64X128 = 65;  // no plan's code either
 inline bool one_round_of_wide_tiles(int32_t M, int32_t N, int bm, int bn) { return tiles_of(M, N, 64, 64) > PLAN_CUS && tiles_of(M, N, bm, bn) <= PLAN_CUS; }
 // A product that the others would cut into `splits` pieces (1: none); dw: on dwords; raw: int32 outputs.
 // Below K = 256 (on dwords 320) the set-up of the wider tile shows (K = 64 3.5 / 3.8); cut products keep their slices beyond
