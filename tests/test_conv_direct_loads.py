@@ -1,10 +1,12 @@
-"""The loads of the convolution kernel for few channels, on the host: for every form, kernel, stride and padding over small
+"""The convolution kernel for few channels, on the host: the forms that the shapes of its GPU tests take, and its loads.  For every form, kernel, stride and padding over small
 images, what each lane requests of the input lies inside the input (the kernel's own conditions, its positions replayed)."""
 import ctypes
 import os
 import subprocess
 
 import pytest
+
+import test_gpu_conv_direct as gpu
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_18574_amd", "csrc")
 SHIM = """
@@ -17,6 +19,12 @@ static ConvDirectCall call_of(int Nb, int H, int W, int Cin, int N, int KH, int 
 extern "C" int form(int Nb, int H, int W, int Cin, int N, int KH, int KW, int stride, int pad) {
   const ConvDirectForm f = conv_direct_form(call_of(Nb, H, W, Cin, N, KH, KW, stride, pad));
   return f.takes ? (f.narrow ? 1000 : 0) + 100 * f.shift + f.nks : -1;
+}
+extern "C" int columns(int N) { return conv_direct_form(call_of(2, 29, 33, 3, N, 3, 3, 1, 1)).bn; }
+extern "C" int takes(int shift, int dword_base) {
+  ConvDirectCall c = call_of(2, 29, 33, 3, 16, 3, 3, 1, 1);
+  c.shift = shift, c.dword_base = dword_base != 0;
+  return conv_direct_form(c).takes;
 }
 // The most bytes that a load reaches beyond the input (before its start: as a negative number), over all tiles, lanes and K-steps; -1000000:
 // not taken.  kinds[0 .. 2]: tiles loaded whole, in part, and at an end of the input.
@@ -66,6 +74,30 @@ def rules(tmp_path_factory):
     so = str(folder / "shim.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", so, str(folder / "shim.cpp")], check=True)
     return ctypes.CDLL(so)
+
+
+NARROW, BYTES_13, TAIL = 1000, 100, 200  # + K-steps
+
+
+def test_forms_of_the_gpu_tests(rules):
+    shapes = next(m.args[1] for m in gpu.test_forms.pytestmark if m.name == "parametrize")
+    assert [rules.form(*s) for s in shapes] == [
+        BYTES_13 + 7, 7, 7, TAIL + 6, NARROW + TAIL + 3, TAIL + 3, 4, NARROW + BYTES_13 + 2, NARROW + 2, NARROW + BYTES_13 + 4, NARROW + BYTES_13 + 3, NARROW + TAIL + 1, BYTES_13 + 5,
+        TAIL + 1, NARROW + BYTES_13 + 1, BYTES_13 + 4, NARROW + TAIL + 3, NARROW + 2, NARROW + BYTES_13 + 2, NARROW + BYTES_13 + 2, NARROW + BYTES_13 + 2, NARROW + BYTES_13 + 1,
+        NARROW + TAIL + 1, NARROW + TAIL + 4, NARROW + TAIL + 4, NARROW + TAIL + 4, -1, NARROW + TAIL + 1]
+    for m in gpu.test_edges_of_images.pytestmark:
+        if m.args[0] == "k,cin":
+            assert all(rules.form(2, edge, edge, cin, 24, k, k, 1, pad) > 0 for k, cin in m.args[1] for edge in (32, 33, 35) for pad in (0, k // 2, k))
+    assert [rules.columns(n) for n in (1, 32, 33, 64, 80, 96, 97, 130, 192)] == [32, 32, 64, 64, 96, 96, 64, 96, 96]
+
+
+def test_calls_left_to_the_others(rules):
+    assert [rules.takes(shift, 1) for shift in (0, 1, 17, 18)] == [0, 1, 1, 0] and not rules.takes(8, 0)
+    # 33 bytes to a kernel row, nine rows, eight of two chunks, a single tap on 189 MB of output, inputs of 15 bytes and, with the dword behind, 19
+    for shape in [(2, 40, 40, 11, 16, 3, 3, 1, 1), (2, 40, 40, 3, 16, 9, 3, 1, 1), (2, 40, 40, 6, 16, 8, 3, 1, 1), (40, 222, 222, 3, 96, 1, 1, 1, 0),
+                  (1, 1, 15, 1, 16, 1, 1, 1, 0), (1, 1, 19, 1, 16, 1, 16, 1, 0)]:
+        assert rules.form(*shape) == -1, shape
+    assert rules.form(1, 2, 4, 2, 16, 1, 1, 1, 0) > 0 and rules.form(1, 1, 16, 1, 16, 1, 1, 1, 0) > 0
 
 
 def check(rules, shape, kinds):

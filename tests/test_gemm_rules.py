@@ -6,6 +6,8 @@ import subprocess
 import pytest
 
 import test_gpu_dword as dword
+import test_gpu_kgroup as kgroup
+import test_gpu_narrow as narrow
 import test_gpu_product_tile as product_tile
 from paper_2505_18574_amd import ops
 
@@ -13,8 +15,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = """
 #include "gemm_rules.hpp"
 extern "C" int product_tile(int M, int N, int K, int st160, int st320) { return ac::choose_product_tile_i8(M, N, K, st160, st320); }
-extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_along_k, int b_along_k, int splits, int workspace, int Cin) {
-  const ac::KGroupCall c = {M, N, K, eb, conv != 0, a_along_k != 0, b_along_k != 0, (int64_t)N * eb, splits, workspace != 0, Cin};
+extern "C" int kgroup(int ragged, int M, int N, int K, int eb, int conv, int a_along_k, int b_along_k, int splits, int workspace, int Cin, int raw) {
+  const ac::KGroupCall c = {M, N, K, eb, conv != 0, a_along_k != 0, b_along_k != 0, (int64_t)N * eb, splits, workspace != 0, Cin, raw != 0};
   return ragged ? ac::kgroup_ragged_rule(c) : ac::kgroup_rule(c);
 }
 extern "C" int one_wave(int M, int N, int K) { return !ac::kgroup_instead_of_one_wave(M, N, K); }
@@ -53,13 +55,13 @@ def test_product_tile_shapes(rules):
     assert [product_tile_of(rules, *shape, False) for shape in product_tile.OTHER_CODES] == [320, 128]
 
 
-def shared_tile(rules, M, N, K, eb=1, conv=False, ragged=False, workspace=True, Cin=0, a_along_k=True, b_along_k=False):
+def shared_tile(rules, M, N, K, eb=1, conv=False, ragged=False, workspace=True, Cin=0, a_along_k=True, b_along_k=False, raw=False):
     """Whether the waves of a workgroup share the call's tiles (dense operands)."""
     need = (ops.ac_gemm_i8_workspace_bytes if eb == 1 else ops.ac_gemm_bf16_workspace_bytes)(M, N, K)
     splits = need // (4 * M * N) if need and (workspace or eb == 2) else 1
     if ragged and eb == 2:
         splits = 1  # never cut
-    return bool(rules.kgroup(ragged, M, N, K, eb, conv, a_along_k, b_along_k, splits, workspace, Cin))
+    return bool(rules.kgroup(ragged, M, N, K, eb, conv, a_along_k, b_along_k, splits, workspace, Cin, raw))
 
 
 def test_shared_tiles_leave_cut_products_that_they_would_slow_down(rules):
@@ -130,6 +132,40 @@ def test_dword_shapes(rules):
             assert ops.ac_gemm_i8_auto_plan(M, N, K, False) == (tile, 1), (M, N, K)
             assert all(rules.dword_tiles(M, N, K, both) for both in (0, 1)) and not shared_tile(rules, M, N, K, workspace=False), (M, N, K)
             assert (K % 16 or N % 16) and M % 16  # each form meets the rule's operands
+
+
+def shapes_of(test):
+    """The last parametrised sizes of a GPU test."""
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and "," in m.args[0])
+
+
+def conv_sizes(nb, edge, cin, cout, k, stride):
+    out = (edge + 2 * (k // 2) - k) // stride + 1
+    return nb * out * out, cout, k * k * cin
+
+
+def test_shared_tile_shapes(rules):
+    """The sizes of the GPU tests lie on the side of each line that they are there for."""
+    taken = [(M, N, K) for M, N, K in shapes_of(kgroup.test_int32_on_two_rounds) if shared_tile(rules, M, N, K, workspace=False, raw=True)]
+    assert taken == [(8193, 32, 624), (16384, 16, 1408), (288, 928, 960), (511, 1008, 944), (300, 932, 956), (4099, 60, 1404)]
+    assert all(256 < -(-M // 32) * -(-N // 32) <= 512 for M, N, K in shapes_of(kgroup.test_int32_on_two_rounds))
+    convs = shapes_of(kgroup.test_convolutions_beside_a_workspace)
+    left = [c for c in convs if not shared_tile(rules, *conv_sizes(*c), conv=True, Cin=c[2])]
+    assert left == [(2, 9, 432, 16, 5, 1), (1, 14, 384, 32, 5, 1), (1, 20, 160, 64, 7, 1), (3, 19, 208, 80, 5, 2), (1, 7, 208, 144, 5, 1), (4, 37, 336, 48, 5, 1), (7, 14, 176, 240, 5, 1),
+                    (33, 9, 272, 160, 3, 1), (3, 31, 208, 128, 5, 1), (13, 16, 224, 112, 5, 1), (17, 15, 272, 96, 5, 1), (5, 28, 112, 128, 5, 1), (14, 7, 400, 416, 3, 1)]
+
+
+def test_narrow_shapes(rules):
+    products = shapes_of(narrow.test_products)
+    assert [s for s in products if not rules.narrow_product(*s)] == [(131073, 16, 112), (40000, 32, 2064)]
+    for c in shapes_of(narrow.test_convolutions):
+        (M, N, K), taps, stride = conv_sizes(*c), c[4] ** 2, c[5]
+        one_wave = K % 64 == 0 and K <= 640 and -(-M // 32) * -(-N // 32) <= 2048
+        assert one_wave == (c == (70, 31, 64, 32, 3, 2)), c  # this one is planned with a wave to a tile
+        # whatever else is planned; not the patch kernel, which needs whole 32s of channels, a stride of 1 and at most 32 taps
+        assert one_wave or all(rules.narrow_conv(M, N, K, taps, stride, 0, stationary) for stationary in (0, 1)), c
+        assert rules.narrow_tile(M, N, K, taps, stride) == (c != (35, 96, 144, 16, 3, 3)) or one_wave, c
+        assert c[2] % 32 != 0 or stride > 1 or taps > 32, c
 
 
 def test_narrow_tiles_leave_what_they_would_slow_down(rules):

@@ -1,7 +1,8 @@
 """GPU parity of the convolution kernel for few channels (kernel rows of at most 32 bytes), bit for bit, where its forms change:
 one and two chunks to a kernel row, windows that start on dwords, that do not, and that need the dword behind; every number of
 K-steps; rows and columns of padding, tiles that touch no edge, one edge and the ends of the input; tiles that cross rows and
-images; several tiles to a wave; column blocks of 32, 64 and 96 with partial columns; calls it leaves to the others."""
+images; several tiles to a wave; column blocks of 32, 64 and 96 with partial columns; odd addresses, which it leaves to the others.
+Which form each shape takes is asked on the host (test_conv_direct_loads.py)."""
 import numpy as np
 import pytest
 import torch
@@ -46,7 +47,7 @@ def check(Nb, H, W, Cin, Cout, KH, KW, stride, pad, shift=8, act=1, offset=0, bi
     (5, 16, 1, 17, 10, 4, 1, 1, 2),     # one column of pixels
     (3, 2, 6, 3, 8, 5, 5, 1, 2),        # images smaller than the kernel: every tile at an end of the input
     (1, 4, 4, 4, 17, 3, 3, 1, 1),       # rows of 16 bytes
-    (1, 5, 5, 3, 17, 3, 3, 1, 1),       # rows of 15: not taken
+    (1, 5, 5, 3, 17, 3, 3, 1, 1),       # ... and of 15
     (1, 6, 6, 3, 16, 3, 3, 1, 20),      # windows of padding only
     (11, 100, 101, 3, 48, 3, 3, 1, 1),  # several tiles to a wave
     (40, 61, 63, 3, 100, 1, 1, 1, 0),   # ... and two column blocks
@@ -54,7 +55,7 @@ def check(Nb, H, W, Cin, Cout, KH, KW, stride, pad, shift=8, act=1, offset=0, bi
     (1, 16, 16, 2, 16, 8, 8, 1, 0),
     (1, 38, 38, 2, 16, 7, 7, 1, 3),     # ... in a tile that pads, the last but one of its rows
     (1, 2048, 15, 2, 16, 8, 7, 1, 3),
-    (1, 1, 19, 1, 16, 1, 16, 1, 0),     # 19 and 20 bytes in all
+    (1, 1, 19, 1, 16, 1, 16, 1, 0),     # 19 bytes in all, left to another kernel, and 20
     (1, 1, 20, 1, 16, 1, 15, 1, 1),
 ])
 def test_forms(Nb, H, W, Cin, Cout, KH, KW, stride, pad):

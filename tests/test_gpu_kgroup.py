@@ -122,7 +122,9 @@ def test_int32_on_two_rounds(M, N, K):
 @pytest.mark.parametrize("Nb,edge,Cin,Cout,k,stride", [
     (1, 40, 384, 16, 5, 1), (2, 9, 400, 16, 5, 1), (2, 9, 432, 16, 5, 1), (1, 14, 352, 32, 5, 1), (1, 14, 384, 32, 5, 1), (1, 20, 128, 48, 7, 1), (1, 20, 160, 64, 7, 1),
     (3, 19, 208, 80, 5, 2), (3, 19, 176, 80, 5, 2), (3, 19, 176, 128, 5, 2), (1, 7, 208, 144, 5, 1), (15, 33, 304, 32, 5, 1), (4, 37, 320, 48, 5, 1), (4, 37, 336, 48, 5, 1),
-    (7, 14, 160, 240, 5, 1), (7, 14, 176, 240, 5, 1), (33, 9, 256, 160, 3, 1), (33, 9, 272, 160, 3, 1)])
+    (7, 14, 160, 240, 5, 1), (7, 14, 176, 240, 5, 1), (33, 9, 256, 160, 3, 1), (33, 9, 272, 160, 3, 1),
+    (3, 31, 192, 128, 5, 1), (3, 31, 208, 128, 5, 1), (13, 16, 208, 112, 5, 1), (13, 16, 224, 112, 5, 1), (17, 15, 256, 96, 5, 1), (17, 15, 272, 96, 5, 1),
+    (5, 28, 96, 128, 5, 1), (5, 28, 112, 128, 5, 1), (14, 7, 400, 400, 3, 1), (14, 7, 400, 416, 3, 1)])
 def test_convolutions_beside_a_workspace(Nb, edge, Cin, Cout, k, stride):
     x, w, b = inputs.conv_i8_inputs(Nb, edge, edge, Cin, Cout, k, k, seed=edge + Cin + Cout)
     want = oracle.conv2d_i8(x, w, b, stride, k // 2, 11, 1)

@@ -26,7 +26,7 @@ def test_products(M, N, K, bias):
 # images, edge, input and output channels, kernel edge, stride
 @pytest.mark.parametrize("workspace", [False, True])
 @pytest.mark.parametrize("nb,edge,cin,cout,k,stride", [
-    (5, 58, 80, 16, 3, 1), (17, 32, 48, 32, 3, 1), (17, 63, 48, 16, 3, 2), (70, 31, 64, 32, 3, 2), (80, 29, 32, 32, 5, 2), (6, 53, 16, 32, 7, 1), (6, 53, 144, 16, 5, 1), (30, 47, 208, 32, 1, 2), (9, 129, 48, 16, 1, 3)])
+    (5, 58, 80, 16, 3, 1), (17, 32, 48, 32, 3, 1), (17, 63, 48, 16, 3, 2), (70, 31, 64, 32, 3, 2), (80, 29, 32, 32, 5, 2), (6, 53, 16, 32, 7, 1), (6, 53, 144, 16, 5, 1), (30, 47, 208, 32, 1, 2), (9, 129, 48, 16, 1, 3), (260, 31, 64, 32, 3, 2), (35, 96, 144, 16, 3, 3), (30, 72, 80, 16, 3, 3)])
 def test_convolutions(nb, edge, cin, cout, k, stride, workspace):
     x, w, b = inputs.conv_i8_inputs(nb, edge, edge, cin, cout, k, k, seed=edge + cin + cout)
     want = oracle.conv2d_i8(x, w, b, stride, k // 2, 9, 1)
