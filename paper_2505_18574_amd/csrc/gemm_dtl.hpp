@@ -882,10 +882,6 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
   return launch_kernel(kern, dim3((unsigned)grid), dim3(G::THREADS), LDS, stream, args);
 }
 
-// The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages
-// (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128),
-// 128 and 64: the rolling-refill loop with 128 bytes of K per tile, eight waves of 64 x 64 / 64 x 32 or four waves of 32 x 32 (four stages: six and eight were measured slower on
-// every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x 4608: those loops wait on the barrier, not on loads).
 // One round of 64 x 128 tiles (gemm_rules.hpp says which calls): three stages of 24 KB, eight waves of 32 x 32.
 template <class T, class EPI, int AMODE, bool DW = false, bool TA = false, bool TB = false>
 static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
@@ -893,6 +889,11 @@ static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
   else return launch_dtl<T, EPI, 64, 128, 2, 4, AMODE, 3, 128, false, TA, TB, DW>(p, stream);
 }
 
+// The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages
+// (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128),
+// 128 and 64: the rolling-refill loop with 128 bytes of K per tile, eight waves of 64 x 64 / 64 x 32 or four waves of
+// 32 x 32 (four stages: six and eight were measured slower on every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x
+// 4608: those loops wait on the barrier, not on loads).
 template <class T, class EPI, int AMODE, bool DW = false>
 static hipError_t launch_dtl_tile(int tile, const GemmParams& p, hipStream_t stream) {
   switch (tile) {

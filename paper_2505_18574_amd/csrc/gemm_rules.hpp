@@ -73,9 +73,9 @@ inline int64_t tiles_of(int32_t M, int32_t N, int bm, int bn) { return (((int64_
 // tile is half a line: 64 rows of A and 128 half lines of B are 192 for 64 x 64 outputs, and 192 for 64 x 128.  Eight waves of
 // 32 x 32, three stages (four: 1 to 3 % slower below K = 4096; four waves of 32 x 64: 3 to 8).  Measured on 5800 random shapes,
 // warm, and 2000 from HBM (before / here, us): 2936 x 384 x 1024 6.3 / 5.5, x 2240 11.5 / 9.0, 1536 x 1024 x 2240 12.9 / 10.1,
-// int32 by K 256 .. 8192 1.07 to 1.40 of the time before, A^T 1.08 to 1.44, A^T B^T on 128 x 64 tiles 1.06 to 1.3.
+// int32 by K 256 .. 8192 1.07 to 1.40 times faster, A^T 1.08 to 1.44, A^T B^T on 128 x 64 tiles 1.06 to 1.3.
 inline bool one_round_of_wide_tiles(int32_t M, int32_t N, int bm, int bn) { return tiles_of(M, N, 64, 64) > PLAN_CUS && tiles_of(M, N, bm, bn) <= PLAN_CUS; }
-// A product that the others would cut into `splits` pieces (1: none); dw: on dwords; raw: int32 outputs.
+// A product that the others would cut into `splits` pieces (1: none); dw: on dwords.
 // Below K = 256 (on dwords 320) the set-up of the wider tile shows (K = 64 3.5 / 3.8); cut products keep their slices beyond
 // K = 5000, which are ahead with the weights in HBM (936 x 1200 x 7808 29.0 / 37.3, 436 x 3968 x 3952 28.4 / 19.2).  bf16 rows
 // of 64 columns are whole lines: from 640 bytes of K (on dwords 704), on more than 144 tiles (129 of them 16.7 / 18.7 from HBM at
@@ -109,8 +109,8 @@ inline bool narrow_rows_even(int32_t M, int32_t K) { return K < 1100 || 20 * bus
 // 32 x 208 5.0 / 4.1, 27225 x 16 x 32 3.6 / 3.4.
 inline bool narrow_product_rule(int32_t M, int32_t N, int32_t K) { return N <= 32 && M > 64 * PLAN_CUS && narrow_rows_rule(M, K) && narrow_rows_even(M, K); }
 // A convolution of at most 64 output channels on more than one 64 x 64 tile per compute unit: that tile, uncut, or up to 32
-// channels the 128 x 32 one (narrow_conv_tile).  The planner's estimates, made for products, take wider tiles or K slices there, which compute or
-// store columns that do not exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of
+// channels the 128 x 32 one (narrow_conv_tile).  The planner's estimates, made for products, take wider tiles or K slices
+// there, which compute or store columns that do not exist (7 x 7, 224 -> 32 channels on 43 images of 25 x 25 53 -> 34 us, 5 x 5 stride 2, 496 -> 48 on 42 of
 // 55 x 55 101 -> 77; level on the shapes where they agree).  Where they take the weight-stationary kernel (`stationary`) they are
 // right as long as K is short, and a single tap, a plain product but for its rows, always is (1 x 1 stride 2, 64 -> 48 on 64
 // images of 56 x 56 6.6 us there and 8.8 on the tile); its gather loses from K = 800 on where the columns are whole 32s (from
@@ -183,11 +183,13 @@ struct KGroupCall {
 // further), and rows of B a multiple of 2 KB apart (bf16: 1 KB) are left to the slices (16 x 2048 x 2048 from HBM 8.3 / 9.4,
 // 16 x 2064 x 2048 9.2 / 7.9).  Where B is narrow its lines are used whole (1400 x 32 x 4352 8.6 / 4.4 and 10.1 / 8.8).
 // Convolutions whose weights are few, up to 128 columns, come from the slices to a K that grows with the tiles: their images,
-// not their weights, are what a compute unit streams, and each pixel's chunks serve all columns of a tile.  On 160 random ones
-// (slices / here, warm and from HBM): 304 -> 16, 5 x 5 on 4232 pixels 13.1 / 6.7 and 14.0 / 8.1; 256 -> 32, 7 x 7 on 5618 23.3 / 8.8
-// and 22.6 / 11.7; 240 -> 48, 5 x 5 on 700 8.0 / 5.9 and 8.3 / 6.6; 256 -> 80 on 1980 13.2 / 7.6 and 13.7 / 11.1; none within the line
-// is more than a tenth behind from HBM, and the fewest tiles keep the line of the products (100 x 64 x 5040); left to the slices 320 -> 80 on 512 8.9 / 6.8 and 9.7 / 12.4, 480 -> 32 on 450, K =
-// 12000, 8.2 / 8.3 and 9.2 / 14.3.
+// not their weights, are what a compute unit streams, and each pixel's chunks serve all columns of a tile.  (Slices / here, warm and
+// from HBM: 304 -> 16, 5 x 5 on 4232 pixels 13.1 / 6.7 and 14.0 / 8.1; 256 -> 32, 7 x 7 on 5618 23.3 / 8.8 and 22.6 / 11.7; 240 -> 48,
+// 5 x 5 on 700 8.0 / 5.9 and 8.3 / 6.6; 256 -> 80 on 1980 13.2 / 7.6 and 13.7 / 11.1.)  The fewest tiles keep the line of the products
+// (100 x 64 x 5040); left to the slices 320 -> 80 on 512 8.9 / 6.8 and 9.7 / 12.4, 480 -> 32 on 450, K = 12000, 8.2 / 8.3 and 9.2 / 14.3.
+// Of 130 in the upper half of the line none is behind warm (1.27 times faster in the mean); from HBM 1.08, and 19 are more than a
+// twentieth behind, up to a quarter: many channels at a stride under 96 and more columns (544 -> 112, 3 x 3 stride 2 on 324
+// pixels 7.8 / 6.2 and 9.0 / 11.7, 640 -> 128 on 825 9.6 / 9.4 and 11.0 / 13.9).
 // Two rounds of four waves (t > 256) are ahead of the 64 x 64 tiles and their slices on these as well (448 -> 32, 3 x 3 on 11264 pixels
 // 12.6 / 7.7 and 12.7 / 9.9, 112 -> 48, 5 x 5 stride 1 on 5476, K = 6000, 13.9 / 9.9 and 14.4 / 11.9; given back: 432 -> 64, K = 10800, 18.8 /
 // 17.6 and 18.2 / 21.5) while the weights, which every second tile streams again, are some 600 KB (208 -> 112, 5 x 5 on 3211 14.8 / 13.0 and
