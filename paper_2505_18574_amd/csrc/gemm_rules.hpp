@@ -139,13 +139,13 @@ inline bool narrow_conv_instead_of_patch(int32_t M, int32_t N, int32_t stride) {
 // 9522 pixels 16.0 / 12.5, 416 -> 336 on 3872 20.0 / 15.3, 128 -> 272 on 61 images of 8 x 8, taken from the patch kernel, 12.9 / 7.1.
 // K beyond 8192 stays with its slices (496 -> 240 on 5746 pixels, K = 24304, 56.8 / 70.7).
 // Up to K = 640 in whole 64s the plan here is the kernel of one wave to a tile, which keeps those it walks in 64 bytes of K, ten waves to a
-// unit, where windows overlap and its tiles are few (64 -> 160, 3 x 3 on 6348 pixels 4.9 / 5.7, stride 2, 64 -> 144 on 6156 5.0 / 5.7, 80 ->
-// 176, 2 x 2 on 5832 4.2 / 4.9, K = 448 0.94 of the time in the mean; with more tiles 64 -> 352, stride 2 on 5239 9.0 / 5.9).  On its 128
-// bytes, six waves to a unit, it is level to 1.5 times slower (128 -> 384, 2 x 2 on 4225 7.4 / 5.3, K = 640 1.25 in the mean), without overlap
+// unit, where windows overlap on up to some six tiles a unit, at a stride four (64 -> 160, 3 x 3 on 6348 pixels 4.9 / 5.7, 64 -> 288 on 5000,
+// 1413 tiles, 5.1 / 5.8, 80 -> 176, 2 x 2 on 5832 4.2 / 4.9; stride 2, 64 -> 144 on 6156, 965 tiles, 5.0 / 5.7; given up: 64 -> 368 on 4050, 1524
+// tiles, 7.1 / 5.9, stride 2, 64 -> 416 on 3200, 1300 tiles, 7.1 / 5.9, 64 -> 352 on 5239 9.0 / 5.9).  On its 128 bytes, six waves to a unit, it is level to 1.5 times slower (128 -> 384, 2 x 2 on 4225 7.4 / 5.3, K = 640 1.25 in the mean), without overlap
 // 1.0 to 1.8 (1 x 1 stride 2, 576 -> 112 on 13068 8.5 / 5.9); other K there never were its (1 x 1 stride 2, 544 -> 192 6.1 / 5.7).
 inline bool wide_conv_rule(int32_t M, int32_t N, int32_t K, int32_t taps, int32_t stride, int64_t bytes) {
   if (!one_round_of_wide_tiles(M, N, 64, 128) || K < 256 || K > 8192) return false;
-  if (K % 128 == 64 && K <= 576 && taps > (int64_t)stride * stride && tiles_of(M, N, 32, 32) <= 1350) return false;
+  if (K % 128 == 64 && K <= 576 && taps > (int64_t)stride * stride && tiles_of(M, N, 32, 32) <= (stride == 1 ? 1500 : 1024)) return false;
   return taps <= 10 * (int64_t)stride * stride || bytes > 2500000;
 }
 

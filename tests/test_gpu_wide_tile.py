@@ -61,7 +61,7 @@ def test_rule(tmp_path):
     assert not rules.product(16385, 128, 512, 1, 0, 1) and not rules.product(1024, 1024, 1024, 1, 0, 1)
     assert not rules.product(2113, 528, 240, 1, 0, 1) and not rules.product(936, 1200, 7808, 1, 0, 2) and rules.product(936, 1200, 7808, 1, 0, 1)
     # tiles of one wave: few of 64 bytes of K whose windows overlap; their other K, more tiles, no overlap, and K that is not theirs
-    for M, N, K, taps, stride, takes in [(6348, 160, 576, 9, 1, 0), (6156, 144, 576, 9, 2, 0), (5832, 176, 320, 4, 1, 0), (5887, 176, 448, 4, 1, 0),
+    for M, N, K, taps, stride, takes in [(6348, 160, 576, 9, 1, 0), (6156, 144, 576, 9, 2, 0), (5832, 176, 320, 4, 1, 0), (5887, 176, 448, 4, 1, 0), (4851, 288, 576, 9, 1, 0), (7803, 192, 576, 9, 1, 0), (3200, 416, 576, 9, 2, 1), (4050, 368, 576, 9, 1, 1),
                                          (5239, 352, 576, 9, 2, 1), (4225, 384, 512, 4, 1, 1), (13068, 112, 576, 1, 2, 1), (7344, 192, 544, 1, 2, 1), (5480, 208, 608, 1, 2, 1), (5832, 208, 640, 4, 1, 1)]:
         assert rules.conv(M, N, K, taps, stride, 5000000) == takes, (M, N, K, taps, stride)
     assert not rules.trans(2113, 532, 1004, 0, 1, 1) and not rules.conv(11264, 128, 3136, 49, 1, 1 << 20)
