@@ -22,6 +22,7 @@
 #include <type_traits>
 #include <utility>
 #include "gemm_mfma.hpp"
+#include "gemm_rules.hpp"
 
 namespace ac {
 
@@ -69,7 +70,10 @@ static __device__ __forceinline__ void wait_vm() {
 // B-tile swizzle.  A transposing read phase touches R k-rows (4 for bf16, 8 for int8) times one
 // SEGB-byte segment (64 / 32 bytes: 32 columns).  With RPW rows per 256-byte bank window, XOR-ing the
 // segment index with (row / RPW) & MASK spreads those R segments over all 64 banks.
-template <int EB, int B_ROW>
+//
+// EDGE 16: the fragments of 16 x 16 MFMA tiles take 16 columns at a time, of two of their four 16-byte K chunks in a phase,
+// ROWS_PER_CHUNK k-rows apart: the odd chunks exchange the halves of a segment.
+template <int EB, int B_ROW, int EDGE = 32>
 struct BSwizzle {
   static constexpr int R = EB == 2 ? 4 : 8;
   static constexpr int SEGB = EB == 2 ? 64 : 32;
@@ -80,23 +84,16 @@ struct BSwizzle {
   static constexpr int MASK = SPAN - 1;
   static_assert(SEGS >= 1 && (SEGS & (SEGS - 1)) == 0 && SPAN >= 1, "B tile width must be a power of two of 32-column segments");
   static __device__ __forceinline__ int seg_xor(int row) { return (row / RPW) & MASK; }
+  static constexpr int ROWS_PER_CHUNK = 16 / EB;
+  static __device__ __forceinline__ int slot_xor(int row) {
+    return (seg_xor(row) << (SEG_SHIFT - 4)) ^ (EDGE == 16 ? ((row / ROWS_PER_CHUNK) & 1) << (SEG_SHIFT - 5) : 0);
+  }
   // logical 16-byte slot held by physical slot `pslot` of k-row `row` (an involution)
-  static __device__ __forceinline__ int slot(int pslot, int row) { return pslot ^ (seg_xor(row) << (SEG_SHIFT - 4)); }
+  static __device__ __forceinline__ int slot(int pslot, int row) { return pslot ^ slot_xor(row); }
 };
 
 // Swizzled B-fragment reads (see TypeI8/TypeBF16::read_col for the lane roles).
 // kb: byte offset of this lane's 16 K-bytes inside the 128-byte K tile; seg: index of the 32-column block.
-template <int B_ROW>
-static __device__ __forceinline__ v4i dtl_read_col_bf16(const unsigned char* Bs, int kb, int seg, int lane) {
-  using S = BSwizzle<2, B_ROW>;
-  const int i = lane & 15, g1 = (lane >> 4) & 1;
-  const int r = (kb >> 1) + (i >> 2);  // k-row; rows r and r + 4 share one swizzle term
-  const unsigned char* p = Bs + r * B_ROW + ((seg ^ S::seg_xor(r)) << 6) + g1 * 32 + 8 * (i & 3);
-  v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(AC_LDS(v4s, p));
-  v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(AC_LDS(v4s, p + 4 * B_ROW));
-  v2i l2 = __builtin_bit_cast(v2i, lo), h2 = __builtin_bit_cast(v2i, hi);
-  return (v4i){l2[0], l2[1], h2[0], h2[1]};
-}
 template <int B_ROW>
 static __device__ __forceinline__ v4i dtl_read_col_i8(const unsigned char* Bs, int kb, int seg, int lane) {
   using S = BSwizzle<1, B_ROW>;
@@ -109,11 +106,15 @@ static __device__ __forceinline__ v4i dtl_read_col_i8(const unsigned char* Bs, i
 }
 // Byte offset, inside a B tile, of the first of the two transposing reads of dtl_read_col (the second lies
 // HI rows further down), and the fragment read at a given address.
-template <class T, int B_ROW>
+// EDGE 16: seg is the index of the 16-column block.
+template <class T, int B_ROW, int EDGE = 32>
 static __device__ __forceinline__ int dtl_col_off(int kb, int seg, int lane) {
-  using S = BSwizzle<T::EB, B_ROW>;
+  using S = BSwizzle<T::EB, B_ROW, EDGE>;
   const int i = lane & 15, g1 = (lane >> 4) & 1;
-  if constexpr (T::EB == 2) {
+  if constexpr (EDGE == 16) {
+    const int r = T::EB == 2 ? (kb >> 1) + (i >> 2) : kb + (i >> 1);
+    return r * B_ROW + (((seg * T::EB) ^ S::slot_xor(r)) << 4) + (T::EB == 2 ? 8 * (i & 3) : 8 * (i & 1));
+  } else if constexpr (T::EB == 2) {
     const int r = (kb >> 1) + (i >> 2);
     return r * B_ROW + ((seg ^ S::seg_xor(r)) << 6) + g1 * 32 + 8 * (i & 3);
   } else {
@@ -134,12 +135,6 @@ static __device__ __forceinline__ v4i dtl_read_col_at(const unsigned char* p) {
     return (v4i){lo[0], lo[1], hi[0], hi[1]};
   }
 }
-template <class T, int B_ROW>
-static __device__ __forceinline__ v4i dtl_read_col(const unsigned char* Bs, int kb, int seg, int lane) {
-  if constexpr (T::EB == 2) return dtl_read_col_bf16<B_ROW>(Bs, kb, seg, lane);
-  else return dtl_read_col_i8<B_ROW>(Bs, kb, seg, lane);
-}
-
 // f(integral_constant<0>), f(integral_constant<1>), ...: one call per LDS stage with the stage index a constant.
 template <class F, int... I>
 static __device__ __forceinline__ void for_each_stage(F&& f, std::integer_sequence<int, I...>) {
@@ -153,17 +148,35 @@ static __device__ __forceinline__ unsigned span_bits(int first, int n, int exten
   return (hi >= 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
 }
 
-template <class T, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KTB_>
+// Swizzle term of a row of KTB bytes of K: rows that share a 256-byte bank window get the same.  A 16-byte LDS read serves lanes
+// 0-3, 12-15 and 20-27 together, then 4-11, 16-19 and 28-31: with 16 x 16 tiles rows 0-3 and 12-15 of one K chunk and rows 4-11 of
+// the next, which the window's number itself puts into the same banks twice where a row has four chunks; its negative does not.
+template <int KTB, int EDGE>
+static __device__ __forceinline__ int k_row_xor(int row) {
+  constexpr int SPR = KTB / 16, RPW = 256 / KTB;
+  return (EDGE == 16 && KTB == 64 ? -(row / RPW) : row / RPW) & (SPR - 1);
+}
+
+// x as a value of its own: what is computed from it stays where it is written.  (Out of the loop over a workgroup's tiles the
+// compiler takes every lane offset that does not change with the tile, some hundred in registers that the tile needs.)
+static __device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+template <class T, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KTB_, int EDGE = 32>
 struct DtlGeometry {
   static constexpr int EB = T::EB;
+  static constexpr int KSB = EDGE == 16 ? 64 : 32;  // K bytes of an MFMA
+  static constexpr int KCH = KSB / 16;              // its 16-byte K chunks: lanes l, l + EDGE, ... hold one each
+  using accv = std::conditional_t<EDGE == 16, typename T::acc4, typename T::accv>;
   static constexpr int KTB = KTB_;                // K bytes per A row per tile (64 or 128)
   static constexpr int BK = KTB / EB;             // K elements per tile == k-rows of the B tile
-  static constexpr int KSTEPS = KTB / 32;         // MFMA K-steps per tile (32 bytes of K each)
+  static constexpr int KSTEPS = KTB / KSB;        // MFMA K-steps per tile
   static constexpr int WAVES = WAVES_M * WAVES_N;
   static constexpr int THREADS = 64 * WAVES;
   static constexpr int A_BYTES = BM * KTB;
   static constexpr int A_SPR = KTB / 16;          // slots per A row
-  static constexpr int A_RPW = 256 / KTB;         // A rows per 256-byte bank window
   static constexpr int A_ROWS_PER_INSTR = 64 / A_SPR;
   static constexpr int B_ROW = BN * EB;           // bytes per k-row of the B tile
   static constexpr int B_SPR = B_ROW / 16;        // slots per k-row
@@ -174,29 +187,28 @@ struct DtlGeometry {
   static constexpr int B_INSTR = B_BYTES / 1024 / WAVES;
   static constexpr int B_ROWS_PER_INSTR = 64 / B_SPR;
   static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  static constexpr int TM = WTM / 32, TN = WTN / 32;
+  static constexpr int TM = WTM / EDGE, TN = WTN / EDGE;
   static_assert(KTB == 64 || KTB == 128, "K tile is 64 or 128 bytes");
   static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0, "tile must split into whole wave loads");
   static_assert(B_SPR <= 64 && 64 % B_SPR == 0, "B row must divide a wave load");
-  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA");
+  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the MFMA's");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
-  // swizzle term of an A row: rows that share a 256-byte bank window get the same term
-  static __device__ __forceinline__ int a_xor(int row) { return (row / A_RPW) & (A_SPR - 1); }
+  static __device__ __forceinline__ int a_xor(int row) { return k_row_xor<KTB, EDGE>(row); }
 };
 
 // Offsets of the dwords of a last K tile from the tile's origin, for a buffer of DW_REACH bytes (lane_offsets_fit keeps the
 // others below that): slot q of the rows from row0 on, byte dw of it; beyond the operand the offset nothing is read at.
 constexpr unsigned DW_REACH = 0xfffffff0u, DW_NOTHING = 0xffffffffu;
-template <int KTB>  // rows of KTB bytes of K, `rows` and `bytes` of them left
+template <int KTB, int EDGE = 32>  // rows of KTB bytes of K, `rows` and `bytes` of them left
 static __device__ __forceinline__ unsigned dword_contiguous(int row0, int q, int dw, int rows, int bytes, int64_t pitch) {
-  constexpr int SPR = KTB / 16, RPW = 256 / KTB;
-  const int row = row0 + q / SPR, kb = ((q % SPR) ^ ((row / RPW) & (SPR - 1))) * 16 + dw;
+  constexpr int SPR = KTB / 16;
+  const int row = row0 + q / SPR, kb = ((q % SPR) ^ k_row_xor<KTB, EDGE>(row)) * 16 + dw;
   return (row < rows) & (kb < bytes) ? (unsigned)row * (unsigned)pitch + (unsigned)kb : DW_NOTHING;
 }
-template <int EB, int ROW>  // k-rows of ROW bytes, `rows` and `bytes` of them left
+template <int EB, int ROW, int EDGE = 32>  // k-rows of ROW bytes, `rows` and `bytes` of them left
 static __device__ __forceinline__ unsigned dword_strided(int row0, int q, int dw, int rows, int bytes, int64_t pitch) {
   constexpr int SPR = ROW / 16;
-  const int row = row0 + q / SPR, col = BSwizzle<EB, ROW>::slot(q % SPR, row) * 16 + dw;
+  const int row = row0 + q / SPR, col = BSwizzle<EB, ROW, EDGE>::slot(q % SPR, row) * 16 + dw;
   return (row < rows) & (col < bytes) ? (unsigned)row * (unsigned)pitch + (unsigned)col : DW_NOTHING;
 }
 
@@ -243,9 +255,20 @@ static __device__ __forceinline__ void tile_coords_mul(int b, int nblocks, int t
   tn = qn;
 }
 
+// Schedules of gemm_dtl_kernel's K loop (each is described at its loop), and the edge of their MFMA tiles.
+enum { DTL_ROLLING, DTL_PINGPONG, DTL_INTERLEAVED };
+template <int SCHEDULE>
+constexpr int dtl_edge = SCHEDULE == DTL_INTERLEAVED ? 16 : 32;
+
 // Whether gemm_dtl_kernel keeps the bias row of its tile in LDS, behind the stages: BN * 4 bytes.
-template <class EPI, int BM, bool PINGPONG>
-constexpr bool has_bias_lds = BM >= 256 && !PINGPONG && std::is_same_v<EPI, EpilogueI8>;
+template <class EPI, int BM, int SCHEDULE>
+constexpr bool has_bias_lds = BM >= 256 && SCHEDULE != DTL_PINGPONG && std::is_same_v<EPI, EpilogueI8>;
+
+// What an epilogue keeps of its operands over the K loop, a column block of the MFMA's edge.
+template <class EPI, int EDGE>
+struct epilogue_pre { using type = typename EPI::Pre; };
+template <>
+struct epilogue_pre<EpilogueI8, 16> { using type = EpilogueI8::Pre16; };
 
 template <int BM, int AMODE>
 using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), ConvArgsWide, ConvArgs>, GemmArgs>;
@@ -262,9 +285,11 @@ using dtl_args = std::conditional_t<AMODE == 1, std::conditional_t<(BM >= 256), 
 // zeros beyond the operands, and its one chunk that could leave a buffer dword by dword; where no zeros face the bytes
 // behind K (both operands K-contiguous) or they could be infinite (bf16), A's fragments of that tile are masked.  A contiguous
 // extent is at least 16 bytes.
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_, bool PINGPONG, bool TA = false, bool TB = false, bool DW = false>
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_, int SCHEDULE, bool TA = false, bool TB = false, bool DW = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const dtl_args<BM, AMODE> p) {
-  using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
+  constexpr bool PINGPONG = SCHEDULE == DTL_PINGPONG, INTERLEAVED = SCHEDULE == DTL_INTERLEAVED;
+  constexpr int EDGE = dtl_edge<SCHEDULE>;
+  using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_, EDGE>;
   constexpr int EB = G::EB;
   static_assert(!(TA || TB) || (AMODE == 0 && EB == 1), "transposed operands: int8 GEMM");
   constexpr int AT_ROW = BM * EB, AT_SPR = AT_ROW / 16, AT_RPI = 64 / AT_SPR;  // A^T tile: bytes, slots per k-row, k-rows per instruction
@@ -280,14 +305,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
   const int nwork = ntiles * p.splits;
 
-  // Cross-item prefetch (ping-pong GEMM only): a persistent workgroup requests the first STAGES-1 K tiles of its
+  // Cross-item prefetch (products of 256 x 256 tiles): a persistent workgroup requests the first STAGES-1 K tiles of its
   // next output tile before it runs the output stage of the current one, so that the pipeline fill of the next
   // tile and the drain of this tile's stores overlap.  Vector-memory operations of a wave complete in issue order,
   // so the waits of the next tile's first trips name the stores that lie between its loads.
-  constexpr bool XPF = PINGPONG && AMODE == 0;
+  constexpr bool XPF = (PINGPONG || INTERLEAVED) && AMODE == 0;
   // lower bound of the vector-memory operations one wave issues in the output stage of a FULL tile
-  constexpr int EPI_VM = EPI::LDS_STAGED ? G::TM * 2 * (16 / (64 / (G::WTN / 4))) : G::TM * G::TN;
-  static_assert(!XPF || (STAGES - 2) * (G::A_INSTR + G::B_INSTR) + EPI_VM <= 63, "vmcnt is a 6-bit counter");
+  constexpr int EPI_VM = EPI::LDS_STAGED ? G::WTM / 16 * (16 / (64 / (G::WTN / 4))) : G::WTM * G::WTN / 1024;
+  constexpr auto vm_count = [](int n) { return n < 63 ? n : 63; };  // vmcnt is a 6-bit counter: naming fewer waits for more
 
   // The bias of a wave's columns waits in LDS behind the stages, where the tile leaves no registers to hold it over the K
   // loop: 16 to 18 of a wave of the 256 x 128 tiles went to scratch (4784 x 1600 x 2048 24.3 -> 21.8 us, 8192 x 1024 x 1024
@@ -298,7 +323,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   // K = 4608, 121.7 and 118.3; 20 such shapes 1.008 in the mean).  The
   // request is the oldest of its wave, so the K loop's first wait covers it and the
   // barrier behind that publishes it; the barrier at the end of the item frees it.
-  constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, PINGPONG>;
+  constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, SCHEDULE>;
+
+  // Stage s: A's tile, then B's, stage after stage; interleaved, all of A's and then all of B's, of 64 KB at most each, which the
+  // 16-bit immediate of an LDS read reaches from one lane address an operand.
+  constexpr int A_STRIDE = INTERLEAVED ? G::A_BYTES : G::STAGE, B_STRIDE = INTERLEAVED ? G::B_BYTES : G::STAGE;
+  constexpr int B_FIRST = INTERLEAVED ? STAGES * G::A_BYTES : G::A_BYTES;
+  static_assert(!INTERLEAVED || (STAGES * G::A_BYTES <= 65536 && STAGES * G::B_BYTES <= 65536), "an immediate of 16 bits");
 
   // ---- item-independent lane roles ---------------------------------------------------------------------
   constexpr int NVAR = G::KTB == 128 ? 2 : 1;
@@ -341,6 +372,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   const unsigned char* b_base = nullptr;
 
   auto setup = [&](int w) {
+    const int lane = INTERLEAVED ? opaque(t & 63) : t & 63;
     split = p.splits > 1 ? w / ntiles : 0;
     const int tile = w - split * ntiles;
     kt0 = split * p.kt_per_split;  // first K tile of this slice
@@ -354,7 +386,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
       g_base[i] = 0, g_rows[i] = g_cols[i] = 0u, a_voff[i] = 0, a_krow[i] = 0;
       if constexpr (TA) {
         const int krow = (wave * G::A_INSTR + i) * AT_RPI + lane / AT_SPR;
-        const int ls = BSwizzle<EB, AT_ROW>::slot(lane % AT_SPR, krow);
+        const int ls = BSwizzle<EB, AT_ROW, EDGE>::slot(lane % AT_SPR, krow);
         a_krow[i] = krow;
         a_voff[i] = (unsigned)krow * (unsigned)(p.lda * EB) + ((m0 + ls * 16) * EB < p.M * EB ? ls * 16 : 0);
       } else if constexpr (AMODE == 0) {
@@ -381,7 +413,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
         continue;
       }
       const int row = (wave * G::B_INSTR + i) * G::B_ROWS_PER_INSTR + lane / G::B_SPR;
-      const int ls = BSwizzle<EB, G::B_ROW>::slot(lane % G::B_SPR, row);
+      const int ls = BSwizzle<EB, G::B_ROW, EDGE>::slot(lane % G::B_SPR, row);
       b_krow[i] = row;
       b_voff[i] = (unsigned)row * (unsigned)(p.ldb * EB) + (n0 * EB + ls * 16 < nbytes ? ls * 16 : 0);
     }
@@ -395,8 +427,8 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 
   // Tiles are issued strictly in order 0, 1, 2, ...: the running bases and tap decode rely on it.
   auto issue_loads = [&](int kt_local, int buf) __attribute__((always_inline)) {
-    const unsigned As = lds0 + buf * G::STAGE;
-    const unsigned Bs = As + G::A_BYTES;
+    const unsigned As = lds0 + buf * A_STRIDE;
+    const unsigned Bs = lds0 + B_FIRST + buf * B_STRIDE;
     const int kt = kt0 + kt_local;
     const int kbase = kt * G::KTB;
     const bool full = kbase + G::KTB <= kbytes - (DW ? 1 : 0);  // wave-uniform; DW: the last tile never is
@@ -411,12 +443,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
           const int j = wave * G::A_INSTR + i, v = (wave * G::A_INSTR + i) & (NVAR - 1);
           if constexpr (TA) {
             dw_load(a_tile, krows - 1, j * AT_RPI, AT_RPI, p.M * EB, a_krow[i] < krows ? a_voff[i] : DW_NOTHING, As + j * 1024, l,
-                    [&](int q, int dw) { return dword_strided<EB, AT_ROW>(j * AT_RPI, q, dw, krows, p.M * EB - m0 * EB, p.lda * EB); });
+                    [&](int q, int dw) { return dword_strided<EB, AT_ROW, EDGE>(j * AT_RPI, q, dw, krows, p.M * EB - m0 * EB, p.lda * EB); });
           } else {
             const int row = j * G::A_ROWS_PER_INSTR + l / G::A_SPR;
             dw_load(a_tile, p.M - 1 - m0, j * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
                     (row < p.M - m0) & (kbase + a_chunk[v] * 16 < kbytes) ? a_voff[i] : DW_NOTHING, As + j * 1024, l,
-                    [&](int q, int dw) { return dword_contiguous<G::KTB>(j * G::A_ROWS_PER_INSTR, q, dw, p.M - m0, kbytes - kbase, p.lda * EB); });
+                    [&](int q, int dw) { return dword_contiguous<G::KTB, EDGE>(j * G::A_ROWS_PER_INSTR, q, dw, p.M - m0, kbytes - kbase, p.lda * EB); });
           }
         }
 #pragma unroll
@@ -426,10 +458,10 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
             const int row = j * G::A_ROWS_PER_INSTR + l / G::A_SPR;
             dw_load(b_tile, p.N - 1 - n0, j * G::A_ROWS_PER_INSTR, G::A_ROWS_PER_INSTR, kbytes,
                     (row < p.N - n0) & (kbase + a_chunk[v] * 16 < kbytes) ? b_voff[i] : DW_NOTHING, Bs + j * 1024, l,
-                    [&](int q, int dw) { return dword_contiguous<G::KTB>(j * G::A_ROWS_PER_INSTR, q, dw, p.N - n0, kbytes - kbase, p.ldb * EB); });
+                    [&](int q, int dw) { return dword_contiguous<G::KTB, EDGE>(j * G::A_ROWS_PER_INSTR, q, dw, p.N - n0, kbytes - kbase, p.ldb * EB); });
           } else {
             dw_load(b_tile, krows - 1, j * G::B_ROWS_PER_INSTR, G::B_ROWS_PER_INSTR, nbytes, b_krow[i] < krows ? b_voff[i] : DW_NOTHING, Bs + j * 1024, l,
-                    [&](int q, int dw) { return dword_strided<EB, G::B_ROW>(j * G::B_ROWS_PER_INSTR, q, dw, krows, nbytes - n0 * EB, p.ldb * EB); });
+                    [&](int q, int dw) { return dword_strided<EB, G::B_ROW, EDGE>(j * G::B_ROWS_PER_INSTR, q, dw, krows, nbytes - n0 * EB, p.ldb * EB); });
           }
         }
         return;  // the last tile: the running bases are not needed any more
@@ -489,68 +521,73 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     b_base += TB ? (int64_t)G::KTB : b_step;
   };
 
-  typename T::accv acc[G::TM][G::TN];
+  typename G::accv acc[G::TM][G::TN];
 
   // ---- fragments ---------------------------------------------------------------------------------------
-  // the lane's A row within a 32-row MFMA tile is lane & 31; tile origins are multiples of 32 rows and do
-  // not change the swizzle term
-  const int a_swz = G::a_xor(lane & 31);
-  const int a_lane_off = (wm * G::WTM + (lane & 31)) * G::KTB;
-  const int b_lane_off_t = (wn * G::WTN + (lane & 31)) * G::KTB;  // B^T: the lane's row of the K-contiguous B tile
+  // the lane's A row within an MFMA tile is lane % EDGE, its K chunk lane / EDGE; tile origins are multiples of 16 rows
+  // and do not change the swizzle term
+  const int l_row = lane % EDGE, l_chunk = lane / EDGE;
+  const int a_swz = G::a_xor(l_row);
+  const int a_lane_off = (wm * G::WTM + l_row) * G::KTB;
+  const int b_lane_off_t = (wn * G::WTN + l_row) * G::KTB;  // B^T: the lane's row of the K-contiguous B tile
   struct Frag {
     v4i a[G::TM], b[G::TN];
   };
   auto read_frags = [&](int buf, int ks, Frag& f) {
-    const unsigned char* As = smem + buf * G::STAGE;
-    const unsigned char* Bs = As + G::A_BYTES;
-    const int chunk = 2 * ks + (lane >> 5);
+    const unsigned char* As = smem + buf * A_STRIDE;
+    const unsigned char* Bs = smem + B_FIRST + buf * B_STRIDE;
+    const int chunk = G::KCH * ks + l_chunk;
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
-      if constexpr (TA) f.a[i] = dtl_read_col<T, AT_ROW>(As, chunk * 16, wm * G::TM + i, lane);
-      else f.a[i] = *(const v4i*)(As + a_lane_off + i * 32 * G::KTB + ((chunk ^ a_swz) << 4));
+      if constexpr (TA) f.a[i] = dtl_read_col_at<T, AT_ROW>(As + dtl_col_off<T, AT_ROW, EDGE>(chunk * 16, wm * G::TM + i, lane));
+      else f.a[i] = *(const v4i*)(As + a_lane_off + i * EDGE * G::KTB + ((chunk ^ a_swz) << 4));
     }
 #pragma unroll
     for (int j = 0; j < G::TN; j++) {
-      if constexpr (TB) f.b[j] = *(const v4i*)(Bs + b_lane_off_t + j * 32 * G::KTB + ((chunk ^ a_swz) << 4));
-      else f.b[j] = dtl_read_col<T, G::B_ROW>(Bs, chunk * 16, wn * G::TN + j, lane);
+      if constexpr (TB) f.b[j] = *(const v4i*)(Bs + b_lane_off_t + j * EDGE * G::KTB + ((chunk ^ a_swz) << 4));
+      else f.b[j] = dtl_read_col_at<T, G::B_ROW>(Bs + dtl_col_off<T, G::B_ROW, EDGE>(chunk * 16, wn * G::TN + j, lane));
     }
   };
   auto mfma_rows = [&](const Frag& f, int i0, int i1) {  // MFMA row tiles i0 .. i1-1 of one K-step
 #pragma unroll
     for (int i = i0; i < i1; i++)
 #pragma unroll
-      for (int j = 0; j < G::TN; j++) acc[i][j] = EPI::SWAP ? T::mfma(f.b[j], f.a[i], acc[i][j]) : T::mfma(f.a[i], f.b[j], acc[i][j]);
+      for (int jj = 0; jj < G::TN; jj++) {
+        const int j = EDGE == 16 && i % 2 == 1 ? G::TN - 1 - jj : jj;
+        acc[i][j] = EPI::SWAP ? T::mfma(f.b[j], f.a[i], acc[i][j]) : T::mfma(f.a[i], f.b[j], acc[i][j]);
+      }
   };
   const int nkt_total = (kbytes + G::KTB - 1) / G::KTB;
   constexpr bool DW_MASK = DW && !TA && (TB || EB == 2);
   auto mask_last = [&](Frag& f, int ks) {
 #pragma unroll
-    for (int i = 0; i < G::TM; i++) f.a[i] = dw_mask(f.a[i], kbytes - (nkt_total - 1) * G::KTB - (2 * ks + (lane >> 5)) * 16);
+    for (int i = 0; i < G::TM; i++) f.a[i] = dw_mask(f.a[i], kbytes - (nkt_total - 1) * G::KTB - (G::KCH * ks + l_chunk) * 16);
   };
   constexpr int PER_TILE = G::A_INSTR + G::B_INSTR;  // outstanding vector-memory ops per tile per wave
   static_assert((STAGES - 1) * PER_TILE <= 63, "vmcnt is a 6-bit counter");
-  using SW = BSwizzle<EB, G::B_ROW>;
-  constexpr int ROWS_PER_CHUNK = 16 / EB;  // k-rows of B that 16 bytes of K span
-  static_assert(ROWS_PER_CHUNK % SW::RPW == 0 && ((ROWS_PER_CHUNK / SW::RPW) & SW::MASK) == 0, "the B swizzle term must not depend on the K-step");
-  constexpr int KS_B = (32 / EB) * G::B_ROW;  // bytes between the B rows of consecutive K-steps
+  using SW = BSwizzle<EB, G::B_ROW, EDGE>;
+  static_assert(SW::ROWS_PER_CHUNK % SW::RPW == 0 && ((SW::ROWS_PER_CHUNK / SW::RPW) & SW::MASK) == 0, "the B swizzle term must not depend on the K-step");
+  constexpr int KS_B = (G::KSB / EB) * G::B_ROW;  // bytes between the B rows of consecutive K-steps
   // a K-contiguous operand needs one lane address per K-step (row tiles are an immediate apart), a K-strided one
   // one per 32-column block (K-steps are an immediate apart)
   constexpr int NAF = TA ? G::TM : G::KSTEPS, NBF = TB ? G::KSTEPS : G::TN;
-  constexpr int KS_A = (32 / EB) * AT_ROW;  // A^T: bytes between the rows of consecutive K-steps
+  constexpr int KS_A = (G::KSB / EB) * AT_ROW;  // A^T: bytes between the rows of consecutive K-steps
   int a_fo[NAF], b_fo[NBF];
 #pragma unroll
   for (int x = 0; x < NAF; x++) {
-    if constexpr (TA) a_fo[x] = dtl_col_off<T, AT_ROW>((lane >> 5) * 16, wm * G::TM + x, lane);
-    else a_fo[x] = a_lane_off + (((2 * x + (lane >> 5)) ^ a_swz) << 4);
+    if constexpr (TA) a_fo[x] = dtl_col_off<T, AT_ROW, EDGE>(l_chunk * 16, wm * G::TM + x, lane);
+    else a_fo[x] = a_lane_off + (((G::KCH * x + l_chunk) ^ a_swz) << 4);
+    if constexpr (INTERLEAVED) a_fo[x] = opaque(a_fo[x]);  // or every stage's sum is a register of its own, 64 KB being out of an immediate's reach
   }
 #pragma unroll
   for (int x = 0; x < NBF; x++) {
-    if constexpr (TB) b_fo[x] = G::A_BYTES + b_lane_off_t + (((2 * x + (lane >> 5)) ^ a_swz) << 4);
-    else b_fo[x] = G::A_BYTES + dtl_col_off<T, G::B_ROW>((lane >> 5) * 16, wn * G::TN + x, lane);
+    if constexpr (TB) b_fo[x] = B_FIRST + b_lane_off_t + (((G::KCH * x + l_chunk) ^ a_swz) << 4);
+    else b_fo[x] = B_FIRST + dtl_col_off<T, G::B_ROW, EDGE>(l_chunk * 16, wn * G::TN + x, lane);
+    if constexpr (INTERLEAVED) b_fo[x] = opaque(b_fo[x]);
   }
   // The immediate offset of an LDS read has 16 bits: stages that begin 64 KB or more into LDS are read through a
   // second set of lane addresses, 64 KB up (made opaque, or the compiler folds them back into one register per read).
-  constexpr bool HI_STAGES = (STAGES - 1) * G::STAGE >= 65536;
+  constexpr bool HI_STAGES = !INTERLEAVED && (STAGES - 1) * G::STAGE >= 65536;
   static_assert((STAGES - 1) * G::STAGE < 2 * 65536, "a third set of lane addresses would be needed");
   int a_fo_hi[NAF], b_fo_hi[NBF];
 #pragma unroll
@@ -568,17 +605,17 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   auto issue_whole = [&](auto lbufc) {  // the next tile in order, a whole one, into stage LBUF
     constexpr int LBUF = decltype(lbufc)::value;
 #pragma unroll
-    for (int i = 0; i < G::A_INSTR; i++) load_to_lds16_so(a_base, a_voff[i], lds0 + LBUF * G::STAGE + (wave * G::A_INSTR + i) * 1024);
+    for (int i = 0; i < G::A_INSTR; i++) load_to_lds16_so(a_base, a_voff[i], lds0 + LBUF * A_STRIDE + (wave * G::A_INSTR + i) * 1024);
 #pragma unroll
-    for (int i = 0; i < G::B_INSTR; i++) load_to_lds16_so(b_base, b_voff[i], lds0 + LBUF * G::STAGE + G::A_BYTES + (wave * G::B_INSTR + i) * 1024);
+    for (int i = 0; i < G::B_INSTR; i++) load_to_lds16_so(b_base, b_voff[i], lds0 + B_FIRST + LBUF * B_STRIDE + (wave * G::B_INSTR + i) * 1024);
     a_base += TA ? a_step_t : (int64_t)G::KTB;
     b_base += TB ? (int64_t)G::KTB : b_step;
   };
   auto issue_whole_rt = [&](int lbuf) {  // the same with the stage as a value (constant after unrolling)
 #pragma unroll
-    for (int i = 0; i < G::A_INSTR; i++) load_to_lds16_so(a_base, a_voff[i], lds0 + lbuf * G::STAGE + (wave * G::A_INSTR + i) * 1024);
+    for (int i = 0; i < G::A_INSTR; i++) load_to_lds16_so(a_base, a_voff[i], lds0 + lbuf * A_STRIDE + (wave * G::A_INSTR + i) * 1024);
 #pragma unroll
-    for (int i = 0; i < G::B_INSTR; i++) load_to_lds16_so(b_base, b_voff[i], lds0 + lbuf * G::STAGE + G::A_BYTES + (wave * G::B_INSTR + i) * 1024);
+    for (int i = 0; i < G::B_INSTR; i++) load_to_lds16_so(b_base, b_voff[i], lds0 + B_FIRST + lbuf * B_STRIDE + (wave * G::B_INSTR + i) * 1024);
     a_base += TA ? a_step_t : (int64_t)G::KTB;
     b_base += TB ? (int64_t)G::KTB : b_step;
   };
@@ -589,11 +626,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
       if constexpr (TA) f.a[i] = dtl_read_col_at<T, AT_ROW>(smem + ((HI ? a_fo_hi[i] : a_fo[i]) + (SOFF + ks * KS_A)));
-      else f.a[i] = *(const v4i*)(smem + ((HI ? a_fo_hi[ks] : a_fo[ks]) + (SOFF + i * 32 * G::KTB)));
+      else f.a[i] = *(const v4i*)(smem + ((HI ? a_fo_hi[ks] : a_fo[ks]) + (SOFF + i * EDGE * G::KTB)));
     }
 #pragma unroll
     for (int j = 0; j < G::TN; j++) {
-      if constexpr (TB) f.b[j] = *(const v4i*)(smem + ((HI ? b_fo_hi[ks] : b_fo[ks]) + (SOFF + j * 32 * G::KTB)));
+      if constexpr (TB) f.b[j] = *(const v4i*)(smem + ((HI ? b_fo_hi[ks] : b_fo[ks]) + (SOFF + j * EDGE * G::KTB)));
       else f.b[j] = dtl_read_col_at<T, G::B_ROW>(smem + ((HI ? b_fo_hi[j] : b_fo[j]) + (SOFF + ks * KS_B)));
     }
   };
@@ -612,20 +649,185 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 #pragma unroll
   for (int i = 0; i < G::TM; i++)
 #pragma unroll
-    for (int j = 0; j < G::TN; j++) acc[i][j] = T::zero();
+    for (int j = 0; j < G::TN; j++) acc[i][j] = typename G::accv{};
 
   // operands of the output stage that do not depend on the product (bias) are requested before the K loop
-  typename EPI::Pre pre[G::TN];
+  typename epilogue_pre<EPI, EDGE>::type pre[G::TN];
   if constexpr (BIAS_LDS) {
     // no row bias: a buffer of no bytes, which reads as zeros (N is at most 2^29)
     const v4i rsrc = buffer_of(p.bias, p.bias != nullptr && p.bias_ld == 0 ? (unsigned)p.N * 4u : 0u);
     if (wave < BN / 64) buffer_to_lds4(rsrc, (unsigned)(n0 + wave * 64 + lane) * 4u, lds0 + G::LDS_BYTES + wave * 256);
   } else {
 #pragma unroll
-    for (int j = 0; j < G::TN; j++) EPI::prefetch(p, n0 + wn * G::WTN + j * 32, lane, pre[j]);
+    for (int j = 0; j < G::TN; j++) EPI::prefetch(p, n0 + wn * G::WTN + j * EDGE, lane, pre[j]);
   }
 
-  if constexpr (PINGPONG) {
+  if constexpr (INTERLEAVED) {
+    // ---- interleaved main loop -------------------------------------------------------------------------
+    // Bound by power: what counts is the energy of a product.  A loop of 16 x 16 MFMAs out of registers alone sustains 4100 TOP/s
+    // (int8, uniform) and 2080 TFLOP/s (bf16, normal) where one of 32 x 32 does 3500 and 1850: half as many accumulators pass
+    // the matrix unit for a product.  Rows of MFMAs alternate their direction, so that one operand stays from each to the next
+    // (without, 3830 and 2030).  Four waves of 128 x 128 read two thirds of the fragments that eight of 128 x 64 do.
+    // One wave to a SIMD, whose MFMAs leave two or three issue slots each for its other instructions (a 16 x 16 MFMA every 17.3
+    // cycles alone, 18.3 with two vector-ALU instructions beside it).  A trip multiplies tile t out of registers and, between
+    // the MFMAs, reads the fragments of tile t + 1 (B's into a second set, a row of A's over its own behind the row's last MFMA)
+    // and requests a tile.  One barrier a trip, behind its first row of MFMAs: past it tile t + 1 is in LDS for everyone, and
+    // everyone has received tile t, whose stage is free.  Eight waves in ping-pong with 16 x 16 MFMAs: 8192^3 int8 432 us, so
+    // 418, with the paired requests below 397, its last trips interleaved too 385, its registers without spills 380; in
+    // ping-pong with 32 x 32 441.  bf16 8192 x 8192 x 4096 461 and 405.
+    static_assert(AMODE == 0 && G::KSTEPS == 1 && EDGE == 16 && G::TN % 2 == 0 && STAGES % 2 == 0, "one K-step a tile, two fragment sets in turn");
+    constexpr int PPR = G::TN / 2, SLOTS = G::TM * PPR;  // places behind two MFMAs: of a row of tiles, of all
+    // A compute unit fetches lines of 128 bytes, two K tiles of a K-contiguous operand: it is requested two tiles at a time, in the
+    // odd trips (both stages are free then), a row's second half right behind its first, which the vector L1 still has: 256
+    // lines a K tile out of the L2 instead of 384, 5 % of the time.
+    constexpr bool PAIR_A = !TA, PAIR_B = TB;
+    static_assert(STAGES == 4, "the waits below count the operations of two trips");
+    v4i fa[G::TM], fb[2][G::TN];
+    if (!started) {
+#pragma unroll(DW ? 1 : STAGES)
+      for (int s = 0; s < STAGES; s++)
+        if (s < nkt) issue_loads(s, s);
+    } else {
+      issue_whole_rt(STAGES - 1);  // the stage that the output stage of the item before worked in
+    }
+    // Fragments of the tile in the stage A_STRIDE (B_STRIDE) times its number behind the first.
+    auto read_a = [&](int i, int at) {
+      if constexpr (TA) fa[i] = dtl_read_col_at<T, AT_ROW>(smem + (a_fo[i] + at));
+      else fa[i] = *(const v4i*)(smem + (a_fo[0] + (at + i * EDGE * G::KTB)));
+    };
+    auto read_b = [&](int j, int at, v4i (&b)[G::TN]) {
+      if constexpr (TB) b[j] = *(const v4i*)(smem + (b_fo[0] + (at + j * EDGE * G::KTB)));
+      else b[j] = dtl_read_col_at<T, G::B_ROW>(smem + (b_fo[j] + at));
+    };
+    if (nkt > 0) {
+      // tile 0 has landed: the younger tiles (and, after a prefetch, the stores between them) may still be in flight
+      if (started && pf_stores) wait_vm<vm_count((STAGES - 1) * PER_TILE + EPI_VM)>();
+      else if (STAGES - 1 < nkt) wait_vm<(STAGES - 1) * PER_TILE>();
+      else wait_vm<0>();
+      block_sync();
+#pragma unroll
+      for (int j = 0; j < G::TN; j++) read_b(j, 0, fb[0]);
+#pragma unroll
+      for (int i = 0; i < G::TM; i++) read_a(i, 0);
+    } else if constexpr (BIAS_LDS) {
+      wait_vm<0>();
+      block_sync();
+    }
+    // The MFMAs of a tile, two by two, with at(place) behind each pair.
+    auto places = [&](const v4i (&b)[G::TN], auto at) {
+      for_each_stage([&](auto sc) {
+        constexpr int S = decltype(sc)::value, i = S / PPR;
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          const int jj = 2 * (S % PPR) + e, j = i % 2 == 1 ? G::TN - 1 - jj : jj;
+          acc[i][j] = EPI::SWAP ? T::mfma(b[j], fa[i], acc[i][j]) : T::mfma(fa[i], b[j], acc[i][j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        at(sc);
+        __builtin_amdgcn_sched_barrier(0);
+      }, std::make_integer_sequence<int, SLOTS>{});
+    };
+    // The row of A that place S reads for the next tile, or -1: a row's fragment is dead behind its last MFMA.
+    constexpr auto row_at = [](int s) { return s == SLOTS - 1 ? G::TM - 1 : s >= PPR && s % PPR == 0 ? s / PPR - 1 : -1; };
+    // Places behind the barrier that read no row of A, up to S.
+    constexpr auto free_before = [](int s) {
+      int n = 0;
+      for (int x = PPR; x < s; x++) n += !(x == SLOTS - 1 || x % PPR == 0);
+      return n;
+    };
+    constexpr int FREE = SLOTS - PPR - G::TM;
+    int kt = 0;
+    auto trip = [&](auto bufc, auto extrac) {
+      constexpr int BUF = decltype(bufc)::value, NBUF = (BUF + 1) % STAGES;
+      constexpr bool ODD = BUF % 2 == 1;
+      constexpr int LOADS_A = (PAIR_A ? (ODD ? 2 : 0) : 1) * G::A_INSTR, LOADS_B = (PAIR_B ? (ODD ? 2 : 0) : 1) * G::B_INSTR;
+      constexpr int LOADS = LOADS_A + LOADS_B, UNITS = G::TN + LOADS;
+      // operations younger than tile kt + 1's: all of two trips' (even); what followed the pairs that it is half of (odd)
+      constexpr int YOUNGER = !ODD || (!PAIR_A && !PAIR_B) ? 2 * PER_TILE : PAIR_A ? (PAIR_B ? 0 : 2 * G::B_INSTR) : G::A_INSTR;
+      auto load = [&](auto lc) {  // load L of the trip: A's, then B's; of a pair the older tile's, one stage below, first
+        constexpr int L = decltype(lc)::value;
+        constexpr bool IS_A = L < LOADS_A, PAIR = IS_A ? PAIR_A : PAIR_B;
+        constexpr int J = IS_A ? L : L - LOADS_A, I = PAIR ? J / 2 : J;
+        constexpr bool OLDER = PAIR && J % 2 == 0;
+        if constexpr (IS_A) {
+          const unsigned As = lds0 + (BUF - OLDER) * A_STRIDE;
+          load_to_lds16_so(PAIR && !OLDER ? a_base + G::KTB : a_base, a_voff[I], As + (wave * G::A_INSTR + I) * 1024);
+        } else {
+          load_to_lds16_so(PAIR && !OLDER ? b_base + G::KTB : b_base, b_voff[I], lds0 + B_FIRST + (BUF - OLDER) * B_STRIDE + (wave * G::B_INSTR + I) * 1024);
+        }
+      };
+      places(fb[BUF & 1], [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if constexpr (S == PPR - 1) {
+          wait_vm<vm_count(YOUNGER + decltype(extrac)::value)>();
+          block_sync();
+        }
+        if constexpr (row_at(S) >= 0) {
+          read_a(row_at(S), NBUF * A_STRIDE);
+        } else if constexpr (S >= PPR) {  // B's fragments and the loads, evenly mixed over the free places
+          constexpr int Q = free_before(S), U0 = Q * UNITS / FREE, U1 = (Q + 1) * UNITS / FREE;
+          for_each_stage([&](auto uc) {
+            constexpr int U = U0 + decltype(uc)::value, L = U * LOADS / UNITS;
+            if constexpr ((U + 1) * LOADS / UNITS > L) load(std::integral_constant<int, L>{});
+            else read_b(U - L, NBUF * B_STRIDE, fb[(BUF & 1) ^ 1]);
+          }, std::make_integer_sequence<int, U1 - U0>{});
+        }
+      });
+      a_base += TA ? a_step_t : PAIR_A ? (ODD ? 2 * (int64_t)G::KTB : 0) : (int64_t)G::KTB;
+      b_base += TB ? (ODD ? 2 * (int64_t)G::KTB : 0) : b_step;
+    };
+    const int lim = nkt < nkt_whole ? nkt : nkt_whole;
+    {
+      // first round after a prefetch across full-tile stores: the loads that trips 0 .. STAGES-3 wait for are
+      // older than those stores, so their waits name them instead of draining them
+      if (started && pf_stores && kt + 2 * STAGES - 1 < lim) {
+        for_each_stage([&](auto bc) {
+          if constexpr (decltype(bc)::value < STAGES - 2) trip(bc, std::integral_constant<int, EPI_VM>{});
+          else trip(bc, std::integral_constant<int, 0>{});
+        }, std::make_integer_sequence<int, STAGES>{});
+        kt += STAGES;
+      }
+    }
+    for (; kt + 2 * STAGES - 1 < lim; kt += STAGES)  // tiles kt + STAGES .. kt + 2 STAGES - 1 are whole
+      for_each_stage([&](auto bc) { trip(bc, std::integral_constant<int, 0>{}); }, std::make_integer_sequence<int, STAGES>{});
+    // The last tiles, up to 2 STAGES - 1 of them, with the stage as a value: what is still to be requested is requested at once,
+    // a tile a trip.  When tile kt + 1 has to have landed two younger ones may be in flight at first, then the one that the
+    // trip before requested.
+    int buf = 0;  // kt is a multiple of STAGES
+    auto last_trip = [&](const v4i (&b)[G::TN], v4i (&nb)[G::TN], auto first) {
+      const int nbuf = (buf + 1) % STAGES;
+      if (kt + STAGES - 1 >= nkt) wait_vm<0>();
+      else if (decltype(first)::value && buf == 0) wait_vm<2 * PER_TILE>();
+      else wait_vm<PER_TILE>();
+      block_sync();
+      if (kt + STAGES < nkt) issue_loads(kt + STAGES, buf);
+      places(b, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if constexpr (S < G::TN) read_b(S, nbuf * B_STRIDE, nb);
+        if constexpr (row_at(S) >= 0) read_a(row_at(S), nbuf * A_STRIDE);
+      });
+      buf = nbuf;
+      kt++;
+    };
+    while (kt + 2 < nkt) {
+      last_trip(fb[0], fb[1], std::true_type{});
+      last_trip(fb[1], fb[0], std::false_type{});
+    }
+    if (kt + 1 < nkt) {
+      last_trip(fb[0], fb[1], std::false_type{});
+#pragma unroll
+      for (int j = 0; j < G::TN; j++) fb[0][j] = fb[1][j];
+    }
+    if (nkt > 0) {
+      if constexpr (DW_MASK) {
+        if (kbytes % 16 != 0 && kt0 + nkt == nkt_total) {
+#pragma unroll
+          for (int i = 0; i < G::TM; i++) fa[i] = dw_mask(fa[i], kbytes - (nkt_total - 1) * G::KTB - l_chunk * 16);
+        }
+      }
+      places(fb[0], [](auto) {});
+    }
+  } else if constexpr (PINGPONG) {
     // ---- ping-pong main loop ---------------------------------------------------------------------------
     // Eight waves, two per SIMD, in two groups of four (one wave of each group on every SIMD).  A wave
     // alternates between a memory phase (issue its share of the direct-to-LDS loads for a later tile, read
@@ -781,11 +983,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 
   // ---- output stage of the finished item; with XPF the next item's first tiles are requested ahead of it ----
   const int em0 = m0, en0 = n0, esplit = split;
+  const int elane = INTERLEAVED ? opaque(lane) : lane;
   const bool efull = em0 + BM <= p.M && en0 + BN <= p.N;  // wave-uniform: no store of this tile is masked
   started = false;
   if constexpr (XPF) {
     // every item of a launch has the same K range here (no K slices); the fill needs STAGES - 1 whole tiles
-    if (work + (int)gridDim.x < nwork && p.splits == 1 && nkt_whole >= STAGES - 1) {
+    if (work + (int)gridDim.x < nwork && p.splits == 1 && nkt_whole >= (INTERLEAVED ? STAGES : STAGES - 1)) {
       block_sync();  // every wave has read its last fragments: stages 0 .. STAGES-2 can take the next item's tiles
       setup(work + (int)gridDim.x);
 #pragma unroll
@@ -804,68 +1007,80 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     // half-waves, four rows apart, still hit different banks.  Otherwise: row pitch WTN + 8 from the LDS base.
     using SV = typename EPI::StagedValue;
     typedef SV sv4 __attribute__((ext_vector_type(4)));
-    constexpr int PITCH = XPF ? G::WTN : G::WTN + 8;
+    // 16 x 16 tiles: the four lane groups are four rows apart; XPF exchanges the quarters of 64 values by (row / 4) % 4, a pitch of
+    // WTN + 4 puts the groups into different banks by itself.
+    constexpr int PITCH = XPF ? G::WTN : EDGE == 16 ? G::WTN + 4 : G::WTN + 8;
+    constexpr auto pcol_of = [](int col, int row) { return !XPF ? col : EDGE == 16 ? col ^ (((row >> 2) & 3) << 4) : col ^ (((row >> 2) & 1) << 5); };
     constexpr int LPR = G::WTN / 4, RPI = 64 / LPR, NI = 16 / RPI;  // lanes per row, rows per instruction, instructions per 16 rows
     static_assert(G::WAVES * 16 * PITCH * 4 <= (XPF ? G::STAGE : G::LDS_BYTES) && 64 % LPR == 0 && 16 % RPI == 0 && sizeof(SV) == 4, "staging region");
     static_assert(!XPF || (G::WTN % 64 == 0), "the half-row exchange needs rows of whole 32-value halves");
     if (!started) block_sync();  // every wave has read its last fragments: the stages are free
-    SV* region = (SV*)(smem + (XPF ? (STAGES - 1) * G::STAGE : 0)) + wave * (16 * PITCH);
-    const int h = lane >> 5, c = lane & 31;
+    constexpr int RB = 16 * PITCH * 4, AW = G::A_BYTES / RB;  // a wave's bytes; XPF: waves that work in A's stage, the others in B's
+    static_assert(!XPF || (AW * RB == G::A_BYTES && (G::WAVES - AW) * RB <= G::B_BYTES), "the last stage, shared out");
+    SV* region = (SV*)(smem + (XPF ? (wave < AW ? (STAGES - 1) * A_STRIDE + wave * RB : B_FIRST + (STAGES - 1) * B_STRIDE + (wave - AW) * RB) : wave * RB));
+    const auto add = EPI::staged_add(p, en0 + wn * G::WTN + (elane % LPR) * 4);  // a lane's four columns are the same in every row
     auto body = [&](auto fullc) {
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
 #pragma unroll
-      for (int hf = 0; hf < 2; hf++) {
+      for (int hf = 0; hf < EDGE / 16; hf++) {
 #pragma unroll
         for (int j = 0; j < G::TN; j++)
 #pragma unroll
-          for (int rr = 0; rr < 8; rr++) {
-            const int row = 8 * (rr / 4) + 4 * h + rr % 4;
-            const int col = XPF ? ((32 * j + c) ^ (h << 5)) : 32 * j + c;  // rows 4 h + ... have bit 2 == h
-            region[row * PITCH + col] = EPI::staged_in(p, acc[i][j][hf * 8 + rr]);
+          for (int rr = 0; rr < EDGE / 4; rr++) {
+            const int row = (EDGE == 16 ? 0 : 8 * (rr / 4)) + 4 * (elane / EDGE) + rr % 4;
+            region[row * PITCH + pcol_of(EDGE * j + elane % EDGE, row)] = EPI::staged_in(p, acc[i][j][hf * 8 + rr]);
           }
+        // Other lanes read what this one wrote.  A wave's LDS accesses are in order, but the compiler orders only those of a lane,
+        // and moves a write whose own lane does not read it past the reads.
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int q = 0; q < NI; q++) {
-          const int row = q * RPI + lane / LPR, col = (lane % LPR) * 4;
-          const int pcol = XPF ? (col ^ (((row >> 2) & 1) << 5)) : col;
-          const sv4 o = *(const sv4*)(region + row * PITCH + pcol);
-          const int m = em0 + wm * G::WTM + i * 32 + hf * 16 + row, n = en0 + wn * G::WTN + col;
+          const int row = q * RPI + elane / LPR, col = (elane % LPR) * 4;
+          const sv4 o = *(const sv4*)(region + row * PITCH + pcol_of(col, row));
+          const int m = em0 + wm * G::WTM + i * EDGE + hf * 16 + row, n = en0 + wn * G::WTN + col;
           // N is a multiple of 4 on this path: a group of four columns is inside or outside
-          if (decltype(fullc)::value || (m < p.M && n < p.N)) EPI::staged_out(p, m, n, o, esplit);
+          if (decltype(fullc)::value || (m < p.M && n < p.N)) EPI::staged_out(p, m, n, o, esplit, add);
         }
+        asm volatile("" ::: "memory");  // ... nor may the next rows be written ahead of the reads
       }
     }
     };
     if (XPF && efull) body(std::true_type{});
     else body(std::false_type{});
+  } else if constexpr (BIAS_LDS && EDGE == 16) {
+    EpilogueI8::Pre16 bias[G::TN];
+#pragma unroll
+    for (int j = 0; j < G::TN; j++) bias[j].bias = *(const v4i*)(smem + G::LDS_BYTES + (wn * G::WTN + j * 16 + 4 * (elane >> 4)) * 4);
+    EPI::wave_tile(p, em0 + wm * G::WTM, en0 + wn * G::WTN, acc, elane, esplit, bias);
   } else if constexpr (BIAS_LDS) {
     const auto pre_of = [&](int j) {
       asm volatile("" ::: "memory");  // read for each block anew: kept over the blocks they are registers again
       typename EPI::Pre b;
 #pragma unroll
-      for (int q = 0; q < 4; q++) b.bias[q] = *(const v4i*)(smem + G::LDS_BYTES + (wn * G::WTN + j * 32 + 8 * q + 4 * (lane >> 5)) * 4);
+      for (int q = 0; q < 4; q++) b.bias[q] = *(const v4i*)(smem + G::LDS_BYTES + (wn * G::WTN + j * 32 + 8 * q + 4 * (elane >> 5)) * 4);
       return b;
     };
-    EPI::template wave_blocks<false, G::TM, G::TN>(p, em0 + wm * G::WTM, en0 + wn * G::WTN, [&](int i, int j) -> const typename T::accv& { return acc[i][j]; }, lane, esplit, pre_of);
+    EPI::template wave_blocks<false, G::TM, G::TN>(p, em0 + wm * G::WTM, en0 + wn * G::WTN, [&](int i, int j) -> const typename T::accv& { return acc[i][j]; }, elane, esplit, pre_of);
   } else if constexpr (has_wave_tile<EPI>::value) {
-    EPI::wave_tile(p, em0 + wm * G::WTM, en0 + wn * G::WTN, acc, lane, esplit, pre);
+    EPI::wave_tile(p, em0 + wm * G::WTM, en0 + wn * G::WTN, acc, elane, esplit, pre);
   } else {
 #pragma unroll
   for (int i = 0; i < G::TM; i++) {
-    const int mrow0 = em0 + wm * G::WTM + i * 32;
+    const int mrow0 = em0 + wm * G::WTM + i * EDGE;
 #pragma unroll
-    for (int j = 0; j < G::TN; j++) EPI::tile(p, mrow0, en0 + wn * G::WTN + j * 32, acc[i][j], lane, esplit, pre[j]);
+    for (int j = 0; j < G::TN; j++) EPI::tile(p, mrow0, en0 + wn * G::WTN + j * EDGE, acc[i][j], elane, esplit, pre[j]);
   }
   }
   block_sync();  // all LDS reads of this tile are done before the next tile refills the LDS stages
   } while ((work += gridDim.x) < nwork);  // tile loop
 }
 
-template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_ = 128, bool PINGPONG = false, bool TA = false, bool TB = false, bool DW = false>
+template <class T, class EPI, int BM, int BN, int WAVES_M, int WAVES_N, int AMODE, int STAGES, int KTB_ = 128, int SCHEDULE = DTL_ROLLING, bool TA = false, bool TB = false, bool DW = false>
 static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
-  using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_>;
-  auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, PINGPONG, TA, TB, DW>;
-  constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, PINGPONG> ? BN * 4 : 0);
+  using G = DtlGeometry<T, BM, BN, WAVES_M, WAVES_N, STAGES, KTB_, dtl_edge<SCHEDULE>>;
+  auto kern = gemm_dtl_kernel<T, EPI, BM, BN, WAVES_M, WAVES_N, AMODE, STAGES, KTB_, SCHEDULE, TA, TB, DW>;
+  constexpr int LDS = G::LDS_BYTES + (has_bias_lds<EPI, BM, SCHEDULE> ? BN * 4 : 0);
   static std::atomic<bool> configured{LDS <= 64 * 1024};
   if (const hipError_t e = allow_dynamic_lds_once(configured, kern, LDS)) return e;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
@@ -885,8 +1100,19 @@ static hipError_t launch_dtl(const GemmParams& p, hipStream_t stream) {
 // One round of 64 x 128 tiles (gemm_rules.hpp says which calls): three stages of 24 KB, eight waves of 32 x 32.
 template <class T, class EPI, int AMODE, bool DW = false, bool TA = false, bool TB = false>
 static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
-  if constexpr (TA && TB) return launch_dtl<T, EPI, 128, 64, 4, 2, AMODE, 3, 128, false, TA, TB, DW>(p, stream);
-  else return launch_dtl<T, EPI, 64, 128, 2, 4, AMODE, 3, 128, false, TA, TB, DW>(p, stream);
+  if constexpr (TA && TB) return launch_dtl<T, EPI, 128, 64, 4, 2, AMODE, 3, 128, DTL_ROLLING, TA, TB, DW>(p, stream);
+  else return launch_dtl<T, EPI, 64, 128, 2, 4, AMODE, 3, 128, DTL_ROLLING, TA, TB, DW>(p, stream);
+}
+
+// 256 x 256 tiles.  Products whose K loop is long enough run interleaved (interleaved_rule); slices, convolutions, the short ones
+// and the output stages that the 16 x 16 tiles do not have stay in ping-pong.
+template <class T, class EPI, int AMODE, bool TA, bool TB, bool DW>
+static hipError_t launch_dtl_256(const GemmParams& p, hipStream_t stream) {
+  constexpr bool I8 = std::is_same_v<EPI, EpilogueI8>;
+  if constexpr (AMODE == 0 && (I8 || std::is_same_v<EPI, EpilogueRawI32> || std::is_same_v<EPI, EpilogueF32>) && !(TA && !TB))
+    if (p.splits <= 1 && interleaved_rule(p.M, p.N, (int64_t)p.K * T::EB, T::EB, I8 ? 1 : 4, TA, TB) && (!I8 || EpilogueI8::takes16(p.shift, p.bias, p.bias_ld)))
+      return launch_dtl<T, EPI, 256, 256, 2, 2, AMODE, 4, 64, DTL_INTERLEAVED, TA, TB, DW>(p, stream);
+  return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, DTL_PINGPONG, TA, TB, DW>(p, stream);
 }
 
 // The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages
@@ -897,10 +1123,10 @@ static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
 template <class T, class EPI, int AMODE, bool DW = false>
 static hipError_t launch_dtl_tile(int tile, const GemmParams& p, hipStream_t stream) {
   switch (tile) {
-    case 256: return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, true, false, false, DW>(p, stream);
-    case 192: return launch_dtl<T, EPI, 256, 128, 4, 2, AMODE, 3, 128, false, false, false, DW>(p, stream);
-    case 128: return launch_dtl<T, EPI, 128, 128, 2, 4, AMODE, 3, 128, false, false, false, DW>(p, stream);
-    default: return launch_dtl<T, EPI, 64, 64, 2, 2, AMODE, 4, 128, false, false, false, DW>(p, stream);
+    case 256: return launch_dtl_256<T, EPI, AMODE, false, false, DW>(p, stream);
+    case 192: return launch_dtl<T, EPI, 256, 128, 4, 2, AMODE, 3, 128, DTL_ROLLING, false, false, DW>(p, stream);
+    case 128: return launch_dtl<T, EPI, 128, 128, 2, 4, AMODE, 3, 128, DTL_ROLLING, false, false, DW>(p, stream);
+    default: return launch_dtl<T, EPI, 64, 64, 2, 2, AMODE, 4, 128, DTL_ROLLING, false, false, DW>(p, stream);
   }
 }
 

@@ -329,7 +329,7 @@ template <int AMODE>
 static hipError_t launch_narrow(GemmParams p, hipStream_t stream) {
   p.splits = 1;
   p.kt_per_split = 0;
-  return launch_dtl<TypeI8, EpilogueI8, 128, 32, 4, 1, AMODE, 3, 128, false>(p, stream);
+  return launch_dtl<TypeI8, EpilogueI8, 128, 32, 4, 1, AMODE, 3, 128>(p, stream);
 }
 
 template <int AMODE>

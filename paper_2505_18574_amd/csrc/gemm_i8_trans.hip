@@ -24,10 +24,10 @@ static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   if constexpr (TA || !DW)  // (B^T on dwords never does)
     if (wide_trans_rule(p.M, p.N, p.K, TA, TB, DW)) return launch_dtl_wide<TypeI8, EpilogueI8, 0, DW, TA, TB>(p, stream);
   switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // no tile but the wide ones is other than square: the 256 x 128 code falls to 128
-    case 256: return launch_dtl<TypeI8, EpilogueI8, 256, 256, 2, 4, 0, 4, 64, true, TA, TB, DW>(p, stream);
+    case 256: return launch_dtl_256<TypeI8, EpilogueI8, 0, TA, TB, DW>(p, stream);
     case 192:
-    case 128: return launch_dtl<TypeI8, EpilogueI8, 128, 128, 2, 4, 0, 3, 128, false, TA, TB, DW>(p, stream);
-    default: return launch_dtl<TypeI8, EpilogueI8, 64, 64, 2, 2, 0, 4, 128, false, TA, TB, DW>(p, stream);
+    case 128: return launch_dtl<TypeI8, EpilogueI8, 128, 128, 2, 4, 0, 3, 128, DTL_ROLLING, TA, TB, DW>(p, stream);
+    default: return launch_dtl<TypeI8, EpilogueI8, 64, 64, 2, 2, 0, 4, 128, DTL_ROLLING, TA, TB, DW>(p, stream);
   }
 }
 

@@ -20,6 +20,8 @@ struct TypeI8 {
   static __device__ __forceinline__ accv mfma(v4i rowop, v4i colop, accv c) {
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(rowop, colop, c, 0, 0, 0);
   }
+  using acc4 = v4i;  // of a 16 x 16 tile
+  static __device__ __forceinline__ acc4 mfma(v4i rowop, v4i colop, acc4 c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(rowop, colop, c, 0, 0, 0); }
   // 16 consecutive k (bytes) of one B column, gathered from K-major LDS rows.
   // Within a 16-lane group lane i supplies the address of 8 bytes of row i/2 and
   // receives 8 k-values of column i.
@@ -43,6 +45,10 @@ struct TypeBF16 {
   }
   static __device__ __forceinline__ accv mfma(v4i rowop, v4i colop, accv c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, rowop), __builtin_bit_cast(v8bf, colop), c, 0, 0, 0);
+  }
+  using acc4 = v4f;
+  static __device__ __forceinline__ acc4 mfma(v4i rowop, v4i colop, acc4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, rowop), __builtin_bit_cast(v8bf, colop), c, 0, 0, 0);
   }
   // 8 consecutive k of one B column: lane i of a 16-lane group addresses 4
   // elements of row i/4 and receives 4 k-values of column i.
@@ -296,6 +302,45 @@ struct EpilogueI8 {
   static __device__ __forceinline__ void wave_tile(const P& p, int mrow0, int ncol0, const ACC (&acc)[TM][TN], int lane, int esplit, const Pre (&pre)[TN]) {
     wave_blocks<BIASED, TM, TN>(p, mrow0, ncol0, [&](int i, int j) -> const ACC& { return acc[i][j]; }, lane, esplit, [&](int j) -> const Pre& { return pre[j]; });
   }
+  // The wave tile as TM x TN tiles of 16 x 16, for shifts 1..17 and no bias or a row of it: lane l holds of each tile the row
+  // l % 16 and the columns 4 (l / 16) .. + 3.  Four tiles of a row are quantised to a dword a lane each and exchanged between
+  // registers and lane groups (a 4 x 4 transpose), after which lane group g stores tile g, 16 bytes of a row a lane.
+  struct Pre16 {
+    v4i bias;  // of the lane's four columns
+  };
+  static bool takes16(int shift, const void* bias, int64_t bias_ld) { return shift >= 1 && shift <= 17 && (bias == nullptr || bias_ld == 0); }
+  template <int TM, int TN, class P>
+  static __device__ __forceinline__ void wave_tile(const P& p, int mrow0, int ncol0, const v4i (&acc)[TM][TN], int lane, int, const Pre16 (&pre)[TN]) {
+    static_assert(TN % 4 == 0, "four tiles at a time");
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    const FastQuant f = fast_quant(p.shift, p.act);
+    int8_t* dst = (int8_t*)p.C + (int64_t)(mrow0 + (lane & 15)) * p.ldc + ncol0 + 16 * (lane >> 4);
+    const int64_t down = 16 * p.ldc;
+    const int rows = p.M - mrow0 - (lane & 15), cols = p.N - ncol0 - 16 * (lane >> 4);
+    auto groups = [&](auto whole) {
+#pragma unroll
+      for (int i = 0; i < TM; i++) {
+#pragma unroll
+        for (int j = 0; j < TN; j += 4) {
+          unsigned d[4];
+#pragma unroll
+          for (int s = 0; s < 4; s++) {
+            const v4i t = acc[i][j + s] + pre[j + s].bias;  // no bias: zeros
+            d[s] = pack4(requant_fast<true>(t[0], f), requant_fast<true>(t[1], f), requant_fast<true>(t[2], f), requant_fast<true>(t[3], f));
+          }
+          const v2u a = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false), b = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+          const v2u lo = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), hi = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+          const v4i o = {(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+          if constexpr (decltype(whole)::value) ((Unaligned16*)(dst + 16 * j))->v = o;
+          else if (16 * i < rows) store_run16(dst + 16 * j, o, cols - 16 * j);
+          __builtin_amdgcn_sched_barrier(0);  // or a tile's worth of them is in flight at once, out of registers
+        }
+        dst += down;
+      }
+    };
+    if (mrow0 + 16 * TM <= p.M && ncol0 + 16 * TN <= p.N) groups(std::true_type{});  // wave-uniform
+    else groups(std::false_type{});
+  }
   // A column of TM blocks with one bias block.
   template <bool BIASED = false, int TM, class ACC, class P>
   static __device__ __forceinline__ void wave_column(const P& p, int mrow0, int ncol0, const ACC (&acc)[TM], int lane, const Pre& pre) {
@@ -377,9 +422,11 @@ struct EpiloguePartialI32 {
   template <class P>
   static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
   template <class P>
-  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int split) {
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int split, int) {
     *(v4i*)(p.partial + ((int64_t)split * p.M + m) * p.N + n) = o;
   }
+  template <class P>
+  static __device__ __forceinline__ int staged_add(const P&, int) { return 0; }
   struct Pre {};
   template <class P>
   static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
@@ -398,12 +445,19 @@ struct EpilogueRawI32 {
   template <class P>
   static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
   template <class P>
-  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int) {
-    if (p.bias) {
-      const int32_t* b = p.bias_ld == 0 ? p.bias + n : p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
-      o += (v4i){b[0], b[1], b[2], b[3]};
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int, v4i add) {
+    if (p.bias && p.bias_ld != 0) {
+      const int32_t* b = p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
+      add = (v4i){b[0], b[1], b[2], b[3]};
     }
-    *(v4i*)((int32_t*)p.C + (int64_t)m * p.ldc + n) = o;
+    *(v4i*)((int32_t*)p.C + (int64_t)m * p.ldc + n) = o + add;
+  }
+  // The bias row's values of columns n .. n + 3 (N is a multiple of 4 on this path), or zeros.
+  template <class P>
+  static __device__ __forceinline__ v4i staged_add(const P& p, int n) {
+    if (p.bias == nullptr || p.bias_ld != 0 || n >= p.N) return (v4i){0, 0, 0, 0};
+    const int32_t* b = p.bias + n;
+    return (v4i){b[0], b[1], b[2], b[3]};
   }
   struct Pre {};
   template <class P>
@@ -437,11 +491,13 @@ struct EpilogueF32 {
   template <class P>
   static __device__ __forceinline__ float staged_in(const P& p, float a) { return p.alpha * a; }
   template <class P>
-  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int) {
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int, int) {
     float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
     if (p.beta != 0.f) o += p.beta * *(const v4f*)dst;
     *(v4f*)dst = o;
   }
+  template <class P>
+  static __device__ __forceinline__ int staged_add(const P&, int) { return 0; }
   struct Pre {};
   template <class P>
   static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}
@@ -491,9 +547,11 @@ struct EpiloguePartialF32 {
   template <class P>
   static __device__ __forceinline__ float staged_in(const P&, float a) { return a; }
   template <class P>
-  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int split) {
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int split, int) {
     *(v4f*)((float*)p.partial + ((int64_t)split * p.M + m) * p.N + n) = o;
   }
+  template <class P>
+  static __device__ __forceinline__ int staged_add(const P&, int) { return 0; }
   struct Pre {};
   template <class P>
   static __device__ __forceinline__ void prefetch(const P&, int, int, Pre&) {}

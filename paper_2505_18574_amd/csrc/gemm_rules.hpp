@@ -267,4 +267,19 @@ inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_alo
   return both_along_k ? t64 > 4 * PLAN_CUS || kbytes >= 1024 : t64 > 3 * PLAN_CUS || kbytes >= 192;
 }
 
+// Whether a product of 256 x 256 tiles, uncut, runs on the interleaved K loop (one wave to a SIMD, 16 x 16 MFMA tiles) instead of the
+// ping-pong one.  A trip of it is a ninth to a fifth faster, its output stage, which one wave to a SIMD works through alone, some
+// 0.5 us a tile slower.  Replayed from a graph, us in ping-pong / interleaved: int8 4096 x 4096 x 2048 33.4 / 30.9, 8192 x 8192 x
+// 1024 67.9 / 72.0, 8192^3 441 / 380; with B^T 4096 x 8192 x 512 24.6 / 26.1, x 1024 37.4 / 35.8; A^T B^T 4096 x 8192 x 512 27.1 / 25.7,
+// x 128 18.9 / 18.8; int32 outputs 4096 x 4096 x 2048 38.0 / 38.9, x 3072 50.9 / 49.8, on more than a tile a compute unit 8192 x
+// 4096 x 1536 68.2 / 68.8, x 2048 80.3 / 77.6; bf16 (bytes of K) 4096 x 4096 x 512 19.1 / 20.5, x 1024 25.0 / 25.1, 8192 x 8192 x 1024
+// 132.5 / 115.5.  A^T alone gains nothing (4096 x 8192 x 4096 111.6 / 109.6, x 8192 210.7 / 212.2): neither operand's lines are
+// requested twice there.
+inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int out_bytes, bool trans_a, bool trans_b) {
+  if (trans_a && !trans_b) return false;
+  if (eb == 2) return kbytes >= 1024;
+  if (out_bytes == 4) return kbytes >= ((int64_t)((M + 255) / 256) * ((N + 255) / 256) > PLAN_CUS ? 2048 : 3072);
+  return kbytes >= (trans_b ? (trans_a ? 512 : 1024) : 2048);
+}
+
 }  // namespace ac

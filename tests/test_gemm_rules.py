@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 import test_gpu_dword as dword
+import test_gpu_interleaved as interleaved
 import test_gpu_kgroup as kgroup
 import test_gpu_narrow as narrow
 import test_gpu_product_tile as product_tile
@@ -24,6 +25,7 @@ extern "C" int narrow_product(int M, int N, int K) { return ac::narrow_product_r
 extern "C" int narrow_conv(int M, int N, int K, int taps, int stride, int one_wave, int stationary) { return ac::narrow_conv_rule(M, N, K, taps, stride, one_wave, stationary); }
 extern "C" int narrow_tile(int M, int N, int K, int taps, int stride) { return ac::narrow_conv_tile(M, N, K, taps, stride); }
 extern "C" int narrow_not_patch(int M, int N, int stride) { return ac::narrow_conv_instead_of_patch(M, N, stride); }
+extern "C" int interleaved(int M, int N, int kbytes, int eb, int out_bytes, int ta, int tb) { return ac::interleaved_rule(M, N, kbytes, eb, out_bytes, ta != 0, tb != 0); }
 extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
@@ -53,6 +55,24 @@ def test_product_tile_shapes(rules):
         for M, N, K in product_tile.SEVERAL_TO_A_WORKGROUP:
             assert product_tile_of(rules, M, N, K, matrix) == TILE_128X256 and -(-M // 128) * -(-N // 256) > 512, (M, N, K)
     assert [product_tile_of(rules, *shape, False) for shape in product_tile.OTHER_CODES] == [320, 128]
+
+
+def test_interleaved_shapes(rules):
+    """Long K loops of 256 x 256 tiles; where the caller names no tile, that tile is the choice."""
+    for M, N, K in interleaved.NAMED_I8:
+        assert rules.interleaved(M, N, K, 1, 1, 0, 0) and not rules.interleaved(M, N, K, 1, 1, 1, 0)
+    for M, N, K in interleaved.NAMED_BF16 + interleaved.CHOSEN_BF16:
+        assert rules.interleaved(M, N, 2 * K, 2, 4, 0, 0)
+    for M, N, K, out, ta, tb in interleaved.CHOSEN:
+        assert rules.interleaved(M, N, K, 1, 4 if out == "i32" else 1, ta, tb)
+        assert -(-M // 256) * -(-N // 256) > 256
+        if out == "i8":
+            assert ops.ac_gemm_i8_auto_plan(M, N, K, False)[0] == 256
+        if out == "i8" and not ta and not tb and K % 16 == 0:
+            assert product_tile_of(rules, M, N, K, False) == 256
+    for M, N, K in interleaved.CHOSEN_BF16:
+        assert ops.ac_gemm_bf16_auto_plan(M, N, K)[0] == 256
+    assert not rules.interleaved(8192, 8192, 1024, 1, 1, 0, 0) and not rules.interleaved(4096, 4096, 2048, 1, 4, 0, 0) and not rules.interleaved(4096, 4096, 512, 2, 4, 0, 0)
 
 
 def shared_tile(rules, M, N, K, eb=1, conv=False, ragged=False, workspace=True, Cin=0, a_along_k=True, b_along_k=False, raw=False):
