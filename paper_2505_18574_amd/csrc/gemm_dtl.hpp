@@ -262,7 +262,7 @@ constexpr int dtl_edge = SCHEDULE == DTL_INTERLEAVED ? 16 : 32;
 
 // Whether gemm_dtl_kernel keeps the bias row of its tile in LDS, behind the stages: BN * 4 bytes.
 template <class EPI, int BM, int SCHEDULE>
-constexpr bool has_bias_lds = BM >= 256 && SCHEDULE != DTL_PINGPONG && std::is_same_v<EPI, EpilogueI8>;
+constexpr bool has_bias_lds = (BM >= 256 ? SCHEDULE != DTL_PINGPONG : SCHEDULE == DTL_INTERLEAVED) && std::is_same_v<EPI, EpilogueI8>;
 
 // What an epilogue keeps of its operands over the K loop, a column block of the MFMA's edge.
 template <class EPI, int EDGE>

@@ -355,7 +355,11 @@ hipError_t dispatch_i8(GemmParams p, hipStream_t stream, bool fast, const GemmPl
   if (AMODE == 0 && !forced && plan.tile != 32 && narrow_product_rule(p.M, p.N, p.K)) return launch_narrow<0>(p, stream);
   if (AMODE == 0 && !forced && plan.tile != 32 && many_tiles(p.M, p.N, p.K)) {
     plan.tile = choose_product_tile_i8(p.M, p.N, p.K, wstat_eligible(p, 160), wstat_eligible(p, 320));
-    if (plan.tile == TILE_128X256) return launch_dtl<TypeI8, EpilogueI8, 128, 256, 2, 4, 0, 3, 64>(p, stream);
+    if (plan.tile == TILE_128X256) {
+      if (interleaved_128x256_rule(p.M, p.N, p.K) && EpilogueI8::takes16(p.shift, p.bias, p.bias_ld))
+        return launch_dtl<TypeI8, EpilogueI8, 128, 256, 2, 2, 0, 4, 64, DTL_INTERLEAVED>(p, stream);
+      return launch_dtl<TypeI8, EpilogueI8, 128, 256, 2, 4, 0, 3, 64>(p, stream);
+    }
   }
   if (plan.splits > 1 && p.partial == nullptr) return hipErrorInvalidValue;
   if (wstat_tile_rows(plan.tile, &ws_bm)) {

@@ -282,4 +282,11 @@ inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int o
   return kbytes >= (trans_b ? (trans_a ? 512 : 1024) : 2048);
 }
 
+// The same question for an int8 product on 128 x 256 tiles (four waves of 64 x 128 instead of eight of 64 x 64, a second wave to a
+// SIMD under whose products the output stage of the first hides).  86 random products, us before / interleaved: on one tile a
+// compute unit 2688 x 1600 x 512 7.5 / 8.6, 3648 x 1344 x 1024 10.7 / 11.3, K = 1536 and 1792 0.97 to 1.08 times as fast, from 2048
+// on 0.99 to 1.16 (3616 x 1856 x 4096 32.4 / 30.1); on more 5088 x 3520 x 512 21.1 / 21.7, x 1024 level, from 1280 on 1.03 to 1.16
+// (4304 x 5504 x 1536 43.3 / 40.9).  bf16 on 256 x 128 tiles the same way 0.88 to 1.09, up and down at any K: not taken.
+inline bool interleaved_128x256_rule(int32_t M, int32_t N, int32_t K) { return K >= (tiles_of(M, N, 128, 256) > PLAN_CUS ? 1280 : 2048); }
+
 }  // namespace ac

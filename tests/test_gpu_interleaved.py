@@ -20,6 +20,10 @@ CHOSEN = [(8200, 4112, 2112, "i8", False, False), (8200, 4112, 1040, "i8", False
 CHOSEN_BF16 = [(8200, 8208, 520), (8200, 8204, 518)]
 
 
+# the 128 x 256 tiles that a product without a plan takes: on one round of them and on more
+CHOSEN_128X256 = [(1105, 4544, 2064), (1361, 4736, 2176), (2257, 3232, 3136), (3297, 6960, 1296), (6049, 3008, 2240)]
+
+
 @pytest.mark.parametrize("shift,kind", [(1, "row"), (17, "row"), (9, "none"), (9, "matrix"), (18, "row"), (0, "row")])
 @pytest.mark.parametrize("M,N,K", NAMED_I8)
 def test_named_tile_i8(M, N, K, shift, kind):
@@ -66,6 +70,19 @@ def test_several_tiles_to_a_workgroup_i8(M, N, K, out, ta, tb):
     r = rows_of(M)
     acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + b  # exact: below 2^53
     np.testing.assert_array_equal(host(C)[r], acc if out == "i32" else oracle.requantise_vec(acc, 11, 0))
+
+
+@pytest.mark.parametrize("shift,kind", [(1, "row"), (17, "none"), (11, "matrix"), (18, "row")])
+@pytest.mark.parametrize("M,N,K", CHOSEN_128X256)
+def test_128x256(M, N, K, shift, kind):
+    A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=M + N + K, bias_matrix=kind == "matrix")
+    t = None if kind == "none" else dev(b)
+    C = torch.full((M + 1, N), 9, dtype=torch.int8, device="cuda")
+    ops.ac_gemm_i8(dev(A), dev(B), t, C[:M], shift, 1)
+    r = rows_of(M)
+    acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + (0 if t is None else b[r] if kind == "matrix" else b)
+    np.testing.assert_array_equal(host(C)[r], oracle.requantise_vec(acc, shift, 1))
+    assert (host(C[M]) == 9).all()
 
 
 @pytest.mark.parametrize("M,N,K", CHOSEN_BF16)
