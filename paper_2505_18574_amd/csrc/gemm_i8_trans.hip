@@ -23,6 +23,8 @@ static hipError_t launch_trans_dtl(const GemmParams& p0, hipStream_t stream) {
   if (kgroup_takes<TypeI8, TA, TB>(p, false, 1)) return launch_kgroup<TypeI8, KGroupI8, 0, TA, TB, DW>(p, stream);
   if constexpr (TA || !DW)  // (B^T on dwords never does)
     if (wide_trans_rule(p.M, p.N, p.K, TA, TB, DW)) return launch_dtl_wide<TypeI8, EpilogueI8, 0, DW, TA, TB>(p, stream);
+  if constexpr (TA && TB && !DW)
+    if (interleaved_at_bt_rule(p.M, p.N, p.K) && EpilogueI8::takes16(p.shift, p.bias, p.bias_ld)) return launch_dtl<TypeI8, EpilogueI8, 128, 256, 2, 2, 0, 4, 64, DTL_INTERLEAVED, TA, TB>(p, stream);
   switch (choose_tile_i8(p.M, p.N, p.K, false)) {  // no tile but the wide ones is other than square: the 256 x 128 code falls to 128
     case 256: return launch_dtl_256<TypeI8, EpilogueI8, 0, TA, TB, DW>(p, stream);
     case 192:

@@ -289,4 +289,14 @@ inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int o
 // (4304 x 5504 x 1536 43.3 / 40.9).  bf16 on 256 x 128 tiles the same way 0.88 to 1.09, up and down at any K: not taken.
 inline bool interleaved_128x256_rule(int32_t M, int32_t N, int32_t K) { return K >= (tiles_of(M, N, 128, 256) > PLAN_CUS ? 1280 : 2048); }
 
+// A^T B^T products on one round of those tiles, where the 128 x 128 ones that they had make two, and that cover little more than
+// the output.  46 random ones 1.02 to 1.28 times as fast (us before / here: 2640 x 2224 x 576 11.8 / 9.9, 848 x 5984 x 768 13.1 / 11.2, 2720
+// x 1728 x 1024 16.0 / 12.5, 736 x 5424 x 2304 24.2 / 19.7, 6448 x 1184 x 5120 52.3 / 42.1); 130 tiles where 250 of 128 x 128 fill the chip
+// 1216 x 3136 x 5120 27.2 / 38.1; a third of the tiles' area outside 6240 x 576 x 768 7.0 / 9.9; on more than a round level.  B^T alone
+// is up and down (2560 x 2832 x 576 11.4 / 10.1, 1920 x 3200 x 2048 18.2 / 19.5, 3008 x 5824 x 1536 39.8 / 43.4): not taken.
+inline bool interleaved_at_bt_rule(int32_t M, int32_t N, int32_t K) {
+  const int64_t tiles = tiles_of(M, N, 128, 256);
+  return tiles <= PLAN_CUS && tiles_of(M, N, 128, 128) > PLAN_CUS && K >= 512 && tiles * (128 * 256) * 4 <= (int64_t)M * N * 5;
+}
+
 }  // namespace ac

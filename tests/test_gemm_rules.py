@@ -27,6 +27,8 @@ extern "C" int narrow_tile(int M, int N, int K, int taps, int stride) { return a
 extern "C" int narrow_not_patch(int M, int N, int stride) { return ac::narrow_conv_instead_of_patch(M, N, stride); }
 extern "C" int interleaved(int M, int N, int kbytes, int eb, int out_bytes, int ta, int tb) { return ac::interleaved_rule(M, N, kbytes, eb, out_bytes, ta != 0, tb != 0); }
 extern "C" int interleaved_128x256(int M, int N, int K) { return ac::interleaved_128x256_rule(M, N, K); }
+extern "C" int interleaved_at_bt(int M, int N, int K) { return ac::interleaved_at_bt_rule(M, N, K); }
+extern "C" int wide_at_bt(int M, int N, int K) { return ac::wide_trans_rule(M, N, K, true, true, false); }
 extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
@@ -75,6 +77,9 @@ def test_interleaved_shapes(rules):
     for M, N, K in interleaved.CHOSEN_128X256:
         assert rules.interleaved_128x256(M, N, K) and product_tile_of(rules, M, N, K, False) == product_tile_of(rules, M, N, K, True) == TILE_128X256
     assert not rules.interleaved_128x256(3648, 1344, 1024) and not rules.interleaved_128x256(5088, 3520, 1024)
+    for M, N, K in interleaved.CHOSEN_AT_BT:
+        assert rules.interleaved_at_bt(M, N, K) and not rules.wide_at_bt(M, N, K)
+    assert not rules.interleaved_at_bt(3792, 784, 4096) and not rules.interleaved_at_bt(3008, 5824, 1536) and not rules.interleaved_at_bt(6240, 576, 768) and not rules.interleaved_at_bt(1216, 3136, 5120)
     for M, N, K in interleaved.CHOSEN_BF16:
         assert ops.ac_gemm_bf16_auto_plan(M, N, K)[0] == 256
     assert not rules.interleaved(8192, 8192, 1024, 1, 1, 0, 0) and not rules.interleaved(4096, 4096, 2048, 1, 4, 0, 0) and not rules.interleaved(4096, 4096, 512, 2, 4, 0, 0)

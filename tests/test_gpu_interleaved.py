@@ -24,6 +24,10 @@ CHOSEN_BF16 = [(8200, 8208, 520), (8200, 8204, 518)]
 CHOSEN_128X256 = [(1105, 4544, 2064), (1361, 4736, 2176), (2257, 3232, 3136), (3297, 6960, 1296), (6049, 3008, 2240)]
 
 
+# ... and A^T B^T products
+CHOSEN_AT_BT = [(1712, 3584, 512), (2128, 2192, 592), (1040, 4112, 1136), (4464, 1744, 704)]
+
+
 @pytest.mark.parametrize("shift,kind", [(1, "row"), (17, "row"), (9, "none"), (9, "matrix"), (18, "row"), (0, "row")])
 @pytest.mark.parametrize("M,N,K", NAMED_I8)
 def test_named_tile_i8(M, N, K, shift, kind):
@@ -79,6 +83,19 @@ def test_128x256(M, N, K, shift, kind):
     t = None if kind == "none" else dev(b)
     C = torch.full((M + 1, N), 9, dtype=torch.int8, device="cuda")
     ops.ac_gemm_i8(dev(A), dev(B), t, C[:M], shift, 1)
+    r = rows_of(M)
+    acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + (0 if t is None else b[r] if kind == "matrix" else b)
+    np.testing.assert_array_equal(host(C)[r], oracle.requantise_vec(acc, shift, 1))
+    assert (host(C[M]) == 9).all()
+
+
+@pytest.mark.parametrize("shift,kind", [(2, "row"), (17, "none"), (11, "matrix")])
+@pytest.mark.parametrize("M,N,K", CHOSEN_AT_BT)
+def test_128x256_at_bt(M, N, K, shift, kind):
+    A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=M + N + K, bias_matrix=kind == "matrix")
+    t = None if kind == "none" else dev(b)
+    C = torch.full((M + 1, N), 9, dtype=torch.int8, device="cuda")
+    ops.ac_gemm_i8_t(dev(A.T), dev(B.T), t, C[:M], shift, 1, trans_a=True, trans_b=True)
     r = rows_of(M)
     acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + (0 if t is None else b[r] if kind == "matrix" else b)
     np.testing.assert_array_equal(host(C)[r], oracle.requantise_vec(acc, shift, 1))
