@@ -275,11 +275,20 @@ inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_alo
 // 4096 x 1536 68.2 / 68.8, x 2048 80.3 / 77.6; bf16 (bytes of K) 4096 x 4096 x 512 19.1 / 20.5, x 1024 25.0 / 25.1, 8192 x 8192 x 1024
 // 132.5 / 115.5.  A^T alone gains nothing (4096 x 8192 x 4096 111.6 / 109.6, x 8192 210.7 / 212.2): neither operand's lines are
 // requested twice there.
+//
+// On one round the loop's gain is that of the power limit, which compute units without a tile lift: the fewer tiles, the longer K
+// has to be (before / here, times as fast: int8 K = 1024 on 225 to 242 tiles 1.02 to 1.13, on 165 to 176 0.90 to 0.96; K = 2048 on 189
+// to 256 0.98 to 1.08, on 144 to 180 0.94 to 1.04; K = 4096 on 187 to 200 1.02 to 1.08; B^T K = 1024 on 240 1.05, on 161 and 210 0.93 and
+// 0.94, K = 1536 on 203 to 255 1.02 to 1.12; bf16 K = 512 on 210 to 247 0.99 to 1.08, on 130 to 168 0.82 to 0.93, K = 2048 on 231 and 240
+// 1.04, on 155 and 169 0.93 and 0.96).
 inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int out_bytes, bool trans_a, bool trans_b) {
   if (trans_a && !trans_b) return false;
-  if (eb == 2) return kbytes >= 1024;
-  if (out_bytes == 4) return kbytes >= ((int64_t)((M + 255) / 256) * ((N + 255) / 256) > PLAN_CUS ? 2048 : 3072);
-  return kbytes >= (trans_b ? (trans_a ? 512 : 1024) : 2048);
+  const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  if (tiles > PLAN_CUS) return kbytes >= (eb == 2 ? 1024 : out_bytes == 4 ? 2048 : !trans_b ? 2048 : trans_a ? 512 : 1024);
+  if (eb == 2) return kbytes >= (tiles >= 208 ? 1024 : 8192) && tiles >= 184;
+  if (out_bytes == 4) return kbytes >= (tiles >= 232 ? 3072 : 4096) && tiles >= 196;
+  if (trans_b) return kbytes >= (tiles >= 216 ? 1024 : tiles >= 192 ? 1536 : 4096) && tiles >= 184;
+  return kbytes >= (tiles >= 232 ? 1024 : tiles >= 196 ? 2048 : 4096) && tiles >= 184;
 }
 
 // The same question for an int8 product on 128 x 256 tiles (four waves of 64 x 128 instead of eight of 64 x 64, a second wave to a

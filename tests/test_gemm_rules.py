@@ -82,6 +82,7 @@ def test_interleaved_shapes(rules):
     assert not rules.interleaved_at_bt(3792, 784, 4096) and not rules.interleaved_at_bt(3008, 5824, 1536) and not rules.interleaved_at_bt(6240, 576, 768) and not rules.interleaved_at_bt(1216, 3136, 5120)
     for M, N, K in interleaved.CHOSEN_BF16:
         assert ops.ac_gemm_bf16_auto_plan(M, N, K)[0] == 256
+    assert not any(rules.interleaved(3136, 3296, k, 1, 1, 0, tb) or rules.interleaved(3136, 3296, k, 2, 4, 0, 0) for k in (1024, 2048, 4096) for tb in (0, 1))  # 169 tiles
     assert not rules.interleaved(8192, 8192, 1024, 1, 1, 0, 0) and not rules.interleaved(4096, 4096, 2048, 1, 4, 0, 0) and not rules.interleaved(4096, 4096, 512, 2, 4, 0, 0)
 
 

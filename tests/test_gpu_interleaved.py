@@ -12,8 +12,9 @@ from paper_2505_18574_amd import inputs, ops
 
 pytestmark = pytest.mark.gpu
 
-NAMED_I8 = [(300, 272, 2048), (257, 512, 2064), (256, 256, 2112), (511, 400, 2176), (70, 1040, 2240), (300, 272, 4096 + 48)]
-NAMED_BF16 = [(300, 272, 512), (257, 520, 520), (256, 256, 544), (511, 400, 576), (70, 1040, 608), (300, 272, 1032)]
+# 184 to 256 tiles of 256 x 256, one round of them
+NAMED_I8 = [(3600, 3344, 2048), (3585, 3600, 2064), (4096, 4096, 1024), (3839, 3984, 1104), (3910, 4096, 1152), (3600, 3344, 2240 + 48)]
+NAMED_BF16 = [(3600, 3600, 512), (3585, 3856, 520), (4096, 4096, 544), (3839, 3984, 576), (3910, 3600, 608), (3600, 3344, 1032)]
 # (M, N, K, out, trans_a, trans_b): more tiles of 256 x 256 than compute units; K whole 16 bytes and whole dwords
 CHOSEN = [(8200, 4112, 2112, "i8", False, False), (8200, 4112, 1040, "i8", False, True), (8208, 8208, 592, "i8", True, True), (4100, 4112, 2064, "i32", False, False),
           (8200, 4100, 2116, "i8", False, False), (8200, 4100, 1092, "i8", False, True), (4100, 4100, 2084, "i32", False, False)]
@@ -32,12 +33,13 @@ CHOSEN_AT_BT = [(1712, 3584, 512), (2128, 2192, 592), (1040, 4112, 1136), (4464,
 @pytest.mark.parametrize("M,N,K", NAMED_I8)
 def test_named_tile_i8(M, N, K, shift, kind):
     A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=M + N + K + shift, bias_matrix=kind == "matrix")
-    if kind == "none":
-        b = None
+    t = None if kind == "none" else dev(b)
+    r = rows_of(M)
+    acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + (0 if t is None else b[r] if kind == "matrix" else b)
     for act in (0, 1):
         C = torch.full((M + 1, N), 9, dtype=torch.int8, device="cuda")
-        ops.ac_gemm_i8_planned(dev(A), dev(B), dev(b), C[:M], shift, act, 256, 1)
-        np.testing.assert_array_equal(host(C[:M]), oracle.gemm_i8(A, B, b, shift, act))
+        ops.ac_gemm_i8_planned(dev(A), dev(B), t, C[:M], shift, act, 256, 1)
+        np.testing.assert_array_equal(host(C)[r], oracle.requantise_vec(acc, shift, act))
         assert (host(C[M]) == 9).all()  # nothing behind the last row
 
 
@@ -46,13 +48,14 @@ def test_named_tile_bf16(M, N, K):
     A, B = inputs.gemm_bf16_inputs(M, N, K, seed=M + N + K)
     C = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device="cuda")
     ops.ac_gemm_bf16_planned(dev(A), dev(B), C[:M], 1.0, 0.0, 256, 1)
-    check_bf16_product_in_full(A, B, host(C[:M]))
+    r = rows_of(M)
+    check_bf16_product_in_full(A[r], B, host(C)[r])
     assert np.isnan(host(C[M])).all()
     old = np.random.default_rng(M).standard_normal((M, N)).astype(np.float32)
     C = dev(old)
     ops.ac_gemm_bf16_planned(dev(A), dev(B), C, 0.5, -2.0, 256, 1)
-    want = oracle.gemm_bf16(A, B, 0.5, -2.0, old)
-    assert np.linalg.norm(host(C) - want) <= 1e-3 * np.linalg.norm(want)
+    want = oracle.gemm_bf16(A[r], B, 0.5, -2.0, old[r])
+    assert np.linalg.norm(host(C)[r] - want) <= 1e-3 * np.linalg.norm(want)
 
 
 def rows_of(M):
@@ -113,9 +116,11 @@ def test_several_tiles_to_a_workgroup_bf16(M, N, K):
 
 def test_output_beside_other_columns():
     """C with a pitch of its own: the columns behind N stay."""
-    M, N, K = 300, 272, 2064
+    M, N, K = NAMED_I8[1]
     A, B, b = inputs.gemm_i8_inputs(M, N, K, seed=5)
     C = torch.full((M, N + 16), 9, dtype=torch.int8, device="cuda")
     ops.ac_gemm_i8_planned(dev(A), dev(B), dev(b), C[:, :N], 9, 1, 256, 1)
-    np.testing.assert_array_equal(host(C)[:, :N], oracle.gemm_i8(A, B, b, 9, 1))
+    r = rows_of(M)
+    acc = (A[r].astype(np.float64) @ B.astype(np.float64)).astype(np.int64) + b
+    np.testing.assert_array_equal(host(C)[r][:, :N], oracle.requantise_vec(acc, 9, 1))
     assert (host(C)[:, N:] == 9).all()
