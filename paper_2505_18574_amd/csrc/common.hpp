@@ -213,8 +213,6 @@ GemmPlan plan_gemm_i8(int32_t M, int32_t N, int32_t K, bool have_workspace, int 
 GemmPlan plan_gemm_bf16(int32_t M, int32_t N, int32_t K);
 // Rows / columns of a tile code (false for an unknown code).
 bool tile_dims(int32_t tile, int* bm, int* bn);
-// Tile code the library picks for an M x N output when nothing else is known (convolutions, fallbacks).
-int choose_tile(int32_t M, int32_t N);
 // Kernel / tile code for a GEMM with more than 256 tiles of 64 x 64 (more than the chip holds at once): of a plan, of
 // transposed operands, of products on dwords and of bf16 (an int8 product without a plan has estimates of its own,
 // choose_product_tile_i8).  From per-code time estimates  t = c0 + rounds * (c1 + c2 * k)  with k = K bytes / 128 and rounds = the number of

@@ -54,17 +54,6 @@ bool tile_dims(int32_t tile, int* bm, int* bn) {
   }
 }
 
-// Shared by both GEMM types: the largest tile that still gives most compute units a workgroup (thresholds from
-// exhaustive plan tables on this chip).  A tile much wider or taller than the problem wastes most of its MFMAs,
-// so a tile needs 3/4 of its edge in both dimensions.
-int choose_tile(int32_t M, int32_t N) {
-  auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  if (M >= 192 && N >= 192 && tiles(256, 256) >= 192) return 256;
-  if (M >= 192 && N >= 96 && tiles(256, 128) >= 192) return 192;
-  if (M >= 96 && N >= 96 && tiles(128, 128) >= 128) return 128;
-  return 64;
-}
-
 namespace {
 int cheapest_tiled(const TiledCost (&c)[4], int32_t M, int32_t N, int64_t k128, double* cost) {
   static const int codes[4] = {64, 128, 192, 256}, per_cu[4] = {2, 1, 1, 1};

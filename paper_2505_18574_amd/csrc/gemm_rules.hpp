@@ -66,6 +66,16 @@ inline int choose_product_tile_i8(int32_t M, int32_t N, int32_t K, bool st160_ru
 }
 
 inline int64_t tiles_of(int32_t M, int32_t N, int bm, int bn) { return (((int64_t)M + bm - 1) / bm) * (((int64_t)N + bn - 1) / bn); }
+
+// Tile code for an M x N output when nothing else is known (int32 outputs, convolutions of large kernels): the largest tile
+// that still gives most compute units a workgroup (thresholds from exhaustive plan tables on this chip).  A tile much wider or
+// taller than the problem wastes most of its MFMAs, so a tile needs 3/4 of its edge in both dimensions.
+inline int choose_tile(int32_t M, int32_t N) {
+  if (M >= 192 && N >= 192 && tiles_of(M, N, 256, 256) >= 192) return 256;
+  if (M >= 192 && N >= 96 && tiles_of(M, N, 256, 128) >= 192) return 192;
+  if (M >= 96 && N >= 96 && tiles_of(M, N, 128, 128) >= 128) return 128;
+  return 64;
+}
 // ---- one round of 64 x 128 tiles ---------------------------------------------------------------------------------------
 // Outputs of more 64 x 64 tiles than compute units (where some of them get two) of which 64 x 128 tiles make at most one to a
 // unit.  What a unit fetches is counted in lines of 128 bytes, one per 1.8 clocks whatever part of it is used (direct-to-LDS

@@ -28,7 +28,9 @@ extern "C" int narrow_not_patch(int M, int N, int stride) { return ac::narrow_co
 extern "C" int interleaved(int M, int N, int kbytes, int eb, int out_bytes, int ta, int tb) { return ac::interleaved_rule(M, N, kbytes, eb, out_bytes, ta != 0, tb != 0); }
 extern "C" int interleaved_128x256(int M, int N, int K) { return ac::interleaved_128x256_rule(M, N, K); }
 extern "C" int interleaved_at_bt(int M, int N, int K) { return ac::interleaved_at_bt_rule(M, N, K); }
-extern "C" int wide_at_bt(int M, int N, int K) { return ac::wide_trans_rule(M, N, K, true, true, false); }
+extern "C" int wide_trans(int M, int N, int K, int ta, int tb, int dw) { return ac::wide_trans_rule(M, N, K, ta != 0, tb != 0, dw != 0); }
+extern "C" int wide_product(int M, int N, int kbytes, int eb, int dw, int splits) { return ac::wide_product_rule(M, N, kbytes, eb, dw != 0, splits); }
+extern "C" int tile(int M, int N) { return ac::choose_tile(M, N); }
 extern "C" int dword_tiles(int M, int N, int kbytes, int both_along_k) { return ac::dword_tiles_rule(M, N, kbytes, both_along_k != 0); }
 """
 TILE_128X256 = 129
@@ -60,28 +62,58 @@ def test_product_tile_shapes(rules):
     assert [product_tile_of(rules, *shape, False) for shape in product_tile.OTHER_CODES] == [320, 128]
 
 
+def last_trips(kb, dw):
+    """K tiles of 64 bytes that the interleaved loop multiplies outside its rounds of four, the very last one apart: a round needs the
+    four tiles behind its own to be whole, which on dwords the last tile never is."""
+    tiles, whole = -(-kb // 64), (kb - dw) // 64
+    kt = 0
+    while kt + 7 < min(tiles, whole):
+        kt += 4
+    return tiles - kt - 1
+
+
 def test_interleaved_shapes(rules):
-    """Long K loops of 256 x 256 tiles; where the caller names no tile, that tile is the choice."""
-    for M, N, K in interleaved.NAMED_I8:
-        assert rules.interleaved(M, N, K, 1, 1, 0, 0) and not rules.interleaved(M, N, K, 1, 1, 1, 0)
-    for M, N, K in interleaved.NAMED_BF16 + interleaved.CHOSEN_BF16:
-        assert rules.interleaved(M, N, 2 * K, 2, 4, 0, 0)
-    for M, N, K, out, ta, tb in interleaved.CHOSEN:
-        assert rules.interleaved(M, N, K, 1, 4 if out == "i32" else 1, ta, tb)
-        assert -(-M // 256) * -(-N // 256) > 256
-        if out == "i8":
-            assert ops.ac_gemm_i8_auto_plan(M, N, K, False)[0] == 256
-        if out == "i8" and not ta and not tb and K % 16 == 0:
-            assert product_tile_of(rules, M, N, K, False) == 256
-    assert {-(-M // 128) * -(-N // 256) > 256 for M, N, K in interleaved.CHOSEN_128X256} == {False, True}
+    """The shapes of the interleaved loop's tests take it, and run each count of last trips in each form."""
+    for form, (eb, ta, tb, out, dw) in interleaved.FORMS.items():
+        for rounds, (tiles, _, _) in interleaved.ROUNDS.items():
+            seen = set()
+            for kb in interleaved.K_BYTES[dw]:
+                M, N, K = interleaved.shape_of(form, rounds, kb)
+                assert -(-M // 256) * -(-N // 256) == tiles and (tiles > 256) == (rounds == "several")
+                assert rules.interleaved(M, N, kb, eb, 1 if out == "i8" else 4, ta, tb), (form, rounds, kb)
+                if out == "i32":
+                    assert rules.tile(M, N) == 256
+                elif eb == 2:
+                    assert tuple(ops.ac_gemm_bf16_auto_plan(M, N, K)) == (256, 1)
+                else:
+                    assert tuple(ops.ac_gemm_i8_auto_plan(M, N, K, False)) == (256, 1)
+                if form == "i8":
+                    assert product_tile_of(rules, M, N, K, False) == 256
+                if ta and not dw:
+                    assert not rules.interleaved_at_bt(M, N, K)
+                if dw:
+                    assert rules.dword_tiles(M, N, kb, not ta and tb)
+                if ta or tb:
+                    assert not rules.wide_trans(M, N, K, ta, tb, dw)
+                else:
+                    assert not rules.wide_product(M, N, kb, eb, dw, 1)
+                assert not rules.kgroup(0, M, N, K, eb, 0, not ta, tb, 1, 0, 0, out == "i32")
+                seen.add(last_trips(kb, dw))
+            assert seen == ({4, 5, 6, 7} if dw else {3, 4, 5, 6, 7}), (form, rounds, seen)
+    for M, N, K, dw in interleaved.SHORT_AT_BT:
+        assert rules.interleaved(M, N, K, 1, 1, 1, 1) and not rules.wide_trans(M, N, K, 1, 1, dw)
+        assert rules.dword_tiles(M, N, K, 0) if dw else not rules.interleaved_at_bt(M, N, K)
+        assert tuple(ops.ac_gemm_i8_auto_plan(M, N, K, False)) == (256, 1) and -(-M // 256) * -(-N // 256) > 256
+    # whole K tiles: with eight a prefetched item runs a whole round of trips, with seven none
+    assert {(dw, (K - dw) // 64) for _, _, K, dw in interleaved.SHORT_AT_BT} == {(False, 8), (False, 9), (True, 7), (True, 8), (True, 9)}
+    assert {(-(-M // 128) * -(-N // 256) > 256, last_trips(K, False)) for M, N, K in interleaved.CHOSEN_128X256} >= {(True, t) for t in (4, 5, 6, 7, 3)} | {(False, 4)}
     for M, N, K in interleaved.CHOSEN_128X256:
         assert rules.interleaved_128x256(M, N, K) and product_tile_of(rules, M, N, K, False) == product_tile_of(rules, M, N, K, True) == TILE_128X256
     assert not rules.interleaved_128x256(3648, 1344, 1024) and not rules.interleaved_128x256(5088, 3520, 1024)
     for M, N, K in interleaved.CHOSEN_AT_BT:
-        assert rules.interleaved_at_bt(M, N, K) and not rules.wide_at_bt(M, N, K)
+        assert rules.interleaved_at_bt(M, N, K) and not rules.wide_trans(M, N, K, 1, 1, 0)
     assert not rules.interleaved_at_bt(3792, 784, 4096) and not rules.interleaved_at_bt(3008, 5824, 1536) and not rules.interleaved_at_bt(6240, 576, 768) and not rules.interleaved_at_bt(1216, 3136, 5120)
-    for M, N, K in interleaved.CHOSEN_BF16:
-        assert ops.ac_gemm_bf16_auto_plan(M, N, K)[0] == 256
+    assert not any(rules.interleaved(M, N, kb, 1, 1, 1, 0) for M, N in ((3601, 4080), (5393, 5392)) for kb in (1024, 4096, 8192))  # A^T alone
     assert not any(rules.interleaved(3136, 3296, k, 1, 1, 0, tb) or rules.interleaved(3136, 3296, k, 2, 4, 0, 0) for k in (1024, 2048, 4096) for tb in (0, 1))  # 169 tiles
     assert not rules.interleaved(8192, 8192, 1024, 1, 1, 0, 0) and not rules.interleaved(4096, 4096, 2048, 1, 4, 0, 0) and not rules.interleaved(4096, 4096, 512, 2, 4, 0, 0)
 

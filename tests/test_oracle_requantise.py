@@ -3,9 +3,11 @@ from fractions import Fraction
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from conftest import read_golden_table
+from gpu_util import check_bf16_product, check_equal, product_i64, requantise
 
 
 def test_rne_rshift_hand_values():
@@ -66,3 +68,38 @@ def test_stage_order_is_immaterial():
         # saturating first at the pre-image of the int8 range is also equivalent
         lo, hi = -128 * (1 << s), 127 * (1 << s)
         np.testing.assert_array_equal(sh(np.clip(acc, lo, hi)), none)
+
+
+@pytest.mark.parametrize("act", [0, 1])
+@pytest.mark.parametrize("shift", [0, 1, 2, 9, 11, 17, 18, 31])
+def test_tensor_form_of_the_stage(shift, act):
+    """The form in which the GPU tests compare whole outputs is the oracle's."""
+    rng = np.random.default_rng(shift)
+    half = 1 << max(shift - 1, 0)
+    v = np.concatenate([rng.integers(-(1 << 31), 1 << 31, size=50000), rng.integers(-300 << shift, 300 << shift, size=50000), np.arange(-600, 600) * half, np.arange(-600, 600) * half + 1,
+                        np.arange(-600, 600) * half - 1, [-(1 << 31), (1 << 31) - 1]]).astype(np.int64)
+    np.testing.assert_array_equal(requantise(torch.from_numpy(v), shift, act).numpy(), oracle.requantise_vec(v, shift, act))
+
+
+def test_whole_outputs_are_compared():
+    """One wrong element anywhere fails the comparisons of whole outputs: each row and column of a 16 x 16 tile, each kind of output."""
+    g = torch.Generator().manual_seed(1)
+    A, B = (torch.randint(-128, 128, shape, dtype=torch.int8, generator=g) for shape in ((48, 40), (40, 36)))
+    acc = product_i64(A, B)
+    np.testing.assert_array_equal(acc.numpy(), A.numpy().astype(np.int64) @ B.numpy().astype(np.int64))
+    a, b = A.to(torch.bfloat16), B.to(torch.bfloat16)
+    out, old = acc.float(), torch.ones(48, 36)
+    check_equal(acc, acc)
+    check_bf16_product(a, b, out)
+    check_bf16_product(a, b, 0.5 * out - 2.0 * old, 0.5, -2.0, old)
+    for r in range(48):
+        c = (7 * r) % 36
+        wrong = acc.clone()
+        wrong[r, c] += 1
+        with pytest.raises(AssertionError):
+            check_equal(wrong, acc)
+        for value in (float("nan"), out[r, c].item() * 1.001 + 100.0):
+            bad = out.clone()
+            bad[r, c] = value
+            with pytest.raises(AssertionError):
+                check_bf16_product(a, b, bad)
