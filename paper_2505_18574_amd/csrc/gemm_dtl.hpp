@@ -135,6 +135,7 @@ static __device__ __forceinline__ v4i dtl_read_col_at(const unsigned char* p) {
     return (v4i){lo[0], lo[1], hi[0], hi[1]};
   }
 }
+
 // f(integral_constant<0>), f(integral_constant<1>), ...: one call per LDS stage with the stage index a constant.
 template <class F, int... I>
 static __device__ __forceinline__ void for_each_stage(F&& f, std::integer_sequence<int, I...>) {
@@ -162,6 +163,12 @@ static __device__ __forceinline__ int k_row_xor(int row) {
 static __device__ __forceinline__ int opaque(int x) {
   asm volatile("" : "+v"(x));
   return x;
+}
+
+template <bool FIRST, class X, class Y>
+static __device__ __forceinline__ auto either(const X& x, const Y& y) {
+  if constexpr (FIRST) return x;
+  else return y;
 }
 
 template <class T, int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int KTB_, int EDGE = 32>
@@ -986,6 +993,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   const int elane = INTERLEAVED ? opaque(lane) : lane;
   const bool efull = em0 + BM <= p.M && en0 + BN <= p.N;  // wave-uniform: no store of this tile is masked
   started = false;
+  // What the output stage adds to a lane's four columns in every row, ahead of the next item's tiles, which would be waited for too.
+  [[maybe_unused]] const auto add = [&] {
+    if constexpr (EPI::LDS_STAGED) return EPI::staged_add(p, en0 + wn * G::WTN + (elane % (G::WTN / 4)) * 4);
+    else return 0;
+  }();
   if constexpr (XPF) {
     // every item of a launch has the same K range here (no K slices); the fill needs STAGES - 1 whole tiles
     if (work + (int)gridDim.x < nwork && p.splits == 1 && nkt_whole >= (INTERLEAVED ? STAGES : STAGES - 1)) {
@@ -1018,12 +1030,25 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     constexpr int RB = 16 * PITCH * 4, AW = G::A_BYTES / RB;  // a wave's bytes; XPF: waves that work in A's stage, the others in B's
     static_assert(!XPF || (AW * RB == G::A_BYTES && (G::WAVES - AW) * RB <= G::B_BYTES), "the last stage, shared out");
     SV* region = (SV*)(smem + (XPF ? (wave < AW ? (STAGES - 1) * A_STRIDE + wave * RB : B_FIRST + (STAGES - 1) * B_STRIDE + (wave - AW) * RB) : wave * RB));
-    const auto add = EPI::staged_add(p, en0 + wn * G::WTN + (elane % LPR) * 4);  // a lane's four columns are the same in every row
-    auto body = [&](auto fullc) {
+    // What is read beside the product is requested for 16 rows at a time, ahead of their way through LDS, and only where there is
+    // something to read: a load among the stores, or one that the compiler takes for pending there, is waited for together with
+    // every store before it, and with the K tiles that follow.  (Read at each store, us, there / here: int32 without a bias 4952 x
+    // 4176 x 2976 91.2 / 82.5, a row 1921 x 416 x 7448 28.0 / 24.6, a matrix 11229 x 2928 x 2464 218 / 152, bf16 with beta 4222 x
+    // 6872 x 840 131 / 93; in ping-pong such a matrix 176 and 101.)
+    auto body = [&](auto fullc, auto readsc) {
+      constexpr bool READS = decltype(readsc)::value;
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
 #pragma unroll
       for (int hf = 0; hf < EDGE / 16; hf++) {
+        [[maybe_unused]] sv4 read[NI] = {};
+        if constexpr (EPI::STAGED_READS) {
+#pragma unroll
+          for (int q = 0; READS && q < NI; q++) {
+            const int m = em0 + wm * G::WTM + i * EDGE + hf * 16 + q * RPI + elane / LPR, n = en0 + wn * G::WTN + (elane % LPR) * 4;
+            if (m < p.M && n < p.N) read[q] = EPI::staged_read(p, m, n);
+          }
+        }
 #pragma unroll
         for (int j = 0; j < G::TN; j++)
 #pragma unroll
@@ -1034,20 +1059,30 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
         // Other lanes read what this one wrote.  A wave's LDS accesses are in order, but the compiler orders only those of a lane,
         // and moves a write whose own lane does not read it past the reads.
         asm volatile("" ::: "memory");
+        if constexpr (READS) {  // received by every lane: what the compiler takes for pending behind a mask it waits for in the next K loop
+#pragma unroll
+          for (int q = 0; q < NI; q++) asm volatile("" : "+v"(read[q]));
+        }
 #pragma unroll
         for (int q = 0; q < NI; q++) {
           const int row = q * RPI + elane / LPR, col = (elane % LPR) * 4;
           const sv4 o = *(const sv4*)(region + row * PITCH + pcol_of(col, row));
           const int m = em0 + wm * G::WTM + i * EDGE + hf * 16 + row, n = en0 + wn * G::WTN + col;
           // N is a multiple of 4 on this path: a group of four columns is inside or outside
-          if (decltype(fullc)::value || (m < p.M && n < p.N)) EPI::staged_out(p, m, n, o, esplit, add);
+          if (decltype(fullc)::value || (m < p.M && n < p.N)) EPI::staged_out(p, m, n, o, esplit, either<READS>(read[q], add));
         }
         asm volatile("" ::: "memory");  // ... nor may the next rows be written ahead of the reads
       }
     }
     };
-    if (XPF && efull) body(std::true_type{});
-    else body(std::false_type{});
+    if constexpr (EPI::STAGED_READS) {
+      if (EPI::staged_reads(p)) body(std::false_type{}, std::true_type{});
+      else if (XPF && efull) body(std::true_type{}, std::false_type{});
+      else body(std::false_type{}, std::false_type{});
+    } else {
+      if (XPF && efull) body(std::true_type{}, std::false_type{});
+      else body(std::false_type{}, std::false_type{});
+    }
   } else if constexpr (BIAS_LDS && EDGE == 16) {
     EpilogueI8::Pre16 bias[G::TN];
 #pragma unroll

@@ -418,6 +418,7 @@ struct EpilogueI8Any {
 struct EpiloguePartialI32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // the workspace is 16-byte aligned and N a multiple of 16 on this path
+  static constexpr bool STAGED_READS = false;
   typedef int StagedValue;
   template <class P>
   static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
@@ -441,23 +442,33 @@ struct EpiloguePartialI32 {
 struct EpilogueRawI32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // C is 16-byte aligned with ldc a multiple of 4 on this path
+  static constexpr bool STAGED_READS = true;
   typedef int StagedValue;
   template <class P>
   static __device__ __forceinline__ int staged_in(const P&, int a) { return a; }
   template <class P>
   static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4i o, int, v4i add) {
-    if (p.bias && p.bias_ld != 0) {
-      const int32_t* b = p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
-      add = (v4i){b[0], b[1], b[2], b[3]};
-    }
     *(v4i*)((int32_t*)p.C + (int64_t)m * p.ldc + n) = o + add;
   }
-  // The bias row's values of columns n .. n + 3 (N is a multiple of 4 on this path), or zeros.
+  // A bias matrix is read element by element, a row once (staged_add).
+  template <class P>
+  static __device__ __forceinline__ bool staged_reads(const P& p) { return p.bias != nullptr && p.bias_ld != 0; }
+  template <class P>
+  static __device__ __forceinline__ v4i staged_read(const P& p, int m, int n) {
+    const int32_t* b = p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
+    return (v4i){b[0], b[1], b[2], b[3]};
+  }
+  // The bias row's values of columns n .. n + 3 (N is a multiple of 4 on this path), or zeros.  They are waited for here: the
+  // compiler would wait at a store, where it knows neither whether they were loaded nor how many requests are younger.
   template <class P>
   static __device__ __forceinline__ v4i staged_add(const P& p, int n) {
-    if (p.bias == nullptr || p.bias_ld != 0 || n >= p.N) return (v4i){0, 0, 0, 0};
-    const int32_t* b = p.bias + n;
-    return (v4i){b[0], b[1], b[2], b[3]};
+    v4i row = {0, 0, 0, 0};
+    if (p.bias != nullptr && p.bias_ld == 0 && n < p.N) {
+      const int32_t* b = p.bias + n;
+      row = (v4i){b[0], b[1], b[2], b[3]};
+      asm volatile("" : "+v"(row));
+    }
+    return row;
   }
   struct Pre {};
   template <class P>
@@ -485,17 +496,26 @@ struct EpilogueRawI32 {
 struct EpilogueF32 {
   static constexpr bool SWAP = false;
   // The direct-to-LDS kernels hand over 4-byte outputs through an LDS transpose: staged_in() is applied to every
-  // accumulator on its way into LDS, staged_out() receives four consecutive columns of one row.
+  // accumulator on its way into LDS, staged_out() receives four consecutive columns of one row and what is added to them:
+  // staged_read()'s values of the same elements where staged_reads() says that there are any, otherwise staged_add()'s, which
+  // are the same in every row.
   static constexpr bool LDS_STAGED = true;
+  static constexpr bool STAGED_READS = true;
   typedef float StagedValue;
   template <class P>
   static __device__ __forceinline__ float staged_in(const P& p, float a) { return p.alpha * a; }
   template <class P>
   static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int, int) {
-    float* dst = (float*)p.C + (int64_t)m * p.ldc + n;
-    if (p.beta != 0.f) o += p.beta * *(const v4f*)dst;
-    *(v4f*)dst = o;
+    *(v4f*)((float*)p.C + (int64_t)m * p.ldc + n) = o;
   }
+  template <class P>
+  static __device__ __forceinline__ void staged_out(const P& p, int m, int n, v4f o, int, v4f old) {
+    *(v4f*)((float*)p.C + (int64_t)m * p.ldc + n) = o + p.beta * old;
+  }
+  template <class P>
+  static __device__ __forceinline__ bool staged_reads(const P& p) { return p.beta != 0.f; }
+  template <class P>
+  static __device__ __forceinline__ v4f staged_read(const P& p, int m, int n) { return *(const v4f*)((const float*)p.C + (int64_t)m * p.ldc + n); }
   template <class P>
   static __device__ __forceinline__ int staged_add(const P&, int) { return 0; }
   struct Pre {};
@@ -543,6 +563,7 @@ struct EpilogueAtomicF32 {
 struct EpiloguePartialF32 {
   static constexpr bool SWAP = false;
   static constexpr bool LDS_STAGED = true;  // the workspace is 16-byte aligned and N a multiple of 8 on this path
+  static constexpr bool STAGED_READS = false;
   typedef float StagedValue;
   template <class P>
   static __device__ __forceinline__ float staged_in(const P&, float a) { return a; }

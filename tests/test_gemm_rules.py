@@ -9,6 +9,7 @@ import test_gpu_dword as dword
 import test_gpu_interleaved as interleaved
 import test_gpu_kgroup as kgroup
 import test_gpu_narrow as narrow
+import test_gpu_output_stage as output_stage
 import test_gpu_product_tile as product_tile
 from paper_2505_18574_amd import ops
 
@@ -245,3 +246,16 @@ def test_narrow_tiles_leave_what_they_would_slow_down(rules):
         assert rules.narrow_conv(M, N, K, taps, stride, 0, 0) and not rules.narrow_conv(M, N, K, taps, stride, 1, 0)
     assert not rules.narrow_tile(35525, 16, 3312, 9, 3) and rules.narrow_tile(35525, 16, 3312, 9, 2) and rules.narrow_tile(35525, 16, 1008, 9, 3) and not rules.narrow_tile(50176, 48, 4608, 9, 1) and not rules.narrow_tile(349856, 16, 1408, 4, 2)
     assert rules.narrow_not_patch(1441557, 16, 2) and not rules.narrow_not_patch(284350, 32, 1)
+
+
+def test_output_stage_shapes(rules):
+    """The shapes of the 4-byte output stages' tests make each tile, none of them on the interleaved loop."""
+    codes = {"64": 64, "128": 128, "256x128": 192, "256": 256, "256, several": 256}
+    for name, (M, N, K) in output_stage.SHAPES.items():
+        for dword in (False, True):
+            n, k = (N, K - 4) if dword else (N + 4 & ~15, K)
+            assert rules.tile(M, n) == codes[name], name
+            assert not rules.interleaved(M, n, k, 1, 4, 0, 0) and not rules.wide_product(M, n, k, 1, dword, 1)
+            assert not rules.kgroup(0, M, n, k, 1, 0, 1, 0, 1, 0, 0, 1)
+            assert not dword or rules.dword_tiles(M, n, k, 0), (name, dword)
+    assert -(-5393 // 256) * -(-5388 // 256) > 256
