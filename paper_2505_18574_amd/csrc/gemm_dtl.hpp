@@ -95,6 +95,17 @@ struct BSwizzle {
 // Swizzled B-fragment reads (see TypeI8/TypeBF16::read_col for the lane roles).
 // kb: byte offset of this lane's 16 K-bytes inside the 128-byte K tile; seg: index of the 32-column block.
 template <int B_ROW>
+static __device__ __forceinline__ v4i dtl_read_col_bf16(const unsigned char* Bs, int kb, int seg, int lane) {
+  using S = BSwizzle<2, B_ROW>;
+  const int i = lane & 15, g1 = (lane >> 4) & 1;
+  const int r = (kb >> 1) + (i >> 2);  // k-row; rows r and r + 4 share one swizzle term
+  const unsigned char* p = Bs + r * B_ROW + ((seg ^ S::seg_xor(r)) << 6) + g1 * 32 + 8 * (i & 3);
+  v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(AC_LDS(v4s, p));
+  v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(AC_LDS(v4s, p + 4 * B_ROW));
+  v2i l2 = __builtin_bit_cast(v2i, lo), h2 = __builtin_bit_cast(v2i, hi);
+  return (v4i){l2[0], l2[1], h2[0], h2[1]};
+}
+template <int B_ROW>
 static __device__ __forceinline__ v4i dtl_read_col_i8(const unsigned char* Bs, int kb, int seg, int lane) {
   using S = BSwizzle<1, B_ROW>;
   const int i = lane & 15, g1 = (lane >> 4) & 1;
@@ -134,6 +145,11 @@ static __device__ __forceinline__ v4i dtl_read_col_at(const unsigned char* p) {
     v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32(AC_LDS(v2i, p + 8 * B_ROW));
     return (v4i){lo[0], lo[1], hi[0], hi[1]};
   }
+}
+template <class T, int B_ROW>
+static __device__ __forceinline__ v4i dtl_read_col(const unsigned char* Bs, int kb, int seg, int lane) {
+  if constexpr (T::EB == 2) return dtl_read_col_bf16<B_ROW>(Bs, kb, seg, lane);
+  else return dtl_read_col_i8<B_ROW>(Bs, kb, seg, lane);
 }
 
 // f(integral_constant<0>), f(integral_constant<1>), ...: one call per LDS stage with the stage index a constant.
@@ -533,42 +549,41 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   // ---- fragments ---------------------------------------------------------------------------------------
   // the lane's A row within an MFMA tile is lane % EDGE, its K chunk lane / EDGE; tile origins are multiples of 16 rows
   // and do not change the swizzle term
-  const int l_row = lane % EDGE, l_chunk = lane / EDGE;
-  const int a_swz = G::a_xor(l_row);
-  const int a_lane_off = (wm * G::WTM + l_row) * G::KTB;
-  const int b_lane_off_t = (wn * G::WTN + l_row) * G::KTB;  // B^T: the lane's row of the K-contiguous B tile
+  const int a_swz = G::a_xor(lane % EDGE);
+  const int a_lane_off = (wm * G::WTM + lane % EDGE) * G::KTB;
+  const int b_lane_off_t = (wn * G::WTN + lane % EDGE) * G::KTB;  // B^T: the lane's row of the K-contiguous B tile
   struct Frag {
     v4i a[G::TM], b[G::TN];
   };
+  // Of 32 x 32 tiles, the other schedules'.  Written out: through dtl_col_off and with lane / 32 in a variable the register
+  // allocator of the A^T products reloaded a lane address from scratch in the K loop (a wait for every request in flight) and kept
+  // the arguments of the dword form in lanes of a vector register (256 x 256 tiles, 2 to 4 % of 14 to 41 us).
   auto read_frags = [&](int buf, int ks, Frag& f) {
     const unsigned char* As = smem + buf * A_STRIDE;
     const unsigned char* Bs = smem + B_FIRST + buf * B_STRIDE;
-    const int chunk = G::KCH * ks + l_chunk;
+    const int chunk = 2 * ks + (lane >> 5);
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
-      if constexpr (TA) f.a[i] = dtl_read_col_at<T, AT_ROW>(As + dtl_col_off<T, AT_ROW, EDGE>(chunk * 16, wm * G::TM + i, lane));
-      else f.a[i] = *(const v4i*)(As + a_lane_off + i * EDGE * G::KTB + ((chunk ^ a_swz) << 4));
+      if constexpr (TA) f.a[i] = dtl_read_col<T, AT_ROW>(As, chunk * 16, wm * G::TM + i, lane);
+      else f.a[i] = *(const v4i*)(As + a_lane_off + i * 32 * G::KTB + ((chunk ^ a_swz) << 4));
     }
 #pragma unroll
     for (int j = 0; j < G::TN; j++) {
-      if constexpr (TB) f.b[j] = *(const v4i*)(Bs + b_lane_off_t + j * EDGE * G::KTB + ((chunk ^ a_swz) << 4));
-      else f.b[j] = dtl_read_col_at<T, G::B_ROW>(Bs + dtl_col_off<T, G::B_ROW, EDGE>(chunk * 16, wn * G::TN + j, lane));
+      if constexpr (TB) f.b[j] = *(const v4i*)(Bs + b_lane_off_t + j * 32 * G::KTB + ((chunk ^ a_swz) << 4));
+      else f.b[j] = dtl_read_col<T, G::B_ROW>(Bs, chunk * 16, wn * G::TN + j, lane);
     }
   };
   auto mfma_rows = [&](const Frag& f, int i0, int i1) {  // MFMA row tiles i0 .. i1-1 of one K-step
 #pragma unroll
     for (int i = i0; i < i1; i++)
 #pragma unroll
-      for (int jj = 0; jj < G::TN; jj++) {
-        const int j = EDGE == 16 && i % 2 == 1 ? G::TN - 1 - jj : jj;
-        acc[i][j] = EPI::SWAP ? T::mfma(f.b[j], f.a[i], acc[i][j]) : T::mfma(f.a[i], f.b[j], acc[i][j]);
-      }
+      for (int j = 0; j < G::TN; j++) acc[i][j] = EPI::SWAP ? T::mfma(f.b[j], f.a[i], acc[i][j]) : T::mfma(f.a[i], f.b[j], acc[i][j]);
   };
   const int nkt_total = (kbytes + G::KTB - 1) / G::KTB;
   constexpr bool DW_MASK = DW && !TA && (TB || EB == 2);
   auto mask_last = [&](Frag& f, int ks) {
 #pragma unroll
-    for (int i = 0; i < G::TM; i++) f.a[i] = dw_mask(f.a[i], kbytes - (nkt_total - 1) * G::KTB - (G::KCH * ks + l_chunk) * 16);
+    for (int i = 0; i < G::TM; i++) f.a[i] = dw_mask(f.a[i], kbytes - (nkt_total - 1) * G::KTB - (2 * ks + (lane >> 5)) * 16);
   };
   constexpr int PER_TILE = G::A_INSTR + G::B_INSTR;  // outstanding vector-memory ops per tile per wave
   static_assert((STAGES - 1) * PER_TILE <= 63, "vmcnt is a 6-bit counter");
@@ -582,14 +597,14 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   int a_fo[NAF], b_fo[NBF];
 #pragma unroll
   for (int x = 0; x < NAF; x++) {
-    if constexpr (TA) a_fo[x] = dtl_col_off<T, AT_ROW, EDGE>(l_chunk * 16, wm * G::TM + x, lane);
-    else a_fo[x] = a_lane_off + (((G::KCH * x + l_chunk) ^ a_swz) << 4);
+    if constexpr (TA) a_fo[x] = dtl_col_off<T, AT_ROW, EDGE>(lane / EDGE * 16, wm * G::TM + x, lane);
+    else a_fo[x] = a_lane_off + (((G::KCH * x + lane / EDGE) ^ a_swz) << 4);
     if constexpr (INTERLEAVED) a_fo[x] = opaque(a_fo[x]);  // or every stage's sum is a register of its own, 64 KB being out of an immediate's reach
   }
 #pragma unroll
   for (int x = 0; x < NBF; x++) {
-    if constexpr (TB) b_fo[x] = B_FIRST + b_lane_off_t + (((G::KCH * x + l_chunk) ^ a_swz) << 4);
-    else b_fo[x] = B_FIRST + dtl_col_off<T, G::B_ROW, EDGE>(l_chunk * 16, wn * G::TN + x, lane);
+    if constexpr (TB) b_fo[x] = B_FIRST + b_lane_off_t + (((G::KCH * x + lane / EDGE) ^ a_swz) << 4);
+    else b_fo[x] = B_FIRST + dtl_col_off<T, G::B_ROW, EDGE>(lane / EDGE * 16, wn * G::TN + x, lane);
     if constexpr (INTERLEAVED) b_fo[x] = opaque(b_fo[x]);
   }
   // The immediate offset of an LDS read has 16 bits: stages that begin 64 KB or more into LDS are read through a
@@ -633,11 +648,11 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
       if constexpr (TA) f.a[i] = dtl_read_col_at<T, AT_ROW>(smem + ((HI ? a_fo_hi[i] : a_fo[i]) + (SOFF + ks * KS_A)));
-      else f.a[i] = *(const v4i*)(smem + ((HI ? a_fo_hi[ks] : a_fo[ks]) + (SOFF + i * EDGE * G::KTB)));
+      else f.a[i] = *(const v4i*)(smem + ((HI ? a_fo_hi[ks] : a_fo[ks]) + (SOFF + i * 32 * G::KTB)));
     }
 #pragma unroll
     for (int j = 0; j < G::TN; j++) {
-      if constexpr (TB) f.b[j] = *(const v4i*)(smem + ((HI ? b_fo_hi[ks] : b_fo[ks]) + (SOFF + j * EDGE * G::KTB)));
+      if constexpr (TB) f.b[j] = *(const v4i*)(smem + ((HI ? b_fo_hi[ks] : b_fo[ks]) + (SOFF + j * 32 * G::KTB)));
       else f.b[j] = dtl_read_col_at<T, G::B_ROW>(smem + ((HI ? b_fo_hi[j] : b_fo[j]) + (SOFF + ks * KS_B)));
     }
   };
@@ -829,7 +844,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
       if constexpr (DW_MASK) {
         if (kbytes % 16 != 0 && kt0 + nkt == nkt_total) {
 #pragma unroll
-          for (int i = 0; i < G::TM; i++) fa[i] = dw_mask(fa[i], kbytes - (nkt_total - 1) * G::KTB - l_chunk * 16);
+          for (int i = 0; i < G::TM; i++) fa[i] = dw_mask(fa[i], kbytes - (nkt_total - 1) * G::KTB - lane / EDGE * 16);
         }
       }
       places(fb[0], [](auto) {});
@@ -1019,9 +1034,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     // half-waves, four rows apart, still hit different banks.  Otherwise: row pitch WTN + 8 from the LDS base.
     using SV = typename EPI::StagedValue;
     typedef SV sv4 __attribute__((ext_vector_type(4)));
-    // 16 x 16 tiles: the four lane groups are four rows apart; XPF exchanges the quarters of 64 values by (row / 4) % 4, a pitch of
-    // WTN + 4 puts the groups into different banks by itself.
-    constexpr int PITCH = XPF ? G::WTN : EDGE == 16 ? G::WTN + 4 : G::WTN + 8;
+    // The four lane groups of 16 x 16 tiles are four rows apart: there XPF exchanges the quarters of 64 values by (row / 4) % 4.
+    static_assert(XPF || EDGE == 32, "16 x 16 tiles: products, which prefetch");
+    constexpr int PITCH = XPF ? G::WTN : G::WTN + 8;
     constexpr auto pcol_of = [](int col, int row) { return !XPF ? col : EDGE == 16 ? col ^ (((row >> 2) & 3) << 4) : col ^ (((row >> 2) & 1) << 5); };
     constexpr int LPR = G::WTN / 4, RPI = 64 / LPR, NI = 16 / RPI;  // lanes per row, rows per instruction, instructions per 16 rows
     static_assert(G::WAVES * 16 * PITCH * 4 <= (XPF ? G::STAGE : G::LDS_BYTES) && 64 % LPR == 0 && 16 % RPI == 0 && sizeof(SV) == 4, "staging region");

@@ -13,6 +13,7 @@ PINGPONG_256 = "256, 256, 2, 4, 0, 4, 64, DTL_PINGPONG"
 # element type, output stage, tile and schedule, A^T, on dwords
 KERNELS = {"i32_64": ("TypeI8", "EpilogueRawI32", ROLLING_64, "false", "false"), "i32_64_dw": ("TypeI8", "EpilogueRawI32", ROLLING_64, "false", "true"),
            "i32_256": ("TypeI8", "EpilogueRawI32", PINGPONG_256, "false", "false"), "i32_256_dw": ("TypeI8", "EpilogueRawI32", PINGPONG_256, "false", "true"),
+           "at_256": ("TypeI8", "EpilogueI8", PINGPONG_256, "true", "false"), "at_256_dw": ("TypeI8", "EpilogueI8", PINGPONG_256, "true", "true"),
            "bf16_64": ("TypeBF16", "EpilogueF32", ROLLING_64, "false", "false"), "bf16_256": ("TypeBF16", "EpilogueF32", PINGPONG_256, "false", "false")}
 
 
@@ -58,3 +59,8 @@ def code(tmp_path_factory):
 def test_no_wait_of_the_compiler_in_the_k_loop(code, kernel):
     bad = [x for b in code[kernel] if any("v_mfma" in y for y in b) for x in b if x.startswith("s_waitcnt") and "vmcnt" in x or "scratch_" in x]
     assert not bad, bad
+
+
+def test_arguments_stay_in_scalar_registers(code):
+    """The dword form of A^T products keeps few of its scalars in lanes of a vector register (it had 660 reads of them)."""
+    assert sum(x.startswith("v_readlane") for b in code["at_256_dw"] for x in b) <= 200
