@@ -1050,17 +1050,19 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     // every store before it, and with the K tiles that follow.  (Read at each store, us, there / here: int32 without a bias 4952 x
     // 4176 x 2976 91.2 / 82.5, a row 1921 x 416 x 7448 28.0 / 24.6, a matrix 11229 x 2928 x 2464 218 / 152, bf16 with beta 4222 x
     // 6872 x 840 131 / 93; in ping-pong such a matrix 176 and 101.)
+    constexpr bool HAS_READS = EPI::STAGED_READS && !INTERLEAVED;  // (launch_dtl_256)
     auto body = [&](auto fullc, auto readsc) {
       constexpr bool READS = decltype(readsc)::value;
 #pragma unroll
     for (int i = 0; i < G::TM; i++) {
 #pragma unroll
       for (int hf = 0; hf < EDGE / 16; hf++) {
-        [[maybe_unused]] sv4 read[NI] = {};
-        if constexpr (EPI::STAGED_READS) {
+        [[maybe_unused]] sv4 read[NI];
+        if constexpr (HAS_READS) {
 #pragma unroll
           for (int q = 0; READS && q < NI; q++) {
             const int m = em0 + wm * G::WTM + i * EDGE + hf * 16 + q * RPI + elane / LPR, n = en0 + wn * G::WTN + (elane % LPR) * 4;
+            asm volatile("" : "=v"(read[q]));  // any value behind the mask (zeros would be kept in registers over the K loop)
             if (m < p.M && n < p.N) read[q] = EPI::staged_read(p, m, n);
           }
         }
@@ -1090,7 +1092,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
       }
     }
     };
-    if constexpr (EPI::STAGED_READS) {
+    if constexpr (HAS_READS) {
       if (EPI::staged_reads(p)) body(std::false_type{}, std::true_type{});
       else if (XPF && efull) body(std::true_type{}, std::false_type{});
       else body(std::false_type{}, std::false_type{});
@@ -1159,9 +1161,13 @@ static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
 template <class T, class EPI, int AMODE, bool TA, bool TB, bool DW>
 static hipError_t launch_dtl_256(const GemmParams& p, hipStream_t stream) {
   constexpr bool I8 = std::is_same_v<EPI, EpilogueI8>;
-  if constexpr (AMODE == 0 && (I8 || std::is_same_v<EPI, EpilogueRawI32> || std::is_same_v<EPI, EpilogueF32>) && !(TA && !TB))
-    if (p.splits <= 1 && interleaved_rule(p.M, p.N, (int64_t)p.K * T::EB, T::EB, I8 ? 1 : 4, TA, TB) && (!I8 || EpilogueI8::takes16(p.shift, p.bias, p.bias_ld)))
+  if constexpr (AMODE == 0 && (I8 || std::is_same_v<EPI, EpilogueRawI32> || std::is_same_v<EPI, EpilogueF32>) && !(TA && !TB)) {
+    bool takes;  // the loop's output stage
+    if constexpr (I8) takes = EpilogueI8::takes16(p.shift, p.bias, p.bias_ld);
+    else takes = !EPI::staged_reads(p);
+    if (takes && p.splits <= 1 && interleaved_rule(p.M, p.N, (int64_t)p.K * T::EB, T::EB, I8 ? 1 : 4, TA, TB))
       return launch_dtl<T, EPI, 256, 256, 2, 2, AMODE, 4, 64, DTL_INTERLEAVED, TA, TB, DW>(p, stream);
+  }
   return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, DTL_PINGPONG, TA, TB, DW>(p, stream);
 }
 

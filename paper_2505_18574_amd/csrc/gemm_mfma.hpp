@@ -452,7 +452,7 @@ struct EpilogueRawI32 {
   }
   // A bias matrix is read element by element, a row once (staged_add).
   template <class P>
-  static __device__ __forceinline__ bool staged_reads(const P& p) { return p.bias != nullptr && p.bias_ld != 0; }
+  static __host__ __device__ __forceinline__ bool staged_reads(const P& p) { return p.bias != nullptr && p.bias_ld != 0; }
   template <class P>
   static __device__ __forceinline__ v4i staged_read(const P& p, int m, int n) {
     const int32_t* b = p.bias + (int64_t)m * p.bias_ld + n;  // only 4-byte aligned
@@ -513,7 +513,7 @@ struct EpilogueF32 {
     *(v4f*)((float*)p.C + (int64_t)m * p.ldc + n) = o + p.beta * old;
   }
   template <class P>
-  static __device__ __forceinline__ bool staged_reads(const P& p) { return p.beta != 0.f; }
+  static __host__ __device__ __forceinline__ bool staged_reads(const P& p) { return p.beta != 0.f; }
   template <class P>
   static __device__ __forceinline__ v4f staged_read(const P& p, int m, int n) { return *(const v4f*)((const float*)p.C + (int64_t)m * p.ldc + n); }
   template <class P>
