@@ -278,35 +278,51 @@ inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_alo
 }
 
 // Whether a product of 256 x 256 tiles, uncut, runs on the interleaved K loop (one wave to a SIMD, 16 x 16 MFMA tiles) instead of the
-// ping-pong one.  A trip of it is a ninth to a fifth faster, its output stage, which one wave to a SIMD works through alone, some
-// 0.5 us a tile slower.  Replayed from a graph, us in ping-pong / interleaved: int8 4096 x 4096 x 2048 33.4 / 30.9, 8192 x 8192 x
-// 1024 67.9 / 72.0, 8192^3 441 / 380; with B^T 4096 x 8192 x 512 24.6 / 26.1, x 1024 37.4 / 35.8; A^T B^T 4096 x 8192 x 512 27.1 / 25.7,
-// x 128 18.9 / 18.8; int32 outputs 4096 x 4096 x 2048 38.0 / 38.9, x 3072 50.9 / 49.8, on more than a tile a compute unit 8192 x
-// 4096 x 1536 68.2 / 68.8, x 2048 80.3 / 77.6; bf16 (bytes of K) 4096 x 4096 x 512 19.1 / 20.5, x 1024 25.0 / 25.1, 8192 x 8192 x 1024
+// ping-pong one.  Its gain is that of the power limit, which compute units without a tile lift; one wave to a SIMD works through fill
+// and output stage alone (and, behind a prefetch, moves accumulators and in the plain int8 form waits for spilled registers).  So K
+// has to be the longer, the more units idle in the mean of the rounds.  Ping-pong / here, times as fast, means over some 6000 random
+// products of 130 to 800 tiles, by tiles a round (168, 192, 212 and from 232 on):
+//   bytes of K      900 to 1300          1800 to 2560          3500 to 6000
+//   int8            .90 .93 .94 .94      .95  .98 1.00 1.03    1.01 1.02 1.06 1.09
+//     several       .96 .92 .91 .93     1.02  .99  .99 1.02    1.08 1.05 1.05 1.08   (2560 to 3500: 1.05 1.02 1.02 1.03)
+//   B^T             .99 .99 1.00 1.01   1.00 1.00 1.01 1.00    1.01 1.01 1.02 1.06
+//     several      1.00 .99 1.00 1.01   1.01 1.01 1.01 1.02    1.03 1.02 1.02 1.03
+//   int32               .94 .95 .99           .98 1.00 1.04         1.03 1.07 1.09
+//     several       .96 .98 .98 1.00    1.00 1.02 1.02 1.07    1.06 1.08 1.08 1.09
+//   bf16            .88 .91 .94 .95      .92  .94  .97 .99      .97  .97 1.03 1.03   (on dwords .01 to .03 more)
+//     several           .93 .94 .95      .98  .97  .99 1.02    1.01 1.06 1.10 1.08
+//   A^T B^T        1.01 1.01 1.03 1.02  1.04 1.08 1.04 1.05    1.04 1.04 1.07 1.07
+//     several      1.02 1.03 1.05 1.01  1.06 1.04 1.05 1.06    1.05 1.02 1.03 1.03
+// Past the lines below 1.05 in the mean of 2331, 14 of them slower by 2.5 to 5.2 %.  8192^3 int8 441 / 380 us, 8192 x 8192 x 1024 bf16
 // 132.5 / 115.5.  A^T alone gains nothing (4096 x 8192 x 4096 111.6 / 109.6, x 8192 210.7 / 212.2): neither operand's lines are
-// requested twice there.
-//
-// On one round the loop's gain is that of the power limit, which compute units without a tile lift: the fewer tiles, the longer K
-// has to be (before / here, times as fast: int8 K = 1024 on 225 to 242 tiles 1.02 to 1.13, on 165 to 176 0.90 to 0.96; K = 2048 on 189
-// to 256 0.98 to 1.08, on 144 to 180 0.94 to 1.04; K = 4096 on 187 to 200 1.02 to 1.08; B^T K = 1024 on 240 1.05, on 161 and 210 0.93 and
-// 0.94, K = 1536 on 203 to 255 1.02 to 1.12; bf16 K = 512 on 210 to 247 0.99 to 1.08, on 130 to 168 0.82 to 0.93, K = 2048 on 231 and 240
-// 1.04, on 155 and 169 0.93 and 0.96).
+// requested twice there.  Lines of K and whole tiles alone held bf16 back by up to 9 % (3674 x 6792 x 616, 405 tiles, 46.7 / 51.5) and
+// int8 by up to 6 % (5203 x 5376 x 2272 63.2 / 67.6).
 inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int out_bytes, bool trans_a, bool trans_b) {
   if (trans_a && !trans_b) return false;
-  const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
-  if (tiles > PLAN_CUS) return kbytes >= (eb == 2 ? 1024 : out_bytes == 4 ? 2048 : !trans_b ? 2048 : trans_a ? 512 : 1024);
-  if (eb == 2) return kbytes >= (tiles >= 208 ? 1024 : 8192) && tiles >= 184;
-  if (out_bytes == 4) return kbytes >= (tiles >= 232 ? 3072 : 4096) && tiles >= 196;
-  if (trans_b) return kbytes >= (tiles >= 216 ? 1024 : tiles >= 192 ? 1536 : 4096) && tiles >= 184;
-  return kbytes >= (tiles >= 232 ? 1024 : tiles >= 196 ? 2048 : 4096) && tiles >= 184;
+  const int64_t tiles = tiles_of(M, N, 256, 256), rounds = (tiles + PLAN_CUS - 1) / PLAN_CUS;
+  if (tiles < 184) return false;
+  int64_t least, per_idle;  // bytes of K, and how many more for an idle unit
+  if (rounds == 1) {
+    least = eb == 2 || out_bytes == 4 ? 2560 : 1024;
+    per_idle = eb == 2 ? 72 : out_bytes == 4 ? 24 : !trans_b ? 48 : trans_a ? 8 : 24;
+  } else {
+    least = eb == 2 || out_bytes == 4 ? 1536 : !trans_b ? 2560 : trans_a ? 512 : 1024;
+    per_idle = eb == 2 ? 48 : out_bytes == 4 ? 16 : trans_b && !trans_a ? 16 : 0;
+  }
+  return (kbytes - least) * rounds >= per_idle * (rounds * PLAN_CUS - tiles);
 }
 
 // The same question for an int8 product on 128 x 256 tiles (four waves of 64 x 128 instead of eight of 64 x 64, a second wave to a
 // SIMD under whose products the output stage of the first hides).  86 random products, us before / interleaved: on one tile a
 // compute unit 2688 x 1600 x 512 7.5 / 8.6, 3648 x 1344 x 1024 10.7 / 11.3, K = 1536 and 1792 0.97 to 1.08 times as fast, from 2048
 // on 0.99 to 1.16 (3616 x 1856 x 4096 32.4 / 30.1); on more 5088 x 3520 x 512 21.1 / 21.7, x 1024 level, from 1280 on 1.03 to 1.16
-// (4304 x 5504 x 1536 43.3 / 40.9).  bf16 on 256 x 128 tiles the same way 0.88 to 1.09, up and down at any K: not taken.
-inline bool interleaved_128x256_rule(int32_t M, int32_t N, int32_t K) { return K >= (tiles_of(M, N, 128, 256) > PLAN_CUS ? 1280 : 2048); }
+// (4304 x 5504 x 1536 43.3 / 40.9).  With a hundred idle units one round needs K of some 2600 (1334 x 3456 x 2512, 154 tiles, 0.95
+// times as fast; 55 others from 2048 on 1.04 in the mean).  bf16 on 256 x 128 tiles the same way 0.88 to 1.09, up and down at any K: not
+// taken.
+inline bool interleaved_128x256_rule(int32_t M, int32_t N, int32_t K) {
+  const int64_t tiles = tiles_of(M, N, 128, 256);
+  return tiles > PLAN_CUS ? K >= 1280 : K >= 2048 && K >= 1792 + 8 * (PLAN_CUS - tiles);
+}
 
 // A^T B^T products on one round of those tiles, where the 128 x 128 ones that they had make two, and that cover little more than
 // the output.  46 random ones 1.02 to 1.28 times as fast (us before / here: 2640 x 2224 x 576 11.8 / 9.9, 848 x 5984 x 768 13.1 / 11.2, 2720

@@ -110,6 +110,7 @@ def test_interleaved_shapes(rules):
     assert {(-(-M // 128) * -(-N // 256) > 256, last_trips(K, False)) for M, N, K in interleaved.CHOSEN_128X256} >= {(True, t) for t in (4, 5, 6, 7, 3)} | {(False, 4)}
     for M, N, K in interleaved.CHOSEN_128X256:
         assert rules.interleaved_128x256(M, N, K) and product_tile_of(rules, M, N, K, False) == product_tile_of(rules, M, N, K, True) == TILE_128X256
+    assert not rules.interleaved_128x256(1334, 3456, 2512) and not rules.interleaved_128x256(1386, 3328, 2192)
     assert not rules.interleaved_128x256(3648, 1344, 1024) and not rules.interleaved_128x256(5088, 3520, 1024)
     for M, N, K in interleaved.CHOSEN_AT_BT:
         assert rules.interleaved_at_bt(M, N, K) and not rules.wide_trans(M, N, K, 1, 1, 0)
@@ -117,6 +118,17 @@ def test_interleaved_shapes(rules):
     assert not any(rules.interleaved(M, N, kb, 1, 1, 1, 0) for M, N in ((3601, 4080), (5393, 5392)) for kb in (1024, 4096, 8192))  # A^T alone
     assert not any(rules.interleaved(3136, 3296, k, 1, 1, 0, tb) or rules.interleaved(3136, 3296, k, 2, 4, 0, 0) for k in (1024, 2048, 4096) for tb in (0, 1))  # 169 tiles
     assert not rules.interleaved(8192, 8192, 1024, 1, 1, 0, 0) and not rules.interleaved(4096, 4096, 2048, 1, 4, 0, 0) and not rules.interleaved(4096, 4096, 512, 2, 4, 0, 0)
+
+
+def test_interleaved_needs_longer_k_where_units_idle(rules):
+    """Products that the loop slows down by 4 to 9 %: few K tiles for the compute units that have none in the last round."""
+    for M, N, K, eb, out, tb in [(3674, 6792, 616, 2, 4, 0), (8380, 5032, 616, 2, 4, 0), (7032, 3680, 928, 2, 4, 0), (13449, 908, 758, 2, 4, 0), (3388, 7192, 888, 2, 4, 0),
+                                 (5203, 5376, 2272, 1, 1, 0), (7150, 5632, 2256, 1, 1, 0), (2639, 5412, 1224, 1, 1, 0), (15212, 1740, 1440, 1, 1, 1), (14288, 2320, 2512, 1, 4, 0)]:
+        assert not rules.interleaved(M, N, K * eb, eb, out, 0, tb), (M, N, K)
+    for M, N, K, eb, out, tb in [(8192, 8192, 8192, 1, 1, 0), (4096, 4096, 4096, 2, 4, 0), (8192, 8192, 1024, 2, 4, 0), (4096, 4096, 2048, 1, 1, 0), (4096, 8192, 1024, 1, 1, 1), (8192, 4096, 2048, 1, 4, 0)]:
+        assert rules.interleaved(M, N, K * eb, eb, out, 0, tb), (M, N, K)
+        # the line rises with the units that idle: one tile more than a round's
+        assert not rules.interleaved(2048, 8448, 1024 * eb if out == 4 else 1024, eb, out, 0, tb)
 
 
 def shared_tile(rules, M, N, K, eb=1, conv=False, ragged=False, workspace=True, Cin=0, a_along_k=True, b_along_k=False, raw=False):

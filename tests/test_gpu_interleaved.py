@@ -37,7 +37,7 @@ CASES = [(form, rounds, kb) for form in FORMS for rounds in ROUNDS for kb in K_B
 # (M, N, K, on dwords) of A^T B^T: short K loops behind a prefetch, eight to ten K tiles, the last whole, of part of a chunk and of several
 SHORT_AT_BT = [(8208, 8208, 512, False), (8208, 8208, 592, False), (8204, 8212, 512, True), (8204, 8212, 516, True), (8204, 8212, 596, True)]
 # the 128 x 256 tiles that a product without a plan takes: on one round of them and on more; and A^T B^T products on one round
-CHOSEN_128X256 = [(1105, 4544, 2064), (1361, 4736, 2176), (2257, 3232, 3136), (3297, 6960, 1296), (6049, 3008, 2240), (3297, 6960, 1408), (3297, 6960, 1520), (3297, 6960, 1536)]
+CHOSEN_128X256 = [(1617, 4544, 2064), (1361, 4736, 2176), (2257, 3232, 3136), (3297, 6960, 1296), (6049, 3008, 2240), (3297, 6960, 1408), (3297, 6960, 1520), (3297, 6960, 1536)]
 CHOSEN_AT_BT = [(1712, 3584, 512), (2128, 2192, 592), (1040, 4112, 1136), (4464, 1744, 704)]
 
 
