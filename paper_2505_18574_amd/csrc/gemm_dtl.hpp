@@ -1042,9 +1042,12 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     static_assert(G::WAVES * 16 * PITCH * 4 <= (XPF ? G::STAGE : G::LDS_BYTES) && 64 % LPR == 0 && 16 % RPI == 0 && sizeof(SV) == 4, "staging region");
     static_assert(!XPF || (G::WTN % 64 == 0), "the half-row exchange needs rows of whole 32-value halves");
     if (!started) block_sync();  // every wave has read its last fragments: the stages are free
-    constexpr int RB = 16 * PITCH * 4, AW = G::A_BYTES / RB;  // a wave's bytes; XPF: waves that work in A's stage, the others in B's
-    static_assert(!XPF || (AW * RB == G::A_BYTES && (G::WAVES - AW) * RB <= G::B_BYTES), "the last stage, shared out");
-    SV* region = (SV*)(smem + (XPF ? (wave < AW ? (STAGES - 1) * A_STRIDE + wave * RB : B_FIRST + (STAGES - 1) * B_STRIDE + (wave - AW) * RB) : wave * RB));
+    constexpr int RB = 16 * PITCH * 4, AW = G::A_BYTES / RB;  // a wave's bytes; interleaved: waves that work in A's stage, the others in B's
+    static_assert(!INTERLEAVED || (AW * RB == G::A_BYTES && (G::WAVES - AW) * RB <= G::B_BYTES), "the last stage, shared out");
+    // (As a number of bytes added to smem, which the interleaved loop's is, the region has the ping-pong kernels keep sixteen addresses
+    // and write a value at a time: int32 1440 x 9504 x 672 23.6 -> 24.5 us.)
+    SV* region = (SV*)(smem + (XPF ? (STAGES - 1) * G::STAGE : 0)) + wave * (16 * PITCH);
+    if constexpr (INTERLEAVED) region = (SV*)(smem + (wave < AW ? (STAGES - 1) * A_STRIDE + wave * RB : B_FIRST + (STAGES - 1) * B_STRIDE + (wave - AW) * RB));
     // What is read beside the product is requested for 16 rows at a time, ahead of their way through LDS, and only where there is
     // something to read: a load among the stores, or one that the compiler takes for pending there, is waited for together with
     // every store before it, and with the K tiles that follow.  (Read at each store, us, there / here: int32 without a bias 4952 x

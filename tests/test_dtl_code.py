@@ -70,3 +70,10 @@ def test_no_wait_of_the_compiler_in_the_k_loop(code, kernel):
 def test_arguments_stay_in_scalar_registers(code):
     """The dword form of A^T products keeps few of its scalars in lanes of a vector register (it had 660 reads of them)."""
     assert sum(x.startswith("v_readlane") for b in code["at_256_dw"] for x in b) <= 200
+
+
+@pytest.mark.parametrize("kernel", ["i32_256", "i32_256_dw", "bf16_256", "i32_interleaved", "bf16_interleaved", "bf16_interleaved_dw"])
+def test_staged_values_are_written_in_pairs(code, kernel):
+    """A lane's sixteen rows lie at two addresses and immediates, not at sixteen addresses."""
+    single, pairs = (sum(x.startswith(op) for b in code[kernel] for x in b) for op in ("ds_write_b32", "ds_write2"))
+    assert pairs >= 100 and single <= pairs // 2, (single, pairs)
