@@ -105,7 +105,7 @@ def make_workloads():
         C = torch.empty((case.M, case.N), dtype=torch.float32, device="cuda")
         wl.append(Workload(case.name, "gemm_bf16", "bf16", case.ops, case.bytes,
                            lambda A, B, C: ops.ac_gemm_bf16(A, B, C, 1.0, 0.0),
-                           [A, B, C], "gemm_dtl_kernel<TypeBF16,EpilogueF32,256,256,2,4,0,4,64,true>", out_idx=(2,)))
+                           [A, B, C], "gemm_dtl_kernel<TypeBF16,EpilogueF32,256,256,2,2,0,4,64,DTL_INTERLEAVED>", out_idx=(2,)))
     case = inputs.BATCHED_F32
     A, B, x, d = (dev(t) for t in inputs.batched_f32_case_inputs(case))
     C = torch.empty((case.batch, case.n, case.n), dtype=torch.float32, device="cuda")

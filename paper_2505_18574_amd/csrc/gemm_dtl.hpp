@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
   const int nwork = ntiles * p.splits;
 
-  // Cross-item prefetch (products of 256 x 256 tiles): a persistent workgroup requests the first STAGES-1 K tiles of its
+  // Cross-item prefetch (products in ping-pong and interleaved, of 256 x 256 tiles and of 128 x 256): a persistent workgroup requests the first STAGES-1 K tiles of its
   // next output tile before it runs the output stage of the current one, so that the pipeline fill of the next
   // tile and the drain of this tile's stores overlap.  Vector-memory operations of a wave complete in issue order,
   // so the waits of the next tile's first trips name the stores that lie between its loads.
@@ -344,8 +344,9 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
   // its K loop is short more often than long (3 x 3, 64 -> 256 on 64 images of 56 x 56 39.2 us so and 41.7 from LDS, 128 -> 256
   // stride 2 on 192 of 28 x 28 22.1 and 22.8, 5 x 5, 48 -> 224 on 90 of 41 x 41 58.5 and 62.1; 512 -> 512 on 64 of 28 x 28,
   // K = 4608, 121.7 and 118.3; 20 such shapes 1.008 in the mean).  The
-  // request is the oldest of its wave, so the K loop's first wait covers it and the
-  // barrier behind that publishes it; the barrier at the end of the item frees it.
+  // request is the oldest of its wave, so the K loop's first wait covers it and the barrier behind that publishes it; behind a
+  // prefetch (interleaved) it is younger than that item's first tiles, and the last trips, which wait for everything ahead of a
+  // barrier, cover it: there are some, since such an item has at least STAGES tiles.  The barrier at the end of the item frees it.
   constexpr bool BIAS_LDS = has_bias_lds<EPI, BM, SCHEDULE>;
 
   // Stage s: A's tile, then B's, stage after stage; interleaved, all of A's and then all of B's, of 64 KB at most each, which the
@@ -695,8 +696,13 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N) gemm_dtl_kernel(const 
     // the MFMAs, reads the fragments of tile t + 1 (B's into a second set, a row of A's over its own behind the row's last MFMA)
     // and requests a tile.  One barrier a trip, behind its first row of MFMAs: past it tile t + 1 is in LDS for everyone, and
     // everyone has received tile t, whose stage is free.  Eight waves in ping-pong with 16 x 16 MFMAs: 8192^3 int8 432 us, so
-    // 418, with the paired requests below 397, its last trips interleaved too 385, its registers without spills 380; in
+    // 418, with the paired requests below 397, its last trips interleaved too 385, with the lane offsets made opaque 380; in
     // ping-pong with 32 x 32 441.  bf16 8192 x 8192 x 4096 461 and 405.
+    //
+    // Registers are all taken.  The rounds of four trips keep everything in place; around them the allocator moves accumulators and
+    // keeps up to 68 bytes a lane in scratch.  The plain int8 form reloads three fragments in its first round behind a prefetch and
+    // waits for all requests there, which costs it short K loops (interleaved_rule).  A single copy of the four trips, its first waits
+    // chosen at run time or naming no stores, moves 536 to 796 accumulators in every round.
     static_assert(AMODE == 0 && G::KSTEPS == 1 && EDGE == 16 && G::TN % 2 == 0 && STAGES % 2 == 0, "one K-step a tile, two fragment sets in turn");
     constexpr int PPR = G::TN / 2, SLOTS = G::TM * PPR;  // places behind two MFMAs: of a row of tiles, of all
     // A compute unit fetches lines of 128 bytes, two K tiles of a K-contiguous operand: it is requested two tiles at a time, in the
@@ -1160,7 +1166,8 @@ static hipError_t launch_dtl_wide(const GemmParams& p, hipStream_t stream) {
 }
 
 // 256 x 256 tiles.  Products whose K loop is long enough run interleaved (interleaved_rule); slices, convolutions, the short ones
-// and the output stages that the 16 x 16 tiles do not have stay in ping-pong.
+// and the output stages that the 16 x 16 tiles do not have stay in ping-pong: int8 shifts and biases (takes16), and those that read a
+// matrix beside the product, whose registers the K loop needs (with them bf16 without beta ran 0.96 times as fast as in ping-pong).
 template <class T, class EPI, int AMODE, bool TA, bool TB, bool DW>
 static hipError_t launch_dtl_256(const GemmParams& p, hipStream_t stream) {
   constexpr bool I8 = std::is_same_v<EPI, EpilogueI8>;
@@ -1174,8 +1181,8 @@ static hipError_t launch_dtl_256(const GemmParams& p, hipStream_t stream) {
   return launch_dtl<T, EPI, 256, 256, 2, 4, AMODE, 4, 64, DTL_PINGPONG, TA, TB, DW>(p, stream);
 }
 
-// The four direct-to-LDS configurations by tile code.  256: eight waves in ping-pong over four 32 KB stages
-// (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM); 192 (256 x 128),
+// The four direct-to-LDS configurations by tile code.  256: launch_dtl_256, eight waves in ping-pong or four interleaved over four 32 KB
+// stages (64 bytes of K per tile; a fifth stage, all of LDS, measured 0.3-1.5 % slower on every large GEMM in ping-pong); 192 (256 x 128),
 // 128 and 64: the rolling-refill loop with 128 bytes of K per tile, eight waves of 64 x 64 / 64 x 32 or four waves of
 // 32 x 32 (four stages: six and eight were measured slower on every few-tile deep-K shape, 7.9 / 8.3 / 9.3 us on 49 x 2048 x
 // 4608: those loops wait on the barrier, not on loads).
