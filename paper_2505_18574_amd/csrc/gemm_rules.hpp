@@ -280,7 +280,7 @@ inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_alo
 // Whether a product of 256 x 256 tiles, uncut, runs on the interleaved K loop (one wave to a SIMD, 16 x 16 MFMA tiles) instead of the
 // ping-pong one.  Its gain is that of the power limit, which compute units without a tile lift; one wave to a SIMD works through fill
 // and output stage alone (and, behind a prefetch, moves accumulators and in the plain int8 form waits for spilled registers).  So K
-// has to be the longer, the more units idle in the mean of the rounds.  Ping-pong / here, times as fast, means over some 7000 random
+// has to be the longer, the more units idle in the last round, and the fewer rounds there are.  Ping-pong / here, times as fast, means over some 8000 random
 // products of 130 to 800 tiles, by tiles a round (168, 192, 212 and from 232 on):
 //   bytes of K      900 to 1300          1800 to 2560          3500 to 6000
 //   int8            .90 .93 .94 .94      .95  .98 1.00 1.03    1.01 1.02 1.06 1.09
@@ -293,7 +293,7 @@ inline bool dword_tiles_rule(int32_t M, int32_t N, int64_t kbytes, bool both_alo
 //     several           .93 .94 .95      .98  .97  .99 1.02    1.01 1.06 1.10 1.08
 //   A^T B^T        1.01 1.01 1.03 1.02  1.04 1.08 1.04 1.05    1.04 1.04 1.07 1.07
 //     several      1.02 1.03 1.05 1.01  1.06 1.04 1.05 1.06    1.05 1.02 1.03 1.03
-// Past the lines below 1.05 in the mean of 2828, 15 of them slower by 2.5 to 5.2 %.  8192^3 int8 441 / 380 us, 8192 x 8192 x 1024 bf16
+// Past the lines below 1.05 in the mean of 2942, 15 of them slower by 2.5 to 4.3 %.  8192^3 int8 441 / 380 us, 8192 x 8192 x 1024 bf16
 // 132.5 / 115.5.  A^T alone gains nothing (4096 x 8192 x 4096 111.6 / 109.6, x 8192 210.7 / 212.2): neither operand's lines are
 // requested twice there.  Lines of K and whole tiles alone held bf16 back by up to 9 % (3674 x 6792 x 616, 405 tiles, 46.7 / 51.5) and
 // int8 by up to 6 % (5203 x 5376 x 2272 63.2 / 67.6).
@@ -301,15 +301,12 @@ inline bool interleaved_rule(int32_t M, int32_t N, int64_t kbytes, int eb, int o
   if (trans_a && !trans_b) return false;
   const int64_t tiles = tiles_of(M, N, 256, 256), rounds = (tiles + PLAN_CUS - 1) / PLAN_CUS;
   if (tiles < 184) return false;
-  int64_t least, per_idle;  // bytes of K, and how many more for an idle unit
-  if (rounds == 1) {
-    least = eb == 2 || out_bytes == 4 ? 2560 : 1024;
-    per_idle = eb == 2 ? 96 : out_bytes == 4 ? 24 : !trans_b ? 48 : trans_a ? 8 : 24;
-  } else {
-    least = eb == 2 || out_bytes == 4 ? 1536 : !trans_b ? 2560 : trans_a ? 512 : 1024;
-    per_idle = eb == 2 ? 48 : out_bytes == 4 ? 16 : trans_b && !trans_a ? 16 : 0;
-  }
-  return (kbytes - least) * rounds >= per_idle * (rounds * PLAN_CUS - tiles);
+  const bool one = rounds == 1, plain_i8 = eb == 1 && out_bytes == 1 && !trans_b;
+  // bytes of K on full rounds, and how many more for a unit that idles in the last one: its share of the launch, and of the lifted
+  // limit, falls with the rounds
+  const int64_t least = eb == 2 || out_bytes == 4 ? (one ? 2560 : 1536) : plain_i8 ? (one ? 1280 : 2560) : trans_a ? (one ? 1024 : 512) : 1024;
+  const int64_t per_idle = eb == 2 ? 96 : out_bytes == 4 ? (one ? 24 : 48) : plain_i8 ? (one ? 48 : 0) : trans_a ? (one ? 8 : 0) : 32;
+  return (kbytes - least) * rounds * rounds >= per_idle * (rounds * PLAN_CUS - tiles);
 }
 
 // The same question for an int8 product on 128 x 256 tiles (four waves of 64 x 128 instead of eight of 64 x 64, a second wave to a
